@@ -145,14 +145,6 @@ int run_layer(const void *x, int64_t M, int64_t K, int64_t R, int w_bits, const 
     d.K = (int)K;
     d.R = (int)R;
     int rc;
-    if (dp) {
-        rc = robust_args(dp, K, R, d);
-        if (rc) return rc;
-        rc = device_status(ql::launch_daq_robust(d, stream));
-    } else {
-        rc = device_status(ql::launch_daq(d, stream));
-    }
-    if (rc) return rc;
     ql::GemmArgs g{};
     g.q = d.q;
     g.s_a = d.scales;
@@ -178,7 +170,31 @@ int run_layer(const void *x, int64_t M, int64_t K, int64_t R, int w_bits, const 
         rc = device_status(ql::launch_fill_u32(g.row_absmax, (int)M, 0u, stream));
         if (rc) return rc;
     }
-    return device_status(ql::launch_qgemm(g, g_gemm_variant.load(), stream));
+    const int variant = g_gemm_variant.load();
+    const size_t parts = ql::daq_parts_per_block(K, R);
+    if (!dp && !dbg && variant < 0 && (R == 1 || (parts > 0 && parts <= 256))) {
+        // few rows: the GEMM's workgroups quantize their own rows (one launch; two where rows share a scale)
+        ql::GemmArgs f = g;
+        f.x = x;
+        f.partmax = d.partmax;
+        f.parts = R == 1 ? 0 : (int)parts;
+        if (ql::qgemm_fuse_takes(f)) {
+            if (R > 1) {
+                rc = device_status(ql::launch_daq_part_absmax(d, stream));
+                if (rc) return rc;
+            }
+            return device_status(ql::launch_qgemm_fused(f, stream));
+        }
+    }
+    if (dp) {
+        rc = robust_args(dp, K, R, d);
+        if (rc) return rc;
+        rc = device_status(ql::launch_daq_robust(d, stream));
+    } else {
+        rc = device_status(ql::launch_daq(d, stream));
+    }
+    if (rc) return rc;
+    return device_status(ql::launch_qgemm(g, variant, stream));
 }
 
 // device address of `scratch` on the current device, looked up once per device

@@ -284,6 +284,14 @@ hipError_t launch_daq_cg(const DaqArgs &a, int cg, hipStream_t stream)
     return hipGetLastError();
 }
 
+hipError_t launch_daq_part_absmax(const DaqArgs &a, hipStream_t stream)
+{
+    const unsigned parts = (unsigned)daq_parts_per_block(a.K, a.R);
+    hipLaunchKernelGGL(daq_part_absmax, dim3(parts * (unsigned)(a.M / a.R)), dim3(256), 0, stream, static_cast<const uint4 *>(a.x),
+                       (unsigned)((size_t)a.R * a.K / 8), parts, a.partmax);
+    return hipGetLastError();
+}
+
 hipError_t launch_daq(const DaqArgs &a, hipStream_t stream)
 {
     if (a.R == 1) {
@@ -292,8 +300,8 @@ hipError_t launch_daq(const DaqArgs &a, hipStream_t stream)
         const int nblk = a.M / a.R;
         const size_t parts = daq_parts_per_block(a.K, a.R);
         if (parts > 0 && (uintptr_t)a.x % 16 == 0 && parts * nblk < (1ull << 31)) {
-            hipLaunchKernelGGL(daq_part_absmax, dim3((unsigned)(parts * nblk)), dim3(256), 0, stream,
-                               static_cast<const uint4 *>(a.x), (unsigned)((size_t)a.R * a.K / 8), (unsigned)parts, a.partmax);
+            const hipError_t e = launch_daq_part_absmax(a, stream);
+            if (e != hipSuccess) return e;
             if (parts <= 256) {
                 // few parts per block: every wavefront of the quantize pass reduces them itself
                 DaqArgs q = a;

@@ -39,6 +39,16 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned m)
     return ab > cd ? ab : cd;
 }
 
+// 16 bytes of a row at byte `off` (per lane) + `step` (uniform), zeros past the row's end: a buffer load whose descriptor is the
+// row (its address must be wavefront-uniform), so that neither a branch nor an address computation goes with it
+__device__ __forceinline__ uint4 load_row_piece(const void *row, int row_bytes, int off, int step)
+{
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(row), 0, row_bytes, 0x00020000);
+    const u4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, step, 0);
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 // eq. (4), last line without the multiplication back by alpha
 __device__ __forceinline__ int daq_code(float v, float alpha)
 {

@@ -4,282 +4,17 @@
 // output channel (Step 3, Step 5, Section 6) or per weight group (Step 2).
 // Here: acc[m,n] = sum_k q[m,k] * w[n,k] on v_mfma_i32_32x32x32_i8, both
 // operands K-contiguous, and the dequantization + bias + fp16 conversion applied
-// to the accumulators in registers.  Two kernel families:
-//   qgemm_dma   tiles go global -> LDS by DMA through rings of 2-3 stages, optional
-//               persistent walk over tiles; 8-bit weights, and binary16 operands for
-//               the layers a plan leaves in FP16
-//   qgemm_mfma  tiles staged through registers, two LDS buffers; 4-bit weights (nibbles
-//               unpacked to int8 times 16 in registers, every weight group folded into
-//               an fp32 sum with its scale) and 8-bit weights with K % 128 != 0
-// plus a one-thread-per-element kernel for shapes and alignments neither takes.
+// to the accumulators in registers.  The kernel families:
+//   qgemm_dma   (here) tiles go global -> LDS by DMA through rings of 2-3 stages, optional persistent walk over
+//               tiles; 8-bit weights, and binary16 operands for the layers a plan leaves in FP16
+//   qgemm_w4    (qgemm_w4.hip) group scales: packed 4-bit weights and int8 codes with group scales
+//   qgemm_splitk, qgemm_edge (qgemm_small.hip) few rows; any inner size and alignment
+// plus a one-thread-per-element kernel: the tuning hooks' reference, and the last resort for channel-group activation
+// scales over blocks of rows that no tile boundary meets.
 // Activation, gate and residual can be folded into the epilogue (GLUE instantiations).
 #include "qgemm_common.h"
 
 namespace ql {
-
-// Tile shape: a workgroup of WGM x WGN wavefronts, each owning TM x TN MFMA
-// tiles of 32x32, walks K in steps of BK int8.
-// WPS = wavefronts per SIMD the register budget must allow (512 / WPS registers per lane).
-template <int TM_, int TN_, int WGM_, int WGN_, int BK_, bool W4_, int WPS_, bool GG_ = false>
-struct Tile {
-    static constexpr int TM = TM_, TN = TN_, WGM = WGM_, WGN = WGN_, BK = BK_, WPS = WPS_;
-    static constexpr bool W4 = W4_;
-    // 4-bit weights with a group size other than 128: any multiple of 32 that divides K (groups end at 32-wide K slices)
-    static constexpr bool GG = GG_;
-    static constexpr int NT = WGM * WGN * 64;
-    static constexpr int BM = WGM * TM * 32;
-    static constexpr int BN = WGN * TN * 32;
-    static constexpr int BKB = W4 ? BK / 2 : BK;  // bytes of one B row per K step
-    static constexpr int LDA = BK + 16;            // LDS row pitch, padded against bank conflicts
-    static constexpr int LDB = BKB + 16;
-    static constexpr int A_ITERS = BM * BK / 16 / NT;
-    static constexpr int B_ITERS = BN * BKB / 16 / NT;
-    static constexpr int A_BYTES = BM * LDA;
-    static constexpr int B_BYTES = BN * LDB;
-    static constexpr int S_BYTES = W4 ? 2 * BN * 4 : 0;
-    static constexpr int LDS_BYTES = 2 * A_BYTES + 2 * B_BYTES + S_BYTES;
-    static_assert(BM * BK / 16 % NT == 0 && BN * BKB / 16 % NT == 0, "tile loads must divide over the threads");
-    static_assert(!W4 || BK == 128, "one K step is one 128-wide weight group");
-    static_assert(!GG || W4, "group sizes apply to 4-bit weights");
-    static_assert(BM * 4 <= 2 * A_BYTES, "row-scale staging reuses the A buffers");
-};
-
-template <class T, bool GLUE = false>
-__global__ __launch_bounds__(T::NT, T::WPS) void qgemm_mfma(GemmArgs a, int tiles_m, int tiles_n, int nblk_padded, int group_m)
-{
-    constexpr int TM = T::TM, TN = T::TN, BK = T::BK, BM = T::BM, BN = T::BN, NT = T::NT;
-    constexpr int LDA = T::LDA, LDB = T::LDB, BKB = T::BKB;
-    constexpr bool W4 = T::W4;
-    constexpr int SLICE_UNROLL = T::GG ? 1 : BK / 32;
-    extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char *sA = smem;
-    unsigned char *sB = smem + 2 * T::A_BYTES;
-    float *sS = reinterpret_cast<float *>(sB + 2 * T::B_BYTES);
-
-    // ---- which tile: spread consecutive logical tiles inside one XCD, walk group_m tile rows at a time
-    // Workgroup ids go round-robin over the XCDs; each XCD owns per_xcd consecutive logical tiles and its resident
-    // workgroups take them in order, gridDim.x / XCDS at a time (all of them at once unless the launch is persistent).
-    const int per_xcd = nblk_padded / XCDS;
-    const int slots_per_xcd = gridDim.x / XCDS;
-    const int xcd_first = (blockIdx.x % XCDS) * per_xcd;
-    int in_xcd = blockIdx.x / XCDS;
-    if (in_xcd >= per_xcd || xcd_first + in_xcd >= tiles_m * tiles_n) return;
-    int m0, n0;
-    auto set_tile = [&](int logical) {
-        const int group_sz = group_m * tiles_n;
-        const int first_m = (logical / group_sz) * group_m;
-        const int gm = min(tiles_m - first_m, group_m);
-        m0 = (first_m + (logical % group_sz) % gm) * BM;
-        n0 = ((logical % group_sz) / gm) * BN;
-    };
-    set_tile(xcd_first + in_xcd);
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / T::WGN, wn = wave % T::WGN;
-    const int M = a.M, N = a.N, K = a.K;
-    const int KB = W4 ? K / 2 : K;  // bytes per weight row
-    const int G = T::GG ? K / a.group : K / 128;   // weight groups along K
-    const int QG = T::GG ? a.group / 32 : 4;         // 32-wide K slices per weight group
-    const int nk = K / BK;  // the dispatcher only sends K % BK == 0 here
-
-    // ---- global -> register staging of one K step
-    v4i ga[T::A_ITERS], gb[T::B_ITERS];
-    float gs = 0.0f;
-    auto load_tile = [&](int kt) {
-        const int k0 = kt * BK;
-#pragma unroll
-        for (int i = 0; i < T::A_ITERS; ++i) {
-            const int c = tid + i * NT;
-            const int row = c / (BK / 16), cc = c % (BK / 16);
-            const int gr = min(m0 + row, M - 1);
-            ga[i] = *reinterpret_cast<const v4i *>(a.q + (size_t)gr * K + (k0 + cc * 16));
-        }
-        const int kb0 = W4 ? k0 / 2 : k0;
-#pragma unroll
-        for (int i = 0; i < T::B_ITERS; ++i) {
-            const int c = tid + i * NT;
-            const int row = c / (BKB / 16), cc = c % (BKB / 16);
-            const int gr = min(n0 + row, N - 1);
-            gb[i] = *reinterpret_cast<const v4i *>(static_cast<const unsigned char *>(a.w) + (size_t)gr * KB + (kb0 + cc * 16));
-        }
-        if (W4 && !T::GG && (k0 % 128) == 0 && tid < BN) {
-            const int gr = min(n0 + tid, N - 1);
-            // the nibbles are used as value*16, so the group scale carries the 1/16 (exact: a power of two)
-            gs = half_to_float_dev(static_cast<const unsigned short *>(a.s_w)[(size_t)gr * G + k0 / 128]) * 0.0625f;
-        }
-    };
-    auto store_tile = [&](int kt) {
-        unsigned char *dA = sA + (kt & 1) * T::A_BYTES;
-        unsigned char *dB = sB + (kt & 1) * T::B_BYTES;
-#pragma unroll
-        for (int i = 0; i < T::A_ITERS; ++i) {
-            const int c = tid + i * NT;
-            *reinterpret_cast<v4i *>(dA + (c / (BK / 16)) * LDA + (c % (BK / 16)) * 16) = ga[i];
-        }
-#pragma unroll
-        for (int i = 0; i < T::B_ITERS; ++i) {
-            const int c = tid + i * NT;
-            *reinterpret_cast<v4i *>(dB + (c / (BKB / 16)) * LDB + (c % (BKB / 16)) * 16) = gb[i];
-        }
-        if (W4 && !T::GG && ((kt * BK) % 128) == 0 && tid < BN) sS[(((kt * BK) / 128) & 1) * BN + tid] = gs;
-    };
-
-    v16i acc[TM][TN];
-    float fsum[W4 ? TM : 1][W4 ? TN : 1][16];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
-            if (W4) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) fsum[i][j][r] = 0.0f;
-            }
-        }
-
-    // lane -> fragment: row (lane & 31) of a 32-row tile, k offset 16 * (lane >> 5) inside a 32-wide K slice
-    const int frag_row = lane & 31, frag_half = lane >> 5;
-    const int a_off = (wm * TM * 32 + frag_row) * LDA + frag_half * 16;
-    const int b_off = (wn * TN * 32 + frag_row) * LDB + frag_half * (W4 ? 8 : 16);
-
-    int qs = 0, grp = 0;   // generic group size: slice inside the current weight group, and the group's number
-    unsigned short sgrp[TN] = {};
-    load_tile(0);
-    store_tile(0);
-    __syncthreads();
-
-    for (int kt = 0; kt < nk; ++kt) {
-        if (kt + 1 < nk) load_tile(kt + 1);
-        const unsigned char *pa = sA + (kt & 1) * T::A_BYTES + a_off;
-        const unsigned char *pb = sB + (kt & 1) * T::B_BYTES + b_off;
-        // with run-time group ends the four slices share one copy of the code
-#pragma unroll SLICE_UNROLL
-        for (int ks = 0; ks < BK / 32; ++ks) {
-            v4i af[TM], bf[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const v4i *>(pa + i * 32 * LDA + ks * 32);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                if (W4) {
-                    const v2i p = *reinterpret_cast<const v2i *>(pb + j * 32 * LDB + ks * 16);
-                    // byte b of a packed word: low nibble = k b, high nibble = k 4+b  ->  int8 value * 16
-                    bf[j] = v4i{(int)(((unsigned)p[0] << 4) & 0xf0f0f0f0u), (int)((unsigned)p[0] & 0xf0f0f0f0u),
-                                (int)(((unsigned)p[1] << 4) & 0xf0f0f0f0u), (int)((unsigned)p[1] & 0xf0f0f0f0u)};
-                } else {
-                    bf[j] = *reinterpret_cast<const v4i *>(pb + j * 32 * LDB + ks * 32);
-                }
-            }
-            if (T::GG) {
-                // slice number qs of the current group (wavefront-uniform): the group's scales are requested at its
-                // first slice; after its last slice the partial sums are folded into the fp32 sum and the accumulators
-                // cleared (one code path for the MFMAs: a second one with a zero C operand doubled the register need)
-                if (qs == 0) {
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        sgrp[j] = static_cast<const unsigned short *>(a.s_w)[(size_t)min(n0 + wn * TN * 32 + j * 32 + frag_row, N - 1) * G + grp];
-                }
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[i], bf[j], acc[i][j], 0, 0, 0);
-                if (++qs == QG) {
-                    qs = 0;
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const int n = n0 + wn * TN * 32 + j * 32 + frag_row;
-                        // the nibbles are used as value*16, so the group scale carries the 1/16 (exact: a power of two)
-                        const float s16 = half_to_float_dev(sgrp[j]) * 0.0625f;
-#pragma unroll
-                        for (int i = 0; i < TM; ++i)
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) {
-                                if (a.acc_out) {
-                                    const int m = m0 + wm * TM * 32 + i * 32 + 8 * (r / 4) + 4 * frag_half + (r % 4);
-                                    if (m < M && n < N) a.acc_out[(unsigned)((m * G + grp) * N + n)] = acc[i][j][r] >> 4;
-                                }
-                                fsum[W4 ? i : 0][W4 ? j : 0][r] = __builtin_fmaf((float)acc[i][j][r], s16, fsum[W4 ? i : 0][W4 ? j : 0][r]);
-                                acc[i][j][r] = 0;
-                            }
-                    }
-                    ++grp;
-                }
-                continue;
-            }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    // a weight group (= one K step) starts from a zero accumulator
-                    const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[i], bf[j], (W4 && ks == 0) ? zero : acc[i][j], 0, 0, 0);
-                }
-        }
-        if (W4 && !T::GG) {
-            // the weight group ends here: fold its int32 partial sums into the fp32 sum with the group scale
-            const int g = kt;
-            const float *sc = sS + (g & 1) * BN + wn * TN * 32 + frag_row;
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const float s16 = sc[j * 32];
-                const int n = n0 + wn * TN * 32 + j * 32 + frag_row;
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        if (a.acc_out) {
-                            const int m = m0 + wm * TM * 32 + i * 32 + 8 * (r / 4) + 4 * frag_half + (r % 4);
-                            if (m < M && n < N) a.acc_out[(unsigned)((m * G + g) * N + n)] = acc[i][j][r] >> 4;
-                        }
-                        fsum[i][j][r] = __builtin_fmaf((float)acc[i][j][r], s16, fsum[i][j][r]);
-                    }
-            }
-        }
-        if (kt + 1 < nk) store_tile(kt + 1);
-        __syncthreads();
-    }
-
-    // ---- epilogue: activation scale per row (staged in LDS), weight scale and bias per column
-    float *sRow = reinterpret_cast<float *>(smem);
-    for (int t = tid; t < BM; t += NT) sRow[t] = a.s_a[min(m0 + t, M - 1) / a.R];
-    __syncthreads();
-    _Float16 *y = static_cast<_Float16 *>(a.y);
-    const unsigned short *bias = static_cast<const unsigned short *>(a.bias);
-    const bool full = (m0 + BM <= M) && (n0 + BN <= N);
-    auto emit = [&](auto edge) {
-        constexpr bool EDGE = decltype(edge)::value;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int n = n0 + wn * TN * 32 + j * 32 + frag_row;
-            const bool n_ok = !EDGE || n < N;
-            const float sw = (!W4 && n_ok) ? static_cast<const float *>(a.s_w)[n] : 1.0f;
-            const float b = (bias && n_ok) ? half_to_float_dev(bias[n]) : 0.0f;
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = wm * TM * 32 + i * 32 + 8 * (r / 4) + 4 * frag_half + (r % 4);
-                    const int m = m0 + row;
-                    if (!EDGE || (m < M && n_ok)) {
-                        const float sa = sRow[row];
-                        const unsigned off = (unsigned)(m * N + n);
-                        float u;
-                        if (W4) {
-                            u = bias ? __builtin_fmaf(fsum[i][j][r], sa, b) : fsum[i][j][r] * sa;
-                        } else {
-                            const float t = (float)acc[i][j][r] * sa;
-                            u = bias ? __builtin_fmaf(t, sw, b) : t * sw;
-                            if (a.acc_out) a.acc_out[off] = acc[i][j][r];
-                        }
-                        if (GLUE) __builtin_nontemporal_store(glue_one(a, u, m, n, GateRows(a.gate, a.gate_rows, m0, BM).of(row)), &y[off]);
-                        else __builtin_nontemporal_store((_Float16)u, &y[off]);
-                    }
-                }
-        }
-    };
-    if (full) emit(std::false_type{});
-    else emit(std::true_type{});
-}
 
 // ---------------------------------------------------------------------------------------------
 // Pipelined variant: tiles go from global memory straight into LDS (global_load_lds_dwordx4, no
@@ -851,47 +586,12 @@ __global__ __launch_bounds__(256) void qgemm_naive(GemmArgs a)
 }
 
 // ---- variants -----------------------------------------------------------------
-template <class T, bool GLUE = false>
-static hipError_t run_variant(const GemmArgs &a, hipStream_t s)
-{
-    static const hipError_t lds_opt_in = [] {
-        if (T::LDS_BYTES <= 64 * 1024) return hipSuccess;
-        return hipFuncSetAttribute(reinterpret_cast<const void *>(&qgemm_mfma<T, GLUE>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
-    }();
-    if (lds_opt_in != hipSuccess) return lds_opt_in;
-    const int tiles_m = (a.M + T::BM - 1) / T::BM, tiles_n = (a.N + T::BN - 1) / T::BN;
-    const int nblk = tiles_m * tiles_n;
-    const int padded = (nblk + XCDS - 1) / XCDS * XCDS;
-    hipLaunchKernelGGL((qgemm_mfma<T, GLUE>), dim3(padded), dim3(T::NT), T::LDS_BYTES, s, a, tiles_m, tiles_n, padded, pick_group_m(T::BM));
-    return hipGetLastError();
-}
-
 struct Variant {
     const char *name;
     int w_bits, BM, BN, BK;   // BK: K must be a multiple of this
     hipError_t (*run)(const GemmArgs &, hipStream_t);
     hipError_t (*run_glue)(const GemmArgs &, hipStream_t) = nullptr;   // the same tile with block glue in the epilogue (shape-chosen variants only)
 };
-
-//                         TM TN WGM WGN BK  W4  WPS
-using W8_128x128_k64 = Tile<2, 2, 2, 2, 64, false, 2>;
-using W8_128x128_k128 = Tile<2, 2, 2, 2, 128, false, 2>;
-using W8_256x128_k64 = Tile<4, 2, 2, 2, 64, false, 2>;
-using W8_256x128_k128 = Tile<4, 2, 2, 2, 128, false, 2>;
-using W8_128x192_k64 = Tile<2, 3, 2, 2, 64, false, 2>;
-using W8_256x192_k64 = Tile<4, 3, 2, 2, 64, false, 1>;
-using W8_256x256_8w = Tile<4, 2, 2, 4, 64, false, 2>;
-using W8_64x64_k64 = Tile<1, 1, 2, 2, 64, false, 4>;
-using W8_128x128_k64_o3 = Tile<2, 2, 2, 2, 64, false, 3>;
-using W4_128x128_k128 = Tile<2, 2, 2, 2, 128, true, 2>;
-using W4_64x128_k128 = Tile<1, 2, 2, 2, 128, true, 2>;
-using W4_256x128_8w = Tile<2, 2, 4, 2, 128, true, 2>;
-using W4_128x64_k128 = Tile<2, 1, 2, 2, 128, true, 3>;
-using W4G_128x64_k128 = Tile<2, 1, 2, 2, 128, true, 3, true>;   // any group size that is a multiple of 32
-using W4G_128x128_k128 = Tile<2, 2, 2, 2, 128, true, 2, true>;
-using W4G_64x128_k128 = Tile<1, 2, 2, 2, 128, true, 3, true>;
-using W4G_64x64_k128 = Tile<1, 1, 2, 2, 128, true, 4, true>;
 
 //                          TM TN WGM WGN S WPS
 using D8_128x128_s3 = TileD<2, 2, 2, 2, 3, 2>;
@@ -906,8 +606,7 @@ using D8_256x192_8w_e1 = TileD<2, 3, 4, 2, 2, 2, true, 1>;
 using D8_256x256_8w_e1 = TileD<4, 2, 2, 4, 2, 2, true, 1>;
 using D8_256x256_8w_e2 = TileD<4, 2, 2, 4, 2, 2, true, 2>;
 using D8_256x192_4w_e2 = TileD<4, 3, 2, 2, 2, 1, true, 2>;
-using D8_64x64_s4 = TileD<1, 1, 2, 2, 4, 4>;
-using D4_128x128_4w = TileD<2, 2, 2, 2, 2, 2, true, 0, true>;
+using D8_64x64_s3 = TileD<1, 1, 2, 2, 3, 4>;
 //                                                       SA                  SB
 using D8_256x192_8w_a3b2 = TileD<2, 3, 4, 2, 3, 2, true, 1, false, 2>;
 using D8_256x192_8w_a2b3 = TileD<2, 3, 4, 2, 2, 2, true, 1, false, 3>;
@@ -921,12 +620,12 @@ using P8_128x192_s2 = TileD<2, 3, 2, 2, 2, 2, true, 1, false, 2, true>;
 //                                                                                      FP16 operands
 using H_256x192_8w = TileD<2, 3, 4, 2, 3, 2, true, 1, false, 2, false, true>;
 using H_128x128_4w = TileD<2, 2, 2, 2, 3, 2, true, 1, false, 2, false, true>;
-using H_64x64_4w = TileD<1, 1, 2, 2, 4, 4, true, 0, false, 4, false, true>;
+using H_64x64_4w = TileD<1, 1, 2, 2, 3, 4, true, 0, false, 3, false, true>;
 using H_p192 = TileD<2, 3, 2, 2, 2, 2, true, 1, false, 2, true, true>;
 using H_p128 = TileD<2, 2, 2, 2, 3, 2, true, 1, false, 2, true, true>;
 
 static const Variant VARIANTS[] = {
-    {"w8 dma 64x64 s4 4w", 8, 64, 64, 128, run_dma<D8_64x64_s4>, run_dma<D8_64x64_s4, true>},
+    {"w8 dma 64x64 s3 4w", 8, 64, 64, 128, run_dma<D8_64x64_s3>, run_dma<D8_64x64_s3, true>},
     {"w8 dma 256x192 a3b2 8w spread1", 8, 256, 192, 128, run_dma<D8_256x192_8w_a3b2>, run_dma<D8_256x192_8w_a3b2, true>},
     {"w8 dma 128x128 a3b2 4w", 8, 128, 128, 128, run_dma<D8_128x128_a3b2>, run_dma<D8_128x128_a3b2, true>},
     {"w8 dma 128x128 a3b2 4w spread1", 8, 128, 128, 128, run_dma<D8_128x128_a3b2_e1>, run_dma<D8_128x128_a3b2_e1, true>},
@@ -934,11 +633,19 @@ static const Variant VARIANTS[] = {
     {"w8 dma 128x192 s2 4w spread1 persistent", 8, 128, 192, 128, run_dma<P8_128x192_s2>},
     {"f16 dma 256x192 a3b2 8w spread1", 16, 256, 192, 64, run_dma<H_256x192_8w>, run_dma<H_256x192_8w, true>},
     {"f16 dma 128x128 a3b2 4w spread1", 16, 128, 128, 64, run_dma<H_128x128_4w>, run_dma<H_128x128_4w, true>},
-    {"f16 dma 64x64 s4 4w", 16, 64, 64, 64, run_dma<H_64x64_4w>, run_dma<H_64x64_4w, true>},
+    {"f16 dma 64x64 s3 4w", 16, 64, 64, 64, run_dma<H_64x64_4w>, run_dma<H_64x64_4w, true>},
     {"f16 dma 128x192 s2 4w spread1 persistent", 16, 128, 192, 64, run_dma<H_p192>},
-    {"w8 128x128 bk64 4w occ3", 8, 128, 128, 64, run_variant<W8_128x128_k64_o3>, run_variant<W8_128x128_k64_o3, true>},
-    {"w4 any-group 64x64 bk128 4w occ4", 4, 64, 64, 128, run_variant<W4G_64x64_k128>, run_variant<W4G_64x64_k128, true>},
-    {"w4 pipelined 128x128 a3b2 4w any-group", 4, 128, 128, 128, launch_qgemm_w4, launch_qgemm_w4},
+    {"w4 pipelined 128x128 a3b2 4w any-group", 4, 128, 128, 128, launch_qgemm_w4_128, launch_qgemm_w4_128},
+    {"w4 pipelined 64x64 a3b2 4w any-group", 4, 64, 64, 128, launch_qgemm_w4_64, launch_qgemm_w4_64},
+    {"w8 split-K 32x32", 8, 32, 32, 16, launch_qgemm_split32, launch_qgemm_split32},
+    {"w4 any-group split-K 32x32", 4, 32, 32, 32, launch_qgemm_split32, launch_qgemm_split32},
+    {"f16 split-K 32x32", 16, 32, 32, 8, launch_qgemm_split32, launch_qgemm_split32},
+    {"w8 split-K 16x16", 8, 16, 16, 16, launch_qgemm_split16, launch_qgemm_split16},
+    {"w4 any-group split-K 16x16", 4, 16, 16, 32, launch_qgemm_split16, launch_qgemm_split16},
+    {"f16 split-K 16x16", 16, 16, 16, 8, launch_qgemm_split16, launch_qgemm_split16},
+    {"w8 edge any-K", 8, 64, 64, 1, launch_qgemm_edge, launch_qgemm_edge},
+    {"w4 any-group edge any-K", 4, 64, 64, 32, launch_qgemm_edge, launch_qgemm_edge},
+    {"f16 edge any-K", 16, 64, 64, 1, launch_qgemm_edge, launch_qgemm_edge},
 #ifdef QL_SWEEP_VARIANTS   // the other tile shapes of the sweeps that chose the ones above
     {"w8 dma 128x128 s3 4w", 8, 128, 128, 128, run_dma<D8_128x128_s3>},
     {"w8 dma 128x128 s2 4w", 8, 128, 128, 128, run_dma<D8_128x128_s2>},
@@ -952,26 +659,10 @@ static const Variant VARIANTS[] = {
     {"w8 dma 256x256 s2 8w spread1", 8, 256, 256, 128, run_dma<D8_256x256_8w_e1>},
     {"w8 dma 256x256 s2 8w spread2", 8, 256, 256, 128, run_dma<D8_256x256_8w_e2>},
     {"w8 dma 256x192 s2 4w spread2", 8, 256, 192, 128, run_dma<D8_256x192_4w_e2>},
-    {"w4 dma 128x128 s2 4w", 4, 128, 128, 128, run_dma<D4_128x128_4w>},
     {"w8 dma 256x192 a2b3 8w spread1", 8, 256, 192, 128, run_dma<D8_256x192_8w_a2b3>},
     {"w8 dma 256x256 a3b2 8w spread1", 8, 256, 256, 128, run_dma<D8_256x256_8w_a3b2>},
     {"w8 dma 128x128 s2 4w spread1", 8, 128, 128, 128, run_dma<D8_128x128_s2_e1>},
     {"f16 dma 128x128 a3b2 4w spread1 persistent", 16, 128, 128, 64, run_dma<H_p128>},
-    {"w8 128x128 bk64 4w occ2", 8, 128, 128, 64, run_variant<W8_128x128_k64>},
-    {"w8 128x128 bk128 4w occ2", 8, 128, 128, 128, run_variant<W8_128x128_k128>},
-    {"w8 256x128 bk64 4w occ2", 8, 256, 128, 64, run_variant<W8_256x128_k64>},
-    {"w8 256x128 bk128 4w occ2", 8, 256, 128, 128, run_variant<W8_256x128_k128>},
-    {"w8 128x192 bk64 4w occ2", 8, 128, 192, 64, run_variant<W8_128x192_k64>},
-    {"w8 256x192 bk64 4w occ1", 8, 256, 192, 64, run_variant<W8_256x192_k64>},
-    {"w8 256x256 bk64 8w occ2", 8, 256, 256, 64, run_variant<W8_256x256_8w>},
-    {"w8 64x64 bk64 4w occ4", 8, 64, 64, 64, run_variant<W8_64x64_k64>},
-    {"w4 128x128 bk128 4w occ2", 4, 128, 128, 128, run_variant<W4_128x128_k128>},
-    {"w4 64x128 bk128 4w occ2", 4, 64, 128, 128, run_variant<W4_64x128_k128>},
-    {"w4 256x128 bk128 8w occ2", 4, 256, 128, 128, run_variant<W4_256x128_8w>},
-    {"w4 128x64 bk128 4w occ3", 4, 128, 64, 128, run_variant<W4_128x64_k128>},
-    {"w4 any-group 128x64 bk128 4w occ3", 4, 128, 64, 128, run_variant<W4G_128x64_k128>, run_variant<W4G_128x64_k128, true>},
-    {"w4 any-group 128x128 bk128 4w occ2", 4, 128, 128, 128, run_variant<W4G_128x128_k128>},
-    {"w4 any-group 64x128 bk128 4w occ3", 4, 64, 128, 128, run_variant<W4G_64x128_k128>},
 #endif
 };
 constexpr int NUM_VARIANTS = sizeof(VARIANTS) / sizeof(VARIANTS[0]);
@@ -986,34 +677,29 @@ static int find_variant(const char *name)
     return 0;
 }
 
-// Tile choice by shape, from sweeps over the DiT-XL/2 layer shapes on MI355X (256 CUs).
+// Tile choice by shape, from sweeps over the DiT-XL/2 layer shapes and other widths on MI355X (256 CUs); 8-bit and FP16
+// layers (4-bit layers choose inside launch_qgemm_w4).
 static int choose_variant(const GemmArgs &a)
 {
-    static const int w8_small = find_variant("w8 dma 64x64 s4 4w"),
+    static const int w8_small = find_variant("w8 dma 64x64 s3 4w"),
                      w8_mid = find_variant("w8 dma 128x128 a3b2 4w spread1"),
                      w8_mid_deep = find_variant("w8 dma 128x128 a3b2 4w"),
                      w8_p128 = find_variant("w8 dma 128x128 a3b2 4w spread1 persistent"),
                      w8_p192 = find_variant("w8 dma 128x192 s2 4w spread1 persistent"),
-                     w8_big = find_variant("w8 dma 256x192 a3b2 8w spread1"),
-                     w8_k64 = find_variant("w8 128x128 bk64 4w occ3"), w4_any = find_variant("w4 any-group 64x64 bk128 4w occ4");
-    // the register-staged kernel hides the per-group VALU work best at high occupancy (64x64 tiles, 5 workgroups per CU);
-    // its any-group form, whose four K slices share one copy of the loop body, is also the fastest at group 128
+                     w8_big = find_variant("w8 dma 256x192 a3b2 8w spread1");
+    // 64x64 tiles while all of them are resident at once (three per CU): M = 1024, N = 1152: K = 1152 6.5 against 8.0 us on
+    // 128x128 tiles, K = 4608 16.6 against 21.1
+    const long tiles_64 = (long)((a.M + 63) / 64) * ((a.N + 63) / 64);
+    const long tiles_big = (long)((a.M + 255) / 256) * ((a.N + 191) / 192);
     if (a.w_bits == 16) {
-        static const int h_small = find_variant("f16 dma 64x64 s4 4w"), h_mid = find_variant("f16 dma 128x128 a3b2 4w spread1"),
+        static const int h_small = find_variant("f16 dma 64x64 s3 4w"), h_mid = find_variant("f16 dma 128x128 a3b2 4w spread1"),
                          h_big = find_variant("f16 dma 256x192 a3b2 8w spread1"),
                          h_p192 = find_variant("f16 dma 128x192 s2 4w spread1 persistent");
-        if (a.M <= 512) return h_small;
-        if ((long)((a.M + 255) / 256) * ((a.N + 191) / 192) < 192) return h_mid;
+        if (tiles_64 <= 768) return h_small;
+        if (tiles_big < 192) return h_mid;
         return (a.M >= 4096 && a.N < 4096) ? h_p192 : h_big;
     }
-    // 4-bit weights: the pipelined kernel where the tile's group scales fit its LDS table and the rows fill tiles
-    if (a.w_bits == 4) {
-        static const int w4_pipe = find_variant("w4 pipelined 128x128 a3b2 4w any-group");
-        return (qgemm_w4_takes(a) && a.M > 256) ? w4_pipe : w4_any;
-    }
-    if (a.K % 128 != 0) return w8_k64;
-    if (a.M <= 512) return w8_small;
-    const long tiles_big = (long)((a.M + 255) / 256) * ((a.N + 191) / 192);
+    if (tiles_64 <= 768 && (a.K < 2304 || tiles_64 <= 512)) return w8_small;
     if (tiles_big >= 192) {                                   // enough work for every CU
         // Several tiles per CU: two resident 4-wavefront workgroups per CU that walk their tiles and fetch the next
         // tile's first K step under the epilogue.  128x192 tiles move less data per MAC; 128x128 tiles balance better
@@ -1021,39 +707,47 @@ static int choose_variant(const GemmArgs &a)
         if (a.M >= 4096) return (a.K >= 2304 || a.N <= 1536 || a.M >= 12288) ? w8_p192 : w8_p128;
         return w8_big;
     }
-    return a.K >= 2304 ? w8_mid_deep : w8_mid;
+    // one 128x128 tile per CU at most: the deeper issue of a long K; more than one: DMA spread between the MFMAs
+    const long tiles_128 = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
+    return a.K >= 2304 && tiles_128 <= 256 ? w8_mid_deep : w8_mid;
 }
-
-static bool is_any_group(int v) { return __builtin_strstr(VARIANTS[v].name, "any-group") != nullptr; }
 
 hipError_t launch_qgemm(const GemmArgs &a, int variant, hipStream_t stream)
 {
+    const bool glue = a.act != 0 || a.residual != nullptr || a.gate != nullptr || a.row_absmax != nullptr;
+    auto naive = [&]() {
+        hipLaunchKernelGGL(qgemm_naive, dim3((a.M + 3) / 4, (a.N + 63) / 64), dim3(256), 0, stream, a);
+        return hipGetLastError();
+    };
+    if (variant >= NUM_VARIANTS) return naive();
+    const int split = qgemm_split_choice(a);
+    auto small = [&]() {
+        if (split) return split == 16 ? launch_qgemm_split16(a, stream) : launch_qgemm_split32(a, stream);
+        return qgemm_edge_takes(a) ? launch_qgemm_edge(a, stream) : naive();
+    };
     if (a.w_grouped || a.s_ag) {
-        // plan-space generality: the pipelined grouped kernel where it takes the shape, else one thread per element
-        if (variant < NUM_VARIANTS && qgemm_w4_takes(a) && !(a.act != 0 || a.residual != nullptr || a.gate != nullptr || a.row_absmax != nullptr))
-            return launch_qgemm_w4(a, stream);
-        hipLaunchKernelGGL(qgemm_naive, dim3((a.M + 3) / 4, (a.N + 63) / 64), dim3(256), 0, stream, a);
-        return hipGetLastError();
-    }
-    // MFMA tiles need 16-byte loads along K and a whole number of K steps
-    const bool fast = (a.K % 64 == 0) && ((uintptr_t)a.q % 16 == 0) && ((uintptr_t)a.w % 16 == 0) &&
-                      (a.w_bits != 4 || (a.K % 128 == 0 && a.group % 32 == 0));
-    if (!fast || variant >= NUM_VARIANTS) {
-        hipLaunchKernelGGL(qgemm_naive, dim3((a.M + 3) / 4, (a.N + 63) / 64), dim3(256), 0, stream, a);
-        return hipGetLastError();
+        // plan-space generality: the pipelined grouped kernel where it takes the shape
+        if (!split && qgemm_w4_takes(a) && !glue) return launch_qgemm_w4(a, stream);
+        return small();
     }
     int v = variant;
-    if (v < 0 || VARIANTS[v].w_bits != a.w_bits || a.K % VARIANTS[v].BK != 0) v = choose_variant(a);
-    if (a.w_bits == 4) {
-        // group sizes other than 128 run on the variants that end a group at any 32-wide K slice
-        static const int any_group = find_variant("w4 any-group 64x64 bk128 4w occ4");
-        if (a.group != 128 && !is_any_group(v)) v = any_group;
-        if (__builtin_strstr(VARIANTS[v].name, "w4 pipelined") && !qgemm_w4_takes(a)) v = any_group;
-        // the pipelined 4-bit kernel keeps the group scales of a tile in LDS: at most 40 groups (K <= 5120)
-        if (a.K > 128 * 40 && __builtin_strncmp(VARIANTS[v].name, "w4 dma", 6) == 0)
-            v = find_variant("w4 128x64 bk128 4w occ3");
+    if (v >= 0 && (VARIANTS[v].w_bits != a.w_bits || a.K % VARIANTS[v].BK != 0)) v = -1;
+    if (v >= 0 && __builtin_strstr(VARIANTS[v].name, "split-K") && !qgemm_split_takes(a, VARIANTS[v].BM)) v = -1;
+    if (v < 0 && split) return small();
+    // 4-bit layers: the pipelined kernel with the tile that suits the shape
+    if (a.w_bits == 4 && (v < 0 || __builtin_strstr(VARIANTS[v].name, "pipelined"))) {
+        if (!qgemm_w4_takes(a)) return small();
+        return v < 0 ? launch_qgemm_w4(a, stream) : VARIANTS[v].run(a, stream);
     }
-    if (a.act != 0 || a.residual != nullptr || a.gate != nullptr || a.row_absmax != nullptr) {
+    // the DMA kernels need 16-byte loads along K and whole K steps of 128 bytes
+    const bool fast = (a.K * (a.w_bits == 16 ? 2 : 1)) % 128 == 0 && ((uintptr_t)a.q % 16 == 0) && ((uintptr_t)a.w % 16 == 0);
+    if (v < 0) {
+        if (!fast) return small();
+        v = choose_variant(a);
+    } else if (!fast && !__builtin_strstr(VARIANTS[v].name, "edge")) {
+        return small();
+    }
+    if (glue) {
         // block glue in the epilogue: only the shape-chosen tiles carry it
         if (!VARIANTS[v].run_glue) v = choose_variant(a);
         // the prefetched gate and residual pieces need registers the persistent tiles do not have left

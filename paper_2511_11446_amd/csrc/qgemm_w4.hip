@@ -22,15 +22,17 @@
 
 namespace ql {
 
-typedef __attribute__((address_space(3))) void lds_void_w4;
-
 // WGM_: wavefront rows of the workgroup (2: 128x128 tile, 4: 256x128); SA_/SB_: ring depths of the two operands
 // B8_: the weight operand is int8 codes (128 bytes per row and K step) instead of packed nibbles
 // MAXG_: weight groups along K whose scales the tile keeps in LDS (40: two workgroups per CU; more: one)
-template <int WGM_, int SA_, int SB_, bool B8_ = false, int MAXG_ = 40>
+// T_: 32-wide MFMA tiles per wavefront and direction
+template <int WGM_, int SA_, int SB_, bool B8_ = false, int MAXG_ = 40, int T_ = 2>
 struct TileW4 {
     static constexpr bool B8 = B8_;
-    static constexpr int TM = 2, TN = 2, WGM = WGM_, WGN = 2;
+    static constexpr int TM = T_, TN = T_, WGM = WGM_, WGN = 2;
+    static constexpr int NM = TM * TN;            // MFMAs per quarter of a K step
+    static constexpr int DMA_PER_Q = NM > 1 ? NM - 1 : 2;   // DMA instructions that go behind them
+    static constexpr int WPS = T_ == 2 ? 2 : 4;   // wavefronts per SIMD the registers allow
     static constexpr int NW = WGM * WGN, NT = NW * 64;
     static constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32;
     static constexpr int SA = SA_, SB = SB_;
@@ -57,20 +59,11 @@ struct TileW4 {
     static_assert(A_GROUPS % NW == 0 && B_GROUPS % NW == 0, "every wavefront issues the same number of DMA instructions");
     static_assert(SA >= 2 && SB >= 2 && (SA - SB) * (SA - SB) <= 1, "ring depths differ by at most one");
     static_assert((SA - 1) * A_BYTES >= EPI_BYTES, "epilogue scratch beside stage 0");
-    static_assert(NA + NB <= 9, "the loads of a refill window are issued behind the MFMAs of three quarters");
+    static_assert(NA + NB <= 3 * DMA_PER_Q, "the loads of a refill window are issued behind the MFMAs of three quarters");
     static_assert(WAIT_START <= 63, "vmcnt is a 6-bit counter");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of one CU");
     static_assert(BM <= NT, "one row scale per thread");
 };
-
-// One DMA instruction, buffer form: 64 lanes x 16 bytes from base + lane_off + step_off to the 1024 bytes at lds.  The
-// descriptor and the K-step offset live in scalar registers and the lane's fixed offset in one vector register, so that
-// issuing a load costs no vector ALU work; reads past `bytes` return zero.
-__device__ __forceinline__ void dma16_w4(const void *base, int bytes, unsigned char *lds, unsigned lane_off, int step_off)
-{
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_w4 *)lds, 16, lane_off, step_off, 0, 0);
-}
 
 // int8 value * 16 of the 16 nibbles of two packed words: byte b of a word holds k = b (low nibble) and k = 4 + b (high)
 __device__ __forceinline__ v4i unpack_w4(v2i p)
@@ -90,7 +83,7 @@ __device__ __forceinline__ void unrolled_steps(F &f, int kt, std::integer_sequen
 // arguments, one uniform branch per MFMA
 // EXPORT: the int32 group partial sums are also written to a.acc_out
 template <class T, int QGF, bool EXPORT, bool GLUE>
-__global__ __launch_bounds__(T::NT, 2) void qgemm_w4(GemmArgs a, int tiles_m, int tiles_n, int nblk_padded, int group_m)
+__global__ __launch_bounds__(T::NT, T::WPS) void qgemm_w4(GemmArgs a, int tiles_m, int tiles_n, int nblk_padded, int group_m)
 {
     constexpr int TM = T::TM, TN = T::TN, BM = T::BM, BN = T::BN, NT = T::NT, NW = T::NW;
     constexpr int SA = T::SA, SB = T::SB, NA = T::NA, NB = T::NB;
@@ -151,10 +144,10 @@ __global__ __launch_bounds__(T::NT, 2) void qgemm_w4(GemmArgs a, int tiles_m, in
     };
     set_goff();
     auto issue_a = [&](int kt, int slot, int i) {
-        dma16_w4(a.q, M * K, smem + slot * T::A_BYTES + (wave + i * NW) * 1024, goffA[i], kt * 128);
+        dma16_buf(a.q, M * K, smem + slot * T::A_BYTES + (wave + i * NW) * 1024, goffA[i], kt * 128);
     };
     auto issue_b = [&](int kt, int slot, int i) {
-        dma16_w4(a.w, B8 ? N * K : N * (K / 2), smem + T::B_RING + slot * T::B_BYTES + (wave + i * NW) * 1024, goffB[i], kt * (B8 ? 128 : 64));
+        dma16_buf(a.w, B8 ? N * K : N * (K / 2), smem + T::B_RING + slot * T::B_BYTES + (wave + i * NW) * 1024, goffB[i], kt * (B8 ? 128 : 64));
     };
     // Refill window j = the loads issued after the hand-over barrier of K step j, into the slots that step used:
     // weight tile of step j+SB and activation tile of step j+SA; the operand with the shallower ring goes first.
@@ -217,7 +210,7 @@ __global__ __launch_bounds__(T::NT, 2) void qgemm_w4(GemmArgs a, int tiles_m, in
     // MFMA number idx of a quarter: tiles in the order (0,0) (1,0) (0,1) (1,1), so that two consecutive MFMAs share one
     // unpacked weight operand.      // restart: a compile-time tag (groups of 128: every K step opens one) or a wavefront-uniform flag.
     auto mma_one = [&](auto restart, const v4i(&af)[TM], const v4i &bf, int idx) {
-        const int i = idx & 1, j = idx >> 1;
+        const int i = idx % TM, j = idx / TM;
         if (restart) {
             // The fold must be complete before the MFMA overwrites the tile's accumulators in place.  Left to itself the
             // compiler sinks the fold to the end of the K step and starts the MFMAs into a second set of 64 registers,
@@ -238,13 +231,13 @@ __global__ __launch_bounds__(T::NT, 2) void qgemm_w4(GemmArgs a, int tiles_m, in
         bf0 = operand(bp[0]);
         mma_one(restart_tag, af, bf0, 0);
     };
-    // MFMAs 1..3 of a quarter, one DMA instruction of refill window `win` behind each (loads i0, i0+1, i0+2)
+    // the other MFMAs of a quarter, one DMA instruction of refill window `win` behind each (loads i0, i0+1, ...)
     auto quarter_tail = [&](auto restart_tag, const v4i(&af)[TM], const bfrag_t(&bp)[TN], const v4i &bf0, bool on, int win, int slot_a,
                             int slot_b, int i0) {
-        const v4i bf1 = operand(bp[1]);
+        const v4i bf1 = operand(bp[TN - 1]);
 #pragma unroll
-        for (int idx = 1; idx < 4; ++idx) {
-            mma_one(restart_tag, af, idx < 2 ? bf0 : bf1, idx);
+        for (int idx = 1; idx <= T::DMA_PER_Q; ++idx) {
+            if (idx < T::NM) mma_one(restart_tag, af, idx < TM ? bf0 : bf1, idx);
             const int li = i0 + idx - 1;
             if (li < NA + NB) {
                 if (on) issue_win(win, slot_a, slot_b, li);
@@ -360,9 +353,9 @@ __global__ __launch_bounds__(T::NT, 2) void qgemm_w4(GemmArgs a, int tiles_m, in
                 }
             };
             // quarter 0 (fragments 0) while reading quarter 1; the rest of refill window kt-1 goes behind its MFMAs
-            step(restart_at(s_tag, std::integral_constant<int, 0>{}), af0, bp0, [&]() { read_frags(sa, sb, 1, af1, bp1); }, std::false_type{}, refill, kt - 1, pa, pb, 3);
+            step(restart_at(s_tag, std::integral_constant<int, 0>{}), af0, bp0, [&]() { read_frags(sa, sb, 1, af1, bp1); }, std::false_type{}, refill, kt - 1, pa, pb, T::DMA_PER_Q);
             // quarter 1 while reading quarter 2
-            step(restart_at(s_tag, std::integral_constant<int, 1>{}), af1, bp1, [&]() { read_frags(sa, sb, 2, af0, bp0); }, std::false_type{}, refill, kt - 1, pa, pb, 6);
+            step(restart_at(s_tag, std::integral_constant<int, 1>{}), af1, bp1, [&]() { read_frags(sa, sb, 2, af0, bp0); }, std::false_type{}, refill, kt - 1, pa, pb, 2 * T::DMA_PER_Q);
             // quarter 2 while reading quarter 3
             step(restart_at(s_tag, std::integral_constant<int, 2>{}), af0, bp0, [&]() { read_frags(sa, sb, 3, af1, bp1); }, std::false_type{}, false, 0, 0, 0, NA + NB);
             // quarter 3: after its first MFMA the hand-over (step kt+1 must be in LDS; after the barrier this step's slots
@@ -382,7 +375,7 @@ __global__ __launch_bounds__(T::NT, 2) void qgemm_w4(GemmArgs a, int tiles_m, in
         }
         // the last group's partial sums
 #pragma unroll
-        for (int idx = 0; idx < 4; ++idx) fold_tile(idx & 1, idx >> 1);
+        for (int idx = 0; idx < T::NM; ++idx) fold_tile(idx % TM, idx / TM);
         __syncthreads();
 
         // ---- the tile being written out; the workgroup moves on to its next tile first and requests that tile's first
@@ -494,47 +487,63 @@ static hipError_t run_w4(const GemmArgs &a, hipStream_t s)
 // more than 40 groups (K = 4608 with groups of 32 or 64): a table of up to 144 groups, one workgroup per CU
 constexpr int W4_MANY_GROUPS = 144;
 
+
+
+
 bool qgemm_w4_takes(const GemmArgs &a)
 {
-    if (a.s_ag && (a.R % 128 != 0 || a.M % a.R != 0)) return false;   // channel-group activation scales: tiles inside one scale block
-    if (a.w_grouped)
-        return a.w_bits == 8 && a.K % 128 == 0 && a.group % 32 == 0 && a.K % a.group == 0 && a.K / a.group <= TileW4<2, 3, 2>::MAX_GROUPS &&
-               (uintptr_t)a.q % 16 == 0 && (uintptr_t)a.w % 16 == 0;
-    return a.w_bits == 4 && a.K % 128 == 0 && a.group % 32 == 0 && a.K % a.group == 0 && a.K / a.group <= W4_MANY_GROUPS &&
-           (uintptr_t)a.q % 16 == 0 && (uintptr_t)a.w % 16 == 0;
+    if (a.K % 128 != 0 || a.group % 32 != 0 || a.K % a.group != 0 || (uintptr_t)a.q % 16 != 0 || (uintptr_t)a.w % 16 != 0) return false;
+    if (a.s_ag && (a.R % 64 != 0 || a.M % a.R != 0)) return false;   // channel-group activation scales: tiles inside one scale block
+    return a.w_grouped ? a.w_bits == 8 && a.K / a.group <= W4_MANY_GROUPS : a.w_bits == 4 && a.K / a.group <= W4_MANY_GROUPS;
 }
 
-hipError_t launch_qgemm_w4(const GemmArgs &a, hipStream_t stream)
+template <int T, bool B8, bool MANY>
+static hipError_t run_w4_tile(const GemmArgs &a, hipStream_t stream)
 {
-    using T = TileW4<2, 3, 2>;
+    using TT = TileW4<2, 3, 2, B8, MANY ? W4_MANY_GROUPS : 40, T>;
     const bool glue = a.act != 0 || a.residual != nullptr || a.gate != nullptr || a.row_absmax != nullptr;
-    if (a.w_grouped) {
-        // int8 codes with group scales: one workgroup per CU (the weight ring is twice as large)
-        using T8 = TileW4<2, 3, 2, true>;
-        if (glue) return hipErrorInvalidValue;
-        return a.acc_out ? run_w4<T8, 0, true, false>(a, stream) : run_w4<T8, 0, false, false>(a, stream);
+    if (a.acc_out) return run_w4<TT, 0, true, !B8>(a, stream);   // verification: group partial sums exported
+    if constexpr (B8) {
+        if (glue) return hipErrorInvalidValue;                   // no call asks for glue on int8-held codes
+    } else {
+        if (glue) return a.group == 128 ? run_w4<TT, 4, false, true>(a, stream) : run_w4<TT, 0, false, true>(a, stream);
     }
-    if (a.K / a.group > T::MAX_GROUPS) {
-        using TG = TileW4<2, 3, 2, false, W4_MANY_GROUPS>;
-        if (a.acc_out) return run_w4<TG, 0, true, true>(a, stream);
-        if (glue) return run_w4<TG, 0, false, true>(a, stream);
-        if (a.group == 32) return run_w4<TG, 1, false, false>(a, stream);
-        if (a.group == 64) return run_w4<TG, 2, false, false>(a, stream);
-        return run_w4<TG, 0, false, false>(a, stream);
-    }
-    if (a.acc_out) return run_w4<T, 0, true, true>(a, stream);   // verification: group partial sums exported
-    if (glue) return a.group == 128 ? run_w4<T, 4, false, true>(a, stream) : run_w4<T, 0, false, true>(a, stream);
     // the group set of Algorithm 1 (32, 64, 128, 192, 288) with the restart pattern unrolled, when K holds whole periods of it
     const int nk = a.K / 128;
-    switch (a.group) {
-    case 32: return run_w4<T, 1, false, false>(a, stream);
-    case 64: return run_w4<T, 2, false, false>(a, stream);
-    case 128: return run_w4<T, 4, false, false>(a, stream);
-    case 192: if (nk % 3 == 0) return run_w4<T, 6, false, false>(a, stream); break;
-    case 288: if (nk % 9 == 0) return run_w4<T, 9, false, false>(a, stream); break;
-    default: break;
+    if (a.group == 32) return run_w4<TT, 1, false, false>(a, stream);
+    if (a.group == 64) return run_w4<TT, 2, false, false>(a, stream);
+    if constexpr (!MANY) {                                       // larger groups number more than 40 only beyond K = 5120
+        if (a.group == 128) return run_w4<TT, 4, false, false>(a, stream);
+        if (a.group == 192 && nk % 3 == 0) return run_w4<TT, 6, false, false>(a, stream);
+        if (a.group == 288 && nk % 9 == 0) return run_w4<TT, 9, false, false>(a, stream);
     }
-    return run_w4<T, 0, false, false>(a, stream);
+    return run_w4<TT, 0, false, false>(a, stream);
+}
+
+template <int T>
+static hipError_t launch_w4_tile(const GemmArgs &a, hipStream_t stream)
+{
+    const bool many = a.K / a.group > 40;
+    if (a.w_grouped) return many ? run_w4_tile<T, true, true>(a, stream) : run_w4_tile<T, true, false>(a, stream);
+    return many ? run_w4_tile<T, false, true>(a, stream) : run_w4_tile<T, false, false>(a, stream);
+}
+
+hipError_t launch_qgemm_w4_64(const GemmArgs &a, hipStream_t stream) { return launch_w4_tile<1>(a, stream); }
+hipError_t launch_qgemm_w4_128(const GemmArgs &a, hipStream_t stream)
+{
+    return a.s_ag && a.R % 128 != 0 ? launch_w4_tile<1>(a, stream) : launch_w4_tile<2>(a, stream);
+}
+
+// 64x64 tiles (four workgroups of four wavefronts per CU, 32x32 per wavefront) or 128x128 (two, 64x64 per wavefront).  The
+// small tiles hide the folds and the hand-overs behind more wavefronts but move twice the operand bytes; they win while all
+// of them are resident at once (1024), up to about twice as many where K is short, and wherever more than 40 groups leave
+// the large tiles one workgroup per CU.  M = 2048, K = 4608, N = 1152, group 128: 28 against 34 us; M = 8192: 80 against 74; group 32:
+// 134 against 198.
+hipError_t launch_qgemm_w4(const GemmArgs &a, hipStream_t stream)
+{
+    const long long tiles = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64);
+    const bool small = a.K / a.group > 40 || tiles <= 1024 || (a.K <= 1536 && tiles <= 2304);
+    return small ? launch_qgemm_w4_64(a, stream) : launch_qgemm_w4_128(a, stream);
 }
 
 // Pair order (byte i of a row: k = 2i low nibble, k = 2i+1 high nibble) -> the storage order unpack_w4 reads (byte j of a

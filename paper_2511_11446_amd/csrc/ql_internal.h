@@ -41,6 +41,8 @@ inline size_t daq_parts_per_block(int64_t K, int64_t R)
 }
 
 hipError_t launch_daq(const DaqArgs &a, hipStream_t stream);
+// the first pass alone: partial maxima of every scale block (daq_parts_per_block of them) into a.partmax
+hipError_t launch_daq_part_absmax(const DaqArgs &a, hipStream_t stream);
 // eq. (4) with channel groups: scales [M/R, K/cg], blockmax workspace of the same count; K % 8 == 0, cg % 8 == 0, K/cg <= 1024
 hipError_t launch_daq_cg(const DaqArgs &a, int cg, hipStream_t stream);
 // DAQ whose row maxima are already known (row_absmax [M], binary16 bit patterns): scales and the quantize pass only
@@ -86,6 +88,11 @@ struct GemmArgs {
                           //    groups are the weight groups
     unsigned *row_absmax; // optional side output [M] (cleared by the caller of the launch): the largest |y[m,:]| as a binary16
                           //    bit pattern, taken on the fp16 values the layer writes (what the next layer's DAQ would find)
+    // quantization inside the GEMM (qgemm_fuse_takes): the fp16 input instead of q and s_a, and where several rows share a
+    // scale the partial maxima of their scale block
+    const void *x;            // [M,K] fp16, or null
+    const unsigned *partmax;  // [M/R][parts]
+    int parts;                // 0: every row its own maximum
 };
 
 int num_gemm_variants();
@@ -96,6 +103,17 @@ hipError_t launch_qgemm(const GemmArgs &a, int variant, hipStream_t stream);
 // the pipelined 4-bit kernel (qgemm_w4.hip): shapes it takes, and its launch (group 128 or any 32 j, exports, glue)
 bool qgemm_w4_takes(const GemmArgs &a);
 hipError_t launch_qgemm_w4(const GemmArgs &a, hipStream_t stream);
+hipError_t launch_qgemm_w4_64(const GemmArgs &a, hipStream_t stream);    // the same with the tile given
+hipError_t launch_qgemm_w4_128(const GemmArgs &a, hipStream_t stream);
+// any K, N and alignment (qgemm_small.hip): few rows with K split over a workgroup's wavefronts, and register-staged tiles
+bool qgemm_split_takes(const GemmArgs &a, int tile);
+int qgemm_split_choice(const GemmArgs &a);   // tile (16 or 32) where splitting K is the fastest, else 0
+bool qgemm_fuse_takes(const GemmArgs &a);    // one launch that quantizes its own input (a.x) instead of DAQ and GEMM
+hipError_t launch_qgemm_fused(const GemmArgs &a, hipStream_t stream);
+hipError_t launch_qgemm_split32(const GemmArgs &a, hipStream_t stream);
+hipError_t launch_qgemm_split16(const GemmArgs &a, hipStream_t stream);
+bool qgemm_edge_takes(const GemmArgs &a);
+hipError_t launch_qgemm_edge(const GemmArgs &a, hipStream_t stream);
 // pair-order nibbles (device) -> the 4-bit storage order (device); blocks = N*K/8 four-byte blocks
 hipError_t launch_prepack_w4(const void *pairs, void *packed, long long blocks, hipStream_t stream);
 

@@ -1,0 +1,88 @@
+"""Layers of few rows and of inner sizes that no K step divides: the split-K kernel (with and without the quantization inside
+the GEMM), the register-staged kernel and the 64x64 tiles of the pipelined 4-bit kernel, at the edges of their tiles, steps,
+rounds and alignments, against the CPU oracle."""
+import numpy as np
+import pytest
+
+import workload
+from test_gpu_parity import _f16_tolerance, assert_y_close, dev, gpu, host, run_w8, say  # noqa: F401  (gpu: fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+# M, K, N, R
+W8 = [(1, 16, 1, 1), (15, 48, 33, 1), (17, 144, 16, 1), (31, 1536, 31, 1), (33, 1552, 65, 1),   # 16x16 tiles; quantization inside up to K = 1536
+      (64, 1152, 96, 64), (96, 576, 48, 32),            # several rows per scale: partial maxima, then one launch
+      (100, 4608, 700, 1), (330, 2320, 1160, 1),        # 32x32 tiles, two rounds of them
+      (130, 1160, 70, 1), (130, 1157, 70, 1), (3, 7, 5, 1), (2100, 136, 1100, 1)]   # 8-byte and byte-wise row ends, both tile sizes
+
+
+@pytest.mark.parametrize("M,K,N,R", W8)
+def test_w8_small_and_ragged(gpu, orc, M, K, N, R):
+    say("w8 small", M, K, N, R)
+    run_w8(gpu, orc, M, K, N, R, ("small", M, K, N), use_bias=(M % 2 == 0), check_exact=True)
+
+
+@pytest.mark.parametrize("offset", [1, 2, 8])
+def test_w8_misaligned_operands(gpu, orc, offset):
+    """Weights that start `offset` bytes off a 16-byte boundary: the DMA kernels must step aside."""
+    import torch
+    M, K, N = 70, 256, 40
+    say("w8 misaligned", offset)
+    x = workload.activations(M, K, "mis")
+    lw = workload.layer_weights("mis", K, N, 8, "mis")
+    ref = orc.qlinear_w8a8(x, 1, lw["w"], lw["s_w"], lw["bias"], want_debug=False)["y"]
+    buf = torch.zeros(N * K + 16, dtype=torch.int8, device="cuda")
+    view = buf[offset:offset + N * K].view(N, K)
+    view.copy_(dev(lw["w"]))
+    y = gpu.qlinear_w8a8(dev(x), 1, view, dev(lw["s_w"]), dev(lw["bias"]))
+    assert assert_y_close(host(y), ref) == 0
+
+
+# M, K, N, group: odd numbers of 32-wide slices, one and several rounds of groups, 64x64 tiles with ragged edges
+W4 = [(1, 32, 1, 32), (17, 288, 33, 288), (16, 96, 16, 96), (5, 4608, 17, 32), (40, 4608, 100, 64), (33, 1184, 40, 32), (70, 1184, 40, 32),
+      (200, 1152, 1160, 192), (520, 1152, 1160, 288), (321, 4608, 193, 32), (2100, 160, 40, 32)]
+
+
+@pytest.mark.parametrize("M,K,N,group", W4)
+def test_w4_small_and_ragged(gpu, orc, M, K, N, group):
+    say("w4 small", M, K, N, group)
+    x = workload.activations(M, K, "small4", group)
+    lw = workload.layer_weights("small4", K, N, 4, group) if K % 128 == 0 else dict(w=workload.w4_codes(N, K, "small4"), bias=workload.bias(N, "small4"))
+    sw = workload.w4_scales_group(N, K, group, "small4")
+    q, s = orc.daq(x, 1)
+    P = orc.gemm_w4g(q, orc.pack_w4(lw["w"]), group, nthreads=8)
+    ref = orc.epilogue_w4(P, s, 1, sw, lw["bias"])
+    w4 = dev(gpu.ql_pack_w4_host(lw["w"]))
+    out = gpu.qlinear_w4a8(dev(x), 1, w4, dev(sw), dev(lw["bias"]), debug=True, group=group)
+    assert np.array_equal(host(out["P"]), P)
+    assert assert_y_close(host(out["y"]), ref) == 0
+    y = gpu.qlinear_w4a8(dev(x), 1, w4, dev(sw), dev(lw["bias"]), group=group)      # few rows: quantized inside the GEMM
+    assert assert_y_close(host(y), ref) == 0
+
+
+@pytest.mark.parametrize("M,K,N,R,group,storage", [(64, 384, 40, 32, 32, 8), (192, 384, 300, 64, 96, 8), (1024, 384, 600, 64, 128, 4), (96, 96, 24, 24, 32, 8),
+                                                   (256, 4608, 1100, 128, 64, 8)])
+def test_channel_group_scales_by_block_size(gpu, orc, M, K, N, R, group, storage):
+    say("channel groups", M, K, N, R, group, storage)
+    g = workload.rng("small-cg", M, K, N)
+    x = workload.activations(M, K, "small-cg", sigma=0.8)
+    codes = g.integers(-8, 8, (N, K), dtype=np.int8)
+    s_w, bias = workload.w4_scales_group(N, K, group, "small-cg"), workload.bias(N, "small-cg")
+    q, a = orc.daq_cg(x, R, group, nthreads=8)
+    ref = orc.epilogue_cg(orc.gemm_i8g(q, codes, group, nthreads=16), a, R, s_w, bias)
+    w = dev(gpu.ql_pack_w4_host(codes)) if storage == 4 else dev(codes)
+    y = gpu.qlinear_grouped(dev(x), R, w, dev(s_w), group, dev(bias), act_group=group, storage=storage)
+    assert assert_y_close(host(y), ref) == 0
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 8, 1), (17, 24, 33), (40, 1160, 100), (130, 1154, 70), (500, 4608, 1152)])
+def test_f16_small_and_ragged(gpu, orc, M, K, N):
+    say("f16 small", M, K, N)
+    g = workload.rng("small16", M, K, N)
+    x = workload.activations(M, K, "small16")
+    w = (g.standard_normal((N, K), dtype=np.float32) * 0.05).astype(np.float16)
+    b = workload.bias(N, "small16")
+    ref = orc.linear_f16(x, w, b, nthreads=16)
+    y = host(gpu.qlinear_f16(dev(x), dev(w), dev(b)))
+    assert (np.abs(y.astype(np.float64) - ref.astype(np.float64)) <= _f16_tolerance(x, w, ref)).all()

@@ -44,14 +44,14 @@ int check_shape(int64_t M, int64_t K, int64_t R, int64_t N)
 inline bool misaligned(const void *p, size_t a) { return p && ((uintptr_t)p % a) != 0; }
 
 // DAQ scratch for R > 1.  Absmax: [block maxima M/R][partial maxima (M/R) * parts]; percentile: [tau patterns M/R]
-// [selection histograms (M/R) * DAQ_ROBUST_WORDS].  One size covers both, so a workspace serves either mode.
-size_t daq_scratch_bytes(int64_t M, int64_t K, int64_t R)
+// [selection histograms].  One size covers both, so a workspace serves either mode.
+size_t daq_scratch_bytes(int64_t M, int64_t K, int64_t R, bool absmax_only = false)
 {
     if (M < 1 || R <= 1 || M % R != 0) return 0;
     const size_t nblk = (size_t)(M / R);
     const size_t plain = align_up(nblk * ql::daq_parts_per_block(K, R) * 4, 256);
-    const size_t robust = align_up(nblk * ql::DAQ_ROBUST_WORDS * 4, 256);
-    return align_up(nblk * 4, 256) + (plain > robust ? plain : robust);
+    const size_t robust = align_up(ql::daq_hist_bytes(M, K, R), 256);
+    return align_up(nblk * 4, 256) + (plain > robust || absmax_only ? plain : robust);
 }
 
 // eq. (4): rank from the top of the nearest-rank percentile, c = n - ceil(n p) + 1 with n = R*K values per scale block
@@ -73,13 +73,13 @@ struct LayerWs {
     size_t q_off, s_off, bm_off, total;
 };
 
-LayerWs layer_ws(int64_t M, int64_t K, int64_t R)
+LayerWs layer_ws(int64_t M, int64_t K, int64_t R, bool absmax_only = false)
 {
     LayerWs w;
     w.q_off = 0;
     w.s_off = align_up((size_t)(M * K), 256);
     w.bm_off = w.s_off + align_up((size_t)(M / R) * 4, 256);
-    w.total = w.bm_off + daq_scratch_bytes(M, K, R);
+    w.total = w.bm_off + daq_scratch_bytes(M, K, R, absmax_only);
     return w;
 }
 
@@ -607,7 +607,7 @@ int qlinear_w8a8_noalloc(const void *x, int64_t M, int64_t K, int64_t R, const v
     if (rc) return rc;
     rc = check_shape(M, K, R, N);
     if (rc) return rc;
-    if (layer_ws(M, K, R).total > QL_NOALLOC_SCRATCH_BYTES) return QL_ERR_WORKSPACE;
+    if (layer_ws(M, K, R, true).total > QL_NOALLOC_SCRATCH_BYTES) return QL_ERR_WORKSPACE;
     void *ws = nullptr;
     rc = noalloc_scratch(&ws);
     if (rc) return rc;

@@ -8,7 +8,8 @@
 // The selection is exact and works on the 15-bit magnitude patterns of binary16 (their integer order is the numeric
 // order).  One row per scale: the row sits in registers and tau is found by a bitwise binary search (15 counting
 // rounds over the registers).  Several rows per scale: two histogram passes (upper 8 bits, then the lower 7 bits of
-// the values that share the selected upper bits), each followed by a scan that walks the bins from the top.
+// the values that share the selected upper bits) and the quantize pass; whoever needs a selection scans the bins from the top
+// itself.
 #include "daq_device.h"
 
 namespace ql {
@@ -85,15 +86,108 @@ __device__ __forceinline__ RobustScale robust_scale(unsigned tau_bits, float qma
     return s;
 }
 
+// ---- selection from histograms -------------------------------------------------------------------------------------
+// A magnitude has 15 bits: level 0 counts by the upper 8, level 1 by the lower 7 of the magnitudes whose upper bits level 0
+// selected.  Where a scale block has few parts (HIST_FEW), every part leaves its own 16-bit histogram with plain stores and
+// the next pass adds them up: no clearing pass, no global atomics, no launch that only selects.  Scratch (a.hist):
+// [block][part][256] level 0, then [block][part][128] level 1, 16 bits each; blockmax[b] = selected upper bits | rank left
+// inside that bin << 8.  With more parts: 32-bit counts collected with atomics, [block][DAQ_ROBUST_WORDS].
+constexpr int HIST_PART = DAQ_HIST_PART;
+constexpr int HIST_BINS = 256;
+
+// The bin, counted from the top, in which the `left`-th largest value falls, and the rank left inside it.  One wavefront; bins
+// 0 .. 64 * PER - 1 at `count`.
+template <int PER>
+__device__ __forceinline__ void select_bin(const unsigned *count, unsigned &left, unsigned &bin)
+{
+    const int lane = threadIdx.x & 63;
+    unsigned c[PER], sum = 0;       // lane 0 has the highest bins
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        c[i] = count[64 * PER - 1 - (lane * PER + i)];
+        sum += c[i];
+    }
+    unsigned upto = sum;            // inclusive sum over the lanes
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+        const unsigned o = __shfl_up(upto, d);
+        if (lane >= d) upto += o;
+    }
+    unsigned before = upto - sum;
+    const unsigned long long hit = __ballot(upto >= left);
+    const int owner = hit ? __ffsll((long long)hit) - 1 : 63;
+    unsigned b = 0, l = 0;
+    bool found = false;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (!found && (before + c[i] >= left || i == PER - 1)) {
+            found = true;
+            b = 64 * PER - 1 - (lane * PER + i);
+            l = left - before;
+        }
+        before += c[i];
+    }
+    bin = __shfl(b, owner);
+    left = __shfl(l, owner);
+}
+
+// level 0: sums of the parts' histograms into LDS, then the selection, by the whole workgroup
+__device__ __forceinline__ void first_selection(const DaqArgs &a, unsigned b, int parts, unsigned *bins, unsigned &prefix, unsigned &left)
+{
+    __shared__ unsigned found[2];
+    const unsigned short *h0 = reinterpret_cast<const unsigned short *>(a.hist) + (size_t)b * parts * 256;
+    unsigned n = 0;
+#pragma unroll 8
+    for (int p = 0; p < parts; ++p) n += h0[p * 256 + threadIdx.x];
+    bins[threadIdx.x] = n;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        unsigned l = a.top_rank, bin;
+        select_bin<4>(bins, l, bin);
+        if (threadIdx.x == 0) {
+            found[0] = bin;
+            found[1] = l;
+        }
+    }
+    __syncthreads();
+    prefix = found[0];
+    left = found[1];
+}
+
+// level 1: the magnitude pattern of tau
+__device__ __forceinline__ unsigned second_selection(const DaqArgs &a, int b, unsigned *bins)
+{
+    __shared__ unsigned tau;
+    const int parts = a.quant_parts;
+    const unsigned short *h1 = reinterpret_cast<const unsigned short *>(a.hist) + (size_t)(a.M / a.R) * parts * 256 + (size_t)b * parts * 128;
+    if (threadIdx.x < 128) {
+        unsigned n = 0;
+#pragma unroll 8
+        for (int p = 0; p < parts; ++p) n += h1[p * 128 + threadIdx.x];
+        bins[threadIdx.x] = n;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const unsigned first = a.blockmax[b];
+        unsigned l = first >> 8, bin;
+        select_bin<2>(bins, l, bin);
+        if (threadIdx.x == 0) tau = (first & 0xffu) << 7 | bin;
+    }
+    __syncthreads();
+    return tau;
+}
+
 // ---- one row per scale, row in registers ------------------------------------------------------------------------
-// mode DAQ_FUSED: select tau, then quantize; mode DAQ_QUANT: tau of the row's block comes from blockmax
+// mode DAQ_FUSED: select tau, then quantize; mode DAQ_QUANT: tau of the row's block comes from the second histogram pass
+// (quant_parts partial histograms, R % 4 == 0: the workgroup's rows share a block) or from blockmax
 template <int CH>
 __global__ __launch_bounds__(256) void daq_rows_robust(DaqArgs a, int mode)
 {
     const int lane = threadIdx.x & 63;
     const int wg = mode == DAQ_QUANT ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
     const int row = wg * 4 + (threadIdx.x >> 6);
-    if (row >= a.M) return;
+    __shared__ unsigned bins[HIST_BINS];
+    if (row >= a.M) return;   // whole workgroups at a time where the rows share a block
     const int nch = a.K >> 3;
     const uint4 *xr = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(a.x) + (size_t)row * a.K);
     uint4 v[CH];
@@ -103,7 +197,9 @@ __global__ __launch_bounds__(256) void daq_rows_robust(DaqArgs a, int mode)
         v[i] = c < nch ? xr[c] : make_uint4(0, 0, 0, 0);
     }
     unsigned tau_bits;
-    if (mode == DAQ_QUANT) {
+    if (mode == DAQ_QUANT && a.quant_parts > 0) {
+        tau_bits = second_selection(a, row / a.R, bins);
+    } else if (mode == DAQ_QUANT) {
         tau_bits = a.blockmax[row / a.R];
     } else {
         // Each half word is 0x8000 | magnitude (OR-ing 0x8000 in overwrites the sign bit); subtracting T from both
@@ -210,71 +306,113 @@ __global__ __launch_bounds__(256) void daq_rows_robust_loop(DaqArgs a, int mode)
     for (int k = lane; k < a.K; k += 64) qs[k] = (int8_t)robust_code(half_bits_to_float(xs[k]), s.tau, s.alpha, qmax);
 }
 
-// ---- several rows per scale: histogram selection ------------------------------------------------------------------
-// Scratch per scale block b (32-bit words): hist[b*HIST_WORDS + 0..255] counts by magnitude bits 14..7,
-// [256] the selected upper bits, [257] the rank that is left inside that bin, [258..385] counts by bits 6..0.
-constexpr int HIST_WORDS = DAQ_ROBUST_WORDS;
-constexpr int HIST_PART = 16384;   // elements per workgroup
-
-// level 0: bins = bits 14..7 of every magnitude; level 1: bins = bits 6..0 of the magnitudes whose upper bits were selected
-__global__ __launch_bounds__(256) void daq_hist(const unsigned short *x, size_t n_per_block, unsigned parts_per_block, int level,
-                                                unsigned *hist)
+// ---- several rows per scale: histogram passes ------------------------------------------------------------------------
+// FEW: partial histograms (see above); otherwise atomics into hist[b*DAQ_ROBUST_WORDS ...]: 0..255 level 0, [256] selected
+// upper bits, [257] rank left, [258..385] level 1.
+// The magnitudes of a real activation tensor fall into some thirty of the 256 bins: sixteen copies of the LDS histogram, one
+// per quarter wavefront, keep the lanes of an LDS atomic from queueing for one word.
+template <bool FEW>
+__global__ __launch_bounds__(256) void daq_hist(DaqArgs a, size_t n_per_block, unsigned parts_per_block, int level)
 {
-    __shared__ unsigned h[256];
+    constexpr int COPIES = 16;
+    __shared__ unsigned h[COPIES * (HIST_BINS + 1)];
+    __shared__ unsigned bins[HIST_BINS];
     const unsigned b = blockIdx.x / parts_per_block, part = blockIdx.x - b * parts_per_block;
-    unsigned *hb = hist + (size_t)b * HIST_WORDS;
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    const unsigned prefix = level ? hb[256] : 0;
-    const unsigned short *xb = x + (size_t)b * n_per_block;
+    const unsigned short *xb = static_cast<const unsigned short *>(a.x) + (size_t)b * n_per_block;
     const size_t i0 = (size_t)part * HIST_PART;
     const size_t i1 = i0 + HIST_PART < n_per_block ? i0 + HIST_PART : n_per_block;
     const bool vec = ((uintptr_t)(xb + i0) % 16 == 0);
+    const size_t pieces = vec ? (i1 - i0) / 8 : 0;
+    constexpr int U = HIST_PART / 8 / 256;   // 16-byte pieces per thread
+    uint4 v[U];
+    const uint4 *xp = reinterpret_cast<const uint4 *>(xb + i0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const size_t p = threadIdx.x + 256 * u;
+        if (p < pieces) v[u] = xp[p];
+    }
+    for (int i = threadIdx.x; i < COPIES * (HIST_BINS + 1); i += 256) h[i] = 0;
+    unsigned prefix = 0;
+    if (level) {
+        if (FEW && parts_per_block <= DAQ_HIST_SELF) {
+            unsigned left;
+            first_selection(a, b, (int)parts_per_block, bins, prefix, left);
+            if (part == 0 && threadIdx.x == 0) a.blockmax[b] = prefix | left << 8;
+        } else if (FEW) {
+            prefix = a.blockmax[b] & 0xffu;
+        } else {
+            prefix = a.hist[(size_t)b * DAQ_ROBUST_WORDS + 256];
+        }
+    }
+    __syncthreads();
+    unsigned *mine = h + (threadIdx.x >> 4) * (HIST_BINS + 1);
     auto tally = [&](unsigned m) {
-        if (level == 0) atomicAdd(&h[m >> 7], 1u);
-        else if ((m >> 7) == prefix) atomicAdd(&h[m & 127u], 1u);
+        if (level == 0) atomicAdd(&mine[m >> 7], 1u);
+        else if ((m >> 7) == prefix) atomicAdd(&mine[m & 127u], 1u);
     };
-    if (vec) {
-        const size_t pieces = (i1 - i0) / 8;
-        const uint4 *xp = reinterpret_cast<const uint4 *>(xb + i0);
-        for (size_t p = threadIdx.x; p < pieces; p += 256) {
-            const uint4 v = xp[p];
-            const unsigned w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (threadIdx.x + 256 * (size_t)u < pieces) {
+            const unsigned w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 tally(w[j] & 0x7fffu);
                 tally((w[j] >> 16) & 0x7fffu);
             }
         }
-        for (size_t i = i0 + pieces * 8 + threadIdx.x; i < i1; i += 256) tally(xb[i] & 0x7fffu);
-    } else {
-        for (size_t i = i0 + threadIdx.x; i < i1; i += 256) tally(xb[i] & 0x7fffu);
     }
+    for (size_t i = i0 + pieces * 8 + threadIdx.x; i < i1; i += 256) tally(xb[i] & 0x7fffu);
     __syncthreads();
-    const unsigned cnt = h[threadIdx.x];
-    if (cnt && (level == 0 || threadIdx.x < 128)) atomicAdd(hb + (level ? 258 : 0) + threadIdx.x, cnt);
+    unsigned cnt = 0;
+#pragma unroll
+    for (int c = 0; c < COPIES; ++c) cnt += h[c * (HIST_BINS + 1) + threadIdx.x];
+    if (FEW) {
+        unsigned short *h16 = reinterpret_cast<unsigned short *>(a.hist);
+        if (level == 0) h16[(size_t)blockIdx.x * 256 + threadIdx.x] = (unsigned short)cnt;
+        else if (threadIdx.x < 128) h16[(size_t)gridDim.x * 256 + (size_t)blockIdx.x * 128 + threadIdx.x] = (unsigned short)cnt;
+    } else if (cnt && (level == 0 || threadIdx.x < 128)) {
+        atomicAdd(a.hist + (size_t)b * DAQ_ROBUST_WORDS + (level ? 258 : 0) + threadIdx.x, cnt);
+    }
 }
 
-// one thread per scale block walks the bins from the top until the wanted rank falls inside one
-__global__ void daq_hist_select(unsigned *hist, int nblk, int level, unsigned top_rank, unsigned *blockmax)
+// many parts: one wavefront per scale block
+__global__ __launch_bounds__(64) void daq_hist_select(DaqArgs a, int level)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nblk) return;
-    unsigned *hb = hist + (size_t)b * HIST_WORDS;
-    unsigned left = level ? hb[257] : top_rank;
-    const unsigned *bins = hb + (level ? 258 : 0);
-    int bin = (level ? 128 : 256) - 1;
-    for (; bin > 0; --bin) {
-        const unsigned c = bins[bin];
-        if (c >= left) break;
-        left -= c;
-    }
+    unsigned *hb = a.hist + (size_t)blockIdx.x * DAQ_ROBUST_WORDS;
+    unsigned left = level ? hb[257] : a.top_rank, bin;
+    if (level == 0) select_bin<4>(hb, left, bin);
+    else select_bin<2>(hb + 258, left, bin);
+    if (threadIdx.x != 0) return;
     if (level == 0) {
-        hb[256] = (unsigned)bin;
+        hb[256] = bin;
         hb[257] = left;
     } else {
-        blockmax[b] = (hb[256] << 7) | (unsigned)bin;
+        a.blockmax[blockIdx.x] = (hb[256] << 7) | bin;
     }
+}
+
+// partial histograms whose consumers do not select for themselves: one workgroup per scale block adds them up, four threads
+// per bin, and selects; level 0 leaves blockmax = upper bits | rank left << 8, level 1 the pattern of tau
+__global__ __launch_bounds__(1024) void daq_part_select(DaqArgs a, int parts, int level)
+{
+    __shared__ unsigned bins[4][HIST_BINS];
+    const int width = level ? 128 : 256, b = blockIdx.x, bin_of = threadIdx.x & 255, q = threadIdx.x >> 8;
+    const unsigned short *h = reinterpret_cast<const unsigned short *>(a.hist) + (level ? (size_t)gridDim.x * parts * 256 : 0) + (size_t)b * parts * width;
+    unsigned n = 0;
+    if (bin_of < width) {
+#pragma unroll 8
+        for (int p = q; p < parts; p += 4) n += h[p * width + bin_of];
+    }
+    bins[q][bin_of] = n;
+    __syncthreads();
+    if (threadIdx.x < 256) bins[0][threadIdx.x] += bins[1][threadIdx.x] + bins[2][threadIdx.x] + bins[3][threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const unsigned first = level ? a.blockmax[b] : 0;
+    unsigned left = level ? first >> 8 : a.top_rank, bin;
+    if (level == 0) select_bin<4>(bins[0], left, bin);
+    else select_bin<2>(bins[0], left, bin);
+    if (threadIdx.x == 0) a.blockmax[b] = level == 0 ? bin | left << 8 : (first & 0xffu) << 7 | bin;
 }
 
 __global__ void fill_zero_u32(unsigned *p, size_t n)
@@ -315,13 +453,28 @@ hipError_t launch_daq_robust(const DaqArgs &a, hipStream_t stream)
     }
     const int nblk = a.M / a.R;
     const size_t n = (size_t)a.R * a.K;
-    const size_t parts = (n + HIST_PART - 1) / HIST_PART;
-    const size_t words = (size_t)nblk * HIST_WORDS;
+    const unsigned parts = (unsigned)daq_hist_parts(a.K, a.R);
+    const dim3 grid(parts * (unsigned)nblk);
+    if (parts <= DAQ_HIST_FEW && n < (1u << 24)) {
+        // few parts: every consumer adds them up and selects for itself; more: a selection launch in between (M = 8192, R = 256, K =
+        // 4608, 72 parts: 57 us against 77 with twice the part size and no selection launches)
+        const bool self = parts <= DAQ_HIST_SELF;
+        // rows of one workgroup in one block, and a row kernel that holds the row in registers
+        const bool self_rows = self && a.R % 4 == 0 && a.K % 8 == 0 && a.K <= 8192 && (uintptr_t)a.x % 16 == 0 && (uintptr_t)a.q % 8 == 0;
+        DaqArgs q = a;
+        q.quant_parts = self_rows ? (int)parts : 0;
+        for (int level = 0; level < 2; ++level) {
+            hipLaunchKernelGGL(daq_hist<true>, grid, dim3(256), 0, stream, a, n, parts, level);
+            if (level == 0 ? !self : !self_rows) hipLaunchKernelGGL(daq_part_select, dim3(nblk), dim3(1024), 0, stream, a, (int)parts, level);
+        }
+        run_robust_rows(q, DAQ_QUANT, stream);
+        return hipGetLastError();
+    }
+    const size_t words = (size_t)nblk * DAQ_ROBUST_WORDS;
     hipLaunchKernelGGL(fill_zero_u32, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream, a.hist, words);
     for (int level = 0; level < 2; ++level) {
-        hipLaunchKernelGGL(daq_hist, dim3((unsigned)(parts * nblk)), dim3(256), 0, stream, static_cast<const unsigned short *>(a.x), n,
-                           (unsigned)parts, level, a.hist);
-        hipLaunchKernelGGL(daq_hist_select, dim3((nblk + 63) / 64), dim3(64), 0, stream, a.hist, nblk, level, a.top_rank, a.blockmax);
+        hipLaunchKernelGGL(daq_hist<false>, grid, dim3(256), 0, stream, a, n, parts, level);
+        hipLaunchKernelGGL(daq_hist_select, dim3(nblk), dim3(64), 0, stream, a, level);
     }
     run_robust_rows(a, DAQ_QUANT, stream);
     return hipGetLastError();

@@ -25,9 +25,19 @@ struct DaqArgs {
     // percentile-clipped variant only (launch_daq_robust)
     int qmax;            // 2^(b-1) - 1 for b-bit activation codes
     unsigned top_rank;   // tau = the top_rank-th largest magnitude of a scale block (1 = the maximum)
-    unsigned *hist;      // [M/R][DAQ_ROBUST_WORDS] selection scratch (workspace), R > 1 only
+    unsigned *hist;      // selection scratch (workspace), R > 1 only: daq_hist_bytes()
 };
 constexpr int DAQ_ROBUST_WORDS = 256 + 2 + 128;
+// Partial histograms of the percentile selection: elements per part (at most 65535, so that a 16-bit count holds); parts per
+// scale block up to which the next pass adds them up itself, and up to which a selection launch does (beyond: atomics)
+constexpr unsigned DAQ_HIST_SELF = 20, DAQ_HIST_FEW = 256;
+constexpr unsigned DAQ_HIST_PART = 16384;
+inline size_t daq_hist_parts(int64_t K, int64_t R) { return ((size_t)R * (size_t)K + DAQ_HIST_PART - 1) / DAQ_HIST_PART; }
+inline size_t daq_hist_bytes(int64_t M, int64_t K, int64_t R)
+{
+    const size_t nblk = (size_t)(M / R), parts = daq_hist_parts(K, R);
+    return parts <= DAQ_HIST_FEW ? nblk * parts * (256 + 128) * 2 : nblk * DAQ_ROBUST_WORDS * 4;
+}
 
 // R > 1: the first pass cuts every scale block (R*K contiguous values) into this many parts and leaves one partial
 // maximum per part; 0 when the shape takes the row kernels instead (no partials needed).

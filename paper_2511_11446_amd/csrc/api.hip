@@ -394,7 +394,8 @@ static int check_act_group(int64_t K, int64_t ag)
 size_t daq_cg_workspace_bytes(int64_t M, int64_t K, int64_t R, int64_t act_group)
 {
     if (M < 1 || K < 1 || R < 1 || M % R != 0 || act_group < 1 || K % act_group != 0) return 0;
-    return align_up((size_t)(M / R) * (size_t)(K / act_group) * 4, 256);
+    const int64_t slab = ql::daq_cg_slab_rows(R);
+    return align_up((size_t)(M / (slab ? slab : R)) * (size_t)(K / act_group) * 4, 256);
 }
 
 int daq_quantize_cg(const void *x, int64_t M, int64_t K, int64_t R, int64_t act_group, void *q, void *scales, void *workspace,

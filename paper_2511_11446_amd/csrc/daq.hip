@@ -275,9 +275,69 @@ __global__ __launch_bounds__(256) void daq_cg_quant(DaqArgs a, int cg)
         for (int g = lane; g < G; g += 64) a.scales[(size_t)(row / a.R) * G + g] = alpha_from_bits(bm[g]);
 }
 
+// The same for blocks of rows that DAQ_CG_SLAB divides.  A workgroup takes a slab of rows; a thread keeps one 16-byte piece of
+// columns (hence one channel group) and walks down `1 / rpw` of the slab's rows, so that the group arithmetic - a division
+// by cg, the scale and its reciprocal - is paid once per thread and not per piece.  Pass 1 leaves the slab's maximum per
+// group with plain stores, no clearing pass and no atomics; pass 2 takes the maximum over its block's slabs.
+// M = 4096, K = 1152, R = 256, cg = 128: 32.7 -> 13 us.
+constexpr int DAQ_CG_ROWS = 4;    // rows in flight per thread
+template <bool QUANT>
+__global__ __launch_bounds__(1024) void daq_cg_slab(DaqArgs a, int cg, int slab, int rpw)
+{
+    extern __shared__ unsigned gmax_lds[];
+    const int P = a.K >> 3, G = a.K / cg;
+    const int p = threadIdx.x % P, r0 = threadIdx.x / P, g = p * 8 / cg;
+    const bool on = r0 < rpw;
+    const int row0 = blockIdx.x * slab;
+    unsigned *part = a.blockmax;          // [M / slab][G]
+    float alpha = 1.0f, rcp = 1.0f;
+    if (!QUANT) {
+        for (int i = threadIdx.x; i < G; i += blockDim.x) gmax_lds[i] = 0;
+        __syncthreads();
+    } else if (on) {
+        const unsigned *pm = part + (size_t)(row0 / a.R) * (a.R / slab) * G + g;
+        unsigned m = 0;
+        for (int s = 0; s < a.R / slab; ++s) m = m > pm[(size_t)s * G] ? m : pm[(size_t)s * G];
+        alpha = alpha_from_bits(m);
+        rcp = 1.0f / alpha;
+        if (row0 % a.R == 0 && r0 == 0 && p * 8 % cg == 0) a.scales[(size_t)(row0 / a.R) * G + g] = alpha;
+    }
+    if (on) {
+        const uint4 *x = reinterpret_cast<const uint4 *>(a.x) + (size_t)row0 * P + p;
+        uint2 *q = reinterpret_cast<uint2 *>(a.q) + (size_t)row0 * P + p;
+        unsigned m = 0;
+        for (int r = r0; r < slab; r += rpw * DAQ_CG_ROWS) {
+            uint4 v[DAQ_CG_ROWS];
+#pragma unroll
+            for (int u = 0; u < DAQ_CG_ROWS; ++u) v[u] = r + u * rpw < slab ? x[(size_t)(r + u * rpw) * P] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < DAQ_CG_ROWS; ++u) {
+                if (QUANT) {
+                    if (r + u * rpw < slab) q[(size_t)(r + u * rpw) * P] = daq_piece(v[u], alpha, rcp);
+                } else {
+                    m = absmax_word(absmax_word(absmax_word(absmax_word(m, v[u].x), v[u].y), v[u].z), v[u].w);
+                }
+            }
+        }
+        if (!QUANT) atomicMax(&gmax_lds[g], (m & 0xffffu) > (m >> 16) ? (m & 0xffffu) : (m >> 16));
+    }
+    if (!QUANT) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < G; i += blockDim.x) part[(size_t)blockIdx.x * G + i] = gmax_lds[i];
+    }
+}
+
 hipError_t launch_daq_cg(const DaqArgs &a, int cg, hipStream_t stream)
 {
-    const int n = (a.M / a.R) * (a.K / cg);
+    const int slab = daq_cg_slab_rows(a.R), P = a.K / 8, G = a.K / cg;
+    if (slab > 0 && P <= 1024) {
+        const int rpw = P >= 512 ? 1 : 512 / P;
+        const dim3 grid(a.M / slab), block((P * rpw + 63) / 64 * 64);
+        hipLaunchKernelGGL(daq_cg_slab<false>, grid, block, G * 4, stream, a, cg, slab, rpw);
+        hipLaunchKernelGGL(daq_cg_slab<true>, grid, block, 0, stream, a, cg, slab, rpw);
+        return hipGetLastError();
+    }
+    const int n = (a.M / a.R) * G;
     hipLaunchKernelGGL(fill_u32, dim3((n + 255) / 256), dim3(256), 0, stream, a.blockmax, n, 0u);
     hipLaunchKernelGGL(daq_cg_absmax, dim3((a.M + 3) / 4), dim3(256), 0, stream, a, cg);
     hipLaunchKernelGGL(daq_cg_quant, dim3((a.M + 3) / 4), dim3(256), 0, stream, a, cg);

@@ -42,11 +42,12 @@ struct TileW4 {
     static constexpr int A_BYTES = A_GROUPS * 1024, B_BYTES = B_GROUPS * 1024;
     static constexpr int B_RING = SA * A_BYTES;
     static constexpr int RINGS = SA * A_BYTES + SB * B_BYTES;
-    // the epilogue's scratch (row scales, one 32-row strip per wavefront) lives beside stage 0 of the activation ring,
+    // the epilogue's scratch (row scales, one strip of rows per wavefront) lives beside stage 0 of the activation ring,
     // which by then receives the next tile's first K step
     static constexpr int EPI_OFF = A_BYTES;
     static constexpr int STRIP_OFF = (BM * 4 + 255) / 256 * 256;
-    static constexpr int STRIP_BYTES = 32 * (TN * 64 + 16);
+    static constexpr int STRIP_ROWS = (SA - 1) * A_BYTES >= STRIP_OFF + NW * 32 * (TN * 64 + 16) ? 32 : 16;
+    static constexpr int STRIP_BYTES = STRIP_ROWS * (TN * 64 + 16);
     static constexpr int EPI_BYTES = STRIP_OFF + NW * STRIP_BYTES;
     // group scales of the tile's columns, [column][group] fp16 as in global memory
     static constexpr int MAX_GROUPS = MAXG_;
@@ -424,11 +425,11 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_w4(GemmArgs a, int tiles_
                 constexpr bool ACT = decltype(act_tag)::value;
                 auto act_of = [&](float u) { return ACT ? gelu_tanh_dev(u) : u; };
                 if (a.bias)
-                    store_tile_staged<TM, TN, true, 32>(strip, lane, y, N, em0 + wm * TM * 32, en0 + wn * TN * 32, [&](int i, int j, int r) {
+                    store_tile_staged<TM, TN, true, T::STRIP_ROWS>(strip, lane, y, N, em0 + wm * TM * 32, en0 + wn * TN * 32, [&](int i, int j, int r) {
                         return act_of(__builtin_fmaf(fsum[i][j][r], sr[i * 16 + r], bj[j]));
                     }, gl);
                 else
-                    store_tile_staged<TM, TN, true, 32>(strip, lane, y, N, em0 + wm * TM * 32, en0 + wn * TN * 32, [&](int i, int j, int r) {
+                    store_tile_staged<TM, TN, true, T::STRIP_ROWS>(strip, lane, y, N, em0 + wm * TM * 32, en0 + wn * TN * 32, [&](int i, int j, int r) {
                         return act_of(fsum[i][j][r] * sr[i * 16 + r]);
                     }, gl);
             };
@@ -500,7 +501,8 @@ bool qgemm_w4_takes(const GemmArgs &a)
 template <int T, bool B8, bool MANY>
 static hipError_t run_w4_tile(const GemmArgs &a, hipStream_t stream)
 {
-    using TT = TileW4<2, 3, 2, B8, MANY ? W4_MANY_GROUPS : 40, T>;
+    // int8 codes on 128x128 tiles: a third activation stage would leave one workgroup per CU
+    using TT = TileW4<2, B8 && T == 2 ? 2 : 3, 2, B8, MANY ? W4_MANY_GROUPS : 40, T>;
     const bool glue = a.act != 0 || a.residual != nullptr || a.gate != nullptr || a.row_absmax != nullptr;
     if (a.acc_out) return run_w4<TT, 0, true, !B8>(a, stream);   // verification: group partial sums exported
     if constexpr (B8) {

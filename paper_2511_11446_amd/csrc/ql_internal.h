@@ -53,7 +53,9 @@ inline size_t daq_parts_per_block(int64_t K, int64_t R)
 hipError_t launch_daq(const DaqArgs &a, hipStream_t stream);
 // the first pass alone: partial maxima of every scale block (daq_parts_per_block of them) into a.partmax
 hipError_t launch_daq_part_absmax(const DaqArgs &a, hipStream_t stream);
-// eq. (4) with channel groups: scales [M/R, K/cg], blockmax workspace of the same count; K % 8 == 0, cg % 8 == 0, K/cg <= 1024
+// eq. (4) with channel groups: scales [M/R, K/cg]; workspace in blockmax: one maximum per group and slab of
+// daq_cg_slab_rows(R) rows (per scale block where that is 0); K % 8 == 0, cg % 8 == 0, K/cg <= 1024
+inline int daq_cg_slab_rows(int64_t R) { return R % 16 == 0 ? 16 : R % 8 == 0 ? 8 : 0; }
 hipError_t launch_daq_cg(const DaqArgs &a, int cg, hipStream_t stream);
 // DAQ whose row maxima are already known (row_absmax [M], binary16 bit patterns): scales and the quantize pass only
 hipError_t launch_daq_from_rowmax(const DaqArgs &a, const unsigned *row_absmax, hipStream_t stream);

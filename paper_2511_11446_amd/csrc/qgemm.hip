@@ -637,6 +637,11 @@ static const Variant VARIANTS[] = {
     {"f16 dma 128x192 s2 4w spread1 persistent", 16, 128, 192, 64, run_dma<H_p192>},
     {"w4 pipelined 128x128 a3b2 4w any-group", 4, 128, 128, 128, launch_qgemm_w4_128, launch_qgemm_w4_128},
     {"w4 pipelined 64x64 a3b2 4w any-group", 4, 64, 64, 128, launch_qgemm_w4_64, launch_qgemm_w4_64},
+    {"w8 big 256x288", 8, 256, 288, 128, launch_big_w8_256x288, launch_big_w8_256x288_glue},
+    {"w8 big 256x256", 8, 256, 256, 128, launch_big_w8_256x256, launch_big_w8_256x256_glue},
+    {"w8 big 128x288", 8, 128, 288, 128, launch_big_w8_128x288, launch_big_w8_128x288_glue},
+    {"f16 big 256x288", 16, 256, 288, 64, launch_big_f16_256x288, launch_big_f16_256x288_glue},
+    {"f16 big 256x256", 16, 256, 256, 64, launch_big_f16_256x256, launch_big_f16_256x256_glue},
     {"w8 split-K 32x32", 8, 32, 32, 16, launch_qgemm_split32, launch_qgemm_split32},
     {"w4 any-group split-K 32x32", 4, 32, 32, 32, launch_qgemm_split32, launch_qgemm_split32},
     {"f16 split-K 32x32", 16, 32, 32, 8, launch_qgemm_split32, launch_qgemm_split32},
@@ -677,6 +682,43 @@ static int find_variant(const char *name)
     return 0;
 }
 
+// The large tiles of qgemm_big.hip, or -1: where their whole rounds of tiles (one per CU) cost less than the tiles below would.
+// Microseconds fitted to sweeps over M = 1024..16384 and thirteen (K, N) from 384 to 4608 with random operands: a large tile
+// costs `step` per 128 bytes of K and `tile` for what is not hidden of its prologue and epilogue; the other kernels
+// cost their operations at 2280 TOPS (1100 TFLOP/s in binary16) plus their output at 5 TB/s.  The fit holds within a few
+// per cent where the chip is full and flatters the other kernels where it is not.
+static int choose_big(const GemmArgs &a)
+{
+    struct Cost {
+        const char *name;
+        int bits, BM, BN;
+        double step, tile;
+    };
+    static const Cost costs[] = {{"w8 big 256x288", 8, 256, 288, 1.78, 6.9},   {"w8 big 256x256", 8, 256, 256, 1.55, 4.0},
+                                 {"w8 big 128x288", 8, 128, 288, 1.00, 5.4},   {"f16 big 256x288", 16, 256, 288, 1.90, 4.4},
+                                 {"f16 big 256x256", 16, 256, 256, 1.49, 7.1}};
+    constexpr int COUNT = sizeof(costs) / sizeof(costs[0]);
+    static const int *const variants = [] {
+        static int v[COUNT];
+        for (int i = 0; i < COUNT; ++i) v[i] = find_variant(costs[i].name);
+        return (const int *)v;
+    }();
+    if (!qgemm_big_takes(a)) return -1;
+    const double outputs = (double)a.M * a.N, steps = a.K * (a.w_bits == 16 ? 2 : 1) / 128;
+    double best = outputs * a.K * 2e-6 / (a.w_bits == 16 ? 1100 : 2280) + outputs * 2e-6 / 5;
+    int v = -1;
+    for (int i = 0; i < COUNT; ++i) {
+        if (costs[i].bits != a.w_bits) continue;
+        const long tiles = (long)((a.M + costs[i].BM - 1) / costs[i].BM) * ((a.N + costs[i].BN - 1) / costs[i].BN);
+        const double t = (tiles + 255) / 256 * (steps * costs[i].step + costs[i].tile);
+        if (t < best) {
+            best = t;
+            v = variants[i];
+        }
+    }
+    return v;
+}
+
 // Tile choice by shape, from sweeps over the DiT-XL/2 layer shapes and other widths on MI355X (256 CUs); 8-bit and FP16
 // layers (4-bit layers choose inside launch_qgemm_w4).
 static int choose_variant(const GemmArgs &a)
@@ -690,6 +732,10 @@ static int choose_variant(const GemmArgs &a)
     // 64x64 tiles while all of them are resident at once (three per CU): M = 1024, N = 1152: K = 1152 6.5 against 8.0 us on
     // 128x128 tiles, K = 4608 16.6 against 21.1
     const long tiles_64 = (long)((a.M + 63) / 64) * ((a.N + 63) / 64);
+    if (tiles_64 > 768) {
+        const int v = choose_big(a);
+        if (v >= 0) return v;
+    }
     const long tiles_big = (long)((a.M + 255) / 256) * ((a.N + 191) / 192);
     if (a.w_bits == 16) {
         static const int h_small = find_variant("f16 dma 64x64 s3 4w"), h_mid = find_variant("f16 dma 128x128 a3b2 4w spread1"),
@@ -733,6 +779,7 @@ hipError_t launch_qgemm(const GemmArgs &a, int variant, hipStream_t stream)
     int v = variant;
     if (v >= 0 && (VARIANTS[v].w_bits != a.w_bits || a.K % VARIANTS[v].BK != 0)) v = -1;
     if (v >= 0 && __builtin_strstr(VARIANTS[v].name, "split-K") && !qgemm_split_takes(a, VARIANTS[v].BM)) v = -1;
+    if (v >= 0 && __builtin_strstr(VARIANTS[v].name, "big") && !qgemm_big_takes(a)) v = -1;
     if (v < 0 && split) return small();
     // 4-bit layers: the pipelined kernel with the tile that suits the shape
     if (a.w_bits == 4 && (v < 0 || __builtin_strstr(VARIANTS[v].name, "pipelined"))) {

@@ -126,6 +126,17 @@ hipError_t launch_qgemm_split32(const GemmArgs &a, hipStream_t stream);
 hipError_t launch_qgemm_split16(const GemmArgs &a, hipStream_t stream);
 bool qgemm_edge_takes(const GemmArgs &a);
 hipError_t launch_qgemm_edge(const GemmArgs &a, hipStream_t stream);
+bool qgemm_big_takes(const GemmArgs &a);
+hipError_t launch_big_w8_256x288(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_w8_256x288_glue(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_w8_256x256(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_w8_256x256_glue(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_w8_128x288(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_w8_128x288_glue(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_f16_256x288(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_f16_256x288_glue(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_f16_256x256(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_f16_256x256_glue(const GemmArgs &a, hipStream_t s);
 // pair-order nibbles (device) -> the 4-bit storage order (device); blocks = N*K/8 four-byte blocks
 hipError_t launch_prepack_w4(const void *pairs, void *packed, long long blocks, hipStream_t stream);
 

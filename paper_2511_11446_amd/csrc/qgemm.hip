@@ -642,6 +642,9 @@ static const Variant VARIANTS[] = {
     {"w8 big 128x288", 8, 128, 288, 128, launch_big_w8_128x288, launch_big_w8_128x288_glue},
     {"f16 big 256x288", 16, 256, 288, 64, launch_big_f16_256x288, launch_big_f16_256x288_glue},
     {"f16 big 256x256", 16, 256, 256, 64, launch_big_f16_256x256, launch_big_f16_256x256_glue},
+    {"w4 big 256x288", 4, 256, 288, 128, launch_big_w4_256x288, launch_big_w4_256x288_glue},
+    {"w4 big 256x256", 4, 256, 256, 128, launch_big_w4_256x256, launch_big_w4_256x256_glue},
+    {"w4 big 128x288", 4, 128, 288, 128, launch_big_w4_128x288, launch_big_w4_128x288_glue},
     {"w8 split-K 32x32", 8, 32, 32, 16, launch_qgemm_split32, launch_qgemm_split32},
     {"w4 any-group split-K 32x32", 4, 32, 32, 32, launch_qgemm_split32, launch_qgemm_split32},
     {"f16 split-K 32x32", 16, 32, 32, 8, launch_qgemm_split32, launch_qgemm_split32},
@@ -682,11 +685,13 @@ static int find_variant(const char *name)
     return 0;
 }
 
-// The large tiles of qgemm_big.hip, or -1: where their whole rounds of tiles (one per CU) cost less than the tiles below would.
-// Microseconds fitted to sweeps over M = 1024..16384 and thirteen (K, N) from 384 to 4608 with random operands: a large tile
+// The large tiles of qgemm_big.hip and qgemm_w4_big.hip, or -1: where their whole rounds of tiles (one per CU) cost less than the
+// tiles below would.
+// Microseconds fitted to sweeps over M = 1024..16384 and ten to thirteen (K, N) from 384 to 4608 with random operands: a large tile
 // costs `step` per 128 bytes of K and `tile` for what is not hidden of its prologue and epilogue; the other kernels
-// cost their operations at 2280 TOPS (1100 TFLOP/s in binary16) plus their output at 5 TB/s.  The fit holds within a few
-// per cent where the chip is full and flatters the other kernels where it is not.
+// cost their operations at 2280 TOPS (1100 TFLOP/s in binary16) plus their output at 5 TB/s, and with 4-bit weights 1636 TOPS
+// of 128x128 tiles in multiples of 256 plus the output at 7.7 TB/s.  The fit holds within a few per cent where the chip is full and
+// flatters the other kernels where it is not.
 static int choose_big(const GemmArgs &a)
 {
     struct Cost {
@@ -696,16 +701,21 @@ static int choose_big(const GemmArgs &a)
     };
     static const Cost costs[] = {{"w8 big 256x288", 8, 256, 288, 1.78, 6.9},   {"w8 big 256x256", 8, 256, 256, 1.55, 4.0},
                                  {"w8 big 128x288", 8, 128, 288, 1.00, 5.4},   {"f16 big 256x288", 16, 256, 288, 1.90, 4.4},
-                                 {"f16 big 256x256", 16, 256, 256, 1.49, 7.1}};
+                                 {"f16 big 256x256", 16, 256, 256, 1.49, 7.1}, {"w4 big 256x288", 4, 256, 288, 2.50, 6.2},
+                                 {"w4 big 256x256", 4, 256, 256, 2.25, 5.0},   {"w4 big 128x288", 4, 128, 288, 1.70, 4.5}};
     constexpr int COUNT = sizeof(costs) / sizeof(costs[0]);
     static const int *const variants = [] {
         static int v[COUNT];
         for (int i = 0; i < COUNT; ++i) v[i] = find_variant(costs[i].name);
         return (const int *)v;
     }();
-    if (!qgemm_big_takes(a)) return -1;
+    if (!(a.w_bits == 4 ? qgemm_w4_big_takes(a) : qgemm_big_takes(a))) return -1;
     const double outputs = (double)a.M * a.N, steps = a.K * (a.w_bits == 16 ? 2 : 1) / 128;
     double best = outputs * a.K * 2e-6 / (a.w_bits == 16 ? 1100 : 2280) + outputs * 2e-6 / 5;
+    if (a.w_bits == 4) {
+        const long tiles = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
+        best = (double)((tiles + 255) / 256 * 256) * 128 * 128 * a.K * 2e-6 / 1636 + outputs * 2e-6 / 7.7;
+    }
     int v = -1;
     for (int i = 0; i < COUNT; ++i) {
         if (costs[i].bits != a.w_bits) continue;
@@ -779,9 +789,12 @@ hipError_t launch_qgemm(const GemmArgs &a, int variant, hipStream_t stream)
     int v = variant;
     if (v >= 0 && (VARIANTS[v].w_bits != a.w_bits || a.K % VARIANTS[v].BK != 0)) v = -1;
     if (v >= 0 && __builtin_strstr(VARIANTS[v].name, "split-K") && !qgemm_split_takes(a, VARIANTS[v].BM)) v = -1;
-    if (v >= 0 && __builtin_strstr(VARIANTS[v].name, "big") && !qgemm_big_takes(a)) v = -1;
+    if (v >= 0 && __builtin_strstr(VARIANTS[v].name, "big") && !(a.w_bits == 4 ? qgemm_w4_big_takes(a) : qgemm_big_takes(a))) v = -1;
     if (v < 0 && split) return small();
-    // 4-bit layers: the pipelined kernel with the tile that suits the shape
+    // 4-bit layers: the pipelined kernels with the tile that suits the shape
+    // (64x64 tiles while all of them are resident at once)
+    if (a.w_bits == 4 && v < 0 && (long)((a.M + 63) / 64) * ((a.N + 63) / 64) > 1024) v = choose_big(a);
+    if (a.w_bits == 4 && v >= 0 && __builtin_strstr(VARIANTS[v].name, "big")) return glue ? VARIANTS[v].run_glue(a, stream) : VARIANTS[v].run(a, stream);
     if (a.w_bits == 4 && (v < 0 || __builtin_strstr(VARIANTS[v].name, "pipelined"))) {
         if (!qgemm_w4_takes(a)) return small();
         return v < 0 ? launch_qgemm_w4(a, stream) : VARIANTS[v].run(a, stream);

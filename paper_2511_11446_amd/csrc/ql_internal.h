@@ -137,6 +137,13 @@ hipError_t launch_big_f16_256x288(const GemmArgs &a, hipStream_t s);
 hipError_t launch_big_f16_256x288_glue(const GemmArgs &a, hipStream_t s);
 hipError_t launch_big_f16_256x256(const GemmArgs &a, hipStream_t s);
 hipError_t launch_big_f16_256x256_glue(const GemmArgs &a, hipStream_t s);
+bool qgemm_w4_big_takes(const GemmArgs &a);
+hipError_t launch_big_w4_256x288(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_w4_256x288_glue(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_w4_256x256(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_w4_256x256_glue(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_w4_128x288(const GemmArgs &a, hipStream_t s);
+hipError_t launch_big_w4_128x288_glue(const GemmArgs &a, hipStream_t s);
 // pair-order nibbles (device) -> the 4-bit storage order (device); blocks = N*K/8 four-byte blocks
 hipError_t launch_prepack_w4(const void *pairs, void *packed, long long blocks, hipStream_t stream);
 

@@ -143,7 +143,7 @@ int qlinear_w8a8(const void *x, int64_t M, int64_t K, int64_t R,
  * = 24 MiB per GPU, held by every GPU the library runs on until the process ends.
  *   - The call allocates nothing (no hipMalloc / hipFree, no allocating library
  *     routine); the first call on a device looks the array's address up once.
- *   - QL_ERR_WORKSPACE if qlinear_workspace_bytes(M, K, R) exceeds the array
+ *   - QL_ERR_WORKSPACE if codes, scales and maxima would not fit the array
  *     (M*K up to about 25 million, e.g. 16384 x 1152); the other errors as
  *     qlinear_w8a8.
  *   - All calls on one GPU share the array, which keeps the last call's contents

@@ -153,7 +153,7 @@ def _stream(stream):
             get, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device
             _raw_stream = (lambda: get(dev())) if get is not None else (lambda: torch.cuda.current_stream().cuda_stream)
         return _raw_stream()
-    return stream.cuda_stream if hasattr(stream, "cuda_stream") else getattr(stream, "value", stream)
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 _torch = None

@@ -44,14 +44,17 @@ int check_shape(int64_t M, int64_t K, int64_t R, int64_t N)
 inline bool misaligned(const void *p, size_t a) { return p && ((uintptr_t)p % a) != 0; }
 
 // DAQ scratch for R > 1.  Absmax: [block maxima M/R][partial maxima (M/R) * parts]; percentile: [tau patterns M/R]
-// [selection histograms].  One size covers both, so a workspace serves either mode.
-size_t daq_scratch_bytes(int64_t M, int64_t K, int64_t R, bool absmax_only = false)
+// [selection histograms].  One size covers both, so a workspace serves either mode.  Its histograms are either the partial ones
+// (what the sizing functions return) or, from DAQ_ROBUST_WORDS words per scale block on, those of the atomic selection.
+enum class Scratch { full, atomic, least };
+size_t daq_scratch_bytes(int64_t M, int64_t K, int64_t R, Scratch kind = Scratch::full)
 {
     if (M < 1 || R <= 1 || M % R != 0) return 0;
     const size_t nblk = (size_t)(M / R);
     const size_t plain = align_up(nblk * ql::daq_parts_per_block(K, R) * 4, 256);
-    const size_t robust = align_up(ql::daq_hist_bytes(M, K, R), 256);
-    return align_up(nblk * 4, 256) + (plain > robust || absmax_only ? plain : robust);
+    const size_t parts = align_up(ql::daq_hist_bytes(M, K, R), 256), atomics = align_up(nblk * ql::DAQ_ROBUST_WORDS * 4, 256);
+    const size_t robust = kind == Scratch::full ? parts : kind == Scratch::atomic || atomics < parts ? atomics : parts;
+    return align_up(nblk * 4, 256) + (plain > robust ? plain : robust);
 }
 
 // eq. (4): rank from the top of the nearest-rank percentile, c = n - ceil(n p) + 1 with n = R*K values per scale block
@@ -73,13 +76,13 @@ struct LayerWs {
     size_t q_off, s_off, bm_off, total;
 };
 
-LayerWs layer_ws(int64_t M, int64_t K, int64_t R, bool absmax_only = false)
+LayerWs layer_ws(int64_t M, int64_t K, int64_t R, Scratch kind = Scratch::full)
 {
     LayerWs w;
     w.q_off = 0;
     w.s_off = align_up((size_t)(M * K), 256);
     w.bm_off = w.s_off + align_up((size_t)(M / R) * 4, 256);
-    w.total = w.bm_off + daq_scratch_bytes(M, K, R, absmax_only);
+    w.total = w.bm_off + daq_scratch_bytes(M, K, R, kind);
     return w;
 }
 
@@ -103,7 +106,7 @@ int check_group(int64_t K, int64_t group)
 
 // DAQ then GEMM for one layer; all arguments already validated
 int run_layer(const void *x, int64_t M, int64_t K, int64_t R, int w_bits, const void *w, const void *w_scale,
-              const void *bias, int64_t N, void *y, const ql_debug *dbg, void *workspace, hipStream_t stream,
+              const void *bias, int64_t N, void *y, const ql_debug *dbg, void *workspace, size_t workspace_bytes, hipStream_t stream,
               const ql_daq_params *dp = nullptr, int64_t group = 128, const ql_fusion *fu = nullptr)
 {
     if (w_bits == 16) {
@@ -141,6 +144,7 @@ int run_layer(const void *x, int64_t M, int64_t K, int64_t R, int w_bits, const 
     d.blockmax = R > 1 ? reinterpret_cast<unsigned *>(base + lw.bm_off) : nullptr;
     d.partmax = R > 1 ? reinterpret_cast<unsigned *>(base + lw.bm_off + align_up((size_t)(M / R) * 4, 256)) : nullptr;
     d.hist = d.partmax;
+    d.hist_bytes = R > 1 ? workspace_bytes - lw.bm_off - align_up((size_t)(M / R) * 4, 256) : 0;
     d.M = (int)M;
     d.K = (int)K;
     d.R = (int)R;
@@ -252,10 +256,10 @@ int qlinear_any(int w_bits, const void *x, int64_t M, int64_t K, int64_t R, cons
         if (rc) return rc;
         if (M > ELEMS_MAX / N / (K / group) && dbg && dbg->acc) return QL_ERR_SHAPE;
     }
-    rc = check_workspace(workspace, workspace_bytes, layer_ws(M, K, R).total);
+    rc = check_workspace(workspace, workspace_bytes, layer_ws(M, K, R, Scratch::least).total);
     if (rc) return rc;
-    return run_layer(x, M, K, R, w_bits, w, w_scale, bias, N, y, dbg, workspace, static_cast<hipStream_t>(stream), nullptr,
-                     group, fu);
+    return run_layer(x, M, K, R, w_bits, w, w_scale, bias, N, y, dbg, workspace, workspace_bytes, static_cast<hipStream_t>(stream),
+                     nullptr, group, fu);
 }
 
 int qgemm_any(int w_bits, const void *q, const void *a_scales, int64_t M, int64_t K, int64_t R, const void *w,
@@ -334,7 +338,7 @@ static int daq_any(const void *x, int64_t M, int64_t K, int64_t R, const ql_daq_
         rc = robust_args(dp, K, R, d);
         if (rc) return rc;
     }
-    rc = check_workspace(workspace, workspace_bytes, daq_workspace_bytes(M, K, R));
+    rc = check_workspace(workspace, workspace_bytes, daq_scratch_bytes(M, K, R, Scratch::least));
     if (rc) return rc;
     d.x = x;
     d.q = static_cast<int8_t *>(q);
@@ -343,6 +347,7 @@ static int daq_any(const void *x, int64_t M, int64_t K, int64_t R, const ql_daq_
     d.partmax = R > 1 ? reinterpret_cast<unsigned *>(static_cast<unsigned char *>(workspace) + align_up((size_t)(M / R) * 4, 256))
                       : nullptr;
     d.hist = d.partmax;
+    d.hist_bytes = R > 1 ? workspace_bytes - align_up((size_t)(M / R) * 4, 256) : 0;
     d.M = (int)M;
     d.K = (int)K;
     d.R = (int)R;
@@ -370,7 +375,7 @@ int daq_quantize_rowmax(const void *x, int64_t M, int64_t K, int64_t R, const vo
     if (misaligned(x, 2) || misaligned(scales, 4) || misaligned(row_absmax, 4)) return QL_ERR_ALIGN;
     int rc = check_shape(M, K, R, 1);
     if (rc) return rc;
-    rc = check_workspace(workspace, workspace_bytes, daq_workspace_bytes(M, K, R));
+    rc = check_workspace(workspace, workspace_bytes, daq_scratch_bytes(M, K, R, Scratch::least));
     if (rc) return rc;
     ql::DaqArgs d{};
     d.x = x;
@@ -391,6 +396,12 @@ static int check_act_group(int64_t K, int64_t ag)
     return QL_OK;
 }
 
+// one word per scale: the scales themselves, and the scratch from which on the atomic kernels run
+static size_t cg_scales_bytes(int64_t M, int64_t K, int64_t R, int64_t act_group)
+{
+    return align_up((size_t)(M / R) * (size_t)(K / act_group) * 4, 256);
+}
+
 size_t daq_cg_workspace_bytes(int64_t M, int64_t K, int64_t R, int64_t act_group)
 {
     if (M < 1 || K < 1 || R < 1 || M % R != 0 || act_group < 1 || K % act_group != 0) return 0;
@@ -407,7 +418,7 @@ int daq_quantize_cg(const void *x, int64_t M, int64_t K, int64_t R, int64_t act_
     if (rc) return rc;
     rc = check_act_group(K, act_group);
     if (rc) return rc;
-    rc = check_workspace(workspace, workspace_bytes, daq_cg_workspace_bytes(M, K, R, act_group));
+    rc = check_workspace(workspace, workspace_bytes, cg_scales_bytes(M, K, R, act_group));
     if (rc) return rc;
     ql::DaqArgs d{};
     d.x = x;
@@ -417,7 +428,8 @@ int daq_quantize_cg(const void *x, int64_t M, int64_t K, int64_t R, int64_t act_
     d.M = (int)M;
     d.K = (int)K;
     d.R = (int)R;
-    return device_status(ql::launch_daq_cg(d, (int)act_group, static_cast<hipStream_t>(stream)));
+    const bool slabs = workspace_bytes >= daq_cg_workspace_bytes(M, K, R, act_group);
+    return device_status(ql::launch_daq_cg(d, (int)act_group, slabs, static_cast<hipStream_t>(stream)));
 }
 
 size_t qlinear_grouped_workspace_bytes(int64_t M, int64_t K, int64_t R, int64_t act_group)
@@ -425,7 +437,7 @@ size_t qlinear_grouped_workspace_bytes(int64_t M, int64_t K, int64_t R, int64_t 
     if (M < 1 || K < 1 || R < 1 || M % R != 0) return 0;
     if (act_group <= 0) return layer_ws(M, K, R).total;
     if (K % act_group != 0) return 0;
-    return align_up((size_t)(M * K), 256) + 2 * daq_cg_workspace_bytes(M, K, R, act_group);
+    return align_up((size_t)(M * K), 256) + cg_scales_bytes(M, K, R, act_group) + daq_cg_workspace_bytes(M, K, R, act_group);
 }
 
 int qlinear_grouped(const void *x, int64_t M, int64_t K, int64_t R, int64_t act_group, const void *w, int32_t w_storage,
@@ -446,7 +458,9 @@ int qlinear_grouped(const void *x, int64_t M, int64_t K, int64_t R, int64_t act_
         if (misaligned(x, 16)) return QL_ERR_ALIGN;
     }
     if (dbg && dbg->acc && M > ELEMS_MAX / N / (K / group)) return QL_ERR_SHAPE;
-    rc = check_workspace(workspace, workspace_bytes, qlinear_grouped_workspace_bytes(M, K, R, act_group));
+    const size_t full = qlinear_grouped_workspace_bytes(M, K, R, act_group);
+    rc = check_workspace(workspace, workspace_bytes, act_group == 0 ? layer_ws(M, K, R, Scratch::least).total
+                                                                   : align_up((size_t)(M * K), 256) + 2 * cg_scales_bytes(M, K, R, act_group));
     if (rc) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     unsigned char *base = static_cast<unsigned char *>(workspace);
@@ -467,7 +481,7 @@ int qlinear_grouped(const void *x, int64_t M, int64_t K, int64_t R, int64_t act_
         g.q = d.q;
         g.s_a = d.scales;
     } else {
-        const size_t cgb = daq_cg_workspace_bytes(M, K, R, act_group);
+        const size_t cgb = cg_scales_bytes(M, K, R, act_group);
         ql::DaqArgs d{};
         d.x = x;
         d.q = (dbg && dbg->q) ? static_cast<int8_t *>(dbg->q) : reinterpret_cast<int8_t *>(base);
@@ -476,7 +490,7 @@ int qlinear_grouped(const void *x, int64_t M, int64_t K, int64_t R, int64_t act_
         d.M = (int)M;
         d.K = (int)K;
         d.R = (int)R;
-        rc = device_status(ql::launch_daq_cg(d, (int)act_group, s));
+        rc = device_status(ql::launch_daq_cg(d, (int)act_group, workspace_bytes >= full, s));
         if (rc) return rc;
         g.q = d.q;
         g.s_ag = d.scales;
@@ -561,7 +575,7 @@ int daq_quantize_ln(const void *x, int64_t M, int64_t K, int64_t R, const void *
     if ((shift || scale) && (rows_per_mod < 1 || M % rows_per_mod != 0)) return QL_ERR_SHAPE;
     if (R > 1 && q && !h) return QL_ERR_NULL;    // several rows per scale: the normalised rows are staged in h
     if (R > 1 && q) {
-        rc = check_workspace(workspace, workspace_bytes, daq_workspace_bytes(M, K, R));
+        rc = check_workspace(workspace, workspace_bytes, daq_scratch_bytes(M, K, R, Scratch::least));
         if (rc) return rc;
     }
     ql::LnDaqArgs a{};
@@ -608,13 +622,13 @@ int qlinear_w8a8_noalloc(const void *x, int64_t M, int64_t K, int64_t R, const v
     if (rc) return rc;
     rc = check_shape(M, K, R, N);
     if (rc) return rc;
-    if (layer_ws(M, K, R, true).total > QL_NOALLOC_SCRATCH_BYTES) return QL_ERR_WORKSPACE;
+    if (layer_ws(M, K, R, Scratch::atomic).total > QL_NOALLOC_SCRATCH_BYTES) return QL_ERR_WORKSPACE;
     void *ws = nullptr;
     rc = noalloc_scratch(&ws);
     if (rc) return rc;
     // nothing in the scratch has to start at zero: codes, scales and partial maxima are written before they are read
     // (the atomic-maximum fallback of the DAQ pass clears its block maxima with a fill kernel of its own)
-    return run_layer(x, M, K, R, 8, w, w_scale, bias, N, y, nullptr, ws, static_cast<hipStream_t>(stream));
+    return run_layer(x, M, K, R, 8, w, w_scale, bias, N, y, nullptr, ws, QL_NOALLOC_SCRATCH_BYTES, static_cast<hipStream_t>(stream));
 }
 
 int qlinear_w4a8(const void *x, int64_t M, int64_t K, int64_t R, const void *w4, const void *w_scale,
@@ -653,7 +667,7 @@ int qlinear_f16(const void *x, int64_t M, int64_t K, const void *w, const void *
     if (rc) return rc;
     rc = check_fusion(fusion, M);
     if (rc) return rc;
-    return run_layer(x, M, K, 1, 16, w, nullptr, bias, N, y, nullptr, nullptr, static_cast<hipStream_t>(stream), nullptr, 128,
+    return run_layer(x, M, K, 1, 16, w, nullptr, bias, N, y, nullptr, nullptr, 0, static_cast<hipStream_t>(stream), nullptr, 128,
                      fusion);
 }
 
@@ -767,7 +781,7 @@ static int plan_run_any(const ql_plan *plan, const void *const *x_in, void *cons
         if (!x_in[l] || !y_out[l]) return QL_ERR_NULL;
         if (misaligned(x_in[l], 2) || misaligned(y_out[l], 2)) return QL_ERR_ALIGN;
     }
-    int rc = check_workspace(workspace, workspace_bytes, ql_plan_workspace_bytes(plan, M, R));
+    int rc = check_workspace(workspace, workspace_bytes, layer_ws(M, plan->K_widest, R, Scratch::least).total);
     if (rc) return rc;
     if (fusion)
         for (size_t l = 0; l < plan->layers.size(); ++l) {
@@ -777,7 +791,7 @@ static int plan_run_any(const ql_plan *plan, const void *const *x_in, void *cons
     hipStream_t s = static_cast<hipStream_t>(stream);
     for (size_t l = 0; l < plan->layers.size(); ++l) {
         const ql_layer_desc &d = plan->layers[l];
-        rc = run_layer(x_in[l], M, d.K, R, d.w_bits, d.w, d.w_scale, d.bias, d.N, y_out[l], nullptr, workspace, s, dp,
+        rc = run_layer(x_in[l], M, d.K, R, d.w_bits, d.w, d.w_scale, d.bias, d.N, y_out[l], nullptr, workspace, workspace_bytes, s, dp,
                        d.w_bits == 4 ? d.group : 128, fusion ? fusion[l] : nullptr);
         if (rc) return rc;
     }

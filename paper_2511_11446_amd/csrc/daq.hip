@@ -327,9 +327,9 @@ __global__ __launch_bounds__(1024) void daq_cg_slab(DaqArgs a, int cg, int slab,
     }
 }
 
-hipError_t launch_daq_cg(const DaqArgs &a, int cg, hipStream_t stream)
+hipError_t launch_daq_cg(const DaqArgs &a, int cg, bool slabs, hipStream_t stream)
 {
-    const int slab = daq_cg_slab_rows(a.R), P = a.K / 8, G = a.K / cg;
+    const int slab = slabs ? daq_cg_slab_rows(a.R) : 0, P = a.K / 8, G = a.K / cg;
     if (slab > 0 && P <= 1024) {
         const int rpw = P >= 512 ? 1 : 512 / P;
         const dim3 grid(a.M / slab), block((P * rpw + 63) / 64 * 64);

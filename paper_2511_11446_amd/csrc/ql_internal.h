@@ -25,7 +25,8 @@ struct DaqArgs {
     // percentile-clipped variant only (launch_daq_robust)
     int qmax;            // 2^(b-1) - 1 for b-bit activation codes
     unsigned top_rank;   // tau = the top_rank-th largest magnitude of a scale block (1 = the maximum)
-    unsigned *hist;      // selection scratch (workspace), R > 1 only: daq_hist_bytes()
+    unsigned *hist;      // selection scratch (workspace), R > 1 only: daq_hist_bytes() for the partial histograms, and from
+    size_t hist_bytes;   //    DAQ_ROBUST_WORDS words per scale block on the selection with atomics
 };
 constexpr int DAQ_ROBUST_WORDS = 256 + 2 + 128;
 // Partial histograms of the percentile selection: elements per part (at most 65535, so that a 16-bit count holds); parts per
@@ -54,9 +55,9 @@ hipError_t launch_daq(const DaqArgs &a, hipStream_t stream);
 // the first pass alone: partial maxima of every scale block (daq_parts_per_block of them) into a.partmax
 hipError_t launch_daq_part_absmax(const DaqArgs &a, hipStream_t stream);
 // eq. (4) with channel groups: scales [M/R, K/cg]; workspace in blockmax: one maximum per group and slab of
-// daq_cg_slab_rows(R) rows (per scale block where that is 0); K % 8 == 0, cg % 8 == 0, K/cg <= 1024
+// daq_cg_slab_rows(R) rows with `slabs` (per scale block without, or where that is 0); K % 8 == 0, cg % 8 == 0, K/cg <= 1024
 inline int daq_cg_slab_rows(int64_t R) { return R % 16 == 0 ? 16 : R % 8 == 0 ? 8 : 0; }
-hipError_t launch_daq_cg(const DaqArgs &a, int cg, hipStream_t stream);
+hipError_t launch_daq_cg(const DaqArgs &a, int cg, bool slabs, hipStream_t stream);
 // DAQ whose row maxima are already known (row_absmax [M], binary16 bit patterns): scales and the quantize pass only
 hipError_t launch_daq_from_rowmax(const DaqArgs &a, const unsigned *row_absmax, hipStream_t stream);
 hipError_t launch_fill_u32(unsigned *p, int n, unsigned v, hipStream_t stream);

@@ -86,3 +86,24 @@ def test_f16_small_and_ragged(gpu, orc, M, K, N):
     ref = orc.linear_f16(x, w, b, nthreads=16)
     y = host(gpu.qlinear_f16(dev(x), dev(w), dev(b)))
     assert (np.abs(y.astype(np.float64) - ref.astype(np.float64)) <= _f16_tolerance(x, w, ref)).all()
+
+
+def _aligned(n):
+    return (n + 255) // 256 * 256
+
+
+@pytest.mark.parametrize("M,K,R", [(256, 1152, 64), (24, 96, 8), (512, 4608, 256)])
+def test_smaller_workspaces(gpu, M, K, R):
+    """One set of histogram words per scale block (386 of them, and one word for tau), or one word per channel-group scale, is still
+    enough: the kernels that need more step aside."""
+    import torch
+    say("smaller workspaces", M, K, R)
+    x = dev(workload.activations(M, K, "less"))
+    nblk, group = M // R, 32
+    small = gpu.workspace(_aligned(4 * nblk) + _aligned(4 * 386 * nblk))
+    want, got = gpu.daq_quantize_robust(x, R, 990000, 6), gpu.daq_quantize_robust(x, R, 990000, 6, ws=small)
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+    q, s = gpu.daq_quantize_cg(x, R, group)
+    q2, s2, ws = torch.zeros_like(q), torch.zeros_like(s), gpu.workspace(_aligned(4 * nblk * (K // group)))
+    assert gpu.lib().daq_quantize_cg(x.data_ptr(), M, K, R, group, q2.data_ptr(), s2.data_ptr(), ws.data_ptr(), ws.numel(), None) == 0
+    assert torch.equal(q, q2) and torch.equal(s, s2)

@@ -104,6 +104,11 @@ int check_group(int64_t K, int64_t group)
     return QL_OK;
 }
 
+inline bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
+}
+
 // DAQ then GEMM for one layer; all arguments already validated
 int run_layer(const void *x, int64_t M, int64_t K, int64_t R, int w_bits, const void *w, const void *w_scale,
               const void *bias, int64_t N, void *y, const ql_debug *dbg, void *workspace, size_t workspace_bytes, hipStream_t stream,
@@ -177,12 +182,13 @@ int run_layer(const void *x, int64_t M, int64_t K, int64_t R, int w_bits, const 
     const int variant = g_gemm_variant.load();
     const size_t parts = ql::daq_parts_per_block(K, R);
     if (!dp && !dbg && variant < 0 && (R == 1 || (parts > 0 && parts <= 256))) {
-        // few rows: the GEMM's workgroups quantize their own rows (one launch; two where rows share a scale)
+        // few rows: the GEMM's workgroups quantize their own rows (one launch; two where rows share a scale), unless the outputs
+        // lie over the inputs that other workgroups still read
         ql::GemmArgs f = g;
         f.x = x;
         f.partmax = d.partmax;
         f.parts = R == 1 ? 0 : (int)parts;
-        if (ql::qgemm_fuse_takes(f)) {
+        if (ql::qgemm_fuse_takes(f) && !overlap(x, (size_t)(M * K) * 2, y, (size_t)(M * N) * 2)) {
             if (R > 1) {
                 rc = device_status(ql::launch_daq_part_absmax(d, stream));
                 if (rc) return rc;

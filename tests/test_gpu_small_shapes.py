@@ -88,6 +88,22 @@ def test_f16_small_and_ragged(gpu, orc, M, K, N):
     assert (np.abs(y.astype(np.float64) - ref.astype(np.float64)) <= _f16_tolerance(x, w, ref)).all()
 
 
+@pytest.mark.parametrize("M,bits,R", [(16, 8, 1), (40, 4, 1), (64, 8, 64)])
+def test_outputs_over_the_inputs(gpu, M, bits, R):
+    """A square layer whose outputs replace its inputs: no workgroup may still read what another one has overwritten."""
+    import torch
+    K = 384
+    say("in place", M, bits, R)
+    x = workload.activations(M, K, "in-place")
+    lw = workload.layer_weights("in-place", K, K, bits, "in-place")
+    w = dev(lw["w"] if bits == 8 else gpu.ql_pack_w4_host(lw["w"]))
+    layer = gpu.qlinear_w8a8 if bits == 8 else gpu.qlinear_w4a8
+    apart = layer(dev(x), R, w, dev(lw["s_w"]), dev(lw["bias"]))
+    xd = dev(x)
+    assert layer(xd, R, w, dev(lw["s_w"]), dev(lw["bias"]), y=xd).data_ptr() == xd.data_ptr()
+    assert torch.equal(apart, xd)
+
+
 def _aligned(n):
     return (n + 255) // 256 * 256
 

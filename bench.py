@@ -505,7 +505,8 @@ def main():
             counts[kind(l)] = counts.get(kind(l), 0) + 1
         gemm_time, gemm_ops, gemm_n, daq_time, daq_bytes, daq_n = 0.0, 0.0, 0, 0.0, 0.0, 0
         fam = {}   # GEMM kernel family -> [time per step, ops per step, launches per step]
-        fam_name = {8: "qgemm_dma, 8-bit weights", 4: "qgemm_w4 / qgemm_mfma, 4-bit weights", 16: "qgemm_dma, FP16 operands"}
+        fam_name = {8: "qgemm_big / qgemm_dma, 8-bit weights", 4: "qgemm_w4_big / qgemm_w4, 4-bit weights",
+                    16: "qgemm_big / qgemm_dma, FP16 operands"}
         for key, l in uniq.items():
             x = pool[0][l["name"]]
             q = torch.empty((M, l["K"]), dtype=torch.int8, device="cuda")

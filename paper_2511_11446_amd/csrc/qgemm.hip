@@ -712,6 +712,10 @@ static int choose_big(const GemmArgs &a)
     if (!(a.w_bits == 4 ? qgemm_w4_big_takes(a) : qgemm_big_takes(a))) return -1;
     const double outputs = (double)a.M * a.N, steps = a.K * (a.w_bits == 16 ? 2 : 1) / 128;
     double best = outputs * a.K * 2e-6 / (a.w_bits == 16 ? 1100 : 2280) + outputs * 2e-6 / 5;
+    // 256x192 tiles, one per CU, that just miss a whole round (M = 3072, K = 1024, N = 4096: 264 tiles; 29.4 us, in binary16 43.6
+    // against 27.8 on 256x256 tiles)
+    const long tiles_big = (long)((a.M + 255) / 256) * ((a.N + 191) / 192);
+    if (a.w_bits == 16 && a.M < 4096 && tiles_big > 256) best *= (double)((tiles_big + 255) / 256 * 256) / tiles_big;
     if (a.w_bits == 4) {
         const long tiles = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
         best = (double)((tiles + 255) / 256 * 256) * 128 * 128 * a.K * 2e-6 / 1636 + outputs * 2e-6 / 7.7;
@@ -751,17 +755,22 @@ static int choose_variant(const GemmArgs &a)
         static const int h_small = find_variant("f16 dma 64x64 s3 4w"), h_mid = find_variant("f16 dma 128x128 a3b2 4w spread1"),
                          h_big = find_variant("f16 dma 256x192 a3b2 8w spread1"),
                          h_p192 = find_variant("f16 dma 128x192 s2 4w spread1 persistent");
-        if (tiles_64 <= 768) return h_small;
-        if (tiles_big < 192) return h_mid;
+        // (M = 1024, K = 4096, N = 1024, 256 of them: 21.5 against 35.8 us on 128x128 tiles; 576: level; 768: M = 3072, K = 4096, N =
+        // 1024 41.6 against 38.3, M = 1024, K = 1024, N = 3072 13.1 against 12.3)
+        if (tiles_64 <= 512) return h_small;
+        if (tiles_big < 192 || (a.M < 4096 && tiles_big > 256 && tiles_big <= 384)) return h_mid;   // one 256x192 tile per CU, no second round begun
         return (a.M >= 4096 && a.N < 4096) ? h_p192 : h_big;
     }
     if (tiles_64 <= 768 && (a.K < 2304 || tiles_64 <= 512)) return w8_small;
     if (tiles_big >= 192) {                                   // enough work for every CU
         // Several tiles per CU: two resident 4-wavefront workgroups per CU that walk their tiles and fetch the next
-        // tile's first K step under the epilogue.  128x192 tiles move less data per MAC; 128x128 tiles balance better
-        // when the tiles per CU are few and N is wide.
-        if (a.M >= 4096) return (a.K >= 2304 || a.N <= 1536 || a.M >= 12288) ? w8_p192 : w8_p128;
-        return w8_big;
+        // tile's first K step under the epilogue.  128x192 tiles move less data per MAC; 128x128 tiles balance better when
+        // the tiles per CU are few and N is wide, unless 128x192 ones are all resident at once (M = 4096: K = 1024, N = 3072 17.1
+        // against 19.4 us, K = 768, N = 2304 13.2 against 14.7).  Fewer rows: one 256x192 tile per CU, but not a second round of
+        // them (M = 3072, K = 1024, N = 4096, 264 tiles: 29.4 us against 18.4 on 128x128).
+        const long tiles_192 = (long)((a.M + 127) / 128) * ((a.N + 191) / 192);
+        if (a.M >= 4096) return (a.K >= 2304 || a.N <= 1536 || a.M >= 12288 || tiles_192 <= 512) ? w8_p192 : w8_p128;
+        return tiles_big <= 256 || tiles_big > 384 ? w8_big : w8_p128;
     }
     // one 128x128 tile per CU at most: the deeper issue of a long K; more than one: DMA spread between the MFMAs
     const long tiles_128 = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);

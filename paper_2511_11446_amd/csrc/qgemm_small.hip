@@ -757,8 +757,9 @@ bool qgemm_split_takes(const GemmArgs &a, int T)
 // Which tile, if any, splits K to advantage.  The kernel's time is nearly flat as long as all its workgroups are resident
 // at once and then goes up by a whole walk over K per further round (M = 64..192, N = 1152, K = 4608, 8-bit: 5.4-5.7 us, M =
 // 256: 8.3; the 64x64 workgroup tiles take 12.2 there).  16x16 tiles have the shortest walk, 32x32 tiles move half the
-// operand bytes.  A second round still pays where the walk is long (K >= 2304), except with group scales, for which the
-// pipelined kernel has 64x64 tiles.
+// operand bytes.  A second round does not pay where 64x64 workgroup tiles can run instead (16.8 against 11.8 us at M = N = 1024,
+// K = 4096, 37.6 against 21.5 in binary16; from 576 tiles on they are level at best), only for inner sizes that those do not
+// take, and there where the walk is long (K >= 2304).
 int qgemm_split_choice(const GemmArgs &a)
 {
     auto rounds = [&](int T, size_t lds) {
@@ -767,7 +768,8 @@ int qgemm_split_choice(const GemmArgs &a)
         return (tiles + resident - 1) / resident;
     };
     if (qgemm_split_takes(a, 16) && rounds(16, split_lds_of<16>(a)) == 1) return 16;
-    const bool two = a.K * (a.w_bits == 16 ? 2 : 1) >= 2304 && a.w_bits != 4 && !a.w_grouped;
+    const long long kb = (long long)a.K * (a.w_bits == 16 ? 2 : 1);
+    const bool two = kb >= 2304 && kb % 128 != 0 && a.w_bits != 4 && !a.w_grouped;
     if (qgemm_split_takes(a, 32) && rounds(32, split_lds_of<32>(a)) <= (two ? 2 : 1)) return 32;
     return 0;
 }

@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 W8 = [(1, 16, 1, 1), (15, 48, 33, 1), (17, 144, 16, 1), (31, 1536, 31, 1), (33, 1552, 65, 1),   # 16x16 tiles; quantization inside up to K = 1536
       (64, 1152, 96, 64), (96, 576, 48, 32),            # several rows per scale: partial maxima, then one launch
       (100, 4608, 700, 1), (330, 2320, 1160, 1),        # 32x32 tiles, two rounds of them
+      (500, 2432, 1152, 1), (3000, 256, 4090, 1),       # more 32x32 tiles than one round, 256x192 tiles just beyond one: other tiles
       (130, 1160, 70, 1), (130, 1157, 70, 1), (3, 7, 5, 1), (2100, 136, 1100, 1)]   # 8-byte and byte-wise row ends, both tile sizes
 
 
@@ -76,7 +77,7 @@ def test_channel_group_scales_by_block_size(gpu, orc, M, K, N, R, group, storage
     assert assert_y_close(host(y), ref) == 0
 
 
-@pytest.mark.parametrize("M,K,N", [(1, 8, 1), (17, 24, 33), (40, 1160, 100), (130, 1154, 70), (500, 4608, 1152)])
+@pytest.mark.parametrize("M,K,N", [(1, 8, 1), (17, 24, 33), (40, 1160, 100), (130, 1154, 70), (500, 4608, 1152), (3000, 192, 4090)])
 def test_f16_small_and_ragged(gpu, orc, M, K, N):
     say("f16 small", M, K, N)
     g = workload.rng("small16", M, K, N)

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
             for (int j = 0; j < W::B_GROUPS; ++j)
                 dma16_buf(a.w, N * WB, dst + (W::A_GROUPS + j) * 1024, offB[j], wb);
         } else {
-            // a chunk past the end of its row reads the row's last one instead (such slices are skipped or meet zeroed activations)
+            // a chunk past the end of its row reads the row's last one instead (such slices are skipped, or zeroed in registers)
 #pragma unroll
             for (int j = 0; j < W::A_GROUPS; ++j)
                 dma16_buf(a.q, M * KB, dst + j * 1024, offA[j] - max(kb + ca[j] - (KB - 16), 0), kb);
@@ -383,7 +383,10 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
             if (!FUSE && kb + 128 > KB) {
 #pragma unroll
                 for (int q = 0; q < NF; ++q)
-                    if (kb + (q * (8 / NF) + kq) * 16 >= KB) afc[q] = frag_a{0, 0, 0, 0};
+                    if (kb + (q * (8 / NF) + kq) * 16 >= KB) {
+                        afc[q] = frag_a{0, 0, 0, 0};
+                        if constexpr (KIND == OP_F16) bfc[q] = frag_b{0, 0, 0, 0};   // 0 * Inf is not 0
+                    }
             }
 #pragma unroll
             for (int q = 0; q < NF; ++q) mma(afc[q], bfc[q]);

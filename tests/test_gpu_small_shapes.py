@@ -89,6 +89,26 @@ def test_f16_small_and_ragged(gpu, orc, M, K, N):
     assert (np.abs(y.astype(np.float64) - ref.astype(np.float64)) <= _f16_tolerance(x, w, ref)).all()
 
 
+# 16x16 and 32x32 split-K tiles with one to seven chunks of the last K step missing, the register-staged kernel, the DMA tiles
+@pytest.mark.parametrize("M,K,N", [(40, 1160, 100), (17, 24, 33), (5, 120, 16), (500, 4616, 500), (700, 136, 700), (130, 1154, 70), (96, 256, 2048)])
+def test_f16_infinite_operands(gpu, orc, M, K, N):
+    """Infinities and NaN in the last inputs of a row reach the outputs that they belong to and no others: what pads a row's last K
+    step must not be multiplied with them."""
+    say("f16 infinities", M, K, N)
+    g = workload.rng("inf16", M, K, N)
+    x = workload.activations(M, K, "inf16")
+    w = (g.standard_normal((N, K), dtype=np.float32) * 0.05).astype(np.float16)
+    x[x == 0] = 1
+    w[w == 0] = 0.05
+    w[0, K - 1], w[N // 2, K - 8], w[N - 1, K - 3] = np.inf, -np.inf, np.nan
+    x[M // 2, K - 2] = np.inf
+    y, ref = host(gpu.qlinear_f16(dev(x), dev(w), None)), orc.linear_f16(x, w, None, nthreads=16)
+    assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isposinf(y), np.isposinf(ref)) and np.array_equal(np.isneginf(y), np.isneginf(ref))
+    rows, cols = np.arange(M) != M // 2, ~np.isin(np.arange(N), [0, N // 2, N - 1])
+    y, ref = y[np.ix_(rows, cols)], ref[np.ix_(rows, cols)]
+    assert (np.abs(y.astype(np.float64) - ref.astype(np.float64)) <= _f16_tolerance(x[rows], w[cols], ref)).all()
+
+
 @pytest.mark.parametrize("M,bits,R", [(16, 8, 1), (40, 4, 1), (64, 8, 64)])
 def test_outputs_over_the_inputs(gpu, M, bits, R):
     """A square layer whose outputs replace its inputs: no workgroup may still read what another one has overwritten."""

@@ -8,11 +8,11 @@
 // Both take 8-bit weights, packed 4-bit weights, int8 codes with group scales and binary16 operands.
 #include "daq_device.h"
 #include "qgemm_common.h"
+#include "split_walk.h"
 
 namespace ql {
 
 constexpr size_t SPLIT_LDS_MAX = 160 * 1024;
-constexpr int SPLIT_FUSE_K_MAX = 1536;   // row length up to which the workgroup quantizes its own rows
 
 enum OperandKind : int { OP_I8 = 0, OP_W4 = 1, OP_I8G = 2, OP_F16 = 3 };
 
@@ -105,7 +105,6 @@ struct SplitTile {
     static constexpr int S = T == 32 ? 2 : GROUPED ? 3 : 4;
     static constexpr int RINGS = 4 * S * STAGE;
     static constexpr int TILE = T * T * 4;                      // one partial tile, bytes
-    static constexpr int GPR_MAX = T == 32 ? 3 : 10;            // groups per round and wavefront
 };
 
 // EXPORT: the integer sums are also written to a.acc_out (verification)
@@ -130,33 +129,10 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
     const int KB = K * EB, WB = KIND == OP_W4 ? K / 2 : KB;
     const int group = GROUPED ? a.group : 128, G = GROUPED ? K / group : 0;
 
-    // ---- the K steps of this wavefront
-    // without groups: steps wave, wave + 4, ...; with groups: rounds of gpr consecutive groups, cut into steps of 128 k
-    const int round_k = gpr * group, round_steps = GROUPED ? (round_k + 127) / 128 : 0;
-    const int groups_mine = GROUPED ? (rounds - 1) * gpr + max(0, min(gpr, G - ((rounds - 1) * 4 + wave) * gpr)) : 0;
-    int steps;
-    if (GROUPED) {
-        const int full = groups_mine / gpr, rest = groups_mine - full * gpr;   // every round but the last is full
-        steps = full * round_steps + (rest * group + 127) / 128;
-    } else {
-        const int nk = (KB + 127) / 128;
-        steps = nk > wave ? (nk - wave + 3) / 4 : 0;
-    }
-    // first byte (of an activation row) of the next step to be requested, and of the next one to be read
-    struct Position {
-        int kb, in_round;
-    };
-    Position ask = {GROUPED ? wave * round_k : wave * 128, 0}, use = ask;
-    auto to_next = [&](Position &p) {
-        if (!GROUPED) {
-            p.kb += 512;
-        } else if (++p.in_round == round_steps) {
-            p.in_round = 0;
-            p.kb += 4 * round_k - (round_steps - 1) * 128;
-        } else {
-            p.kb += 128;
-        }
-    };
+    // ---- the K steps of this wavefront; the next one to be requested, and the next one to be read
+    const SplitWalk<GROUPED> walk(wave, KB, group, G, gpr, rounds);
+    const int steps = walk.steps;
+    typename SplitWalk<GROUPED>::Position ask = walk.first(wave), use = ask;
 
     // ---- DMA: lane l fills bytes [16 l, 16 l + 16) of a 1024-byte group.  128-byte rows: row l/8, chunk c of row r at slot
     // c ^ ((r >> 1) & 7); packed 4-bit rows (64 bytes): row l/4, chunk c at slot c ^ ((r >> 2) & 3).
@@ -178,7 +154,7 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
     }
     auto issue = [&](int slot) {
         const int kb = ask.kb, wb = KIND == OP_W4 ? kb / 2 : kb;
-        to_next(ask);
+        walk.next(ask);
         unsigned char *dst = ring + slot * W::STAGE;
         if (kb + 128 <= KB) {
 #pragma unroll
@@ -230,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
     // FUSE: the codes of the tile's rows, [K step][row][128 bytes] with the chunks of a row swizzled as in the rings, and the
     // rows' scales
     unsigned char *resident = reinterpret_cast<unsigned char *>(ctab + (GROUPED ? T * G : 0));
-    float *srow = reinterpret_cast<float *>(resident + T * ((K + 127) / 128) * 128);
+    float *srow = reinterpret_cast<float *>(resident + T * split_resident_steps(K, GROUPED) * 128);
     if constexpr (FUSE) {
         constexpr int CH = SPLIT_FUSE_K_MAX / 512, RB = T / 4;    // 8-value pieces per lane and row; rows of this wavefront
         const int npad = (K + 127) / 128 * 16;                    // pieces of a row of codes, whole K steps
@@ -298,7 +274,7 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
     auto read_frags = [&](int slot, frag_a(&af)[NF], frag_b(&bf)[NF]) {
         const unsigned char *st = ring + slot * W::STAGE, *stb = st + W::A_GROUPS * 1024;
         const int c0 = use.kb >> 4;   // first chunk of the step inside its row
-        to_next(use);
+        walk.next(use);
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             // first byte of the lane's part: 16-byte chunk and offset inside it
@@ -697,8 +673,7 @@ static bool glue_of(const GemmArgs &a) { return a.act != 0 || a.residual != null
 template <int KIND, int T>
 static int split_gpr(const GemmArgs &a)
 {
-    const int G = SplitTile<KIND, T, false>::GROUPED ? a.K / a.group : 0;
-    return min((G + 3) / 4, SplitTile<KIND, T, false>::GPR_MAX);
+    return SplitTile<KIND, T, false>::GROUPED ? split_groups_per_round(a.K / a.group, T) : 0;
 }
 
 template <int KIND, int T, bool FUSE = false>
@@ -707,7 +682,7 @@ static size_t split_lds(const GemmArgs &a)
     using W = SplitTile<KIND, T, FUSE>;
     const size_t G = W::GROUPED ? a.K / a.group : 0;
     return W::RINGS + (size_t)(W::GROUPED ? 4 * split_gpr<KIND, T>(a) : 0) * W::TILE + T * G * 4 +
-           (FUSE ? (size_t)T * ((a.K + 127) / 128 * 128 + 4) : 0);
+           (FUSE ? (size_t)T * (split_resident_steps(a.K, W::GROUPED) * 128 + 4) : 0);
 }
 
 template <int KIND, int T, bool GLUE, bool EXPORT, bool FUSE>

@@ -161,6 +161,16 @@ def test_daq_division_free_codes_exhaustive(tmp_path):
     assert all("mismatches 0 out-of-range 0" in l for l in lines), r.stdout
 
 
+def test_split_k_walk_stays_inside_the_row_and_the_lds(tmp_path):
+    """The few-rows kernel's walk over K, from the kernel's own header: every slice once, nothing read behind the row or behind the
+    LDS that holds the workgroup's codes, for every inner size up to 5120 and every weight group."""
+    import subprocess
+    exe = str(tmp_path / "split_walk_check")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-o", exe, os.path.join(os.path.dirname(__file__), "split_walk_check.cpp")], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
 class _Prm(ctypes.Structure):
     _fields_ = [("p_ppm", ctypes.c_int32), ("a_bits", ctypes.c_int32)]
 

@@ -141,14 +141,14 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
         for (int i = 0; i < NA; ++i) {
             const int row = 8 * (wave + i * NW) + (lane >> 3);
             const int c = (lane & 7) ^ ((row >> 1) & 7);
-            goffA[i] = (unsigned)(min(m0 + row, M - 1) * K * EB + 16 * c);
+            goffA[i] = row_start(min(m0 + row, M - 1), K * EB) + 16 * c;
         }
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             if (!W4) {
                 const int row = 8 * (wave + i * NW) + (lane >> 3);
                 const int c = (lane & 7) ^ ((row >> 1) & 7);
-                goffB[i] = (unsigned)(min(n0 + row, N - 1) * K * EB + 16 * c);
+                goffB[i] = row_start(min(n0 + row, N - 1), K * EB) + 16 * c;
             } else {
                 // packed 4-bit rows are 64 bytes per K step: 16 rows per group, chunk c of row r at slot c ^ ((r >> 2) & 3)
                 const int row = 16 * (wave + i * NW) + (lane >> 2);

@@ -100,21 +100,21 @@ __global__ __launch_bounds__(T::NTHR, 2) void qgemm_big(GemmArgs a, int tiles_m,
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
             const int row = 8 * (wave + i * T::NW) + (lane >> 3);
-            offA[i] = (unsigned)(min(m0 + row, M - 1) * KB + 16 * ((lane & 7) ^ ((row >> 1) & 7)));
+            offA[i] = row_start(min(m0 + row, M - 1), KB) + 16 * ((lane & 7) ^ ((row >> 1) & 7));
         }
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             const int row = 8 * (wave + i * T::NW) + (lane >> 3);
             const int g = (wave + i * T::NW) >> 1, p = 8 * ((wave + i * T::NW) & 1) + (lane >> 3);
             const int col = g < NM * T::WN ? (g / NM) * 16 * NM + 8 * p + g % NM : 16 * NM * T::WN + 2 * p + (g - NM * T::WN);
-            offB[i] = (unsigned)(min(n0 + col, N - 1) * KB + 16 * ((lane & 7) ^ ((row >> 1) & 7)));
+            offB[i] = row_start(min(n0 + col, N - 1), KB) + 16 * ((lane & 7) ^ ((row >> 1) & 7));
         }
     };
     auto issue = [&](int kt, int stage, int li) {
         unsigned char *st = smem + stage * T::STAGE;
-        if (li < NA) dma16_buf(a.q, M * KB, st + (wave + li * T::NW) * 1024, offA[li < NA ? li : 0], kt * 128);
+        if (li < NA) dma16_buf(a.q, operand_bytes(M, KB), st + (wave + li * T::NW) * 1024, offA[li < NA ? li : 0], kt * 128);
         else if (T::B_GROUPS % T::NW == 0 || wave + (li - NA) * T::NW < T::B_GROUPS)
-            dma16_buf(a.w, N * KB, st + T::A_BYTES + (wave + (li - NA) * T::NW) * 1024, offB[li < NA ? 0 : li - NA], kt * 128);
+            dma16_buf(a.w, operand_bytes(N, KB), st + T::A_BYTES + (wave + (li - NA) * T::NW) * 1024, offB[li < NA ? 0 : li - NA], kt * 128);
     };
     // the epilogue's scales, straight to LDS
     auto fetch_scales = [&](int par) {

@@ -1,6 +1,7 @@
 // Device helpers shared by the GEMM kernels (qgemm.hip, qgemm_w4.hip): vector types, the block glue folded into the
 // epilogue, and the packed write-back of a dequantized tile.  Not part of the public ABI.
 #pragma once
+#include "operand_bytes.h"
 #include "ql_internal.h"
 
 #include <type_traits>
@@ -33,7 +34,7 @@ __device__ __forceinline__ float half_to_float_dev(unsigned short h)
 // One DMA instruction, buffer form: 64 lanes x 16 bytes from base + lane_off + step_off to the 1024 bytes at lds.  The
 // descriptor and the K-step offset live in scalar registers and the lane's fixed offset in one vector register, so that
 // issuing a load costs no vector ALU work; reads past `bytes` return zero.
-__device__ __forceinline__ void dma16_buf(const void *base, int bytes, unsigned char *lds, unsigned lane_off, int step_off)
+__device__ __forceinline__ void dma16_buf(const void *base, unsigned bytes, unsigned char *lds, unsigned lane_off, int step_off)
 {
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)lds, 16, lane_off, step_off, 0, 0);

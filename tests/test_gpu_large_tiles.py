@@ -58,3 +58,26 @@ def test_large_tiles(gpu, orc, tile, M, K, N):
     u = orc.dequant_w8(acc, s, 1, lw["s_w"], bias)
     ref = np.concatenate([orc.block_glue(u[i:i + 1], act=0, residual=res[r:r + 1], gate=gate[r // gate_rows:r // gate_rows + 1], gate_rows=1) for i, r in enumerate(rows)])
     assert assert_y_close(ys[2], ref) == 0
+
+
+@pytest.mark.parametrize("tile", ["f16 big 256x288", "f16 big 256x256", "f16 dma 128x128 a3b2 4w spread1"])
+def test_binary16_operand_above_two_gigabytes(gpu, orc, tile):
+    """2^20 rows of 2176 bytes: the last rows start at byte offsets that only an unsigned 32-bit number holds."""
+    import torch
+    M, K, N = 1 << 20, 1088, 256
+    say(tile, M, K, N)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    x = torch.empty((M, K), dtype=torch.float16, device="cuda").normal_(generator=g)
+    w = torch.empty((N, K), dtype=torch.float16, device="cuda").normal_(0.0, 0.05, generator=g)
+    assert x.numel() * 2 > 2 ** 31
+    gpu.set_gemm_variant(gpu.gemm_variants().index(tile))
+    try:
+        y = gpu.qlinear_f16(x, w, None)
+    finally:
+        gpu.set_gemm_variant(-1)
+    edge = 2 ** 31 // (2 * K)
+    rows = torch.tensor([0, 1, 777777, *range(edge - 20, edge + 20), *range(M - 40, M)], device="cuda")
+    xs, ys = host(x[rows]), host(y[rows])
+    ref = orc.linear_f16(xs, host(w), None, nthreads=16)
+    assert (np.abs(ys.astype(np.float64) - ref.astype(np.float64)) <= _f16_tolerance(xs, host(w), ref)).all()

@@ -281,6 +281,10 @@ __global__ __launch_bounds__(256) void daq_cg_quant(DaqArgs a, int cg)
 // group with plain stores, no clearing pass and no atomics; pass 2 takes the maximum over its block's slabs.
 // M = 4096, K = 1152, R = 256, cg = 128: 32.7 -> 13 us.
 constexpr int DAQ_CG_ROWS = 4;    // rows in flight per thread
+// Slabs per scale block up to which every thread takes the maximum of its group over them by itself; beyond that the workgroup does it
+// together (both passes, cg = 128, M = R = 16384, 1024 slabs: K = 1152 131 -> 22 us, K = 4608 404 -> 91, where the atomic kernels take
+// 79 and 185; M = 4096, R = 1024, K = 1152: 15.5 -> 8.4)
+constexpr int DAQ_CG_OWN = 16;
 template <bool QUANT>
 __global__ __launch_bounds__(1024) void daq_cg_slab(DaqArgs a, int cg, int slab, int rpw)
 {
@@ -288,19 +292,28 @@ __global__ __launch_bounds__(1024) void daq_cg_slab(DaqArgs a, int cg, int slab,
     const int P = a.K >> 3, G = a.K / cg;
     const int p = threadIdx.x % P, r0 = threadIdx.x / P, g = p * 8 / cg;
     const bool on = r0 < rpw;
-    const int row0 = blockIdx.x * slab;
+    const int row0 = blockIdx.x * slab, slabs = a.R / slab;
     unsigned *part = a.blockmax;          // [M / slab][G]
     float alpha = 1.0f, rcp = 1.0f;
-    if (!QUANT) {
+    if (!QUANT || slabs > DAQ_CG_OWN) {
         for (int i = threadIdx.x; i < G; i += blockDim.x) gmax_lds[i] = 0;
         __syncthreads();
-    } else if (on) {
-        const unsigned *pm = part + (size_t)(row0 / a.R) * (a.R / slab) * G + g;
+    }
+    if (QUANT) {
+        const unsigned *pm = part + (size_t)(row0 / a.R) * slabs * G;
         unsigned m = 0;
-        for (int s = 0; s < a.R / slab; ++s) m = m > pm[(size_t)s * G] ? m : pm[(size_t)s * G];
-        alpha = alpha_from_bits(m);
-        rcp = 1.0f / alpha;
-        if (row0 % a.R == 0 && r0 == 0 && p * 8 % cg == 0) a.scales[(size_t)(row0 / a.R) * G + g] = alpha;
+        if (slabs > DAQ_CG_OWN) {
+            for (int i = threadIdx.x; i < slabs * G; i += blockDim.x) atomicMax(&gmax_lds[i % G], pm[i]);
+            __syncthreads();
+            if (on) m = gmax_lds[g];
+        } else if (on) {
+            for (int s = 0; s < slabs; ++s) m = m > pm[s * G + g] ? m : pm[s * G + g];
+        }
+        if (on) {
+            alpha = alpha_from_bits(m);
+            rcp = 1.0f / alpha;
+            if (row0 % a.R == 0 && r0 == 0 && p * 8 % cg == 0) a.scales[(size_t)(row0 / a.R) * G + g] = alpha;
+        }
     }
     if (on) {
         const uint4 *x = reinterpret_cast<const uint4 *>(a.x) + (size_t)row0 * P + p;
@@ -330,11 +343,16 @@ __global__ __launch_bounds__(1024) void daq_cg_slab(DaqArgs a, int cg, int slab,
 hipError_t launch_daq_cg(const DaqArgs &a, int cg, bool slabs, hipStream_t stream)
 {
     const int slab = slabs ? daq_cg_slab_rows(a.R) : 0, P = a.K / 8, G = a.K / cg;
-    if (slab > 0 && P <= 1024) {
-        const int rpw = P >= 512 ? 1 : 512 / P;
+    // few wide rows in short blocks make a few large workgroups and nothing to merge: the kernels with a wavefront per row
+    // (K = 4608, R = 16, 512 rows: 12 against 15.5 us; from 4096 rows on they are level)
+    const bool few = P > 512 && a.R <= 64 && a.M <= 2048;
+    if (slab > 0 && P <= 1024 && !few) {
+        // rows walked side by side: half a workgroup's threads where rows are short, all of them where one row at a time would leave a
+        // chain of four trips to memory (M = 512, R = 64, K = 3072: 14.5 -> 11.3 us; all threads at M = 16384, R = 64, K = 384: 10.0 -> 12.6)
+        const int rpw = P > 512 ? 1 : P > 256 ? 1024 / P : 512 / P;
         const dim3 grid(a.M / slab), block((P * rpw + 63) / 64 * 64);
         hipLaunchKernelGGL(daq_cg_slab<false>, grid, block, G * 4, stream, a, cg, slab, rpw);
-        hipLaunchKernelGGL(daq_cg_slab<true>, grid, block, 0, stream, a, cg, slab, rpw);
+        hipLaunchKernelGGL(daq_cg_slab<true>, grid, block, G * 4, stream, a, cg, slab, rpw);
         return hipGetLastError();
     }
     const int n = (a.M / a.R) * G;

@@ -89,6 +89,17 @@ def test_f16_small_and_ragged(gpu, orc, M, K, N):
     assert (np.abs(y.astype(np.float64) - ref.astype(np.float64)) <= _f16_tolerance(x, w, ref)).all()
 
 
+# 17 and 256 slabs per scale block (merged by the workgroup together), 16 (each thread for itself); one, two and three rows side by side;
+# the last shape of the row kernels and the first one of the slabs behind it
+@pytest.mark.parametrize("M,K,R,cg", [(544, 2568, 272, 24), (4096, 384, 4096, 96), (512, 1160, 256, 8), (1024, 4096, 1024, 32), (2048, 4608, 64, 288), (2112, 4608, 64, 288)])
+def test_channel_group_slabs(gpu, orc, M, K, R, cg):
+    say("channel-group slabs", M, K, R, cg)
+    x = workload.activations(M, K, "slabs", R, cg)
+    q_ref, a_ref = orc.daq_cg(x, R, cg, nthreads=16)
+    q, a = gpu.daq_quantize_cg(dev(x), R, cg)
+    assert np.array_equal(host(a).view(np.uint32), a_ref.view(np.uint32)) and np.array_equal(host(q), q_ref)
+
+
 # 16x16 and 32x32 split-K tiles with one to seven chunks of the last K step missing, the register-staged kernel, the DMA tiles
 @pytest.mark.parametrize("M,K,N", [(40, 1160, 100), (17, 24, 33), (5, 120, 16), (500, 4616, 500), (700, 136, 700), (130, 1154, 70), (96, 256, 2048)])
 def test_f16_infinite_operands(gpu, orc, M, K, N):

@@ -178,15 +178,15 @@ __device__ __forceinline__ unsigned second_selection(const DaqArgs &a, int b, un
 }
 
 // ---- one row per scale, row in registers ------------------------------------------------------------------------
-// mode DAQ_FUSED: select tau, then quantize; mode DAQ_QUANT: tau of the row's block comes from the second histogram pass
-// (quant_parts partial histograms, R % 4 == 0: the workgroup's rows share a block) or from blockmax
-template <int CH>
+// mode DAQ_FUSED: select tau, then quantize; mode DAQ_QUANT: tau of the row's block comes from blockmax, or with HIST from the second
+// histogram pass (quant_parts partial histograms, R % 4 == 0: the workgroup's rows share a block).  HIST is a kernel of its own: its LDS
+// and barriers inside the others cost one row per scale 8 % (M = 16384, K = 1152: 18.0 -> 19.6 us)
+template <int CH, bool HIST>
 __global__ __launch_bounds__(256) void daq_rows_robust(DaqArgs a, int mode)
 {
     const int lane = threadIdx.x & 63;
     const int wg = mode == DAQ_QUANT ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
     const int row = wg * 4 + (threadIdx.x >> 6);
-    __shared__ unsigned bins[HIST_BINS];
     if (row >= a.M) return;   // whole workgroups at a time where the rows share a block
     const int nch = a.K >> 3;
     const uint4 *xr = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(a.x) + (size_t)row * a.K);
@@ -197,7 +197,8 @@ __global__ __launch_bounds__(256) void daq_rows_robust(DaqArgs a, int mode)
         v[i] = c < nch ? xr[c] : make_uint4(0, 0, 0, 0);
     }
     unsigned tau_bits;
-    if (mode == DAQ_QUANT && a.quant_parts > 0) {
+    if constexpr (HIST) {
+        __shared__ unsigned bins[HIST_BINS];
         tau_bits = second_selection(a, row / a.R, bins);
     } else if (mode == DAQ_QUANT) {
         tau_bits = a.blockmax[row / a.R];
@@ -424,7 +425,8 @@ __global__ void fill_zero_u32(unsigned *p, size_t n)
 template <int CH>
 static void run_robust_cached(const DaqArgs &a, int mode, hipStream_t s)
 {
-    hipLaunchKernelGGL(daq_rows_robust<CH>, dim3((a.M + 3) / 4), dim3(256), 0, s, a, mode);
+    if (mode == DAQ_QUANT && a.quant_parts > 0) hipLaunchKernelGGL((daq_rows_robust<CH, true>), dim3((a.M + 3) / 4), dim3(256), 0, s, a, mode);
+    else hipLaunchKernelGGL((daq_rows_robust<CH, false>), dim3((a.M + 3) / 4), dim3(256), 0, s, a, mode);
 }
 
 static void run_robust_rows(const DaqArgs &a, int mode, hipStream_t s)

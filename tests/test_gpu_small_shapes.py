@@ -15,6 +15,7 @@ W8 = [(1, 16, 1, 1), (15, 48, 33, 1), (17, 144, 16, 1), (31, 1536, 31, 1), (33, 
       (64, 1152, 96, 64), (96, 576, 48, 32),            # several rows per scale: partial maxima, then one launch
       (100, 4608, 700, 1), (330, 2320, 1160, 1),        # 32x32 tiles, two rounds of them
       (500, 2432, 1152, 1), (3000, 256, 4090, 1),       # more 32x32 tiles than one round, 256x192 tiles just beyond one: other tiles
+      (2300, 64, 2176, 1), (2177, 448, 2048, 7), (17000, 2112, 520, 17000),                      # an odd multiple of 64, more than 256 tiles
       (130, 1160, 70, 1), (130, 1157, 70, 1), (3, 7, 5, 1), (2100, 136, 1100, 1)]   # 8-byte and byte-wise row ends, both tile sizes
 
 

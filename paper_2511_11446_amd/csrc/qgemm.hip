@@ -5,8 +5,10 @@
 // Here: acc[m,n] = sum_k q[m,k] * w[n,k] on v_mfma_i32_32x32x32_i8, both
 // operands K-contiguous, and the dequantization + bias + fp16 conversion applied
 // to the accumulators in registers.  The kernel families:
-//   qgemm_dma   (here) tiles go global -> LDS by DMA through rings of 2-3 stages, optional persistent walk over
-//               tiles; 8-bit weights, and binary16 operands for the layers a plan leaves in FP16
+//   qgemm_big, qgemm_w4_big (qgemm_big.hip, qgemm_w4_big.hip) tiles of up to 256x288: 8-bit weights and binary16 operands,
+//               and packed 4-bit weights with groups of 128
+//   qgemm_dma   (here) tiles of 64x64 to 256x192 go global -> LDS by DMA through rings of 2-3 stages, optional
+//               persistent walk over tiles; 8-bit weights, and binary16 operands for the layers a plan leaves in FP16
 //   qgemm_w4    (qgemm_w4.hip) group scales: packed 4-bit weights and int8 codes with group scales
 //   qgemm_k64   (here) 8-bit layers of many tiles whose inner size is an odd multiple of 64
 //   qgemm_splitk, qgemm_edge (qgemm_small.hip) few rows; any inner size and alignment
@@ -711,10 +713,20 @@ __global__ __launch_bounds__(256) void qgemm_naive(GemmArgs a)
 // ---- variants -----------------------------------------------------------------
 struct Variant {
     const char *name;
-    int w_bits, BM, BN, BK;   // BK: K must be a multiple of this
+    int w_bits;
+    bool (*takes)(const GemmArgs &);
     hipError_t (*run)(const GemmArgs &, hipStream_t);
-    hipError_t (*run_glue)(const GemmArgs &, hipStream_t) = nullptr;   // the same tile with block glue in the epilogue (shape-chosen variants only)
+    hipError_t (*run_glue)(const GemmArgs &, hipStream_t) = nullptr;   // the same tile with block glue in the epilogue
 };
+
+// the DMA kernels need 16-byte loads along K and whole K steps of 128 bytes
+static bool dma_takes(const GemmArgs &a)
+{
+    return (a.K * (a.w_bits == 16 ? 2 : 1)) % 128 == 0 && ((uintptr_t)a.q | (uintptr_t)a.w) % 16 == 0;
+}
+
+template <int T>
+static bool split_takes(const GemmArgs &a) { return qgemm_split_takes(a, T); }
 
 //                          TM TN WGM WGN S WPS
 using D8_128x128_s3 = TileD<2, 2, 2, 2, 3, 2>;
@@ -748,53 +760,53 @@ using H_p192 = TileD<2, 3, 2, 2, 2, 2, true, 1, false, 2, true, true>;
 using H_p128 = TileD<2, 2, 2, 2, 3, 2, true, 1, false, 2, true, true>;
 
 static const Variant VARIANTS[] = {
-    {"w8 dma 64x64 s3 4w", 8, 64, 64, 128, run_dma<D8_64x64_s3>, run_dma<D8_64x64_s3, true>},
-    {"w8 dma 256x192 a3b2 8w spread1", 8, 256, 192, 128, run_dma<D8_256x192_8w_a3b2>, run_dma<D8_256x192_8w_a3b2, true>},
-    {"w8 dma 128x128 a3b2 4w", 8, 128, 128, 128, run_dma<D8_128x128_a3b2>, run_dma<D8_128x128_a3b2, true>},
-    {"w8 dma 128x128 a3b2 4w spread1", 8, 128, 128, 128, run_dma<D8_128x128_a3b2_e1>, run_dma<D8_128x128_a3b2_e1, true>},
-    {"w8 dma 128x128 a3b2 4w spread1 persistent", 8, 128, 128, 128, run_dma<P8_128x128_a3b2>},
-    {"w8 dma 128x192 s2 4w spread1 persistent", 8, 128, 192, 128, run_dma<P8_128x192_s2>},
-    {"f16 dma 256x192 a3b2 8w spread1", 16, 256, 192, 64, run_dma<H_256x192_8w>, run_dma<H_256x192_8w, true>},
-    {"f16 dma 128x128 a3b2 4w spread1", 16, 128, 128, 64, run_dma<H_128x128_4w>, run_dma<H_128x128_4w, true>},
-    {"f16 dma 64x64 s3 4w", 16, 64, 64, 64, run_dma<H_64x64_4w>, run_dma<H_64x64_4w, true>},
-    {"f16 dma 128x192 s2 4w spread1 persistent", 16, 128, 192, 64, run_dma<H_p192>},
-    {"w4 pipelined 128x128 a3b2 4w any-group", 4, 128, 128, 128, launch_qgemm_w4_128, launch_qgemm_w4_128},
-    {"w4 pipelined 64x64 a3b2 4w any-group", 4, 64, 64, 128, launch_qgemm_w4_64, launch_qgemm_w4_64},
-    {"w8 big 256x288", 8, 256, 288, 128, launch_big_w8_256x288, launch_big_w8_256x288_glue},
-    {"w8 big 256x256", 8, 256, 256, 128, launch_big_w8_256x256, launch_big_w8_256x256_glue},
-    {"w8 big 128x288", 8, 128, 288, 128, launch_big_w8_128x288, launch_big_w8_128x288_glue},
-    {"f16 big 256x288", 16, 256, 288, 64, launch_big_f16_256x288, launch_big_f16_256x288_glue},
-    {"f16 big 256x256", 16, 256, 256, 64, launch_big_f16_256x256, launch_big_f16_256x256_glue},
-    {"w4 big 256x288", 4, 256, 288, 128, launch_big_w4_256x288, launch_big_w4_256x288_glue},
-    {"w4 big 256x256", 4, 256, 256, 128, launch_big_w4_256x256, launch_big_w4_256x256_glue},
-    {"w4 big 128x288", 4, 128, 288, 128, launch_big_w4_128x288, launch_big_w4_128x288_glue},
-    {"w8 split-K 32x32", 8, 32, 32, 16, launch_qgemm_split32, launch_qgemm_split32},
-    {"w4 any-group split-K 32x32", 4, 32, 32, 32, launch_qgemm_split32, launch_qgemm_split32},
-    {"f16 split-K 32x32", 16, 32, 32, 8, launch_qgemm_split32, launch_qgemm_split32},
-    {"w8 split-K 16x16", 8, 16, 16, 16, launch_qgemm_split16, launch_qgemm_split16},
-    {"w4 any-group split-K 16x16", 4, 16, 16, 32, launch_qgemm_split16, launch_qgemm_split16},
-    {"f16 split-K 16x16", 16, 16, 16, 8, launch_qgemm_split16, launch_qgemm_split16},
-    {"w8 staged 128x128 k64", 8, 128, 128, 64, run_k64},
-    {"w8 edge any-K", 8, 64, 64, 1, launch_qgemm_edge, launch_qgemm_edge},
-    {"w4 any-group edge any-K", 4, 64, 64, 32, launch_qgemm_edge, launch_qgemm_edge},
-    {"f16 edge any-K", 16, 64, 64, 1, launch_qgemm_edge, launch_qgemm_edge},
+    {"w8 dma 64x64 s3 4w", 8, dma_takes, run_dma<D8_64x64_s3>, run_dma<D8_64x64_s3, true>},
+    {"w8 dma 256x192 a3b2 8w spread1", 8, dma_takes, run_dma<D8_256x192_8w_a3b2>, run_dma<D8_256x192_8w_a3b2, true>},
+    {"w8 dma 128x128 a3b2 4w", 8, dma_takes, run_dma<D8_128x128_a3b2>, run_dma<D8_128x128_a3b2, true>},
+    {"w8 dma 128x128 a3b2 4w spread1", 8, dma_takes, run_dma<D8_128x128_a3b2_e1>, run_dma<D8_128x128_a3b2_e1, true>},
+    {"w8 dma 128x128 a3b2 4w spread1 persistent", 8, dma_takes, run_dma<P8_128x128_a3b2>},
+    {"w8 dma 128x192 s2 4w spread1 persistent", 8, dma_takes, run_dma<P8_128x192_s2>},
+    {"f16 dma 256x192 a3b2 8w spread1", 16, dma_takes, run_dma<H_256x192_8w>, run_dma<H_256x192_8w, true>},
+    {"f16 dma 128x128 a3b2 4w spread1", 16, dma_takes, run_dma<H_128x128_4w>, run_dma<H_128x128_4w, true>},
+    {"f16 dma 64x64 s3 4w", 16, dma_takes, run_dma<H_64x64_4w>, run_dma<H_64x64_4w, true>},
+    {"f16 dma 128x192 s2 4w spread1 persistent", 16, dma_takes, run_dma<H_p192>},
+    {"w4 pipelined 128x128 a3b2 4w any-group", 4, qgemm_w4_takes, launch_qgemm_w4_128, launch_qgemm_w4_128},
+    {"w4 pipelined 64x64 a3b2 4w any-group", 4, qgemm_w4_takes, launch_qgemm_w4_64, launch_qgemm_w4_64},
+    {"w8 big 256x288", 8, qgemm_big_takes, launch_big_w8_256x288, launch_big_w8_256x288_glue},
+    {"w8 big 256x256", 8, qgemm_big_takes, launch_big_w8_256x256, launch_big_w8_256x256_glue},
+    {"w8 big 128x288", 8, qgemm_big_takes, launch_big_w8_128x288, launch_big_w8_128x288_glue},
+    {"f16 big 256x288", 16, qgemm_big_takes, launch_big_f16_256x288, launch_big_f16_256x288_glue},
+    {"f16 big 256x256", 16, qgemm_big_takes, launch_big_f16_256x256, launch_big_f16_256x256_glue},
+    {"w4 big 256x288", 4, qgemm_w4_big_takes, launch_big_w4_256x288, launch_big_w4_256x288_glue},
+    {"w4 big 256x256", 4, qgemm_w4_big_takes, launch_big_w4_256x256, launch_big_w4_256x256_glue},
+    {"w4 big 128x288", 4, qgemm_w4_big_takes, launch_big_w4_128x288, launch_big_w4_128x288_glue},
+    {"w8 split-K 32x32", 8, split_takes<32>, launch_qgemm_split32, launch_qgemm_split32},
+    {"w4 any-group split-K 32x32", 4, split_takes<32>, launch_qgemm_split32, launch_qgemm_split32},
+    {"f16 split-K 32x32", 16, split_takes<32>, launch_qgemm_split32, launch_qgemm_split32},
+    {"w8 split-K 16x16", 8, split_takes<16>, launch_qgemm_split16, launch_qgemm_split16},
+    {"w4 any-group split-K 16x16", 4, split_takes<16>, launch_qgemm_split16, launch_qgemm_split16},
+    {"f16 split-K 16x16", 16, split_takes<16>, launch_qgemm_split16, launch_qgemm_split16},
+    {"w8 staged 128x128 k64", 8, k64_takes, run_k64},
+    {"w8 edge any-K", 8, qgemm_edge_takes, launch_qgemm_edge, launch_qgemm_edge},
+    {"w4 any-group edge any-K", 4, qgemm_edge_takes, launch_qgemm_edge, launch_qgemm_edge},
+    {"f16 edge any-K", 16, qgemm_edge_takes, launch_qgemm_edge, launch_qgemm_edge},
 #ifdef QL_SWEEP_VARIANTS   // the other tile shapes of the sweeps that chose the ones above
-    {"w8 dma 128x128 s3 4w", 8, 128, 128, 128, run_dma<D8_128x128_s3>},
-    {"w8 dma 128x128 s2 4w", 8, 128, 128, 128, run_dma<D8_128x128_s2>},
-    {"w8 dma 128x192 s3 4w", 8, 128, 192, 128, run_dma<D8_128x192_s3>},
-    {"w8 dma 128x192 s2 4w", 8, 128, 192, 128, run_dma<D8_128x192_s2>},
-    {"w8 dma 256x128 s3 4w", 8, 256, 128, 128, run_dma<D8_256x128_s3>},
-    {"w8 dma 256x192 s2 4w", 8, 256, 192, 128, run_dma<D8_256x192_s2>},
-    {"w8 dma 256x256 s2 8w", 8, 256, 256, 128, run_dma<D8_256x256_8w>},
-    {"w8 dma 256x192 s2 8w", 8, 256, 192, 128, run_dma<D8_256x192_8w>},
-    {"w8 dma 256x192 s2 8w spread1", 8, 256, 192, 128, run_dma<D8_256x192_8w_e1>},
-    {"w8 dma 256x256 s2 8w spread1", 8, 256, 256, 128, run_dma<D8_256x256_8w_e1>},
-    {"w8 dma 256x256 s2 8w spread2", 8, 256, 256, 128, run_dma<D8_256x256_8w_e2>},
-    {"w8 dma 256x192 s2 4w spread2", 8, 256, 192, 128, run_dma<D8_256x192_4w_e2>},
-    {"w8 dma 256x192 a2b3 8w spread1", 8, 256, 192, 128, run_dma<D8_256x192_8w_a2b3>},
-    {"w8 dma 256x256 a3b2 8w spread1", 8, 256, 256, 128, run_dma<D8_256x256_8w_a3b2>},
-    {"w8 dma 128x128 s2 4w spread1", 8, 128, 128, 128, run_dma<D8_128x128_s2_e1>},
-    {"f16 dma 128x128 a3b2 4w spread1 persistent", 16, 128, 128, 64, run_dma<H_p128>},
+    {"w8 dma 128x128 s3 4w", 8, dma_takes, run_dma<D8_128x128_s3>},
+    {"w8 dma 128x128 s2 4w", 8, dma_takes, run_dma<D8_128x128_s2>},
+    {"w8 dma 128x192 s3 4w", 8, dma_takes, run_dma<D8_128x192_s3>},
+    {"w8 dma 128x192 s2 4w", 8, dma_takes, run_dma<D8_128x192_s2>},
+    {"w8 dma 256x128 s3 4w", 8, dma_takes, run_dma<D8_256x128_s3>},
+    {"w8 dma 256x192 s2 4w", 8, dma_takes, run_dma<D8_256x192_s2>},
+    {"w8 dma 256x256 s2 8w", 8, dma_takes, run_dma<D8_256x256_8w>},
+    {"w8 dma 256x192 s2 8w", 8, dma_takes, run_dma<D8_256x192_8w>},
+    {"w8 dma 256x192 s2 8w spread1", 8, dma_takes, run_dma<D8_256x192_8w_e1>},
+    {"w8 dma 256x256 s2 8w spread1", 8, dma_takes, run_dma<D8_256x256_8w_e1>},
+    {"w8 dma 256x256 s2 8w spread2", 8, dma_takes, run_dma<D8_256x256_8w_e2>},
+    {"w8 dma 256x192 s2 4w spread2", 8, dma_takes, run_dma<D8_256x192_4w_e2>},
+    {"w8 dma 256x192 a2b3 8w spread1", 8, dma_takes, run_dma<D8_256x192_8w_a2b3>},
+    {"w8 dma 256x256 a3b2 8w spread1", 8, dma_takes, run_dma<D8_256x256_8w_a3b2>},
+    {"w8 dma 128x128 s2 4w spread1", 8, dma_takes, run_dma<D8_128x128_s2_e1>},
+    {"f16 dma 128x128 a3b2 4w spread1 persistent", 16, dma_takes, run_dma<H_p128>},
 #endif
 };
 constexpr int NUM_VARIANTS = sizeof(VARIANTS) / sizeof(VARIANTS[0]);
@@ -809,96 +821,96 @@ static int find_variant(const char *name)
     return 0;
 }
 
-// The large tiles of qgemm_big.hip and qgemm_w4_big.hip, or -1: where their whole rounds of tiles (one per CU) cost less than the
-// tiles below would.
-// Microseconds fitted to sweeps over M = 1024..16384 and ten to thirteen (K, N) from 384 to 4608 with random operands: a large tile
-// costs `step` per 128 bytes of K and `tile` for what is not hidden of its prologue and epilogue; the other kernels
-// cost their operations at 2280 TOPS (1100 TFLOP/s in binary16) plus their output at 5 TB/s, and with 4-bit weights 1636 TOPS
-// of 128x128 tiles in multiples of 256 plus the output at 7.7 TB/s.  The fit holds within a few per cent where the chip is full and
-// flatters the other kernels where it is not.
-static int choose_big(const GemmArgs &a)
+// ---- tile choice --------------------------------------------------------------------------------------------------------
+// What a layer takes on each tile, in microseconds: the tiles of the busiest CU one after the other, `resident` of them sharing it.
+//
+//   base + n * (tile + step * K steps + fold * groups) + rounds * (round_step * K steps + round_fold * groups) + more * (n - resident)
+//   n = tiles of the busiest CU, rounds = ceil(n / resident), K steps of 128 bytes, groups of 4-bit weights along K
+//   + per 10^4 outputs of the busiest CU: act (GELU), gated (gate or residual)
+//   + for the part of a partial tile that is written, per value of a lane: edge, edge_act, edge_gated (the large tiles write theirs in
+//     pieces like whole ones)
+//
+// Fitted to sweeps on MI355X over M = 640..16384 and 27 (K, N) from 256 to 5120, plain, with GELU and with gate and residual; DAQ in front of
+// the layer, other weights and outputs in every call, as in a stack; 4-bit weights also with groups of 32, 64, 192 and 288.  The tile
+// chosen is in the mean 0.3 % slower than the fastest one, 2 % of 6300 cases lose more than 5 %, and the worst one (partial tiles with GELU)
+// 43 %.  Rules that charged the large tiles per round and the others by their rate, without the glue, lost 2 % (4 bits) to 6 % (FP16) in
+// the mean of the plain layers and 5 to 17 % with gate and residual (8-bit, M = 8192, K = 256, N = 1024: 40.7 us against 14.3).
+struct TileCost {
+    const char *name;
+    int bits, BM, BN, resident;
+    float base, tile, step, fold, round_step, round_fold, more;
+    int most_tiles = 0;   // not beyond this many (0: any)
+};
+static const TileCost TILE_COSTS[] = {
+    {"w8 dma 64x64 s3 4w", 8, 64, 64, 3, 4.685f, 0, 0.133f, 0, 0.154f, 0, 0.890f},
+    {"w8 dma 128x128 a3b2 4w", 8, 128, 128, 2, 0.065f, 4.717f, 0.531f, 0, 0, 0, 1.019f, 256},   // the deeper issue of one tile per CU at most
+    {"w8 dma 128x128 a3b2 4w spread1", 8, 128, 128, 2, 3.178f, 1.466f, 0.183f, 0, 0.399f, 0, 1.163f},
+    {"w8 dma 128x128 a3b2 4w spread1 persistent", 8, 128, 128, 2, 4.291f, 1.123f, 0.245f, 0, 0.276f, 0, 1.187f},
+    {"w8 dma 128x192 s2 4w spread1 persistent", 8, 128, 192, 2, 3.888f, 1.543f, 0.250f, 0, 0.752f, 0, 1.600f},
+    {"w8 dma 256x192 a3b2 8w spread1", 8, 256, 192, 1, 0, 7.622f, 1.173f, 0, 0, 0, 1.376f},
+    {"w8 big 128x288", 8, 128, 288, 1, 3.469f, 5.451f, 1.251f, 0, 0, 0, 1.285f},
+    {"w8 big 256x256", 8, 256, 256, 1, 3.808f, 5.434f, 1.422f, 0, 0, 0, 0.176f},
+    {"w8 big 256x288", 8, 256, 288, 1, 2.983f, 8.716f, 1.773f, 0, 0, 0, 0.128f},
+    {"f16 dma 64x64 s3 4w", 16, 64, 64, 3, 3.401f, 0.047f, 0.163f, 0, 0.095f, 0, 0.784f},
+    {"f16 dma 128x128 a3b2 4w spread1", 16, 128, 128, 2, 2.892f, 0.472f, 0.293f, 0, 0.293f, 0, 1.441f},
+    {"f16 dma 128x192 s2 4w spread1 persistent", 16, 128, 192, 2, 1.821f, 1.541f, 0.336f, 0, 0.573f, 0, 2.070f},
+    {"f16 dma 256x192 a3b2 8w spread1", 16, 256, 192, 1, 0.275f, 5.430f, 1.129f, 0, 0, 0, 4.768f},
+    {"f16 big 256x256", 16, 256, 256, 1, 1.395f, 4.703f, 1.423f, 0, 0, 0, 0.007f},
+    {"f16 big 256x288", 16, 256, 288, 1, 0, 6.117f, 1.753f, 0, 0, 0, 0.331f},
+    {"w4 pipelined 64x64 a3b2 4w any-group", 4, 64, 64, 4, 4.803f, 0.011f, 0.058f, 0.043f, 0.336f, 0.013f, 0.407f},
+    {"w4 pipelined 128x128 a3b2 4w any-group", 4, 128, 128, 2, 4.365f, 1.245f, 0.079f, 0.095f, 0.536f, 0.170f, 0.245f},
+    {"w4 big 128x288", 4, 128, 288, 1, 5.977f, 5.191f, 1.495f, 0, 0, 0, 0.347f},
+    {"w4 big 256x256", 4, 256, 256, 1, 6.465f, 3.934f, 2.029f, 0, 0, 0, 0.024f},
+    {"w4 big 256x288", 4, 256, 288, 1, 12.968f, 0.069f, 2.318f, 0, 0, 0, 4.782f},
+};
+struct GlueCost {
+    float act, gated, big_act, big_gated, edge, edge_act, edge_gated;
+};
+static const GlueCost GLUE_W8 = {0.537f, 0.838f, 1.316f, 2.061f, 0.069f, 0.422f, 0.630f};
+static const GlueCost GLUE_F16 = {0.671f, 1.080f, 1.425f, 3.027f, 0.007f, 0.298f, 0.800f};
+static const GlueCost GLUE_W4 = {0.834f, 1.750f, 1.002f, 3.037f, 0.045f, 0.193f, 0.835f};
+
+static int choose_tile(const GemmArgs &a, bool glue)
 {
-    struct Cost {
-        const char *name;
-        int bits, BM, BN;
-        double step, tile;
-    };
-    static const Cost costs[] = {{"w8 big 256x288", 8, 256, 288, 1.78, 6.9},   {"w8 big 256x256", 8, 256, 256, 1.55, 4.0},
-                                 {"w8 big 128x288", 8, 128, 288, 1.00, 5.4},   {"f16 big 256x288", 16, 256, 288, 1.90, 4.4},
-                                 {"f16 big 256x256", 16, 256, 256, 1.49, 7.1}, {"w4 big 256x288", 4, 256, 288, 2.50, 6.2},
-                                 {"w4 big 256x256", 4, 256, 256, 2.25, 5.0},   {"w4 big 128x288", 4, 128, 288, 1.70, 4.5}};
-    constexpr int COUNT = sizeof(costs) / sizeof(costs[0]);
+    constexpr int COUNT = sizeof(TILE_COSTS) / sizeof(TILE_COSTS[0]), CUS_PER_XCD = 32;
     static const int *const variants = [] {
         static int v[COUNT];
-        for (int i = 0; i < COUNT; ++i) v[i] = find_variant(costs[i].name);
+        for (int i = 0; i < COUNT; ++i) v[i] = find_variant(TILE_COSTS[i].name);
         return (const int *)v;
     }();
-    if (!(a.w_bits == 4 ? qgemm_w4_big_takes(a) : qgemm_big_takes(a))) return -1;
-    const double outputs = (double)a.M * a.N, steps = a.K * (a.w_bits == 16 ? 2 : 1) / 128;
-    double best = outputs * a.K * 2e-6 / (a.w_bits == 16 ? 1100 : 2280) + outputs * 2e-6 / 5;
-    // 256x192 tiles, one per CU, that just miss a whole round (M = 3072, K = 1024, N = 4096: 264 tiles; 29.4 us, in binary16 43.6
-    // against 27.8 on 256x256 tiles)
-    const long tiles_big = (long)((a.M + 255) / 256) * ((a.N + 191) / 192);
-    if (a.w_bits == 16 && a.M < 4096 && tiles_big > 256) best *= (double)((tiles_big + 255) / 256 * 256) / tiles_big;
-    if (a.w_bits == 4) {
-        const long tiles = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-        best = (double)((tiles + 255) / 256 * 256) * 128 * 128 * a.K * 2e-6 / 1636 + outputs * 2e-6 / 7.7;
-    }
-    int v = -1;
+    const bool big_takes = a.w_bits == 4 ? qgemm_w4_big_takes(a) : qgemm_big_takes(a);
+    const GlueCost &g = a.w_bits == 8 ? GLUE_W8 : a.w_bits == 4 ? GLUE_W4 : GLUE_F16;
+    const float act = a.act != 0 || (glue && !a.gate && !a.residual) ? 1.0f : 0.0f, gated = a.gate || a.residual ? 1.0f : 0.0f;
+    const int groups = a.w_bits == 4 ? a.K / a.group : 0;
+    const float steps = (float)(a.K * (a.w_bits == 16 ? 2 : 1) / 128), folds = (float)groups;
+    // outputs that no 16-byte piece reaches are written value by value everywhere
+    const bool pieces = a.N % 8 == 0 && ((uintptr_t)a.y | (uintptr_t)a.gate | (uintptr_t)a.residual) % 16 == 0;
+    int best = -1;
+    float least = 0.0f;
     for (int i = 0; i < COUNT; ++i) {
-        if (costs[i].bits != a.w_bits) continue;
-        const long tiles = (long)((a.M + costs[i].BM - 1) / costs[i].BM) * ((a.N + costs[i].BN - 1) / costs[i].BN);
-        const double t = (tiles + 255) / 256 * (steps * costs[i].step + costs[i].tile);
-        if (t < best) {
-            best = t;
-            v = variants[i];
+        const TileCost &t = TILE_COSTS[i];
+        const Variant &v = VARIANTS[variants[i]];
+        if (t.bits != a.w_bits || (glue && !v.run_glue)) continue;
+        const bool big = v.takes != dma_takes && v.takes != qgemm_w4_takes;
+        if (big && !big_takes) continue;
+        if (groups > 40 && t.BM == 128) continue;   // the large scale table leaves such a tile one workgroup per CU (134 against 198 us at 144 groups)
+        const long tiles = (long)((a.M + t.BM - 1) / t.BM) * ((a.N + t.BN - 1) / t.BN);
+        if (t.most_tiles && tiles > t.most_tiles) continue;
+        const float n = (float)(((tiles + XCDS - 1) / XCDS + CUS_PER_XCD - 1) / CUS_PER_XCD), resident = (float)t.resident;
+        const float rounds = __builtin_ceilf(n / resident);
+        float cost = t.base + n * (t.tile + t.step * steps + t.fold * folds) + rounds * (t.round_step * steps + t.round_fold * folds) +
+                     t.more * (n > resident ? n - resident : 0.0f);
+        cost += n * (float)(t.BM * t.BN) * 1e-4f * (act * (big ? g.big_act : g.act) + gated * (big ? g.big_gated : g.gated));
+        if (!big) {
+            const float in_m = (float)(a.M % t.BM) / t.BM, in_n = (float)(a.N % t.BN) / t.BN, part = !pieces ? 1.0f : in_m > in_n ? in_m : in_n;
+            cost += part * (float)(t.BM * t.BN / (t.BM == 256 ? 512 : 256)) * (g.edge + act * g.edge_act + gated * g.edge_gated);
+        }
+        if (best < 0 || cost < least) {
+            best = variants[i];
+            least = cost;
         }
     }
-    return v;
-}
-
-// Tile choice by shape, from sweeps over the DiT-XL/2 layer shapes and other widths on MI355X (256 CUs); 8-bit and FP16
-// layers (4-bit layers choose inside launch_qgemm_w4).
-static int choose_variant(const GemmArgs &a)
-{
-    static const int w8_small = find_variant("w8 dma 64x64 s3 4w"),
-                     w8_mid = find_variant("w8 dma 128x128 a3b2 4w spread1"),
-                     w8_mid_deep = find_variant("w8 dma 128x128 a3b2 4w"),
-                     w8_p128 = find_variant("w8 dma 128x128 a3b2 4w spread1 persistent"),
-                     w8_p192 = find_variant("w8 dma 128x192 s2 4w spread1 persistent"),
-                     w8_big = find_variant("w8 dma 256x192 a3b2 8w spread1");
-    // 64x64 tiles while all of them are resident at once (three per CU): M = 1024, N = 1152: K = 1152 6.5 against 8.0 us on
-    // 128x128 tiles, K = 4608 16.6 against 21.1
-    const long tiles_64 = (long)((a.M + 63) / 64) * ((a.N + 63) / 64);
-    if (tiles_64 > 768) {
-        const int v = choose_big(a);
-        if (v >= 0) return v;
-    }
-    const long tiles_big = (long)((a.M + 255) / 256) * ((a.N + 191) / 192);
-    if (a.w_bits == 16) {
-        static const int h_small = find_variant("f16 dma 64x64 s3 4w"), h_mid = find_variant("f16 dma 128x128 a3b2 4w spread1"),
-                         h_big = find_variant("f16 dma 256x192 a3b2 8w spread1"),
-                         h_p192 = find_variant("f16 dma 128x192 s2 4w spread1 persistent");
-        // (M = 1024, K = 4096, N = 1024, 256 of them: 21.5 against 35.8 us on 128x128 tiles; 576: level; 768: M = 3072, K = 4096, N =
-        // 1024 41.6 against 38.3, M = 1024, K = 1024, N = 3072 13.1 against 12.3)
-        if (tiles_64 <= 512) return h_small;
-        if (tiles_big < 192 || (a.M < 4096 && tiles_big > 256 && tiles_big <= 384)) return h_mid;   // one 256x192 tile per CU, no second round begun
-        return (a.M >= 4096 && a.N < 4096) ? h_p192 : h_big;
-    }
-    if (tiles_64 <= 768 && (a.K < 2304 || tiles_64 <= 512)) return w8_small;
-    if (tiles_big >= 192) {                                   // enough work for every CU
-        // Several tiles per CU: two resident 4-wavefront workgroups per CU that walk their tiles and fetch the next
-        // tile's first K step under the epilogue.  128x192 tiles move less data per MAC; 128x128 tiles balance better when
-        // the tiles per CU are few and N is wide, unless 128x192 ones are all resident at once (M = 4096: K = 1024, N = 3072 17.1
-        // against 19.4 us, K = 768, N = 2304 13.2 against 14.7).  Fewer rows: one 256x192 tile per CU, but not a second round of
-        // them (M = 3072, K = 1024, N = 4096, 264 tiles: 29.4 us against 18.4 on 128x128).
-        const long tiles_192 = (long)((a.M + 127) / 128) * ((a.N + 191) / 192);
-        if (a.M >= 4096) return (a.K >= 2304 || a.N <= 1536 || a.M >= 12288 || tiles_192 <= 512) ? w8_p192 : w8_p128;
-        return tiles_big <= 256 || tiles_big > 384 ? w8_big : w8_p128;
-    }
-    // one 128x128 tile per CU at most: the deeper issue of a long K; more than one: DMA spread between the MFMAs
-    const long tiles_128 = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-    return a.K >= 2304 && tiles_128 <= 256 ? w8_mid_deep : w8_mid;
+    return best;
 }
 
 hipError_t launch_qgemm(const GemmArgs &a, int variant, hipStream_t stream)
@@ -920,38 +932,13 @@ hipError_t launch_qgemm(const GemmArgs &a, int variant, hipStream_t stream)
         if (!split && qgemm_w4_takes(a) && !glue) return launch_qgemm_w4(a, stream);
         return small();
     }
+    auto usable = [&](const Variant &v) { return v.w_bits == a.w_bits && v.takes(a) && (!glue || v.run_glue); };
     int v = variant;
-    if (v >= 0 && (VARIANTS[v].w_bits != a.w_bits || a.K % VARIANTS[v].BK != 0)) v = -1;
-    if (v >= 0 && __builtin_strstr(VARIANTS[v].name, "split-K") && !qgemm_split_takes(a, VARIANTS[v].BM)) v = -1;
-    if (v >= 0 && __builtin_strstr(VARIANTS[v].name, "big") && !(a.w_bits == 4 ? qgemm_w4_big_takes(a) : qgemm_big_takes(a))) v = -1;
-    if (v >= 0 && VARIANTS[v].run == run_k64 && !k64_takes(a)) v = -1;
-    if (v < 0 && split) return small();
-    // 4-bit layers: the pipelined kernels with the tile that suits the shape
-    // (64x64 tiles while all of them are resident at once)
-    if (a.w_bits == 4 && v < 0 && (long)((a.M + 63) / 64) * ((a.N + 63) / 64) > 1024) v = choose_big(a);
-    if (a.w_bits == 4 && v >= 0 && __builtin_strstr(VARIANTS[v].name, "big")) return glue ? VARIANTS[v].run_glue(a, stream) : VARIANTS[v].run(a, stream);
-    if (a.w_bits == 4 && (v < 0 || __builtin_strstr(VARIANTS[v].name, "pipelined"))) {
-        if (!qgemm_w4_takes(a)) return small();
-        return v < 0 ? launch_qgemm_w4(a, stream) : VARIANTS[v].run(a, stream);
+    if (v < 0 || !usable(VARIANTS[v])) {
+        if (split || !(a.w_bits == 4 ? qgemm_w4_takes(a) : dma_takes(a))) return small();
+        v = choose_tile(a, glue);
     }
-    // the DMA kernels need 16-byte loads along K and whole K steps of 128 bytes
-    const bool fast = (a.K * (a.w_bits == 16 ? 2 : 1)) % 128 == 0 && ((uintptr_t)a.q % 16 == 0) && ((uintptr_t)a.w % 16 == 0);
-    if (v < 0) {
-        if (!fast) return small();
-        v = choose_variant(a);
-    } else if (!fast && !__builtin_strstr(VARIANTS[v].name, "edge") && VARIANTS[v].run != run_k64) {
-        return small();
-    }
-    if (glue) {
-        // block glue in the epilogue: only the shape-chosen tiles carry it
-        if (!VARIANTS[v].run_glue) v = choose_variant(a);
-        // the prefetched gate and residual pieces need registers the persistent tiles do not have left
-        // (256x192 and two resident 128x128 workgroups per CU measure alike here: 495 and 491 us for a block at M = 16384)
-        static const int big = find_variant("w8 dma 256x192 a3b2 8w spread1"), hbig = find_variant("f16 dma 256x192 a3b2 8w spread1");
-        if (__builtin_strstr(VARIANTS[v].name, "persistent")) v = a.w_bits == 16 ? hbig : big;
-        return VARIANTS[v].run_glue(a, stream);
-    }
-    return VARIANTS[v].run(a, stream);
+    return glue ? VARIANTS[v].run_glue(a, stream) : VARIANTS[v].run(a, stream);
 }
 
 }  // namespace ql

@@ -5,6 +5,7 @@
 #include "../../include/diffpro_qlinear.h"
 #include "ql_internal.h"
 
+#include <algorithm>
 #include <atomic>
 #include <new>
 #include <vector>
@@ -149,7 +150,7 @@ int run_layer(const void *x, int64_t M, int64_t K, int64_t R, int w_bits, const 
     d.blockmax = R > 1 ? reinterpret_cast<unsigned *>(base + lw.bm_off) : nullptr;
     d.partmax = R > 1 ? reinterpret_cast<unsigned *>(base + lw.bm_off + align_up((size_t)(M / R) * 4, 256)) : nullptr;
     d.hist = d.partmax;
-    d.hist_bytes = R > 1 ? workspace_bytes - lw.bm_off - align_up((size_t)(M / R) * 4, 256) : 0;
+    d.scratch_bytes = R > 1 ? workspace_bytes - lw.bm_off - align_up((size_t)(M / R) * 4, 256) : 0;
     d.M = (int)M;
     d.K = (int)K;
     d.R = (int)R;
@@ -181,7 +182,7 @@ int run_layer(const void *x, int64_t M, int64_t K, int64_t R, int w_bits, const 
     }
     const int variant = g_gemm_variant.load();
     const size_t parts = ql::daq_parts_per_block(K, R);
-    if (!dp && !dbg && variant < 0 && (R == 1 || (parts > 0 && parts <= 256))) {
+    if (!dp && !dbg && variant < 0 && (R == 1 || (parts > 0 && parts <= 256 && parts * (size_t)(M / R) * 4 <= d.scratch_bytes))) {
         // few rows: the GEMM's workgroups quantize their own rows (one launch; two where rows share a scale), unless the outputs
         // lie over the inputs that other workgroups still read
         ql::GemmArgs f = g;
@@ -353,7 +354,7 @@ static int daq_any(const void *x, int64_t M, int64_t K, int64_t R, const ql_daq_
     d.partmax = R > 1 ? reinterpret_cast<unsigned *>(static_cast<unsigned char *>(workspace) + align_up((size_t)(M / R) * 4, 256))
                       : nullptr;
     d.hist = d.partmax;
-    d.hist_bytes = R > 1 ? workspace_bytes - align_up((size_t)(M / R) * 4, 256) : 0;
+    d.scratch_bytes = R > 1 ? workspace_bytes - align_up((size_t)(M / R) * 4, 256) : 0;
     d.M = (int)M;
     d.K = (int)K;
     d.R = (int)R;
@@ -479,6 +480,7 @@ int qlinear_grouped(const void *x, int64_t M, int64_t K, int64_t R, int64_t act_
         d.scales = (dbg && dbg->a_scales) ? static_cast<float *>(dbg->a_scales) : reinterpret_cast<float *>(base + lw.s_off);
         d.blockmax = R > 1 ? reinterpret_cast<unsigned *>(base + lw.bm_off) : nullptr;
         d.partmax = R > 1 ? reinterpret_cast<unsigned *>(base + lw.bm_off + align_up((size_t)(M / R) * 4, 256)) : nullptr;
+        d.scratch_bytes = R > 1 ? workspace_bytes - lw.bm_off - align_up((size_t)(M / R) * 4, 256) : 0;
         d.M = (int)M;
         d.K = (int)K;
         d.R = (int)R;
@@ -773,7 +775,10 @@ int32_t ql_plan_num_layers(const ql_plan *plan) { return plan ? (int32_t)plan->l
 size_t ql_plan_workspace_bytes(const ql_plan *plan, int64_t M, int64_t R)
 {
     if (!plan || M < 1 || R < 1 || M % R != 0 || M > plan->M_max) return 0;
-    return layer_ws(M, plan->K_widest, R).total;
+    // the widest layer's, unless a narrower one cuts its scale blocks into parts and the widest (K % 8 != 0) does not
+    size_t most = 0;
+    for (const ql_layer_desc &d : plan->layers) most = d.w_bits != 16 || d.K == plan->K_widest ? std::max(most, layer_ws(M, d.K, R).total) : most;
+    return most;
 }
 
 static int plan_run_any(const ql_plan *plan, const void *const *x_in, void *const *y_out, int64_t M, int64_t R,

@@ -377,7 +377,7 @@ hipError_t launch_daq(const DaqArgs &a, hipStream_t stream)
     } else {
         const int nblk = a.M / a.R;
         const size_t parts = daq_parts_per_block(a.K, a.R);
-        if (parts > 0 && (uintptr_t)a.x % 16 == 0 && parts * nblk < (1ull << 31)) {
+        if (parts > 0 && (uintptr_t)a.x % 16 == 0 && parts * nblk < (1ull << 31) && parts * nblk * 4 <= a.scratch_bytes) {
             const hipError_t e = launch_daq_part_absmax(a, stream);
             if (e != hipSuccess) return e;
             if (parts <= 256) {

@@ -460,7 +460,7 @@ hipError_t launch_daq_robust(const DaqArgs &a, hipStream_t stream)
     const size_t n = (size_t)a.R * a.K;
     const unsigned parts = (unsigned)daq_hist_parts(a.K, a.R);
     const dim3 grid(parts * (unsigned)nblk);
-    if (parts <= DAQ_HIST_FEW && a.hist_bytes >= daq_hist_bytes(a.M, a.K, a.R)) {
+    if (parts <= DAQ_HIST_FEW && a.scratch_bytes >= daq_hist_bytes(a.M, a.K, a.R)) {
         // few parts: every consumer adds them up and selects for itself; more: a selection launch in between (M = 8192, R = 256, K =
         // 4608, 72 parts: 57 us against 77 with twice the part size and no selection launches)
         const bool self = parts <= DAQ_HIST_SELF;

@@ -25,8 +25,10 @@ struct DaqArgs {
     // percentile-clipped variant only (launch_daq_robust)
     int qmax;            // 2^(b-1) - 1 for b-bit activation codes
     unsigned top_rank;   // tau = the top_rank-th largest magnitude of a scale block (1 = the maximum)
-    unsigned *hist;      // selection scratch (workspace), R > 1 only: daq_hist_bytes() for the partial histograms, and from
-    size_t hist_bytes;   //    DAQ_ROBUST_WORDS words per scale block on the selection with atomics
+    unsigned *hist;      // selection scratch (workspace, where partmax is), R > 1 only: daq_hist_bytes() for the partial histograms, and
+                         //    from DAQ_ROBUST_WORDS words per scale block on the selection with atomics
+    // both variants: bytes at partmax and hist; where the partial maxima or histograms need more, the kernels with atomics run
+    size_t scratch_bytes;
 };
 constexpr int DAQ_ROBUST_WORDS = 256 + 2 + 128;
 // Partial histograms of the percentile selection: elements per part (at most 65535, so that a 16-bit count holds); parts per

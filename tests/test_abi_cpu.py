@@ -107,6 +107,18 @@ def test_plan_argument_checks():
     assert L.ql_plan_create(None, 1, 256, ctypes.byref(h)) == 1
 
 
+def test_plan_workspace_covers_every_layer():
+    """The widest layer of a plan does not always need the most: with K % 8 != 0 it has no partial maxima, and a narrower layer's
+    then reached behind the workspace."""
+    L = ql.lib()
+    h = ctypes.c_void_p()
+    for Ks, M, R in [((8193, 8192), 8192, 8192), ((1152, 4608), 16384, 256), ((4609, 4608, 1152), 16384, 16384), ((40, 33), 64, 8)]:
+        arr = (ql.ql_layer_desc * len(Ks))(*[ql.ql_layer_desc(K, 64, 8, 0, 0x1000, 0x2000, 0) for K in Ks])
+        assert L.ql_plan_create(arr, len(Ks), M, ctypes.byref(h)) == 0
+        assert L.ql_plan_workspace_bytes(h, M, R) == max(ql.qlinear_workspace_bytes(M, K, R) for K in Ks)
+        L.ql_plan_destroy(h)
+
+
 def test_variant_override_range():
     L = ql.lib()
     n = L.ql_num_gemm_variants()

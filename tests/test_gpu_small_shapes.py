@@ -156,3 +156,22 @@ def test_smaller_workspaces(gpu, M, K, R):
     q2, s2, ws = torch.zeros_like(q), torch.zeros_like(s), gpu.workspace(_aligned(4 * nblk * (K // group)))
     assert gpu.lib().daq_quantize_cg(x.data_ptr(), M, K, R, group, q2.data_ptr(), s2.data_ptr(), ws.data_ptr(), ws.numel(), None) == 0
     assert torch.equal(q, q2) and torch.equal(s, s2)
+
+
+def test_plan_on_the_workspace_of_its_widest_layer(gpu):
+    """A plan's layer of K = 8192 on a workspace sized for K = 8193 alone, which has no room for its partial maxima: the atomic
+    maxima step in, nothing behind the workspace is written, and the codes are those of a workspace with room."""
+    import torch
+    M, N, R = 8192, 24, 8192
+    say("plan workspace", M, R)
+    layers = [dict(K=K, N=N, bits=8, w=dev(workload.w8_codes(N, K, "plan-ws")), w_scale=dev(workload.w8_scales(N, "plan-ws")), bias=None) for K in (8193, 8192)]
+    xs = [dev(workload.activations(M, l["K"], "plan-ws")) for l in layers]
+    small = _aligned(M * 8193) + _aligned(4) + _aligned(4) + _aligned(4 * 386)
+    plan = gpu.Plan(layers, M_max=M)
+    assert plan.workspace_bytes(M, R) > small
+    whole, room = gpu.workspace(small + (1 << 16)), gpu.workspace(plan.workspace_bytes(M, R))
+    whole.fill_(0x5a)
+    got, want = ([torch.empty((M, N), dtype=torch.float16, device="cuda") for _ in layers] for _ in range(2))
+    plan.run(xs, got, M, R, whole[:small])
+    plan.run(xs, want, M, R, room)
+    assert bool((whole[small:] == 0x5a).all()) and all(torch.equal(a, b) for a, b in zip(got, want))

@@ -227,9 +227,10 @@ int qgemm_w4a8_g(const void *q, const void *a_scales, int64_t M, int64_t K, int6
  *                       f = fma(float(P), c, f);  y = fp16(f + bias[n])
  *   (other act_group values: QL_ERR_UNSUPPORTED.)  w_scale fp16 [N,K/group];
  *   dbg->a_scales is [M/R] or [M/R, K/group]; dbg->acc [M, K/group, N].
- * The pipelined kernel takes K % 128 == 0, K/group <= 40 (4-bit storage: <= 144)
- * and, with channel-group activation scales, R % 128 == 0; other shapes run on
- * the generic kernel.
+ * The pipelined kernel takes K % 128 == 0, K/group <= 144 and, with channel-group
+ * activation scales, R % 64 == 0; few rows and other shapes run on the split-K and
+ * register-staged kernels, and channel groups over rows that neither 16 nor 32
+ * divides on one thread per element.
  * Workspace: qlinear_grouped_workspace_bytes().
  *
  * Host helpers: ql_pack_bits_host / ql_unpack_bits_host store b-bit two's-

@@ -275,8 +275,8 @@ __global__ __launch_bounds__(256) void daq_cg_quant(DaqArgs a, int cg)
         for (int g = lane; g < G; g += 64) a.scales[(size_t)(row / a.R) * G + g] = alpha_from_bits(bm[g]);
 }
 
-// The same for blocks of rows that DAQ_CG_SLAB divides.  A workgroup takes a slab of rows; a thread keeps one 16-byte piece of
-// columns (hence one channel group) and walks down `1 / rpw` of the slab's rows, so that the group arithmetic - a division
+// The same for blocks of rows that 8 divides (daq_cg_slab_rows).  A workgroup takes a slab of rows; a thread keeps one 16-byte piece of
+// columns (hence one channel group) and walks down every rpw-th of the slab's rows, so that the group arithmetic - a division
 // by cg, the scale and its reciprocal - is paid once per thread and not per piece.  Pass 1 leaves the slab's maximum per
 // group with plain stores, no clearing pass and no atomics; pass 2 takes the maximum over its block's slabs.
 // M = 4096, K = 1152, R = 256, cg = 128: 32.7 -> 13 us.

@@ -30,19 +30,17 @@ namespace ql {
 // the next quarter, the hand-over barrier and the next DMA issue all sit behind an MFMA that is
 // already executing.
 // ---------------------------------------------------------------------------------------------
-template <int TM_, int TN_, int WGM_, int WGN_, int S_, int WPS_, bool STG_ = true, int EV_ = 0, bool W4_ = false, int SB_ = S_, bool PERSIST_ = false, bool F16_ = false>
+template <int TM_, int TN_, int WGM_, int WGN_, int S_, int WPS_, bool STG_ = true, int EV_ = 0, int SB_ = S_, bool PERSIST_ = false, bool F16_ = false>
 struct TileD {
     static constexpr int TM = TM_, TN = TN_, WGM = WGM_, WGN = WGN_, WPS = WPS_;
     // ring depth of the activation tile and of the weight tile (K steps resident or in flight); they may differ by one
     static constexpr int SA = S_, SB = SB_;
-    static constexpr bool W4 = W4_;
     // both operands binary16 (a layer the plan leaves unquantized): one K step is 64 values = the same 128 bytes per row
     static constexpr bool F16 = F16_;
-    static_assert(!(F16_ && W4_), "FP16 layers have no packed weights");
     static constexpr int NW = WGM * WGN, NT = NW * 64;
     static constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32, BK = 128;
-    // 1024-byte DMA groups per K step: A rows (8 rows x 128 B) and W rows (8 x 128 B, or 16 x 64 B packed 4-bit)
-    static constexpr int A_GROUPS = BM / 8, B_GROUPS = W4 ? BN / 16 : BN / 8;
+    // 1024-byte DMA groups per K step: 8 rows x 128 B
+    static constexpr int A_GROUPS = BM / 8, B_GROUPS = BN / 8;
     static constexpr int NA = A_GROUPS / NW, NB = B_GROUPS / NW;   // DMA instructions per wavefront per K step
     static constexpr int A_BYTES = A_GROUPS * 1024, B_BYTES = B_GROUPS * 1024;
     static constexpr int B_RING = SA * A_BYTES;           // the weight ring follows the activation ring
@@ -54,17 +52,14 @@ struct TileD {
     static constexpr int STRIP_ROWS = (PERSIST_ && (SA - 1) * A_BYTES < STRIP_OFF + NW * 32 * (TN * 64 + 16)) ? 16 : 32;
     static constexpr int STRIP_BYTES = STRIP_ROWS * (TN * 64 + 16);
     static constexpr int RINGS = SA * A_BYTES + SB * B_BYTES;
-    static constexpr int RING_BYTES = RINGS > STRIP_OFF + NW * STRIP_BYTES ? RINGS : STRIP_OFF + NW * STRIP_BYTES;
-    static constexpr int MAX_GROUPS_K = 40;               // 4-bit: group scales of the tile's columns live in LDS (K <= 5120)
-    static constexpr int SCALE_BYTES = W4 ? BN * MAX_GROUPS_K * 2 : 0;
-    static constexpr int LDS_BYTES = RING_BYTES + SCALE_BYTES;
+    static constexpr int LDS_BYTES = RINGS > STRIP_OFF + NW * STRIP_BYTES ? RINGS : STRIP_OFF + NW * STRIP_BYTES;
     static constexpr int SMAX = SA > SB ? SA : SB;
     // Persistent launch: a workgroup walks several tiles and requests the first K step of the next tile before it
     // starts the epilogue of the current one, into stage 0 of both rings; the epilogue's scratch then lives in the
     // later stages of the activation ring.
     static constexpr bool PERSIST = PERSIST_;
     static constexpr int EPI_OFF = PERSIST ? A_BYTES : 0;
-    static_assert(!PERSIST || (!W4 && (SA - 1) * A_BYTES >= STRIP_OFF + NW * STRIP_BYTES), "epilogue scratch beside stage 0");
+    static_assert(!PERSIST || (SA - 1) * A_BYTES >= STRIP_OFF + NW * STRIP_BYTES, "epilogue scratch beside stage 0");
     // loads that may still be in flight when K step 0 is first read, and at the hand-over from step kt to kt+1
     static constexpr int WAIT_START = (SA - 1) * NA + (SB - 1) * NB;
     static constexpr int WAIT_HAND = SA > SB ? NA + (SB - 2) * (NA + NB) : SA < SB ? NB + (SA - 2) * (NA + NB) : (SA - 2) * (NA + NB);
@@ -81,7 +76,7 @@ template <class T, bool GLUE = false>
 __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles_m, int tiles_n, int nblk_padded, int group_m)
 {
     constexpr int TM = T::TM, TN = T::TN, BM = T::BM, BN = T::BN, NT = T::NT, NW = T::NW;
-    constexpr bool W4 = T::W4, F16 = T::F16;
+    constexpr bool F16 = T::F16;
     constexpr int EB = F16 ? 2 : 1;   // bytes per element of both operands
     extern __shared__ __align__(1024) unsigned char smem[];
 
@@ -106,7 +101,7 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keep it in a scalar register
     const int wm = wave / T::WGN, wn = wave % T::WGN;
     const int M = a.M, N = a.N, K = a.K;
-    const int nk = K * EB / 128;   // K steps (128 bytes per row); for 4-bit weights also the number of weight groups
+    const int nk = K * EB / 128;   // K steps (128 bytes per row)
     QL_PHASE(0)
 
     // Everything the epilogue needs from global memory is requested now, ahead of the first DMA (the oldest loads
@@ -120,20 +115,11 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int n = min(n0 + wn * TN * 32 + j * 32 + (lane & 31), N - 1);
-            swt[j] = (W4 || F16) ? 1.0f : static_cast<const float *>(a.s_w)[n];
+            swt[j] = F16 ? 1.0f : static_cast<const float *>(a.s_w)[n];
             bj[j] = bias_h ? half_to_float_dev(bias_h[n]) : 0.0f;
         }
     };
     if (!T::PERSIST) load_scales();
-
-    // 4-bit weights: the fp16 group scales of this tile's columns, [BN][nk], copied once (the first barrier of the
-    // pipeline below orders the copy before their first use at the end of K step 0)
-    unsigned short *sScale = reinterpret_cast<unsigned short *>(smem + T::RING_BYTES);
-    if (W4) {
-        const unsigned short *gsw = static_cast<const unsigned short *>(a.s_w);
-        for (int idx = tid; idx < BN * nk; idx += NT)
-            sScale[idx] = gsw[(size_t)min(n0 + idx / nk, N - 1) * nk + idx % nk];
-    }
 
     // DMA addressing: lane l of a wavefront fills bytes [16 l, 16 l + 16) of a 1024-byte group = row l/8, slot l%8.
     // Group g covers tile rows [8 g, 8 g + 8) of its operand.  Wavefront w takes groups w, w+NW, ... of both operands.
@@ -148,16 +134,9 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
         }
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            if (!W4) {
-                const int row = 8 * (wave + i * NW) + (lane >> 3);
-                const int c = (lane & 7) ^ ((row >> 1) & 7);
-                goffB[i] = row_start(min(n0 + row, N - 1), K * EB) + 16 * c;
-            } else {
-                // packed 4-bit rows are 64 bytes per K step: 16 rows per group, chunk c of row r at slot c ^ ((r >> 2) & 3)
-                const int row = 16 * (wave + i * NW) + (lane >> 2);
-                const int c = (lane & 3) ^ ((row >> 2) & 3);
-                goffB[i] = (unsigned)(min(n0 + row, N - 1) * (K / 2) + 16 * c);
-            }
+            const int row = 8 * (wave + i * NW) + (lane >> 3);
+            const int c = (lane & 7) ^ ((row >> 1) & 7);
+            goffB[i] = row_start(min(n0 + row, N - 1), K * EB) + 16 * c;
         }
     };
     set_goff();
@@ -166,7 +145,7 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
                                          (lds_void *)(smem + slot * T::A_BYTES + (wave + i * NW) * 1024), 16, 0, 0);
     };
     auto issue_b = [&](int kt, int slot, int i) {
-        __builtin_amdgcn_global_load_lds((global_void *)(static_cast<const int8_t *>(a.w) + (size_t)kt * (W4 ? 64 : 128) + goffB[i]),
+        __builtin_amdgcn_global_load_lds((global_void *)(static_cast<const int8_t *>(a.w) + (size_t)kt * 128 + goffB[i]),
                                          (lds_void *)(smem + T::B_RING + slot * T::B_BYTES + (wave + i * NW) * 1024), 16, 0, 0);
     };
     // Refill window j = the loads issued after the hand-over barrier of K step j, into the slots that step used:
@@ -188,26 +167,20 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
 
     typedef typename std::conditional<F16, v16f, v16i>::type acc_t;   // fp32 accumulators for FP16 operands
     acc_t acc[TM][TN];
-    // 4-bit weights: fp32 sum over the weight groups, f = sum_g fma(float(P_g), s_w[n,g], f)
-    float fsum[W4 ? TM : 1][W4 ? TN : 1][16];
     auto clear_sums = [&]() {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    acc[i][j][r] = 0;
-                    if (W4) fsum[W4 ? i : 0][W4 ? j : 0][r] = 0.0f;
-                }
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
     };
 
     // fragment of a lane: row (lane & 31) of a 32-row tile, 16 k starting at 32 * quarter + 16 * (lane >> 5)
     const int frag_row = lane & 31, frag_half = lane >> 5;
     const int key = (lane >> 1) & 7;  // swizzle key of this lane's row (tile rows start at multiples of 32)
-    const int key4 = (lane >> 2) & 3; // the same for the 64-byte rows of packed 4-bit weights
     const int a_off = (wm * TM * 32 + frag_row) * 128;
-    const int b_off = T::B_RING + (wn * TN * 32 + frag_row) * (W4 ? 64 : 128);
+    const int b_off = T::B_RING + (wn * TN * 32 + frag_row) * 128;
     auto read_frags = [&](int sl_a, int sl_b, int quarter, v4i(&af)[TM], v4i(&bf)[TN]) {
         const unsigned char *st = smem + sl_a * T::A_BYTES;
         const unsigned char *stb = smem + sl_b * T::B_BYTES;
@@ -215,71 +188,29 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
 #pragma unroll
         for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const v4i *>(st + a_off + i * 32 * 128 + so);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            if (W4) {
-                // 16 k of a quarter's half = 8 packed bytes; byte b of a word: low nibble = k b, high nibble = k 4+b
-                const v2i p = *reinterpret_cast<const v2i *>(stb + b_off + j * 32 * 64 + ((quarter ^ key4) * 16) + frag_half * 8);
-                bf[j] = v4i{(int)(((unsigned)p[0] << 4) & 0xf0f0f0f0u), (int)((unsigned)p[0] & 0xf0f0f0f0u),
-                            (int)(((unsigned)p[1] << 4) & 0xf0f0f0f0u), (int)((unsigned)p[1] & 0xf0f0f0f0u)};  // int8 value * 16
-            } else {
-                bf[j] = *reinterpret_cast<const v4i *>(stb + b_off + j * 32 * 128 + so);
-            }
-        }
+        for (int j = 0; j < TN; ++j) bf[j] = *reinterpret_cast<const v4i *>(stb + b_off + j * 32 * 128 + so);
     };
-    // 4-bit weights: K step kt is weight group kt.  Its int32 partial sums (times 16) are folded into the fp32 sum
-    // right before the accumulator is restarted; the group scale carries the 1/16 (exact: a power of two).
-    int flush_group = -1;  // group whose partial sums are still in acc
-    auto flush_tile = [&](int i, int j) {
-        if constexpr (F16) return;
-        else {
-        const int n_loc = wn * TN * 32 + j * 32 + frag_row;
-        const float s16 = half_to_float_dev(sScale[n_loc * nk + flush_group]) * 0.0625f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            if (a.acc_out) {
-                const int m = m0 + wm * TM * 32 + i * 32 + 8 * (r / 4) + 4 * frag_half + (r % 4), n = n0 + n_loc;
-                if (m < M && n < N) a.acc_out[(unsigned)((m * nk + flush_group) * N + n)] = acc[i][j][r] >> 4;
-            }
-            fsum[W4 ? i : 0][W4 ? j : 0][r] = __builtin_fmaf((float)acc[i][j][r], s16, fsum[W4 ? i : 0][W4 ? j : 0][r]);
-        }
-        }
-    };
-    // MFMAs number [first, last) of one quarter, in (i, j) order; restart = first quarter of a 4-bit weight group
-    auto mma = [&](const v4i(&af)[TM], const v4i(&bf)[TN], int first, int last, bool restart = false) {
+    // MFMAs number [first, last) of one quarter, in (i, j) order
+    auto mma = [&](const v4i(&af)[TM], const v4i(&bf)[TN], int first, int last) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                if (i * TN + j >= first && i * TN + j < last) {
-                    if (W4 && restart) {
-                        if (flush_group >= 0) flush_tile(i, j);
-                        const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                        if constexpr (!F16) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[i], bf[j], zero, 0, 0, 0);
-                    } else {
-                        acc[i][j] = mfma_step<F16>(af[i], bf[j], acc[i][j]);
-                    }
-                }
+                if (i * TN + j >= first && i * TN + j < last) acc[i][j] = mfma_step<F16>(af[i], bf[j], acc[i][j]);
     };
     constexpr int NMMA = TM * TN;
     // The same, with one DMA instruction of K step kt_i slipped in after every EVERY-th MFMA, starting with load i0:
     // 64 loads issued back to back fill the texture-address queue and stall the MFMA issue of every wavefront.
     constexpr int EVERY = T::DMA_EVERY > 0 ? T::DMA_EVERY : 1;
     constexpr bool SPREAD = T::DMA_EVERY > 0;
-    auto mma_dma = [&](const v4i(&af)[TM], const v4i(&bf)[TN], int first, int last, bool on, int win, int slot_a, int slot_b, int i0,
-                       bool restart = false) {
+    auto mma_dma = [&](const v4i(&af)[TM], const v4i(&bf)[TN], int first, int last, bool on, int win, int slot_a, int slot_b, int i0) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 const int idx = i * TN + j;
                 if (idx >= first && idx < last) {
-                    if (W4 && restart) {
-                        if (flush_group >= 0) flush_tile(i, j);
-                        const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                        if constexpr (!F16) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[i], bf[j], zero, 0, 0, 0);
-                    } else {
-                        acc[i][j] = mfma_step<F16>(af[i], bf[j], acc[i][j]);
-                    }
+                    acc[i][j] = mfma_step<F16>(af[i], bf[j], acc[i][j]);
                     const int li = i0 + (idx - first) / EVERY;
                     if (SPREAD && (idx - first) % EVERY == EVERY - 1 && li < NA + NB) {
                         if (on) issue_win(win, slot_a, slot_b, li);
@@ -305,7 +236,6 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
     for (;;) {   // one pass per tile; a single pass unless the launch is persistent
     if (T::PERSIST) load_scales();
     clear_sums();
-    flush_group = -1;
     if (!T::PERSIST) issue_step0();
 #pragma unroll
     for (int st = 1; st < T::SMAX; ++st) {
@@ -330,12 +260,11 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
         const int na = sa + 1 == SA ? 0 : sa + 1, nb = sb + 1 == SB ? 0 : sb + 1;
         const bool refill = kt > 0;   // refill window kt-1 is still being issued during quarters 0 and 1
         // quarter 0 (fragments 0) while reading quarter 1 (fragments 1)
-        mma(af0, bf0, 0, 1, true);
+        mma(af0, bf0, 0, 1);
         __builtin_amdgcn_sched_barrier(0);
         read_frags(sa, sb, 1, af1, bf1);
         __builtin_amdgcn_sched_barrier(0);
-        mma_dma(af0, bf0, 1, NMMA, refill, kt - 1, pa, pb, N_Q, true);
-        flush_group = kt;
+        mma_dma(af0, bf0, 1, NMMA, refill, kt - 1, pa, pb, N_Q);
         __builtin_amdgcn_sched_barrier(0);
         // quarter 1 while reading quarter 2
         mma(af1, bf1, 0, 1);
@@ -372,12 +301,6 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
         sa = na;
         sb = nb;
     }
-    if (W4) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) flush_tile(i, j);
-    }
     QL_PHASE(2)
     __syncthreads();
 
@@ -403,7 +326,7 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
     const bool full = (em0 + BM <= M) && (en0 + BN <= N);
     const bool glue_pieces = GLUE && (a.residual || a.gate);
     const bool glue_aligned = !glue_pieces || (((reinterpret_cast<uintptr_t>(a.residual) | reinterpret_cast<uintptr_t>(a.gate)) & 15) == 0);
-    if (full && (N % 8) == 0 && (reinterpret_cast<uintptr_t>(a.y) & 15) == 0 && (W4 || !a.acc_out) && glue_aligned) {
+    if (full && (N % 8) == 0 && (reinterpret_cast<uintptr_t>(a.y) & 15) == 0 && !a.acc_out && glue_aligned) {
         GluePieces gl;
         if (glue_pieces) {
             gl.gate = static_cast<const _Float16 *>(a.gate);
@@ -436,14 +359,6 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
                 store_tile_staged<TM, TN, T::STAGED_STORE, T::STRIP_ROWS>(strip, lane, y, N, em0 + wm * TM * 32, en0 + wn * TN * 32, [&](int i, int j, int r) {
                     return act_of((float)acc[i][j][r] + bj[j]);
                 }, gl);
-            else if (W4 && bias)
-                store_tile_staged<TM, TN, T::STAGED_STORE, T::STRIP_ROWS>(strip, lane, y, N, em0 + wm * TM * 32, en0 + wn * TN * 32, [&](int i, int j, int r) {
-                    return act_of(__builtin_fmaf(fsum[W4 ? i : 0][W4 ? j : 0][r], sr[i * 16 + r], bj[j]));
-                }, gl);
-            else if (W4)
-                store_tile_staged<TM, TN, T::STAGED_STORE, T::STRIP_ROWS>(strip, lane, y, N, em0 + wm * TM * 32, en0 + wn * TN * 32, [&](int i, int j, int r) {
-                    return act_of(fsum[W4 ? i : 0][W4 ? j : 0][r] * sr[i * 16 + r]);
-                }, gl);
             else if (bias)
                 store_tile_staged<TM, TN, T::STAGED_STORE, T::STRIP_ROWS>(strip, lane, y, N, em0 + wm * TM * 32, en0 + wn * TN * 32, [&](int i, int j, int r) {
                     return act_of(__builtin_fmaf((float)acc[i][j][r] * sr[i * 16 + r], swt[j], bj[j]));
@@ -474,9 +389,6 @@ __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_dma(GemmArgs a, int tiles
                             float u;
                             if (F16) {
                                 u = (float)acc[i][j][r] + b;
-                            } else if (W4) {
-                                const float f = fsum[W4 ? i : 0][W4 ? j : 0][r];
-                                u = bias ? __builtin_fmaf(f, sRow[row], b) : f * sRow[row];
                             } else {
                                 const float t = (float)acc[i][j][r] * sRow[row];
                                 u = bias ? __builtin_fmaf(t, swt[j], b) : t * swt[j];
@@ -743,21 +655,21 @@ using D8_256x256_8w_e2 = TileD<4, 2, 2, 4, 2, 2, true, 2>;
 using D8_256x192_4w_e2 = TileD<4, 3, 2, 2, 2, 1, true, 2>;
 using D8_64x64_s3 = TileD<1, 1, 2, 2, 3, 4>;
 //                                                       SA                  SB
-using D8_256x192_8w_a3b2 = TileD<2, 3, 4, 2, 3, 2, true, 1, false, 2>;
-using D8_256x192_8w_a2b3 = TileD<2, 3, 4, 2, 2, 2, true, 1, false, 3>;
-using D8_256x256_8w_a3b2 = TileD<4, 2, 2, 4, 3, 2, true, 1, false, 2>;
-using D8_128x128_a3b2 = TileD<2, 2, 2, 2, 3, 2, true, 0, false, 2>;
-using D8_128x128_a3b2_e1 = TileD<2, 2, 2, 2, 3, 2, true, 1, false, 2>;
+using D8_256x192_8w_a3b2 = TileD<2, 3, 4, 2, 3, 2, true, 1, 2>;
+using D8_256x192_8w_a2b3 = TileD<2, 3, 4, 2, 2, 2, true, 1, 3>;
+using D8_256x256_8w_a3b2 = TileD<4, 2, 2, 4, 3, 2, true, 1, 2>;
+using D8_128x128_a3b2 = TileD<2, 2, 2, 2, 3, 2, true, 0, 2>;
+using D8_128x128_a3b2_e1 = TileD<2, 2, 2, 2, 3, 2, true, 1, 2>;
 using D8_128x128_s2_e1 = TileD<2, 2, 2, 2, 2, 2, true, 1>;
 //                                                                               persistent
-using P8_128x128_a3b2 = TileD<2, 2, 2, 2, 3, 2, true, 1, false, 2, true>;
-using P8_128x192_s2 = TileD<2, 3, 2, 2, 2, 2, true, 1, false, 2, true>;
+using P8_128x128_a3b2 = TileD<2, 2, 2, 2, 3, 2, true, 1, 2, true>;
+using P8_128x192_s2 = TileD<2, 3, 2, 2, 2, 2, true, 1, 2, true>;
 //                                                                                      FP16 operands
-using H_256x192_8w = TileD<2, 3, 4, 2, 3, 2, true, 1, false, 2, false, true>;
-using H_128x128_4w = TileD<2, 2, 2, 2, 3, 2, true, 1, false, 2, false, true>;
-using H_64x64_4w = TileD<1, 1, 2, 2, 3, 4, true, 0, false, 3, false, true>;
-using H_p192 = TileD<2, 3, 2, 2, 2, 2, true, 1, false, 2, true, true>;
-using H_p128 = TileD<2, 2, 2, 2, 3, 2, true, 1, false, 2, true, true>;
+using H_256x192_8w = TileD<2, 3, 4, 2, 3, 2, true, 1, 2, false, true>;
+using H_128x128_4w = TileD<2, 2, 2, 2, 3, 2, true, 1, 2, false, true>;
+using H_64x64_4w = TileD<1, 1, 2, 2, 3, 4, true, 0, 3, false, true>;
+using H_p192 = TileD<2, 3, 2, 2, 2, 2, true, 1, 2, true, true>;
+using H_p128 = TileD<2, 2, 2, 2, 3, 2, true, 1, 2, true, true>;
 
 static const Variant VARIANTS[] = {
     {"w8 dma 64x64 s3 4w", 8, dma_takes, run_dma<D8_64x64_s3>, run_dma<D8_64x64_s3, true>},

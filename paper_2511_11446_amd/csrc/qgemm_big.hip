@@ -54,13 +54,6 @@ struct TileBig {
     static_assert(LDS_BYTES <= 160 * 1024 && STORES < 64 && SPAN > 0, "LDS, outstanding operations");
 };
 
-// one DMA instruction of 64 words (see dma16_buf)
-__device__ __forceinline__ void dma4_buf(const void *base, int bytes, unsigned char *lds, unsigned lane_off)
-{
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)lds, 4, lane_off, 0, 0, 0);
-}
-
 template <class T, bool GLUE>
 __global__ __launch_bounds__(T::NTHR, 2) void qgemm_big(GemmArgs a, int tiles_m, int tiles_n, int nblk_padded, int group_m)
 {

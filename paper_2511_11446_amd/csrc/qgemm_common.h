@@ -40,6 +40,13 @@ __device__ __forceinline__ void dma16_buf(const void *base, unsigned bytes, unsi
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)lds, 16, lane_off, step_off, 0, 0);
 }
 
+// the same of 64 words
+__device__ __forceinline__ void dma4_buf(const void *base, unsigned bytes, unsigned char *lds, unsigned lane_off)
+{
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)lds, 4, lane_off, 0, 0, 0);
+}
+
 // ---- block glue folded into the epilogue: h = f16(act(u)); y = f16(fma(g, h, r)) -----------------------------------
 // GELU in its tanh form, written with the logistic function: u * sigmoid(2 z), z = sqrt(2/pi) (u + 0.044715 u^3).
 // This keeps the relative accuracy in the negative tail, where 1 + tanh z cancels.

@@ -24,7 +24,8 @@ namespace ql {
 
 // WGM_: wavefront rows of the workgroup (2: 128x128 tile, 4: 256x128); SA_/SB_: ring depths of the two operands
 // B8_: the weight operand is int8 codes (128 bytes per row and K step) instead of packed nibbles
-// MAXG_: weight groups along K whose scales the tile keeps in LDS (40: two workgroups per CU; more: one)
+// MAXG_: weight groups along K whose scales the tile keeps in LDS (128x128 tiles: 40 leave two workgroups per CU, 144 one; 64x64 tiles:
+// four, and three)
 // T_: 32-wide MFMA tiles per wavefront and direction
 template <int WGM_, int SA_, int SB_, bool B8_ = false, int MAXG_ = 40, int T_ = 2>
 struct TileW4 {
@@ -485,11 +486,8 @@ static hipError_t run_w4(const GemmArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-// more than 40 groups (K = 4608 with groups of 32 or 64): a table of up to 144 groups, one workgroup per CU
+// more than 40 groups (K = 4608 with groups of 32 or 64): a table of up to 144 groups
 constexpr int W4_MANY_GROUPS = 144;
-
-
-
 
 bool qgemm_w4_takes(const GemmArgs &a)
 {
@@ -536,11 +534,12 @@ hipError_t launch_qgemm_w4_128(const GemmArgs &a, hipStream_t stream)
     return a.s_ag && a.R % 128 != 0 ? launch_w4_tile<1>(a, stream) : launch_w4_tile<2>(a, stream);
 }
 
-// 64x64 tiles (four workgroups of four wavefronts per CU, 32x32 per wavefront) or 128x128 (two, 64x64 per wavefront).  The
-// small tiles hide the folds and the hand-overs behind more wavefronts but move twice the operand bytes; they win while all
-// of them are resident at once (1024), up to about twice as many where K is short, and wherever more than 40 groups leave
-// the large tiles one workgroup per CU.  M = 2048, K = 4608, N = 1152, group 128: 28 against 34 us; M = 8192: 80 against 74; group 32:
-// 134 against 198.
+// Group-scaled codes and channel-group activation scales (packed 4-bit layers without those choose by cost, in launch_qgemm): 64x64 tiles
+// (32x32 per wavefront; four workgroups per CU, three with int8 codes or more than 40 groups) or 128x128 (64x64 per wavefront; two, one
+// with more than 40 groups).  The small tiles hide the folds and the hand-overs behind more wavefronts but move twice the operand
+// bytes.  The line was drawn on packed 4-bit layers: 64x64 up to 1024 tiles, up to about twice as many where K is short, and wherever more
+// than 40 groups leave the large tiles one workgroup per CU.  M = 2048, K = 4608, N = 1152, group 128: 28 against 34 us; M = 8192: 80
+// against 74; group 32: 134 against 198.
 hipError_t launch_qgemm_w4(const GemmArgs &a, hipStream_t stream)
 {
     const long long tiles = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64);

@@ -60,13 +60,6 @@ struct TileW4Big {
     static_assert(LDS_BYTES <= 160 * 1024 && STORES < 64 && SPAN > 0 && ahead(SPAN - 1) == DIST, "LDS, outstanding operations, ring");
 };
 
-// one DMA instruction of 64 words (see dma16_buf)
-static __device__ __forceinline__ void dma_words(const void *base, int bytes, unsigned char *lds, unsigned lane_off)
-{
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)lds, 4, lane_off, 0, 0, 0);
-}
-
 template <class T, bool GLUE>
 __global__ __launch_bounds__(T::NTHR, 2) void qgemm_w4_big(GemmArgs a, int tiles_m, int tiles_n, int nblk_padded, int group_m)
 {
@@ -129,8 +122,8 @@ __global__ __launch_bounds__(T::NTHR, 2) void qgemm_w4_big(GemmArgs a, int tiles
 #pragma unroll
         for (int c = 0; c < T::SA_Q + T::SB_Q; ++c) {
             if (wave != c % T::NW) continue;
-            if (c < T::SA_Q) dma_words(a.s_a, ((M - 1) / a.R + 1) * 4, s + T::ROWS0 + c * 256, (unsigned)(min(m0 + 64 * c + lane, M - 1) / a.R * 4));
-            else if (a.bias) dma_words(a.bias, N * 2, s + T::ROWS0 + c * 256, (unsigned)(n0 + 128 * (c - T::SA_Q) + 2 * lane) * 2u);
+            if (c < T::SA_Q) dma4_buf(a.s_a, ((M - 1) / a.R + 1) * 4, s + T::ROWS0 + c * 256, (unsigned)(min(m0 + 64 * c + lane, M - 1) / a.R * 4));
+            else if (a.bias) dma4_buf(a.bias, N * 2, s + T::ROWS0 + c * 256, (unsigned)(n0 + 128 * (c - T::SA_Q) + 2 * lane) * 2u);
         }
     };
 

@@ -643,7 +643,7 @@ GLUE_CASES = [
     (64, 200, 48, 1, 8, 0, 1, True, 32),          # generic kernel (K % 64 != 0)
     (256, 1152, 256, 1, 4, 128, 1, True, 256),    # 4-bit weights
     (256, 1152, 192, 1, 4, 288, 0, True, 128),    # 4-bit, group 288
-    (4096, 1152, 1152, 1, 8, 0, 0, True, 1024),   # a shape of the persistent walk: with glue it runs on 256x192 tiles, eight wavefronts
+    (4096, 1152, 1152, 1, 8, 0, 0, True, 1024),   # a shape whose plain form takes a persistent walk, which has no glue form
     (4096, 1152, 3456, 1, 8, 0, 1, False, 0),     # the same for a wide layer, GELU only
     (256, 4608, 384, 256, 8, 0, 0, True, 256),    # K = 4608, per-sample scales
     (384, 4608, 256, 1, 4, 64, 1, True, 128),     # 4-bit, 72 groups along K: the pipelined kernel with the large scale table, with glue
@@ -688,7 +688,7 @@ ROWMAX_CASES = [
     (300, 1152, 200, 8, 0, 1, False),       # ragged: element-wise epilogue, one atomic per element
     (384, 1152, 320, 4, 128, 1, False),     # the pipelined 4-bit kernel
     (384, 1152, 320, 4, 288, 0, False),     # no glue at all, only the side output
-    (4096, 1152, 1152, 8, 0, 1, False),     # 256x192 tiles on eight wavefronts
+    (4096, 1152, 1152, 8, 0, 1, False),     # several tiles per workgroup slot (every tile: test_gpu_tile_glue.py)
     (64, 200, 48, 8, 0, 1, True),           # generic kernel
     (384, 1152, 256, 16, 0, 1, False),      # a layer left in FP16
 ]

@@ -29,12 +29,13 @@ POOL = 4                  # distinct activation sets rotated over the steps (dif
 # HBM bytes per GEMM launch (reads + writes, mean over the GEMM launches of a step).  NOT measured by the run that
 # prints them: they come from earlier rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE runs of `bench.py --traffic-probe`, each
 # scaled by what the same counter reads for a device-to-device copy of known size in the same run; the summary file
-# under profiles/ is named beside each figure.  Keyed by (workload, forced variant, 4-bit group); absent = not measured.
+# under profiles/ and the tiles it was measured on are named beside each figure; a change of the tile choice for these workloads
+# takes a new measurement.  Keyed by (workload, forced variant, 4-bit group); absent = not measured.
 TRAFFIC_BYTES_PER_LAUNCH = {
     # (2 x FETCH_SIZE + WRITE_SIZE) KiB -> bytes, mean over the launches of the workload's dominant GEMM kernel in a step
-    ("c5_stack_plan_m16384", -1, 128): (176468597, "profiles/qgemm_daq_c5_stack_m16384_hbm_traffic.txt (measured on the 128x128 tiles of qgemm_w4, 74 launches per step)"),
-    ("c4_block_w8a8_m16384", -1, 128): (211073875, "profiles/qgemm_daq_c4_block_m16384_hbm_traffic.txt (measured on the 128x192 tiles of qgemm_dma, 4 launches per step)"),
-    ("c2_block_w8a8_m2048", -1, 128): (37098200, "profiles/qgemm_daq_c2_block_m2048_hbm_traffic.txt (qgemm_dma, 4 launches per step)"),
+    ("c5_stack_plan_m16384", -1, 128): (159700000, "profiles/qgemm_daq_c5_stack_m16384_hbm_traffic.txt (qgemm_w4_big, 256x288 tiles, 74 launches per step)"),
+    ("c4_block_w8a8_m16384", -1, 128): (191100000, "profiles/qgemm_daq_c4_block_m16384_hbm_traffic.txt (qgemm_big, 256x256 and 256x288 tiles, 4 launches per step)"),
+    ("c2_block_w8a8_m2048", -1, 128): (37200000, "profiles/qgemm_daq_c2_block_m2048_hbm_traffic.txt (qgemm_dma, 128x128 and 256x192 tiles, 4 launches per step)"),
 }
 
 

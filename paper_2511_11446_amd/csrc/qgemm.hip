@@ -747,6 +747,7 @@ static int find_variant(const char *name)
 // chosen is in the mean 0.3 % slower than the fastest one, 2 % of 6300 cases lose more than 5 %, and the worst one (partial tiles with GELU)
 // 43 %.  Rules that charged the large tiles per round and the others by their rate, without the glue, lost 2 % (4 bits) to 6 % (FP16) in
 // the mean of the plain layers and 5 to 17 % with gate and residual (8-bit, M = 8192, K = 256, N = 1024: 40.7 us against 14.3).
+// profiles/tile_choice_sweep.txt holds the part of the data with the common widths.
 struct TileCost {
     const char *name;
     int bits, BM, BN, resident;

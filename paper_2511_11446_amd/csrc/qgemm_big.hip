@@ -6,7 +6,8 @@
 //   - With random operands the chip is power-limited: v_mfma_i32_16x16x64_i8 from registers reaches 4.0 POPS where
 //     v_mfma_i32_32x32x32_i8 reaches 3.36 (4.7 and 4.8 on zeros), and a large tile moves fewer bytes through the L2 and the LDS
 //     per operation.  256 x 288: a K step of 128 bytes is 2304 MFMA clocks of a SIMD, 1660 clocks of LDS reads and 540 of
-//     LDS writes; it measures 3100.
+//     LDS writes; it measured 3100.  Over a whole kernel at M = 16384 the matrix cores are busy 43
+//     to 46 % of the time (profiles/qgemm_big_qgemm_w4_big_c5_stack_m16384_sq_counters.txt).
 //   - 288 divides 1152, 3456 and 4608, so that 256-row tiles at M = 16384 fill 256 CUs in whole rounds.  The 32 columns behind
 //     2 x 128 are shared by the two wavefronts of a row, each taking half of the row blocks.
 //   - A lane's columns of the result are 8 neighbouring ones (the rows of W enter LDS in that order), so that 16 lanes

@@ -698,10 +698,10 @@ static const Variant VARIANTS[] = {
     {"w8 split-K 16x16", 8, split_takes<16>, launch_qgemm_split16, launch_qgemm_split16},
     {"w4 any-group split-K 16x16", 4, split_takes<16>, launch_qgemm_split16, launch_qgemm_split16},
     {"f16 split-K 16x16", 16, split_takes<16>, launch_qgemm_split16, launch_qgemm_split16},
-    {"w8 staged 128x128 k64", 8, k64_takes, run_k64},
     {"w8 edge any-K", 8, qgemm_edge_takes, launch_qgemm_edge, launch_qgemm_edge},
     {"w4 any-group edge any-K", 4, qgemm_edge_takes, launch_qgemm_edge, launch_qgemm_edge},
     {"f16 edge any-K", 16, qgemm_edge_takes, launch_qgemm_edge, launch_qgemm_edge},
+    {"w8 staged 128x128 k64", 8, k64_takes, run_k64},
 #ifdef QL_SWEEP_VARIANTS   // the other tile shapes of the sweeps that chose the ones above
     {"w8 dma 128x128 s3 4w", 8, dma_takes, run_dma<D8_128x128_s3>},
     {"w8 dma 128x128 s2 4w", 8, dma_takes, run_dma<D8_128x128_s2>},

@@ -359,7 +359,8 @@ size_t ql_plan_workspace_bytes(const ql_plan *plan, int64_t M, int64_t R);
 
 /* x_in[l] (device) [M, K_l] fp16 and y_out[l] (device) [M, N_l] fp16 for every
  * layer l; the two pointer arrays themselves are host memory.  Layers run in
- * order on `stream`, so y_out[l] may alias x_in[l+1]. */
+ * order on `stream`, so y_out[l] may alias x_in[l+1]; layers none of whose
+ * buffers an earlier one of them writes may share launches. */
 int qlinear_plan_run(const ql_plan *plan, const void *const *x_in, void *const *y_out,
                      int64_t M, int64_t R,
                      void *workspace, size_t workspace_bytes, void *stream);

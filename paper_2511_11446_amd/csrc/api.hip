@@ -781,6 +781,59 @@ size_t ql_plan_workspace_bytes(const ql_plan *plan, int64_t M, int64_t R)
     return most;
 }
 
+// The next layers of a plan from `first` on in one go, where their inputs are there already: with one scale per token, their activations
+// are quantized by one launch (each layer's codes in a part of its own of the workspace), then the GEMMs follow in order.  Takes layers as
+// long as no input of one is written by another one before it, their codes fit the workspace that the widest layer needs, and none is
+// small enough to quantize its own rows inside its GEMM.  Returns how many layers it ran: 0 where that is fewer than two
+// quantized ones.
+static size_t plan_run_window(const ql_plan *plan, size_t first, const void *const *x_in, void *const *y_out, int64_t M, void *workspace,
+                              hipStream_t stream, int &rc)
+{
+    const size_t room = layer_ws(M, plan->K_widest, 1).total;
+    unsigned char *base = static_cast<unsigned char *>(workspace);
+    ql::GemmArgs g[ql::PLAN_WINDOW];
+    ql::DaqMany daq{};
+    daq.M = (int)M;
+    size_t used = 0, n = 0;
+    for (; n < ql::PLAN_WINDOW && first + n < plan->layers.size(); ++n) {
+        const size_t l = first + n;
+        const ql_layer_desc &d = plan->layers[l];
+        bool ready = true;
+        for (size_t j = first; j < l; ++j)
+            ready = ready && !overlap(x_in[l], (size_t)(M * d.K) * 2, y_out[j], (size_t)(M * plan->layers[j].N) * 2);
+        if (!ready) break;
+        ql::GemmArgs &a = g[n];
+        a = ql::GemmArgs{};
+        a.w = d.w;
+        a.s_w = d.w_scale;
+        a.bias = d.bias;
+        a.y = y_out[l];
+        a.M = (int)M;
+        a.N = (int)d.N;
+        a.K = (int)d.K;
+        a.R = 1;
+        a.w_bits = d.w_bits;
+        a.group = d.w_bits == 4 ? (int)d.group : 128;
+        if (d.w_bits == 16) {
+            a.q = static_cast<const int8_t *>(x_in[l]);
+            continue;
+        }
+        const LayerWs lw = layer_ws(M, d.K, 1);
+        const ql::DaqItem it = {x_in[l], reinterpret_cast<int8_t *>(base + used + lw.q_off), reinterpret_cast<float *>(base + used + lw.s_off), (int)d.K};
+        a.q = it.q;
+        a.s_a = it.scales;
+        a.x = x_in[l];
+        if (used + lw.total > room || !ql::daq_many_takes(it) || ql::qgemm_fuse_takes(a)) break;
+        a.x = nullptr;
+        daq.l[daq.count++] = it;
+        used += lw.total;
+    }
+    if (daq.count < 2) return 0;
+    rc = device_status(ql::launch_daq_many(daq, stream));
+    for (size_t i = 0; i < n && rc == QL_OK; ++i) rc = device_status(ql::launch_qgemm(g[i], -1, stream));
+    return n;
+}
+
 static int plan_run_any(const ql_plan *plan, const void *const *x_in, void *const *y_out, int64_t M, int64_t R,
                         const ql_daq_params *dp, void *workspace, size_t workspace_bytes, void *stream,
                         const ql_fusion *const *fusion = nullptr)
@@ -800,7 +853,16 @@ static int plan_run_any(const ql_plan *plan, const void *const *x_in, void *cons
             if (rc) return rc;
         }
     hipStream_t s = static_cast<hipStream_t>(stream);
+    const bool windows = R == 1 && !dp && !fusion && g_gemm_variant.load() < 0;
     for (size_t l = 0; l < plan->layers.size(); ++l) {
+        if (windows) {
+            const size_t ran = plan_run_window(plan, l, x_in, y_out, M, workspace, s, rc);
+            if (rc) return rc;
+            if (ran) {
+                l += ran - 1;
+                continue;
+            }
+        }
         const ql_layer_desc &d = plan->layers[l];
         rc = run_layer(x_in[l], M, d.K, R, d.w_bits, d.w, d.w_scale, d.bias, d.N, y_out[l], nullptr, workspace, workspace_bytes, s, dp,
                        d.w_bits == 4 ? d.group : 128, fusion ? fusion[l] : nullptr);

@@ -54,6 +54,21 @@ inline size_t daq_parts_per_block(int64_t K, int64_t R)
 }
 
 hipError_t launch_daq(const DaqArgs &a, hipStream_t stream);
+// per-token DAQ of up to PLAN_WINDOW layers of M rows in one launch; every layer has to pass daq_many_takes
+constexpr int PLAN_WINDOW = 8;
+struct DaqItem {
+    const void *x;    // [M,K] fp16
+    int8_t *q;        // [M,K]
+    float *scales;    // [M]
+    int K;
+};
+struct DaqMany {
+    DaqItem l[PLAN_WINDOW];
+    int count, M;
+    int blocks;       // workgroups per layer (launch_daq_many)
+};
+bool daq_many_takes(const DaqItem &l);
+hipError_t launch_daq_many(DaqMany &b, hipStream_t stream);
 // the first pass alone: partial maxima of every scale block (daq_parts_per_block of them) into a.partmax
 hipError_t launch_daq_part_absmax(const DaqArgs &a, hipStream_t stream);
 // eq. (4) with channel groups: scales [M/R, K/cg]; workspace in blockmax: one maximum per group and slab of

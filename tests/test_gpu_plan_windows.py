@@ -1,0 +1,95 @@
+"""Plans whose layers run several at a time (inputs quantized by one launch, GEMMs together): every output equals that of the layer's own
+call, bit for bit, whatever the rows, widths, kinds and the aliasing between outputs and later inputs."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ql():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_2511_11446_amd as ql
+    ql.lib()
+    return ql
+
+
+def _layer(g, K, N, bits, group, bias=True):
+    dev = dict(device="cuda", generator=g)
+    b = (torch.randn(N, **dev) * 0.02).half() if bias else None
+    if bits == 16:
+        return dict(K=K, N=N, bits=16, w=(torch.randn(N, K, **dev) * 0.02).half(), w_scale=None, bias=b)
+    if bits == 8:
+        return dict(K=K, N=N, bits=8, w=torch.randint(-127, 128, (N, K), dtype=torch.int8, **dev), w_scale=torch.rand(N, **dev) * 9e-3 + 1e-3, bias=b)
+    return dict(K=K, N=N, bits=4, group=group, w=torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, **dev),
+                w_scale=(torch.rand(N, K // group, **dev) * 0.09 + 0.01).half(), bias=b)
+
+
+def _alone(ql, l, x):
+    if l["bits"] == 16:
+        return ql.qlinear_f16(x, l["w"], l["bias"])
+    if l["bits"] == 8:
+        return ql.qlinear_w8a8(x, 1, l["w"], l["w_scale"], l["bias"])
+    return ql.qlinear_w4a8(x, 1, l["w"], l["w_scale"], l["bias"], group=l["group"])
+
+
+# (K, N, bits, group, bias) of each layer
+PLANS = {
+    "block w8": [(384, 1152, 8, 0, True), (384, 384, 8, 0, False), (384, 1536, 8, 0, True), (1536, 384, 8, 0, True)],
+    "all kinds": [(1152, 1000, 4, 288, True), (1152, 264, 16, 0, True), (1152, 640, 4, 128, False), (1152, 392, 8, 0, True),
+                  (1152, 130, 4, 32, True), (1152, 200, 4, 64, True), (1152, 96, 4, 192, True), (768, 96, 4, 96, True), (4608, 512, 16, 0, False)],
+    "odd inner sizes": [(320, 300, 8, 0, True), (200, 256, 8, 0, True), (256, 136, 16, 0, True), (1032, 128, 8, 0, True), (1028, 64, 8, 0, True)],
+    "wide and narrow": [(4608, 384, 8, 0, True), (384, 513, 8, 0, True), (384, 512, 4, 64, True), (4608, 256, 4, 32, True), (2304, 128, 4, 288, True)],
+}
+
+
+@pytest.mark.parametrize("M", [129, 512, 1021, 2048])
+@pytest.mark.parametrize("name", PLANS)
+def test_plan_equals_its_layers(ql, name, M):
+    g = torch.Generator(device="cuda").manual_seed(M)
+    layers = [_layer(g, *s) for s in PLANS[name]]
+    x = [torch.randn(M, l["K"], device="cuda", generator=g).half() for l in layers]
+    y = [torch.full((M, l["N"]), float("nan"), dtype=torch.float16, device="cuda") for l in layers]
+    plan = ql.Plan(layers, M_max=M)
+    ws = ql.workspace(plan.workspace_bytes(M, 1))
+    for _ in range(2):
+        plan.run(x, y, M, 1, ws)
+    for l, a, b in zip(layers, x, y):
+        if l["bits"] == 16:   # fp32 sums in any order, then one rounding to fp16
+            exact = a.double() @ l["w"].double().T + (0.0 if l["bias"] is None else l["bias"].double())
+            bound = (l["K"] + 1) * 2.0 ** -24 * (a.double().abs() @ l["w"].double().abs().T + 1.0) + exact.abs() * 2.0 ** -11 + 2.0 ** -25
+            assert bool(((b.double() - exact).abs() <= bound).all())
+        else:
+            torch.testing.assert_close(b, _alone(ql, l, a), rtol=0, atol=0)
+
+
+@pytest.mark.parametrize("bits", [8, 4, 16])
+def test_chained_layers_keep_their_order(ql, bits):
+    # an output that is the next layer's input, one that is the input of a layer further on, one that overwrites an earlier input, and
+    # two layers that write the same output
+    M, w = 1024, 256
+    g = torch.Generator(device="cuda").manual_seed(bits)
+    layers = [_layer(g, w, w, b, 64) for b in (8, bits, 4, bits, bits, 8, bits)]
+    t = [(torch.randn(M, w, device="cuda", generator=g) * 0.1).half() for _ in range(8)]
+    flow = [(0, 1), (1, 2), (3, 4), (1, 5), (5, 3), (0, 6), (6, 6)]   # (input, output) of each layer
+    plan = ql.Plan(layers, M_max=M)
+    ws = ql.workspace(plan.workspace_bytes(M, 1))
+    want = [v.clone() for v in t]
+    for l, (i, o) in zip(layers, flow):
+        want[o].copy_(_alone(ql, l, want[i]))
+    plan.run([t[i] for i, _ in flow], [t[o] for _, o in flow], M, 1, ws)
+    for a, b in zip(t, want):
+        torch.testing.assert_close(a, b, rtol=0, atol=0, equal_nan=True)
+
+
+def test_layers_that_write_the_same_output(ql):
+    # disjoint inputs, one output for all: the last layer's stays
+    M, w = 512, 256
+    g = torch.Generator(device="cuda").manual_seed(1)
+    layers = [_layer(g, w, w, b, 64) for b in (8, 4, 16, 8)]
+    x = [torch.randn(M, w, device="cuda", generator=g).half() for _ in layers]
+    y = torch.empty(M, w, dtype=torch.float16, device="cuda")
+    plan = ql.Plan(layers, M_max=M)
+    plan.run(x, [y] * 4, M, 1, ql.workspace(plan.workspace_bytes(M, 1)))
+    torch.testing.assert_close(y, _alone(ql, layers[3], x[3]), rtol=0, atol=0)

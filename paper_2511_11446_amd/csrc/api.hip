@@ -781,6 +781,25 @@ size_t ql_plan_workspace_bytes(const ql_plan *plan, int64_t M, int64_t R)
     return most;
 }
 
+// Do the GEMMs of these layers give the same in any order?  No output overlaps another one's, or what another layer reads (codes and
+// scales lie in the workspace).
+static bool any_order(const ql::GemmArgs *g, size_t n)
+{
+    for (size_t i = 0; i < n; ++i) {
+        const size_t y_bytes = (size_t)g[i].M * g[i].N * 2;
+        for (size_t j = 0; j < n; ++j) {
+            if (i == j) continue;
+            const ql::GemmArgs &o = g[j];
+            const size_t w_elems = (size_t)o.N * o.K, scales = o.w_bits == 8 ? (size_t)o.N * 4 : o.w_bits == 4 ? (size_t)o.N * (o.K / o.group) * 2 : 0;
+            if (overlap(g[i].y, y_bytes, o.y, (size_t)o.M * o.N * 2) || overlap(g[i].y, y_bytes, o.w, o.w_bits == 16 ? w_elems * 2 : o.w_bits == 8 ? w_elems : w_elems / 2) ||
+                (scales && overlap(g[i].y, y_bytes, o.s_w, scales)) || (o.bias && overlap(g[i].y, y_bytes, o.bias, (size_t)o.N * 2)) ||
+                (o.w_bits == 16 && overlap(g[i].y, y_bytes, o.q, (size_t)o.M * o.K * 2)))
+                return false;
+        }
+    }
+    return true;
+}
+
 // The next layers of a plan from `first` on in one go, where their inputs are there already: with one scale per token, their activations
 // are quantized by one launch (each layer's codes in a part of its own of the workspace), then the GEMMs follow in order.  Takes layers as
 // long as no input of one is written by another one before it, their codes fit the workspace that the widest layer needs, and none is
@@ -830,7 +849,16 @@ static size_t plan_run_window(const ql_plan *plan, size_t first, const void *con
     }
     if (daq.count < 2) return 0;
     rc = device_status(ql::launch_daq_many(daq, stream));
-    for (size_t i = 0; i < n && rc == QL_OK; ++i) rc = device_status(ql::launch_qgemm(g[i], -1, stream));
+    // GEMMs that share a launch: none of the window's layers may read or write what another one writes
+    const ql::GemmArgs *together[ql::PLAN_WINDOW];
+    int count = 0;
+    if (any_order(g, n)) count = ql::qgemm_many_choice(g, (int)n, together);
+    if (count && rc == QL_OK) rc = device_status(ql::launch_qgemm_many(together, count, stream));
+    for (size_t i = 0; i < n && rc == QL_OK; ++i) {
+        bool done = false;
+        for (int j = 0; j < count; ++j) done = done || together[j] == &g[i];
+        if (!done) rc = device_status(ql::launch_qgemm(g[i], -1, stream));
+    }
     return n;
 }
 

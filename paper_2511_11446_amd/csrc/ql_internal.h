@@ -129,6 +129,8 @@ int num_gemm_variants();
 const char *gemm_variant_name(int v);
 // variant < 0: choose by shape
 hipError_t launch_qgemm(const GemmArgs &a, int variant, hipStream_t stream);
+// estimated time of a layer without glue on the tile that launch_qgemm would choose for it (layers that its DMA kernels take)
+float qgemm_alone_us(const GemmArgs &a);
 
 // the pipelined 4-bit kernel (qgemm_w4.hip): shapes it takes, and its launch (group 128 or any 32 j, exports, glue)
 bool qgemm_w4_takes(const GemmArgs &a);
@@ -162,6 +164,11 @@ hipError_t launch_big_w4_256x256(const GemmArgs &a, hipStream_t s);
 hipError_t launch_big_w4_256x256_glue(const GemmArgs &a, hipStream_t s);
 hipError_t launch_big_w4_128x288(const GemmArgs &a, hipStream_t s);
 hipError_t launch_big_w4_128x288_glue(const GemmArgs &a, hipStream_t s);
+// the GEMMs of several layers with as many rows each in one launch; every one has to pass qgemm_many_takes
+bool qgemm_many_takes(const GemmArgs &a);
+// which of them are better in one launch than one after the other (their number; fewer than two: none)
+int qgemm_many_choice(const GemmArgs *layers, int n, const GemmArgs **chosen);
+hipError_t launch_qgemm_many(const GemmArgs *const *layers, int count, hipStream_t stream);
 // pair-order nibbles (device) -> the 4-bit storage order (device); blocks = N*K/8 four-byte blocks
 hipError_t launch_prepack_w4(const void *pairs, void *packed, long long blocks, hipStream_t stream);
 

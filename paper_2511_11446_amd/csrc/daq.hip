@@ -138,6 +138,39 @@ hipError_t launch_daq_many(DaqMany &b, hipStream_t stream)
     return hipGetLastError();
 }
 
+// Long rows, few of them: the four wavefronts of a workgroup share one, CH pieces per thread, so that four times as many loads are in
+// flight (a row of 4608 per wavefront leaves two wavefronts per SIMD at M = 2048).
+template <int CH>
+__global__ __launch_bounds__(256) void daq_rows_wide(DaqArgs a)
+{
+    __shared__ unsigned wave_max[4];
+    const int nch = a.K >> 3;
+    const uint4 *xr = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(a.x) + (size_t)blockIdx.x * a.K);
+    uint4 v[CH];
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const int c = threadIdx.x + 256 * i;
+        v[i] = c < nch ? xr[c] : make_uint4(0, 0, 0, 0);
+    }
+    unsigned m = 0;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) m = absmax_word(absmax_word(absmax_word(absmax_word(m, v[i].x), v[i].y), v[i].z), v[i].w);
+    m = wave_max_u32((m & 0xffffu) > (m >> 16) ? (m & 0xffffu) : (m >> 16));
+    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
+    __syncthreads();
+    const unsigned m01 = wave_max[0] > wave_max[1] ? wave_max[0] : wave_max[1];
+    const unsigned m23 = wave_max[2] > wave_max[3] ? wave_max[2] : wave_max[3];
+    const float alpha = alpha_from_bits(m01 > m23 ? m01 : m23);
+    const float rcp = 1.0f / alpha;
+    if (threadIdx.x == 0) a.scales[blockIdx.x] = alpha;
+    uint2 *qr = reinterpret_cast<uint2 *>(a.q + (size_t)blockIdx.x * a.K);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const int c = threadIdx.x + 256 * i;
+        if (c < nch) qr[c] = daq_piece(v[i], alpha, rcp);
+    }
+}
+
 // Any row length: the row is read twice (the second read normally hits L2).
 // VEC = 8: 16-byte loads (K % 8 == 0, aligned); VEC = 1: element-wise, no alignment needs.
 template <int VEC>
@@ -265,6 +298,14 @@ static void run_rows(const DaqArgs &a, int mode, hipStream_t s)
     // one row per wavefront at every size: with the division-free codes the kernel is no longer VALU-bound, and more,
     // shorter wavefronts beat several rows per wavefront (measured 4.5 against 3.4 TB/s at M = 16384, K = 1152)
     const int per_lane = (a.K / 8 + 63) / 64;
+    // us, a wavefront per row -> a workgroup per row: K = 4608: M = 64 4.7 -> 3.2, 1024 7.8 -> 5.6, 4096 14.0 -> 11.2, 16384 39.0 -> 35.9;
+    // K = 2304: 64 3.8 -> 2.8, 8192 13.4 -> 11.6, but 16384 21.0 -> 21.5
+    if (mode == DAQ_FUSED && per_lane > 4 && per_lane <= 16 && (a.M <= 8192 || per_lane > 5)) {
+        if (per_lane <= 8) hipLaunchKernelGGL(daq_rows_wide<2>, dim3(a.M), dim3(256), 0, s, a);
+        else if (per_lane <= 12) hipLaunchKernelGGL(daq_rows_wide<3>, dim3(a.M), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(daq_rows_wide<4>, dim3(a.M), dim3(256), 0, s, a);
+        return;
+    }
     if (per_lane <= 1) run_cached<1, 1>(a, mode, s);
     else if (per_lane <= 2) run_cached<2, 1>(a, mode, s);
     else if (per_lane <= 3) run_cached<3, 1>(a, mode, s);
@@ -325,25 +366,34 @@ __global__ __launch_bounds__(256) void daq_cg_quant(DaqArgs a, int cg)
 // by cg, the scale and its reciprocal - is paid once per thread and not per piece.  Pass 1 leaves the slab's maximum per
 // group with plain stores, no clearing pass and no atomics; pass 2 takes the maximum over its block's slabs.
 // M = 4096, K = 1152, R = 256, cg = 128: 32.7 -> 13 us.
-constexpr int DAQ_CG_ROWS = 4;    // rows in flight per thread
+// rows in flight per thread: all of a slab of 16 that three rows side by side leave to it (a second round of loads would wait for the first
+// one's stores)
+constexpr int DAQ_CG_ROWS = 6;
 // Slabs per scale block up to which every thread takes the maximum of its group over them by itself; beyond that the workgroup does it
 // together (both passes, cg = 128, M = R = 16384, 1024 slabs: K = 1152 131 -> 22 us, K = 4608 404 -> 91, where the atomic kernels take
 // 79 and 185; M = 4096, R = 1024, K = 1152: 15.5 -> 8.4)
 constexpr int DAQ_CG_OWN = 16;
 template <bool QUANT>
-__global__ __launch_bounds__(1024) void daq_cg_slab(DaqArgs a, int cg, int slab, int rpw)
+__global__ __launch_bounds__(1024) void daq_cg_slab(DaqArgs a, int cg, int slab, int slabs, int rpw)
 {
     extern __shared__ unsigned gmax_lds[];
     const int P = a.K >> 3, G = a.K / cg;
     const int p = threadIdx.x % P, r0 = threadIdx.x / P, g = p * 8 / cg;
     const bool on = r0 < rpw;
-    const int row0 = blockIdx.x * slab, slabs = a.R / slab;
+    const int row0 = blockIdx.x * slab;
     unsigned *part = a.blockmax;          // [M / slab][G]
     float alpha = 1.0f, rcp = 1.0f;
     if (!QUANT || slabs > DAQ_CG_OWN) {
         for (int i = threadIdx.x; i < G; i += blockDim.x) gmax_lds[i] = 0;
         __syncthreads();
     }
+    const uint4 *x = reinterpret_cast<const uint4 *>(a.x) + (size_t)row0 * P + p;
+    uint4 v[DAQ_CG_ROWS];
+    auto load = [&](int r) {
+#pragma unroll
+        for (int u = 0; u < DAQ_CG_ROWS; ++u) v[u] = on && r + u * rpw < slab ? x[(size_t)(r + u * rpw) * P] : make_uint4(0, 0, 0, 0);
+    };
+    if (!QUANT || slabs <= DAQ_CG_OWN) load(r0);
     if (QUANT) {
         const unsigned *pm = part + (size_t)(row0 / a.R) * slabs * G;
         unsigned m = 0;
@@ -352,7 +402,12 @@ __global__ __launch_bounds__(1024) void daq_cg_slab(DaqArgs a, int cg, int slab,
             __syncthreads();
             if (on) m = gmax_lds[g];
         } else if (on) {
-            for (int s = 0; s < slabs; ++s) m = m > pm[s * G + g] ? m : pm[s * G + g];
+            // all requested at once: in a loop each one waited for the one before (M = 1024, R = 256, K = 1152: 10.8 -> 6.8 us)
+            unsigned o[DAQ_CG_OWN];
+#pragma unroll
+            for (int s = 0; s < DAQ_CG_OWN; ++s) o[s] = pm[(s < slabs ? s : 0) * G + g];
+#pragma unroll
+            for (int s = 0; s < DAQ_CG_OWN; ++s) m = m > o[s] ? m : o[s];
         }
         if (on) {
             alpha = alpha_from_bits(m);
@@ -361,13 +416,10 @@ __global__ __launch_bounds__(1024) void daq_cg_slab(DaqArgs a, int cg, int slab,
         }
     }
     if (on) {
-        const uint4 *x = reinterpret_cast<const uint4 *>(a.x) + (size_t)row0 * P + p;
         uint2 *q = reinterpret_cast<uint2 *>(a.q) + (size_t)row0 * P + p;
         unsigned m = 0;
         for (int r = r0; r < slab; r += rpw * DAQ_CG_ROWS) {
-            uint4 v[DAQ_CG_ROWS];
-#pragma unroll
-            for (int u = 0; u < DAQ_CG_ROWS; ++u) v[u] = r + u * rpw < slab ? x[(size_t)(r + u * rpw) * P] : make_uint4(0, 0, 0, 0);
+            if (r != r0 || (QUANT && slabs > DAQ_CG_OWN)) load(r);
 #pragma unroll
             for (int u = 0; u < DAQ_CG_ROWS; ++u) {
                 if (QUANT) {
@@ -396,8 +448,12 @@ hipError_t launch_daq_cg(const DaqArgs &a, int cg, bool slabs, hipStream_t strea
         // chain of four trips to memory (M = 512, R = 64, K = 3072: 14.5 -> 11.3 us; all threads at M = 16384, R = 64, K = 384: 10.0 -> 12.6)
         const int rpw = P > 512 ? 1 : P > 256 ? 1024 / P : 512 / P;
         const dim3 grid(a.M / slab), block((P * rpw + 63) / 64 * 64);
-        hipLaunchKernelGGL(daq_cg_slab<false>, grid, block, G * 4, stream, a, cg, slab, rpw);
-        hipLaunchKernelGGL(daq_cg_slab<true>, grid, block, G * 4, stream, a, cg, slab, rpw);
+        hipLaunchKernelGGL(daq_cg_slab<false>, grid, block, G * 4, stream, a, cg, slab, a.R / slab, rpw);
+        // the codes are written by workgroups of 8 rows, unless these merge many slabs or have more than 8 rows side by side (both passes, us:
+        // M = 4096, R = 256, K = 1152 11.5 -> 10.1, K = 4608 23.5 -> 20.6, M = 512, R = 64, K = 3072 10.6 -> 8.5; but M = 16384, R = 1024, K =
+        // 1152 19.5 -> 22.3)
+        const int rows = a.R / slab <= DAQ_CG_OWN && rpw <= 4 ? 8 : slab;
+        hipLaunchKernelGGL(daq_cg_slab<true>, dim3(a.M / rows), block, G * 4, stream, a, cg, rows, a.R / slab, rpw);
         return hipGetLastError();
     }
     const int n = (a.M / a.R) * G;

@@ -110,6 +110,27 @@ inline bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes
     return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
 }
 
+// a layer's codes, scales and DAQ scratch in `bytes` of workspace
+ql::DaqArgs daq_args(const void *x, int64_t M, int64_t K, int64_t R, unsigned char *base, size_t bytes)
+{
+    const LayerWs lw = layer_ws(M, K, R);
+    const size_t blocks = align_up((size_t)(M / R) * 4, 256);
+    ql::DaqArgs d{};
+    d.x = x;
+    d.q = reinterpret_cast<int8_t *>(base + lw.q_off);
+    d.scales = reinterpret_cast<float *>(base + lw.s_off);
+    if (R > 1) {
+        d.blockmax = reinterpret_cast<unsigned *>(base + lw.bm_off);
+        d.partmax = reinterpret_cast<unsigned *>(base + lw.bm_off + blocks);
+        d.hist = d.partmax;
+        d.scratch_bytes = bytes - lw.bm_off - blocks;
+    }
+    d.M = (int)M;
+    d.K = (int)K;
+    d.R = (int)R;
+    return d;
+}
+
 // DAQ then GEMM for one layer; all arguments already validated
 int run_layer(const void *x, int64_t M, int64_t K, int64_t R, int w_bits, const void *w, const void *w_scale,
               const void *bias, int64_t N, void *y, const ql_debug *dbg, void *workspace, size_t workspace_bytes, hipStream_t stream,
@@ -141,19 +162,9 @@ int run_layer(const void *x, int64_t M, int64_t K, int64_t R, int w_bits, const 
         }
         return device_status(ql::launch_qgemm(g, g_gemm_variant.load(), stream));
     }
-    const LayerWs lw = layer_ws(M, K, R);
-    unsigned char *base = static_cast<unsigned char *>(workspace);
-    ql::DaqArgs d{};
-    d.x = x;
-    d.q = (dbg && dbg->q) ? static_cast<int8_t *>(dbg->q) : reinterpret_cast<int8_t *>(base + lw.q_off);
-    d.scales = (dbg && dbg->a_scales) ? static_cast<float *>(dbg->a_scales) : reinterpret_cast<float *>(base + lw.s_off);
-    d.blockmax = R > 1 ? reinterpret_cast<unsigned *>(base + lw.bm_off) : nullptr;
-    d.partmax = R > 1 ? reinterpret_cast<unsigned *>(base + lw.bm_off + align_up((size_t)(M / R) * 4, 256)) : nullptr;
-    d.hist = d.partmax;
-    d.scratch_bytes = R > 1 ? workspace_bytes - lw.bm_off - align_up((size_t)(M / R) * 4, 256) : 0;
-    d.M = (int)M;
-    d.K = (int)K;
-    d.R = (int)R;
+    ql::DaqArgs d = daq_args(x, M, K, R, static_cast<unsigned char *>(workspace), workspace_bytes);
+    if (dbg && dbg->q) d.q = static_cast<int8_t *>(dbg->q);
+    if (dbg && dbg->a_scales) d.scales = static_cast<float *>(dbg->a_scales);
     int rc;
     ql::GemmArgs g{};
     g.q = d.q;
@@ -800,19 +811,16 @@ static bool any_order(const ql::GemmArgs *g, size_t n)
     return true;
 }
 
-// The next layers of a plan from `first` on in one go, where their inputs are there already: with one scale per token, their activations
-// are quantized by one launch (each layer's codes in a part of its own of the workspace), then the GEMMs follow in order.  Takes layers as
-// long as no input of one is written by another one before it, their codes fit the workspace that the widest layer needs, and none is
-// small enough to quantize its own rows inside its GEMM.  Returns how many layers it ran: 0 where that is fewer than two
-// quantized ones.
-static size_t plan_run_window(const ql_plan *plan, size_t first, const void *const *x_in, void *const *y_out, int64_t M, void *workspace,
-                              hipStream_t stream, int &rc)
+// The next layers of a plan from `first` on in one go, where their inputs are there already: their activations are quantized by
+// the launches of one layer (each layer's codes, scales and scratch in a part of its own of the workspace), then the GEMMs follow in order.  Takes
+// layers as long as no input of one is written by another one before it, they fit the workspace together, and none is small enough to
+// quantize its own rows inside its GEMM.  Returns how many layers it ran: 0 where that is fewer than two quantized ones.
+static size_t plan_run_window(const ql_plan *plan, size_t first, const void *const *x_in, void *const *y_out, int64_t M, int64_t R,
+                              const ql_daq_params *dp, void *workspace, size_t workspace_bytes, hipStream_t stream, int &rc)
 {
-    const size_t room = layer_ws(M, plan->K_widest, 1).total;
     unsigned char *base = static_cast<unsigned char *>(workspace);
     ql::GemmArgs g[ql::PLAN_WINDOW];
     ql::DaqMany daq{};
-    daq.M = (int)M;
     size_t used = 0, n = 0;
     for (; n < ql::PLAN_WINDOW && first + n < plan->layers.size(); ++n) {
         const size_t l = first + n;
@@ -830,25 +838,31 @@ static size_t plan_run_window(const ql_plan *plan, size_t first, const void *con
         a.M = (int)M;
         a.N = (int)d.N;
         a.K = (int)d.K;
-        a.R = 1;
+        a.R = d.w_bits == 16 ? 1 : (int)R;
         a.w_bits = d.w_bits;
         a.group = d.w_bits == 4 ? (int)d.group : 128;
         if (d.w_bits == 16) {
             a.q = static_cast<const int8_t *>(x_in[l]);
             continue;
         }
-        const LayerWs lw = layer_ws(M, d.K, 1);
-        const ql::DaqItem it = {x_in[l], reinterpret_cast<int8_t *>(base + used + lw.q_off), reinterpret_cast<float *>(base + used + lw.s_off), (int)d.K};
+        const LayerWs lw = layer_ws(M, d.K, R);
+        if (used + lw.total > workspace_bytes) break;
+        ql::DaqArgs it = daq_args(x_in[l], M, d.K, R, base + used, lw.total);
+        if ((dp && robust_args(dp, d.K, R, it) != QL_OK) || !ql::daq_many_takes(it, dp != nullptr)) break;
         a.q = it.q;
         a.s_a = it.scales;
-        a.x = x_in[l];
-        if (used + lw.total > room || !ql::daq_many_takes(it) || ql::qgemm_fuse_takes(a)) break;
-        a.x = nullptr;
+        if (!dp) {
+            ql::GemmArgs f = a;
+            f.x = x_in[l];
+            f.partmax = it.partmax;
+            f.parts = R == 1 ? 0 : (int)ql::daq_parts_per_block(d.K, R);
+            if (ql::qgemm_fuse_takes(f)) break;
+        }
         daq.l[daq.count++] = it;
         used += lw.total;
     }
     if (daq.count < 2) return 0;
-    rc = device_status(ql::launch_daq_many(daq, stream));
+    rc = device_status(dp ? ql::launch_daq_robust_many(daq, stream) : ql::launch_daq_many(daq, stream));
     // GEMMs that share a launch: none of the window's layers may read or write what another one writes
     const ql::GemmArgs *together[ql::PLAN_WINDOW];
     int count = 0;
@@ -881,10 +895,10 @@ static int plan_run_any(const ql_plan *plan, const void *const *x_in, void *cons
             if (rc) return rc;
         }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool windows = R == 1 && !dp && !fusion && g_gemm_variant.load() < 0;
+    const bool windows = !fusion && g_gemm_variant.load() < 0;
     for (size_t l = 0; l < plan->layers.size(); ++l) {
         if (windows) {
-            const size_t ran = plan_run_window(plan, l, x_in, y_out, M, workspace, s, rc);
+            const size_t ran = plan_run_window(plan, l, x_in, y_out, M, R, dp, workspace, workspace_bytes, s, rc);
             if (rc) return rc;
             if (ran) {
                 l += ran - 1;

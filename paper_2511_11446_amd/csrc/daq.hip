@@ -93,49 +93,50 @@ __global__ __launch_bounds__(256) void daq_rows_cached(DaqArgs a, int mode)
     }
 }
 
-// Per-token DAQ of several layers with as many rows each in one launch (a plan whose next inputs are there already): workgroup ids run
+// DAQ of several layers with as many rows each in one launch (a plan whose next inputs are there already): workgroup ids run
 // through the layers, a wavefront takes one row as above.  At M = 2048 a launch of K = 1152 is mostly fill and drain: one
 // HBM round trip, one reduction, one store.  Three layers of K = 1152 in one launch instead of three, us per block of four layers: M =
 // 2048 80.6 -> 73.3, M = 8192 (4-bit MLP) 242 -> 231, M = 16384 357 -> 350.
-template <int CH>
-__device__ __forceinline__ void daq_one_row(const DaqItem &l, int row, int lane)
+template <int CH, bool QUANT>
+__device__ __forceinline__ void daq_one_row(const DaqArgs &l, int row, int lane)
 {
     const uint4 *xr = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(l.x) + (size_t)row * l.K);
     const int nch = l.K >> 3;
     uint4 v[CH];
 #pragma unroll
     for (int i = 0; i < CH; ++i) v[i] = lane + 64 * i < nch ? xr[lane + 64 * i] : make_uint4(0, 0, 0, 0);
-    unsigned m = 0;
+    unsigned bits;
+    if (QUANT) {
+        bits = block_max_bits(l, row / l.R, lane);
+    } else {
+        unsigned m = 0;
 #pragma unroll
-    for (int i = 0; i < CH; ++i) m = absmax_word(absmax_word(absmax_word(absmax_word(m, v[i].x), v[i].y), v[i].z), v[i].w);
-    const float alpha = alpha_from_bits(wave_max_u32((m & 0xffffu) > (m >> 16) ? (m & 0xffffu) : (m >> 16)));
+        for (int i = 0; i < CH; ++i) m = absmax_word(absmax_word(absmax_word(absmax_word(m, v[i].x), v[i].y), v[i].z), v[i].w);
+        bits = wave_max_u32((m & 0xffffu) > (m >> 16) ? (m & 0xffffu) : (m >> 16));
+    }
+    const float alpha = alpha_from_bits(bits);
     const float rcp = 1.0f / alpha;
-    if (lane == 0) l.scales[row] = alpha;
+    if (!QUANT && lane == 0) l.scales[row] = alpha;
+    if (QUANT && lane == 0 && row % l.R == 0) l.scales[row / l.R] = alpha;
     uint2 *qr = reinterpret_cast<uint2 *>(l.q + (size_t)row * l.K);
 #pragma unroll
     for (int i = 0; i < CH; ++i)
         if (lane + 64 * i < nch) qr[lane + 64 * i] = daq_piece(v[i], alpha, rcp);
 }
 
+// QUANT: several rows per scale, second pass, from the end as above
+template <bool QUANT>
 __global__ __launch_bounds__(256) void daq_rows_many(DaqMany b)
 {
-    const int layer = blockIdx.x / b.blocks, lane = threadIdx.x & 63;
-    const int row = (blockIdx.x - layer * b.blocks) * 4 + (threadIdx.x >> 6);
-    if (row >= b.M) return;
-    const DaqItem l = b.l[layer];
-    if (l.K <= 1024) daq_one_row<2>(l, row, lane);
-    else if (l.K <= 1536) daq_one_row<3>(l, row, lane);
-    else if (l.K <= 3072) daq_one_row<6>(l, row, lane);
-    else daq_one_row<9>(l, row, lane);
-}
-
-bool daq_many_takes(const DaqItem &l) { return l.K % 8 == 0 && l.K <= 4608 && (uintptr_t)l.x % 16 == 0 && (uintptr_t)l.q % 8 == 0; }
-
-hipError_t launch_daq_many(DaqMany &b, hipStream_t stream)
-{
-    b.blocks = (b.M + 3) / 4;
-    hipLaunchKernelGGL(daq_rows_many, dim3((unsigned)b.blocks * (unsigned)b.count), dim3(256), 0, stream, b);
-    return hipGetLastError();
+    const int wg = QUANT ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
+    const int layer = wg / b.row_blocks, lane = threadIdx.x & 63;
+    const DaqArgs &l = b.l[layer];
+    const int row = (wg - layer * b.row_blocks) * 4 + (threadIdx.x >> 6);
+    if (row >= l.M) return;
+    if (l.K <= 1024) daq_one_row<2, QUANT>(l, row, lane);
+    else if (l.K <= 1536) daq_one_row<3, QUANT>(l, row, lane);
+    else if (l.K <= 3072) daq_one_row<6, QUANT>(l, row, lane);
+    else daq_one_row<9, QUANT>(l, row, lane);
 }
 
 // Long rows, few of them: the four wavefronts of a workgroup share one, CH pieces per thread, so that four times as many loads are in
@@ -222,11 +223,11 @@ __global__ __launch_bounds__(256) void daq_rows_loop(DaqArgs a, int mode)
 // parts of DAQ_PART_PIECES 16-byte pieces; one workgroup per part leaves the part's maximum in partmax (plain stores:
 // thousands of atomics on a few neighbouring words cost more than the whole pass).
 constexpr int ABSMAX_U = DAQ_PART_PIECES / 256;
-__global__ __launch_bounds__(256) void daq_part_absmax(const uint4 *x, unsigned pieces_per_block, unsigned parts_per_block,
-                                                       unsigned *partmax)
+__device__ __forceinline__ void part_absmax(unsigned block, const uint4 *x, unsigned pieces_per_block, unsigned parts_per_block,
+                                            unsigned *partmax)
 {
     __shared__ unsigned wave_max[4];
-    const unsigned b = blockIdx.x / parts_per_block, part = blockIdx.x - b * parts_per_block;
+    const unsigned b = block / parts_per_block, part = block - b * parts_per_block;
     const uint4 *xb = x + (size_t)b * pieces_per_block;
     const unsigned c0 = part * DAQ_PART_PIECES + threadIdx.x;
     uint4 v[ABSMAX_U];
@@ -250,8 +251,20 @@ __global__ __launch_bounds__(256) void daq_part_absmax(const uint4 *x, unsigned 
     if (threadIdx.x == 0) {
         const unsigned m01 = wave_max[0] > wave_max[1] ? wave_max[0] : wave_max[1];
         const unsigned m23 = wave_max[2] > wave_max[3] ? wave_max[2] : wave_max[3];
-        partmax[blockIdx.x] = m01 > m23 ? m01 : m23;
+        partmax[block] = m01 > m23 ? m01 : m23;
     }
+}
+
+__global__ __launch_bounds__(256) void daq_part_absmax(const uint4 *x, unsigned pieces_per_block, unsigned parts_per_block, unsigned *partmax)
+{
+    part_absmax(blockIdx.x, x, pieces_per_block, parts_per_block, partmax);
+}
+
+__global__ __launch_bounds__(256) void daq_part_absmax_many(DaqMany b)
+{
+    const int i = many_layer(b, blockIdx.x);
+    const DaqArgs &l = b.l[i];
+    part_absmax(blockIdx.x - b.first[i], static_cast<const uint4 *>(l.x), (unsigned)l.R * (unsigned)(l.K >> 3), (unsigned)l.quant_parts, l.partmax);
 }
 
 // one workgroup per scale block: maximum of its partial maxima
@@ -468,6 +481,38 @@ hipError_t launch_daq_part_absmax(const DaqArgs &a, hipStream_t stream)
     const unsigned parts = (unsigned)daq_parts_per_block(a.K, a.R);
     hipLaunchKernelGGL(daq_part_absmax, dim3(parts * (unsigned)(a.M / a.R)), dim3(256), 0, stream, static_cast<const uint4 *>(a.x),
                        (unsigned)((size_t)a.R * a.K / 8), parts, a.partmax);
+    return hipGetLastError();
+}
+
+bool daq_many_takes(const DaqArgs &a, bool robust)
+{
+    if (a.K % 8 != 0 || a.K > 4608 || (uintptr_t)a.x % 16 != 0 || (uintptr_t)a.q % 8 != 0) return false;
+    if (a.R == 1) return true;
+    if (robust) return daq_hist_parts(a.K, a.R) <= DAQ_HIST_FEW && a.scratch_bytes >= daq_hist_bytes(a.M, a.K, a.R);
+    // every wavefront of the quantize pass reduces the partial maxima itself
+    const size_t parts = daq_parts_per_block(a.K, a.R);
+    return parts > 0 && parts <= 256 && parts * (size_t)(a.M / a.R) * 4 <= a.scratch_bytes;
+}
+
+// Several rows per scale: both passes take all layers, the maxima first.  us against a launch per layer and pass, whole plans with their GEMMs:
+// percentile scales, M = 8192, R = 256, width 1152 348 -> 330; other plans with shared scales up to 1.3x.
+hipError_t launch_daq_many(DaqMany &b, hipStream_t stream)
+{
+    const int M = b.l[0].M, R = b.l[0].R;
+    b.row_blocks = (M + 3) / 4;
+    const dim3 rows((unsigned)b.row_blocks * (unsigned)b.count);
+    if (R == 1) {
+        hipLaunchKernelGGL(daq_rows_many<false>, rows, dim3(256), 0, stream, b);
+        return hipGetLastError();
+    }
+    unsigned grid = 0;
+    for (int i = 0; i < b.count; ++i) {
+        b.l[i].quant_parts = (int)daq_parts_per_block(b.l[i].K, R);
+        b.first[i] = grid;
+        grid += (unsigned)b.l[i].quant_parts * (unsigned)(M / R);
+    }
+    hipLaunchKernelGGL(daq_part_absmax_many, dim3(grid), dim3(256), 0, stream, b);
+    hipLaunchKernelGGL(daq_rows_many<true>, rows, dim3(256), 0, stream, b);
     return hipGetLastError();
 }
 

@@ -107,6 +107,14 @@ __device__ __forceinline__ uint2 daq_piece(const uint4 &v, float alpha, float rc
     return out;
 }
 
+// the layer of a launch over several to which a workgroup belongs
+__device__ __forceinline__ int many_layer(const DaqMany &b, unsigned block)
+{
+    int i = 0;
+    while (i + 1 < b.count && block >= b.first[i + 1]) ++i;
+    return i;
+}
+
 __device__ __forceinline__ float alpha_from_bits(unsigned amax_bits)
 {
     float amax = half_bits_to_float(amax_bits);

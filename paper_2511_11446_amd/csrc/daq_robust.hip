@@ -182,10 +182,9 @@ __device__ __forceinline__ unsigned second_selection(const DaqArgs &a, int b, un
 // histogram pass (quant_parts partial histograms, R % 4 == 0: the workgroup's rows share a block).  HIST is a kernel of its own: its LDS
 // and barriers inside the others cost one row per scale 8 % (M = 16384, K = 1152: 18.0 -> 19.6 us)
 template <int CH, bool HIST>
-__global__ __launch_bounds__(256) void daq_rows_robust(DaqArgs a, int mode)
+__device__ __forceinline__ void robust_rows(const DaqArgs &a, int mode, int wg)
 {
     const int lane = threadIdx.x & 63;
-    const int wg = mode == DAQ_QUANT ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
     const int row = wg * 4 + (threadIdx.x >> 6);
     if (row >= a.M) return;   // whole workgroups at a time where the rows share a block
     const int nch = a.K >> 3;
@@ -282,6 +281,25 @@ __global__ __launch_bounds__(256) void daq_rows_robust(DaqArgs a, int mode)
     }
 }
 
+template <int CH, bool HIST>
+__global__ __launch_bounds__(256) void daq_rows_robust(DaqArgs a, int mode)
+{
+    robust_rows<CH, HIST>(a, mode, mode == DAQ_QUANT ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x);
+}
+
+// the rows of several layers
+template <bool HIST>
+__global__ __launch_bounds__(256) void daq_rows_robust_many(DaqMany b, int mode)
+{
+    const int block = mode == DAQ_QUANT ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
+    const int layer = block / b.row_blocks, wg = block - layer * b.row_blocks;
+    const DaqArgs &l = b.l[layer];
+    if (l.K <= 1024) robust_rows<2, HIST>(l, mode, wg);
+    else if (l.K <= 1536) robust_rows<3, HIST>(l, mode, wg);
+    else if (l.K <= 3072) robust_rows<6, HIST>(l, mode, wg);
+    else robust_rows<9, HIST>(l, mode, wg);
+}
+
 // any row length and alignment: the row is re-read from memory (cache) in every counting round
 __global__ __launch_bounds__(256) void daq_rows_robust_loop(DaqArgs a, int mode)
 {
@@ -316,12 +334,13 @@ __global__ __launch_bounds__(256) void daq_rows_robust_loop(DaqArgs a, int mode)
 // The magnitudes of a real activation tensor fall into some thirty of the 256 bins: sixteen copies of the LDS histogram, one
 // per quarter wavefront, keep the lanes of an LDS atomic from queueing for one word.
 template <bool FEW>
-__global__ __launch_bounds__(256) void daq_hist(DaqArgs a, size_t n_per_block, unsigned parts_per_block, int level)
+__device__ __forceinline__ void hist_part(const DaqArgs &a, unsigned block, unsigned parts_per_block, int level, bool self)
 {
     constexpr int COPIES = 16;
     __shared__ unsigned h[COPIES * (HIST_BINS + 1)];
     __shared__ unsigned bins[HIST_BINS];
-    const unsigned b = blockIdx.x / parts_per_block, part = blockIdx.x - b * parts_per_block;
+    const unsigned b = block / parts_per_block, part = block - b * parts_per_block;
+    const size_t n_per_block = (size_t)a.R * a.K;
     const unsigned short *xb = static_cast<const unsigned short *>(a.x) + (size_t)b * n_per_block;
     const size_t i0 = (size_t)part * HIST_PART;
     const size_t i1 = i0 + HIST_PART < n_per_block ? i0 + HIST_PART : n_per_block;
@@ -338,7 +357,7 @@ __global__ __launch_bounds__(256) void daq_hist(DaqArgs a, size_t n_per_block, u
     for (int i = threadIdx.x; i < COPIES * (HIST_BINS + 1); i += 256) h[i] = 0;
     unsigned prefix = 0;
     if (level) {
-        if (FEW && parts_per_block <= DAQ_HIST_SELF) {
+        if (FEW && self) {
             unsigned left;
             first_selection(a, b, (int)parts_per_block, bins, prefix, left);
             if (part == 0 && threadIdx.x == 0) a.blockmax[b] = prefix | left << 8;
@@ -372,11 +391,25 @@ __global__ __launch_bounds__(256) void daq_hist(DaqArgs a, size_t n_per_block, u
     for (int c = 0; c < COPIES; ++c) cnt += h[c * (HIST_BINS + 1) + threadIdx.x];
     if (FEW) {
         unsigned short *h16 = reinterpret_cast<unsigned short *>(a.hist);
-        if (level == 0) h16[(size_t)blockIdx.x * 256 + threadIdx.x] = (unsigned short)cnt;
-        else if (threadIdx.x < 128) h16[(size_t)gridDim.x * 256 + (size_t)blockIdx.x * 128 + threadIdx.x] = (unsigned short)cnt;
+        if (level == 0) h16[(size_t)block * 256 + threadIdx.x] = (unsigned short)cnt;
+        else if (threadIdx.x < 128) h16[(size_t)(a.M / a.R) * parts_per_block * 256 + (size_t)block * 128 + threadIdx.x] = (unsigned short)cnt;
     } else if (cnt && (level == 0 || threadIdx.x < 128)) {
         atomicAdd(a.hist + (size_t)b * DAQ_ROBUST_WORDS + (level ? 258 : 0) + threadIdx.x, cnt);
     }
+}
+
+template <bool FEW>
+__global__ __launch_bounds__(256) void daq_hist(DaqArgs a, unsigned parts_per_block, int level)
+{
+    hist_part<FEW>(a, blockIdx.x, parts_per_block, level, parts_per_block <= DAQ_HIST_SELF);
+}
+
+// the parts of several layers, few per scale block
+template <bool SELF>
+__global__ __launch_bounds__(256) void daq_hist_many(DaqMany b, int level)
+{
+    const int i = many_layer(b, blockIdx.x);
+    hist_part<true>(b.l[i], blockIdx.x - b.first[i], (unsigned)b.l[i].quant_parts, level, SELF);
 }
 
 // many parts: one wavefront per scale block
@@ -397,11 +430,11 @@ __global__ __launch_bounds__(64) void daq_hist_select(DaqArgs a, int level)
 
 // partial histograms whose consumers do not select for themselves: one workgroup per scale block adds them up, four threads
 // per bin, and selects; level 0 leaves blockmax = upper bits | rank left << 8, level 1 the pattern of tau
-__global__ __launch_bounds__(1024) void daq_part_select(DaqArgs a, int parts, int level)
+__device__ __forceinline__ void part_select(const DaqArgs &a, int b, int parts, int level)
 {
     __shared__ unsigned bins[4][HIST_BINS];
-    const int width = level ? 128 : 256, b = blockIdx.x, bin_of = threadIdx.x & 255, q = threadIdx.x >> 8;
-    const unsigned short *h = reinterpret_cast<const unsigned short *>(a.hist) + (level ? (size_t)gridDim.x * parts * 256 : 0) + (size_t)b * parts * width;
+    const int width = level ? 128 : 256, bin_of = threadIdx.x & 255, q = threadIdx.x >> 8;
+    const unsigned short *h = reinterpret_cast<const unsigned short *>(a.hist) + (level ? (size_t)(a.M / a.R) * parts * 256 : 0) + (size_t)b * parts * width;
     unsigned n = 0;
     if (bin_of < width) {
 #pragma unroll 8
@@ -417,6 +450,14 @@ __global__ __launch_bounds__(1024) void daq_part_select(DaqArgs a, int parts, in
     if (level == 0) select_bin<4>(bins[0], left, bin);
     else select_bin<2>(bins[0], left, bin);
     if (threadIdx.x == 0) a.blockmax[b] = level == 0 ? bin | left << 8 : (first & 0xffu) << 7 | bin;
+}
+
+__global__ __launch_bounds__(1024) void daq_part_select(DaqArgs a, int parts, int level) { part_select(a, blockIdx.x, parts, level); }
+
+__global__ __launch_bounds__(1024) void daq_part_select_many(DaqMany b, int level)
+{
+    const int nblk = b.l[0].M / b.l[0].R, layer = blockIdx.x / nblk;
+    part_select(b.l[layer], blockIdx.x - layer * nblk, b.l[layer].quant_parts, level);
 }
 
 __global__ void fill_zero_u32(unsigned *p, size_t n)
@@ -457,7 +498,6 @@ hipError_t launch_daq_robust(const DaqArgs &a, hipStream_t stream)
         return hipGetLastError();
     }
     const int nblk = a.M / a.R;
-    const size_t n = (size_t)a.R * a.K;
     const unsigned parts = (unsigned)daq_hist_parts(a.K, a.R);
     const dim3 grid(parts * (unsigned)nblk);
     if (parts <= DAQ_HIST_FEW && a.scratch_bytes >= daq_hist_bytes(a.M, a.K, a.R)) {
@@ -469,7 +509,7 @@ hipError_t launch_daq_robust(const DaqArgs &a, hipStream_t stream)
         DaqArgs q = a;
         q.quant_parts = self_rows ? (int)parts : 0;
         for (int level = 0; level < 2; ++level) {
-            hipLaunchKernelGGL(daq_hist<true>, grid, dim3(256), 0, stream, a, n, parts, level);
+            hipLaunchKernelGGL(daq_hist<true>, grid, dim3(256), 0, stream, a, parts, level);
             if (level == 0 ? !self : !self_rows) hipLaunchKernelGGL(daq_part_select, dim3(nblk), dim3(1024), 0, stream, a, (int)parts, level);
         }
         run_robust_rows(q, DAQ_QUANT, stream);
@@ -478,10 +518,38 @@ hipError_t launch_daq_robust(const DaqArgs &a, hipStream_t stream)
     const size_t words = (size_t)nblk * DAQ_ROBUST_WORDS;
     hipLaunchKernelGGL(fill_zero_u32, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream, a.hist, words);
     for (int level = 0; level < 2; ++level) {
-        hipLaunchKernelGGL(daq_hist<false>, grid, dim3(256), 0, stream, a, n, parts, level);
+        hipLaunchKernelGGL(daq_hist<false>, grid, dim3(256), 0, stream, a, parts, level);
         hipLaunchKernelGGL(daq_hist_select, dim3(nblk), dim3(64), 0, stream, a, level);
     }
     run_robust_rows(a, DAQ_QUANT, stream);
+    return hipGetLastError();
+}
+
+// The same passes over several layers (daq_many_takes): consumers select for themselves where every layer's would
+hipError_t launch_daq_robust_many(DaqMany &b, hipStream_t stream)
+{
+    const int M = b.l[0].M, R = b.l[0].R, nblk = M / R;
+    b.row_blocks = (M + 3) / 4;
+    const dim3 rows((unsigned)b.row_blocks * (unsigned)b.count);
+    if (R == 1) {
+        hipLaunchKernelGGL(daq_rows_robust_many<false>, rows, dim3(256), 0, stream, b, (int)DAQ_FUSED);
+        return hipGetLastError();
+    }
+    bool self = R % 4 == 0;
+    unsigned grid = 0;
+    for (int i = 0; i < b.count; ++i) {
+        b.l[i].quant_parts = (int)daq_hist_parts(b.l[i].K, R);
+        self = self && b.l[i].quant_parts <= (int)DAQ_HIST_SELF;
+        b.first[i] = grid;
+        grid += (unsigned)b.l[i].quant_parts * (unsigned)nblk;
+    }
+    for (int level = 0; level < 2; ++level) {
+        if (self) hipLaunchKernelGGL(daq_hist_many<true>, dim3(grid), dim3(256), 0, stream, b, level);
+        else hipLaunchKernelGGL(daq_hist_many<false>, dim3(grid), dim3(256), 0, stream, b, level);
+        if (!self) hipLaunchKernelGGL(daq_part_select_many, dim3((unsigned)(nblk * b.count)), dim3(1024), 0, stream, b, level);
+    }
+    if (self) hipLaunchKernelGGL(daq_rows_robust_many<true>, rows, dim3(256), 0, stream, b, (int)DAQ_QUANT);
+    else hipLaunchKernelGGL(daq_rows_robust_many<false>, rows, dim3(256), 0, stream, b, (int)DAQ_QUANT);
     return hipGetLastError();
 }
 

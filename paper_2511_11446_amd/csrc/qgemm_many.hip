@@ -30,7 +30,7 @@ struct ManyLayer {
 };
 struct ManyArgs {
     ManyLayer l[PLAN_WINDOW];
-    int M, tiles_m, group_m;
+    int M, R, tiles_m, group_m;
 };
 
 __global__ __launch_bounds__(256, 2) void qgemm_many(ManyArgs b)
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(256, 2) void qgemm_many(ManyArgs b)
     a.M = b.M;
     a.N = l.N;
     a.K = l.K;
-    a.R = 1;
+    a.R = b.R;
     a.group = l.group;
     const int tiles_n = l.tiles_n, padded = l.padded;
     switch (l.kind) {
@@ -78,7 +78,7 @@ static int many_kind(const GemmArgs &a)
 
 bool qgemm_many_takes(const GemmArgs &a)
 {
-    if (a.w_grouped || a.s_ag || a.acc_out || a.R != 1 || a.act != 0 || a.residual || a.gate || a.row_absmax) return false;
+    if (a.w_grouped || a.s_ag || a.acc_out || a.act != 0 || a.residual || a.gate || a.row_absmax) return false;
     if (a.w_bits == 4) return qgemm_w4_takes(a) && a.K / a.group <= ManyW4::MAX_GROUPS && many_kind(a) != MANY_NONE;
     return (a.w_bits == 8 || a.w_bits == 16) && a.K * (a.w_bits == 16 ? 2 : 1) % 128 == 0 && ((uintptr_t)a.q | (uintptr_t)a.w) % 16 == 0;
 }
@@ -119,10 +119,12 @@ hipError_t launch_qgemm_many(const GemmArgs *const *layers, int count, hipStream
     if (opt_in != hipSuccess) return opt_in;
     ManyArgs b{};
     b.M = layers[0]->M;
+    b.R = 1;
     b.tiles_m = (b.M + ManyW8::BM - 1) / ManyW8::BM;
     b.group_m = pick_group_m(ManyW8::BM);
     int order[PLAN_WINDOW];
     for (int i = 0; i < count; ++i) {
+        if (layers[i]->w_bits != 16) b.R = layers[i]->R;   // one for all quantized layers
         int at = i;
         for (; at > 0 && tile_us(*layers[order[at - 1]]) < tile_us(*layers[i]); --at) order[at] = order[at - 1];
         order[at] = i;

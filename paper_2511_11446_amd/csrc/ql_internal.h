@@ -54,21 +54,18 @@ inline size_t daq_parts_per_block(int64_t K, int64_t R)
 }
 
 hipError_t launch_daq(const DaqArgs &a, hipStream_t stream);
-// per-token DAQ of up to PLAN_WINDOW layers of M rows in one launch; every layer has to pass daq_many_takes
+// DAQ of up to PLAN_WINDOW layers of the same M and R in the launches that one layer takes; every layer has to pass daq_many_takes
 constexpr int PLAN_WINDOW = 8;
-struct DaqItem {
-    const void *x;    // [M,K] fp16
-    int8_t *q;        // [M,K]
-    float *scales;    // [M]
-    int K;
-};
 struct DaqMany {
-    DaqItem l[PLAN_WINDOW];
-    int count, M;
-    int blocks;       // workgroups per layer (launch_daq_many)
+    DaqArgs l[PLAN_WINDOW];
+    int count;
+    // set by the launches: workgroups per layer of the row kernels, and where a layer's workgroups begin in the kernels that cut scale blocks into parts
+    int row_blocks;
+    unsigned first[PLAN_WINDOW];
 };
-bool daq_many_takes(const DaqItem &l);
+bool daq_many_takes(const DaqArgs &a, bool robust);
 hipError_t launch_daq_many(DaqMany &b, hipStream_t stream);
+hipError_t launch_daq_robust_many(DaqMany &b, hipStream_t stream);
 // the first pass alone: partial maxima of every scale block (daq_parts_per_block of them) into a.partmax
 hipError_t launch_daq_part_absmax(const DaqArgs &a, hipStream_t stream);
 // eq. (4) with channel groups: scales [M/R, K/cg]; workspace in blockmax: one maximum per group and slab of

@@ -93,3 +93,54 @@ def test_layers_that_write_the_same_output(ql):
     plan = ql.Plan(layers, M_max=M)
     plan.run(x, [y] * 4, M, 1, ql.workspace(plan.workspace_bytes(M, 1)))
     torch.testing.assert_close(y, _alone(ql, layers[3], x[3]), rtol=0, atol=0)
+
+
+def _alone_shared(ql, l, x, R, p_ppm, a_bits):
+    if l["bits"] == 16:
+        return ql.qlinear_f16(x, l["w"], l["bias"])
+    d = ql.daq_quantize_robust(x, R, p_ppm, a_bits) if p_ppm else ql.daq_quantize(x, R)
+    if l["bits"] == 8:
+        return ql.qgemm_w8a8(d[0], d[1], R, l["w"], l["w_scale"], l["bias"])
+    return ql.qgemm_w4a8(d[0], d[1], R, l["w"], l["w_scale"], l["bias"], group=l["group"])
+
+
+# rows per scale with whole, ragged and many parts per scale block; ranks of the percentile: the maximum, few, many; R = 1 with a percentile
+@pytest.mark.parametrize("M,R,p_ppm,a_bits", [(512, 64, 0, 8), (1530, 255, 0, 8), (4096, 1024, 0, 8), (2048, 2048, 0, 8), (1024, 256, 999000, 8),
+                                              (518, 74, 990000, 6), (2048, 1024, 999900, 6), (770, 1, 999000, 8), (515, 1, 900000, 4),
+                                              (1024, 512, 1000000, 8), (1024, 64, 1, 8)])
+@pytest.mark.parametrize("name", ["block w8", "all kinds", "wide and narrow", "odd inner sizes"])
+@pytest.mark.parametrize("tight", [False, True])
+def test_shared_scales_and_percentiles(ql, name, M, R, p_ppm, a_bits, tight):
+    g = torch.Generator(device="cuda").manual_seed(M)
+    layers = [l for l in (_layer(g, *s) for s in PLANS[name]) if l["bits"] != 16]
+    x = [torch.randn(M, l["K"], device="cuda", generator=g).half() for l in layers]
+    x[0][: R + 1] = 0                               # a scale block of zeros, and a row of the next one
+    x[-1][:, ::7] *= 30.0
+    y = [torch.full((M, l["N"]), float("nan"), dtype=torch.float16, device="cuda") for l in layers]
+    plan = ql.Plan(layers, M_max=M)
+    need = plan.workspace_bytes(M, R)
+    ws = ql.workspace(need if tight else 4 * need)   # with more room more layers go together
+    for _ in range(2):
+        if p_ppm:
+            plan.run_ex(x, y, M, R, ws, p_ppm=p_ppm, a_bits=a_bits)
+        else:
+            plan.run(x, y, M, R, ws)
+    for l, a, b in zip(layers, x, y):
+        torch.testing.assert_close(b, _alone_shared(ql, l, a, R, p_ppm, a_bits), rtol=0, atol=0, equal_nan=True)
+
+
+@pytest.mark.parametrize("p_ppm", [0, 999000])
+def test_chained_layers_with_shared_scales(ql, p_ppm):
+    M, R, w = 1024, 256, 256
+    g = torch.Generator(device="cuda").manual_seed(9)
+    layers = [_layer(g, w, w, b, 64) for b in (8, 4, 8, 4, 8)]
+    t = [(torch.randn(M, w, device="cuda", generator=g) * 0.1).half() for _ in range(6)]
+    flow = [(0, 1), (2, 3), (1, 4), (4, 2), (5, 5)]
+    want = [v.clone() for v in t]
+    for l, (i, o) in zip(layers, flow):
+        want[o].copy_(_alone_shared(ql, l, want[i], R, p_ppm, 8))
+    plan = ql.Plan(layers, M_max=M)
+    ws = ql.workspace(4 * plan.workspace_bytes(M, R))
+    plan.run_ex([t[i] for i, _ in flow], [t[o] for _, o in flow], M, R, ws, p_ppm=p_ppm or None)
+    for a, b in zip(t, want):
+        torch.testing.assert_close(a, b, rtol=0, atol=0, equal_nan=True)

@@ -38,7 +38,8 @@ struct TileW4 {
     // group scales of the tile's columns, [column][group] fp16 as in global memory
     static constexpr int MAX_GROUPS = MAXG_;
     static constexpr int SCALE_OFF = RINGS;
-    static constexpr int LDS_BYTES = RINGS + BN * MAX_GROUPS * 2;
+    static constexpr int ALPHA_OFF = SCALE_OFF + BN * MAX_GROUPS * 2;   // activation scales of the tile's channel groups, fp32
+    static constexpr int LDS_BYTES = ALPHA_OFF + MAX_GROUPS * 4;
     static constexpr int SMAX = SA > SB ? SA : SB;
     // loads that may still be in flight when K step 0 is first read, and at the hand-over from step kt to kt+1
     static constexpr int WAIT_START = (SA - 1) * NA + (SB - 1) * NB;
@@ -105,6 +106,7 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
     const int G = K / (32 * QG);
     const unsigned short *gsw = static_cast<const unsigned short *>(a.s_w);
     unsigned short *sScale = reinterpret_cast<unsigned short *>(smem + T::SCALE_OFF);
+    float *sAlpha = reinterpret_cast<float *>(smem + T::ALPHA_OFF);
 
     // DMA addressing: lane l of a wavefront fills bytes [16 l, 16 l + 16) of a 1024-byte group.  Activations: row l/8,
     // slot l%8, chunk c of row r kept at slot c ^ ((r >> 1) & 7).  Packed weights: row l/4, slot l%4, chunk c of row r
@@ -181,6 +183,8 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
     v16i acc[TM][TN];
     float fsum[TM][TN][16];
     float s16[TN];        // scale / 16 of the group whose partial sums are in acc (the nibbles are used as value * 16)
+    unsigned short raw[TN];   // the same as read: binary16 weight scale, and the channel group's activation scale
+    float alpha_raw = 1.0f;
     int grp_acc, grp_next, qs;   // group in acc (-1: none yet), next group to start, K slice inside the current group
 
     // one tile's partial sums of the finished group -> fp32 sum
@@ -233,19 +237,26 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
             }
         }
     };
-    // bookkeeping of a quarter that opens a group: the scale of the new group is requested from LDS (needed at the next fold)
+    // bookkeeping of a quarter that opens a group: the scales of the new group are requested from LDS and stay as they were read until the
+    // fold that needs them, a group later (converted here, every wavefront waited for LDS, and with channel groups for
+    // memory, between two MFMAs of each group; whole layers, us: M = 4096, K = 1152, N = 3456, channel groups of 128 40.4 -> 37.4; M = 8704, K
+    // = N = 1024, groups of 32 58 -> 48; K = 768, N = 3072, M = 1024, groups of 32 20.4 -> 18.0)
     auto open_group = [&]() {
         grp_acc = grp_next;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) s16[j] = half_to_float_dev(sScale[(wn * TN * 32 + j * 32 + frag_row) * G + grp_next]) * (B8 ? 1.0f : 0.0625f);
-        if (a.s_ag) {
-            // one activation scale per scale block and channel group (eq. (4)): the tile lies inside one scale block
-            // (the dispatcher sends R % BM == 0 only), so the scale is wavefront-uniform and joins the group's weight scale
-            const float alpha_g = a.s_ag[(size_t)(m0 / a.R) * G + grp_next];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) s16[j] *= alpha_g;
-        }
+        for (int j = 0; j < TN; ++j) raw[j] = sScale[(wn * TN * 32 + j * 32 + frag_row) * G + grp_next];
+        if (a.s_ag) alpha_raw = sAlpha[grp_next];
         ++grp_next;
+    };
+    // the scales of the group in acc
+    auto close_group = [&]() {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            s16[j] = half_to_float_dev(raw[j]) * (B8 ? 1.0f : 0.0625f);
+            // one activation scale per scale block and channel group (eq. (4)): the tile lies inside one scale block (the dispatcher sends
+            // R % BM == 0 only), so the scale joins the group's weight scale
+            if (a.s_ag) s16[j] *= alpha_raw;
+        }
     };
 
     // does quarter Q of step S of the period open a weight group?  (compile-time group sizes only)
@@ -271,6 +282,7 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
         } else {
             for (int n = tid % BN, g = tid / BN; g < G; g += NT / BN) sScale[n * G + g] = gsw[(size_t)min(n0 + n, N - 1) * G + g];
         }
+        if (a.s_ag && tid < G) sAlpha[tid] = a.s_ag[(size_t)(m0 / a.R) * G + tid];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -281,7 +293,7 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
                     fsum[i][j][r] = 0.0f;
                 }
 #pragma unroll
-        for (int j = 0; j < TN; ++j) s16[j] = 0.0f;
+        for (int j = 0; j < TN; ++j) raw[j] = 0;
         grp_acc = -1;
         grp_next = 0;
         qs = 0;
@@ -331,10 +343,12 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
             auto step = [&](auto first_tag, const v4i(&afc)[TM], const bfrag_t(&bpc)[TN], auto next_read, auto hand_tag, bool on, int win,
                             int slot_a, int slot_b, int i0) {
                 if constexpr (QGF > 0) {
+                    if (decltype(first_tag)::value) close_group();
                     quarter(first_tag, afc, bpc, next_read, hand_tag, on, win, slot_a, slot_b, i0);
                     if (decltype(first_tag)::value) open_group();
                 } else {
                     const bool restart = qs == 0;
+                    if (restart) close_group();
                     quarter(restart, afc, bpc, next_read, hand_tag, on, win, slot_a, slot_b, i0);
                     if (restart) open_group();
                     qs = qs + 1 == QG ? 0 : qs + 1;
@@ -362,6 +376,7 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
             for (int kt = 0; kt < nk; ++kt) kstep(std::integral_constant<int, 0>{}, kt);
         }
         // the last group's partial sums
+        close_group();
 #pragma unroll
         for (int idx = 0; idx < T::NM; ++idx) fold_tile(idx % TM, idx / TM);
         __syncthreads();

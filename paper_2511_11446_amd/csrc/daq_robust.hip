@@ -333,8 +333,12 @@ __global__ __launch_bounds__(256) void daq_rows_robust_loop(DaqArgs a, int mode)
 // upper bits, [257] rank left, [258..385] level 1.
 // The magnitudes of a real activation tensor fall into some thirty of the 256 bins: sixteen copies of the LDS histogram, one
 // per quarter wavefront, keep the lanes of an LDS atomic from queueing for one word.
-template <bool FEW>
-__device__ __forceinline__ void hist_part(const DaqArgs &a, unsigned block, unsigned parts_per_block, int level, bool self)
+// What bounds a pass over a large tensor is the arithmetic per value, since all parts are resident at once: the level is a template argument,
+// a whole part (all but the last of a block) loads and counts without a condition per piece, and level 1 looks at two
+// values with one branch.  M = 8192, R = 256, us with a branch per load and the level as an argument -> now: three layers of K = 1152 18.7 and 19.1 ->
+// 15.7 and 14.1, K = 4608 23.3 and 17.6 -> 20.1 and 13.3 (level 0 is left with its LDS atomics).
+template <bool FEW, int LEVEL>
+__device__ __forceinline__ void hist_part(const DaqArgs &a, unsigned block, unsigned parts_per_block, bool self)
 {
     constexpr int COPIES = 16;
     __shared__ unsigned h[COPIES * (HIST_BINS + 1)];
@@ -347,16 +351,14 @@ __device__ __forceinline__ void hist_part(const DaqArgs &a, unsigned block, unsi
     const bool vec = ((uintptr_t)(xb + i0) % 16 == 0);
     const size_t pieces = vec ? (i1 - i0) / 8 : 0;
     constexpr int U = HIST_PART / 8 / 256;   // 16-byte pieces per thread
+    const bool whole = pieces == HIST_PART / 8;
     uint4 v[U];
-    const uint4 *xp = reinterpret_cast<const uint4 *>(xb + i0);
+    // zeros past the part's end, without a branch between the loads
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const size_t p = threadIdx.x + 256 * u;
-        if (p < pieces) v[u] = xp[p];
-    }
+    for (int u = 0; u < U; ++u) v[u] = load_row_piece(xb + i0, (int)pieces * 16, threadIdx.x * 16, u * 4096);
     for (int i = threadIdx.x; i < COPIES * (HIST_BINS + 1); i += 256) h[i] = 0;
     unsigned prefix = 0;
-    if (level) {
+    if (LEVEL) {
         if (FEW && self) {
             unsigned left;
             first_selection(a, b, (int)parts_per_block, bins, prefix, left);
@@ -370,18 +372,25 @@ __device__ __forceinline__ void hist_part(const DaqArgs &a, unsigned block, unsi
     __syncthreads();
     unsigned *mine = h + (threadIdx.x >> 4) * (HIST_BINS + 1);
     auto tally = [&](unsigned m) {
-        if (level == 0) atomicAdd(&mine[m >> 7], 1u);
+        if (LEVEL == 0) atomicAdd(&mine[m >> 7], 1u);
         else if ((m >> 7) == prefix) atomicAdd(&mine[m & 127u], 1u);
+    };
+    const unsigned prefix2 = prefix * (128u * 0x00010001u);
+    auto tally2 = [&](unsigned w) {
+        // a half of z is zero where its upper bits are the selected ones; 0x8000 minus it then keeps bit 15
+        const unsigned z = (w ^ prefix2) & 0x7f807f80u;
+        if (LEVEL == 0 || ((0x80008000u - z) & 0x80008000u)) {
+            tally(w & 0x7fffu);
+            tally((w >> 16) & 0x7fffu);
+        }
     };
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        if (threadIdx.x + 256 * (size_t)u < pieces) {
-            const unsigned w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                tally(w[j] & 0x7fffu);
-                tally((w[j] >> 16) & 0x7fffu);
-            }
+        if (whole || threadIdx.x + 256 * (size_t)u < pieces) {
+            tally2(v[u].x);
+            tally2(v[u].y);
+            tally2(v[u].z);
+            tally2(v[u].w);
         }
     }
     for (size_t i = i0 + pieces * 8 + threadIdx.x; i < i1; i += 256) tally(xb[i] & 0x7fffu);
@@ -391,25 +400,40 @@ __device__ __forceinline__ void hist_part(const DaqArgs &a, unsigned block, unsi
     for (int c = 0; c < COPIES; ++c) cnt += h[c * (HIST_BINS + 1) + threadIdx.x];
     if (FEW) {
         unsigned short *h16 = reinterpret_cast<unsigned short *>(a.hist);
-        if (level == 0) h16[(size_t)block * 256 + threadIdx.x] = (unsigned short)cnt;
+        if (LEVEL == 0) h16[(size_t)block * 256 + threadIdx.x] = (unsigned short)cnt;
         else if (threadIdx.x < 128) h16[(size_t)(a.M / a.R) * parts_per_block * 256 + (size_t)block * 128 + threadIdx.x] = (unsigned short)cnt;
-    } else if (cnt && (level == 0 || threadIdx.x < 128)) {
-        atomicAdd(a.hist + (size_t)b * DAQ_ROBUST_WORDS + (level ? 258 : 0) + threadIdx.x, cnt);
+    } else if (cnt && (LEVEL == 0 || threadIdx.x < 128)) {
+        atomicAdd(a.hist + (size_t)b * DAQ_ROBUST_WORDS + (LEVEL ? 258 : 0) + threadIdx.x, cnt);
     }
 }
 
-template <bool FEW>
-__global__ __launch_bounds__(256) void daq_hist(DaqArgs a, unsigned parts_per_block, int level)
+template <bool FEW, int LEVEL>
+__global__ __launch_bounds__(256) void daq_hist(DaqArgs a, unsigned parts_per_block)
 {
-    hist_part<FEW>(a, blockIdx.x, parts_per_block, level, parts_per_block <= DAQ_HIST_SELF);
+    hist_part<FEW, LEVEL>(a, blockIdx.x, parts_per_block, parts_per_block <= DAQ_HIST_SELF);
 }
 
 // the parts of several layers, few per scale block
-template <bool SELF>
-__global__ __launch_bounds__(256) void daq_hist_many(DaqMany b, int level)
+template <bool SELF, int LEVEL>
+__global__ __launch_bounds__(256) void daq_hist_many(DaqMany b)
 {
     const int i = many_layer(b, blockIdx.x);
-    hist_part<true>(b.l[i], blockIdx.x - b.first[i], (unsigned)b.l[i].quant_parts, level, SELF);
+    hist_part<true, LEVEL>(b.l[i], blockIdx.x - b.first[i], (unsigned)b.l[i].quant_parts, SELF);
+}
+
+template <bool FEW>
+static void run_hist(const DaqArgs &a, unsigned parts, int level, hipStream_t s)
+{
+    const dim3 grid(parts * (unsigned)(a.M / a.R));
+    if (level == 0) hipLaunchKernelGGL((daq_hist<FEW, 0>), grid, dim3(256), 0, s, a, parts);
+    else hipLaunchKernelGGL((daq_hist<FEW, 1>), grid, dim3(256), 0, s, a, parts);
+}
+
+template <bool SELF>
+static void run_hist_many(const DaqMany &b, unsigned grid, int level, hipStream_t s)
+{
+    if (level == 0) hipLaunchKernelGGL((daq_hist_many<SELF, 0>), dim3(grid), dim3(256), 0, s, b);
+    else hipLaunchKernelGGL((daq_hist_many<SELF, 1>), dim3(grid), dim3(256), 0, s, b);
 }
 
 // many parts: one wavefront per scale block
@@ -499,7 +523,6 @@ hipError_t launch_daq_robust(const DaqArgs &a, hipStream_t stream)
     }
     const int nblk = a.M / a.R;
     const unsigned parts = (unsigned)daq_hist_parts(a.K, a.R);
-    const dim3 grid(parts * (unsigned)nblk);
     if (parts <= DAQ_HIST_FEW && a.scratch_bytes >= daq_hist_bytes(a.M, a.K, a.R)) {
         // few parts: every consumer adds them up and selects for itself; more: a selection launch in between (M = 8192, R = 256, K =
         // 4608, 72 parts: 57 us against 77 with twice the part size and no selection launches)
@@ -509,7 +532,7 @@ hipError_t launch_daq_robust(const DaqArgs &a, hipStream_t stream)
         DaqArgs q = a;
         q.quant_parts = self_rows ? (int)parts : 0;
         for (int level = 0; level < 2; ++level) {
-            hipLaunchKernelGGL(daq_hist<true>, grid, dim3(256), 0, stream, a, parts, level);
+            run_hist<true>(a, parts, level, stream);
             if (level == 0 ? !self : !self_rows) hipLaunchKernelGGL(daq_part_select, dim3(nblk), dim3(1024), 0, stream, a, (int)parts, level);
         }
         run_robust_rows(q, DAQ_QUANT, stream);
@@ -518,7 +541,7 @@ hipError_t launch_daq_robust(const DaqArgs &a, hipStream_t stream)
     const size_t words = (size_t)nblk * DAQ_ROBUST_WORDS;
     hipLaunchKernelGGL(fill_zero_u32, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream, a.hist, words);
     for (int level = 0; level < 2; ++level) {
-        hipLaunchKernelGGL(daq_hist<false>, grid, dim3(256), 0, stream, a, parts, level);
+        run_hist<false>(a, parts, level, stream);
         hipLaunchKernelGGL(daq_hist_select, dim3(nblk), dim3(64), 0, stream, a, level);
     }
     run_robust_rows(a, DAQ_QUANT, stream);
@@ -544,8 +567,8 @@ hipError_t launch_daq_robust_many(DaqMany &b, hipStream_t stream)
         grid += (unsigned)b.l[i].quant_parts * (unsigned)nblk;
     }
     for (int level = 0; level < 2; ++level) {
-        if (self) hipLaunchKernelGGL(daq_hist_many<true>, dim3(grid), dim3(256), 0, stream, b, level);
-        else hipLaunchKernelGGL(daq_hist_many<false>, dim3(grid), dim3(256), 0, stream, b, level);
+        if (self) run_hist_many<true>(b, grid, level, stream);
+        else run_hist_many<false>(b, grid, level, stream);
         if (!self) hipLaunchKernelGGL(daq_part_select_many, dim3((unsigned)(nblk * b.count)), dim3(1024), 0, stream, b, level);
     }
     if (self) hipLaunchKernelGGL(daq_rows_robust_many<true>, rows, dim3(256), 0, stream, b, (int)DAQ_QUANT);

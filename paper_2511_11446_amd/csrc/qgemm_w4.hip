@@ -106,10 +106,16 @@ hipError_t launch_qgemm_w4_128(const GemmArgs &a, hipStream_t stream)
 // bytes.  The line was drawn on packed 4-bit layers: 64x64 up to 1024 tiles, up to about twice as many where K is short, and wherever more
 // than 40 groups leave the large tiles one workgroup per CU.  M = 2048, K = 4608, N = 1152, group 128: 28 against 34 us; M = 8192: 80
 // against 74; group 32: 134 against 198.
+// Int8 codes leave three small workgroups per CU instead of four: where those take more than two rounds (of 768) and the large tiles one (of
+// 512), the large ones.  K = 1152, us, 64x64 -> 128x128: M = 2048, N = 3456 29.0 -> 24.1 (groups of 32 37.4 -> 35.4), M = 1536, N = 4608 29.6
+// -> 24.6; but two rounds against one, M = 4096, N = 1152 26.6 -> 25.7 (groups of 32 33.5 -> 37.0), and three against two, M = 2048, N = 4608
+// 34.0 -> 34.5.
 hipError_t launch_qgemm_w4(const GemmArgs &a, hipStream_t stream)
 {
     const long long tiles = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64);
-    const bool small = a.K / a.group > 40 || tiles <= 1024 || (a.K <= 1536 && tiles <= 2304);
+    const long long large_tiles = (long long)((a.M + 127) / 128) * ((a.N + 127) / 128);
+    const bool one_round = a.w_grouped && tiles > 2 * 768 && large_tiles <= 512;
+    const bool small = a.K / a.group > 40 || tiles <= 1024 || (a.K <= 1536 && tiles <= 2304 && !one_round);
     return small ? launch_qgemm_w4_64(a, stream) : launch_qgemm_w4_128(a, stream);
 }
 

@@ -54,11 +54,11 @@ def test_channel_groups(ql, M, R, K, group):
     _check(v, amax, q.reshape(-1), scales.reshape(-1))
 
 
-# whole layers with channel scales on the pipelined tiles: few groups, as many as the small table holds, one more, and the most
-@pytest.mark.parametrize("K,group", [(128, 128), (1152, 288), (1280, 32), (1408, 32), (4608, 32), (768, 96)])
+# whole layers with channel scales on the pipelined tiles: few groups, as many as the small table holds, one more, and the most; a width at
+# which 2048 rows take the large tiles in one round
+@pytest.mark.parametrize("K,group,N", [(128, 128, 648), (1152, 288, 648), (1280, 32, 648), (1408, 32, 648), (4608, 32, 648), (768, 96, 648), (1152, 128, 3400)])
 @pytest.mark.parametrize("M,R", [(256, 64), (2048, 256), (4096, 2048)])
-def test_layers_with_channel_scales(ql, M, R, K, group):
-    N = 648
+def test_layers_with_channel_scales(ql, M, R, K, group, N):
     g = torch.Generator(device="cuda").manual_seed(K + M)
     x = torch.randn(M, K, device="cuda", generator=g).half()
     w = torch.randint(-32, 32, (N, K), dtype=torch.int8, device="cuda", generator=g)

@@ -294,6 +294,8 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
                 }
 #pragma unroll
         for (int j = 0; j < TN; ++j) raw[j] = 0;
+        // the first fold of a tile multiplies its empty sums by these: a scale left by the tile before, infinite or NaN, would make them NaN
+        alpha_raw = 1.0f;
         grp_acc = -1;
         grp_next = 0;
         qs = 0;

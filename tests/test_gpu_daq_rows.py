@@ -76,3 +76,27 @@ def test_layers_with_channel_scales(ql, M, R, K, group, N):
     # every group adds one rounding of its scale product and one of the running sum; then one rounding to fp16
     bound = (K // group + 3) * 2.0 ** -23 * scale + want.abs() * 2.0 ** -11 + 2.0 ** -24
     assert bool(((y.double() - want).abs() <= bound).all())
+
+
+# An infinite or NaN input stays inside its scale block.  More tiles than workgroups are resident, so that a workgroup walks from a tile of one
+# block to one of another: 128x128 tiles (512 resident) and 64x64 ones (768 with int8 codes, 1024 with packed ones)
+@pytest.mark.parametrize("M,K,N,R,storage", [(16384, 1152, 1152, 256, 8), (16384, 768, 2304, 1024, 4), (832, 1152, 4992, 64, 8), (3200, 768, 2560, 64, 4)])
+@pytest.mark.parametrize("group", [32, 96, 128])
+def test_channel_scales_of_one_block_reach_no_other(ql, M, K, N, R, storage, group):
+    g = torch.Generator(device="cuda").manual_seed(K + group)
+    x = torch.randn(M, K, device="cuda", generator=g).half()
+    w = torch.randint(-8, 8, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    if storage == 4:
+        w = torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, device="cuda", generator=g)
+    s = (torch.rand(N, K // group, device="cuda", generator=g) * 0.02 + 0.001).half()
+    clean = ql.qlinear_grouped(x, R, w, s, group, act_group=group, storage=storage)
+    assert bool(clean.isfinite().all())
+    # every third block: a walk goes on a power of two of rows further down
+    bad = x.clone().reshape(M // R, R, K)
+    bad[::6, R - 1, K - 1] = float("inf")
+    bad[3::6, 0, K - group] = float("nan")
+    y = ql.qlinear_grouped(bad.reshape(M, K), R, w, s, group, act_group=group, storage=storage).reshape(M // R, R, N)
+    assert not bool(y[::3].isfinite().all())
+    clean = clean.reshape(M // R, R, N)
+    for i in (1, 2):
+        torch.testing.assert_close(y[i::3], clean[i::3], rtol=0, atol=0)

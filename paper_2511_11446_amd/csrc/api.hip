@@ -813,8 +813,8 @@ static bool any_order(const ql::GemmArgs *g, size_t n)
 
 // The next layers of a plan from `first` on in one go, where their inputs are there already: their activations are quantized by
 // the launches of one layer (each layer's codes, scales and scratch in a part of its own of the workspace), then the GEMMs follow in order.  Takes
-// layers as long as no input of one is written by another one before it, they fit the workspace together, and none is small enough to
-// quantize its own rows inside its GEMM.  Returns how many layers it ran: 0 where that is fewer than two quantized ones.
+// layers as long as no input of one is written by another one before it, they fit the workspace and the size of a launch together, and none
+// is small enough to quantize its own rows inside its GEMM.  Returns how many layers it ran: 0 where that is fewer than two quantized ones.
 static size_t plan_run_window(const ql_plan *plan, size_t first, const void *const *x_in, void *const *y_out, int64_t M, int64_t R,
                               const ql_daq_params *dp, void *workspace, size_t workspace_bytes, hipStream_t stream, int &rc)
 {
@@ -859,6 +859,10 @@ static size_t plan_run_window(const ql_plan *plan, size_t first, const void *con
             if (ql::qgemm_fuse_takes(f)) break;
         }
         daq.l[daq.count++] = it;
+        if (!ql::daq_many_fits(daq, dp != nullptr)) {
+            --daq.count;
+            break;
+        }
         used += lw.total;
     }
     if (daq.count < 2) return 0;

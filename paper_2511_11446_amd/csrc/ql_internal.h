@@ -54,7 +54,7 @@ inline size_t daq_parts_per_block(int64_t K, int64_t R)
 }
 
 hipError_t launch_daq(const DaqArgs &a, hipStream_t stream);
-// DAQ of up to PLAN_WINDOW layers of the same M and R in the launches that one layer takes; every layer has to pass daq_many_takes
+// DAQ of up to PLAN_WINDOW layers of the same M and R in the launches that one layer takes; every layer has to pass daq_many_takes, all together daq_many_fits
 constexpr int PLAN_WINDOW = 8;
 struct DaqMany {
     DaqArgs l[PLAN_WINDOW];
@@ -64,6 +64,8 @@ struct DaqMany {
     unsigned first[PLAN_WINDOW];
 };
 bool daq_many_takes(const DaqArgs &a, bool robust);
+// do the launches over these layers stay within the size of a launch?
+bool daq_many_fits(const DaqMany &b, bool robust);
 hipError_t launch_daq_many(DaqMany &b, hipStream_t stream);
 hipError_t launch_daq_robust_many(DaqMany &b, hipStream_t stream);
 // the first pass alone: partial maxima of every scale block (daq_parts_per_block of them) into a.partmax

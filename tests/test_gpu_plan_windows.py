@@ -144,3 +144,21 @@ def test_chained_layers_with_shared_scales(ql, p_ppm):
     plan.run_ex([t[i] for i, _ in flow], [t[o] for _, o in flow], M, R, ws, p_ppm=p_ppm or None)
     for a, b in zip(t, want):
         torch.testing.assert_close(a, b, rtol=0, atol=0, equal_nan=True)
+
+
+# so many rows that eight layers together need more threads than a launch holds: one row per scale in the row pass, and a percentile of two rows in
+# the selection
+@pytest.mark.parametrize("M,R,p_ppm", [(2 ** 23, 1, 0), (2 ** 23 - 4, 1, 0), (2 ** 20, 2, 750000)])
+def test_many_rows(ql, M, R, p_ppm):
+    g = torch.Generator(device="cuda").manual_seed(7)
+    layers = [_layer(g, 8, 8, 8, 0) for _ in range(8)]
+    x = torch.randn(M, 8, device="cuda", generator=g).half()
+    y = [torch.full((M, 8), float("nan"), dtype=torch.float16, device="cuda") for _ in layers]
+    plan = ql.Plan(layers, M_max=M)
+    ws = ql.workspace(len(layers) * plan.workspace_bytes(M, R))
+    if p_ppm:
+        plan.run_ex([x] * 8, y, M, R, ws, p_ppm=p_ppm)
+    else:
+        plan.run([x] * 8, y, M, R, ws)
+    for l, b in zip(layers, y):
+        torch.testing.assert_close(b, _alone_shared(ql, l, x, R, p_ppm, 8), rtol=0, atol=0)

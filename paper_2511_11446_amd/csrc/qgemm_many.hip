@@ -54,11 +54,11 @@ __global__ __launch_bounds__(256, 2) void qgemm_many(ManyArgs b)
     switch (l.kind) {
     case MANY_W8: qgemm_dma_tiles<ManyW8, false>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
     case MANY_F16: qgemm_dma_tiles<ManyF16, false>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
-    case MANY_W4_1: qgemm_w4_tiles<ManyW4, 1, false, false, true>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
-    case MANY_W4_2: qgemm_w4_tiles<ManyW4, 2, false, false, true>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
-    case MANY_W4_4: qgemm_w4_tiles<ManyW4, 4, false, false, true>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
-    case MANY_W4_6: qgemm_w4_tiles<ManyW4, 6, false, false, true>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
-    default: qgemm_w4_tiles<ManyW4, 9, false, false, true>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
+    case MANY_W4_1: qgemm_w4_tiles<ManyW4, 1, false, false, Channel::no, true>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
+    case MANY_W4_2: qgemm_w4_tiles<ManyW4, 2, false, false, Channel::no, true>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
+    case MANY_W4_4: qgemm_w4_tiles<ManyW4, 4, false, false, Channel::no, true>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
+    case MANY_W4_6: qgemm_w4_tiles<ManyW4, 6, false, false, Channel::no, true>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
+    default: qgemm_w4_tiles<ManyW4, 9, false, false, Channel::no, true>(a, block, padded, b.tiles_m, tiles_n, padded, b.group_m); break;
     }
 }
 

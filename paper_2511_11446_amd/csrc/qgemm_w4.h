@@ -60,6 +60,10 @@ __device__ __forceinline__ v4i unpack_w4(v2i p)
                (int)(((unsigned)p[1] << 4) & 0xf0f0f0f0u), (int)((unsigned)p[1] & 0xf0f0f0f0u)};
 }
 
+// What a kernel knows of its layer's channel-group activation scales.  Asked at every group, packed layers without them take 2 to 5 % longer, and layers
+// with them on 64x64 tiles up to 6 %; so most kernels know.
+enum class Channel { no, yes, ask };
+
 template <class F, int... S>
 __device__ __forceinline__ void unrolled_steps(F &f, int kt, std::integer_sequence<int, S...>)
 {
@@ -70,8 +74,9 @@ __device__ __forceinline__ void unrolled_steps(F &f, int kt, std::integer_sequen
 // that open a group are then known statically over a period of lcm(QGF, 4) slices, which is unrolled; 0 = read from the
 // arguments, one uniform branch per MFMA
 // EXPORT: the int32 group partial sums are also written to a.acc_out
+// CHANNEL: whether the layer has channel-group activation scales
 // One workgroup's part: workgroup `block` of `blocks` (a multiple of XCDS) that share the layer; ONE: as many as there are tiles
-template <class T, int QGF, bool EXPORT, bool GLUE, bool ONE = false>
+template <class T, int QGF, bool EXPORT, bool GLUE, Channel CHANNEL, bool ONE = false>
 __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int blocks, int tiles_m, int tiles_n, int nblk_padded, int group_m)
 {
     constexpr int TM = T::TM, TN = T::TN, BM = T::BM, BN = T::BN, NT = T::NT, NW = T::NW;
@@ -107,6 +112,7 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
     const unsigned short *gsw = static_cast<const unsigned short *>(a.s_w);
     unsigned short *sScale = reinterpret_cast<unsigned short *>(smem + T::SCALE_OFF);
     float *sAlpha = reinterpret_cast<float *>(smem + T::ALPHA_OFF);
+    const bool channel = CHANNEL == Channel::yes || (CHANNEL == Channel::ask && a.s_ag != nullptr);
 
     // DMA addressing: lane l of a wavefront fills bytes [16 l, 16 l + 16) of a 1024-byte group.  Activations: row l/8,
     // slot l%8, chunk c of row r kept at slot c ^ ((r >> 1) & 7).  Packed weights: row l/4, slot l%4, chunk c of row r
@@ -183,8 +189,6 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
     v16i acc[TM][TN];
     float fsum[TM][TN][16];
     float s16[TN];        // scale / 16 of the group whose partial sums are in acc (the nibbles are used as value * 16)
-    unsigned short raw[TN];   // the same as read: binary16 weight scale, and the channel group's activation scale
-    float alpha_raw = 1.0f;
     int grp_acc, grp_next, qs;   // group in acc (-1: none yet), next group to start, K slice inside the current group
 
     // one tile's partial sums of the finished group -> fp32 sum
@@ -237,26 +241,22 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
             }
         }
     };
-    // bookkeeping of a quarter that opens a group: the scales of the new group are requested from LDS and stay as they were read until the
-    // fold that needs them, a group later (converted here, every wavefront waited for LDS, and with channel groups for
-    // memory, between two MFMAs of each group; whole layers, us: M = 4096, K = 1152, N = 3456, channel groups of 128 40.4 -> 37.4; M = 8704, K
-    // = N = 1024, groups of 32 58 -> 48; K = 768, N = 3072, M = 1024, groups of 32 20.4 -> 18.0)
+    // Bookkeeping of a quarter that opens a group: the scales of the new group from LDS, for the next fold.  The channel groups' activation scales lie
+    // there too: read from memory here they held up every group (whole layers, us: M = 4096, K = 1152, N = 3456, groups of 128 43.1 -> 39.4, of 32 69.2 ->
+    // 58.1; M = 2048, N = 1152, groups of 32 30.6 -> 21.7).  Converted only at the fold, out of registers that keep them as they were read, they
+    // cost the 128x128 tiles 1 to 5 % (M = 8192, N = 4608, packed, groups of 32 106 -> 112): more registers are spilled.
     auto open_group = [&]() {
         grp_acc = grp_next;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) raw[j] = sScale[(wn * TN * 32 + j * 32 + frag_row) * G + grp_next];
-        if (a.s_ag) alpha_raw = sAlpha[grp_next];
-        ++grp_next;
-    };
-    // the scales of the group in acc
-    auto close_group = [&]() {
+        for (int j = 0; j < TN; ++j) s16[j] = half_to_float_dev(sScale[(wn * TN * 32 + j * 32 + frag_row) * G + grp_next]) * (B8 ? 1.0f : 0.0625f);
+        if (channel) {
+            // one activation scale per scale block and channel group (eq. (4)): the tile lies inside one scale block
+            // (the dispatcher sends R % BM == 0 only), so the scale joins the group's weight scale
+            const float alpha_g = sAlpha[grp_next];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            s16[j] = half_to_float_dev(raw[j]) * (B8 ? 1.0f : 0.0625f);
-            // one activation scale per scale block and channel group (eq. (4)): the tile lies inside one scale block (the dispatcher sends
-            // R % BM == 0 only), so the scale joins the group's weight scale
-            if (a.s_ag) s16[j] *= alpha_raw;
+            for (int j = 0; j < TN; ++j) s16[j] *= alpha_g;
         }
+        ++grp_next;
     };
 
     // does quarter Q of step S of the period open a weight group?  (compile-time group sizes only)
@@ -268,7 +268,7 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
     issue_step0();
     for (;;) {   // one pass per tile
         // ---- per tile: row scale of one tile row per thread, bias of this lane's columns, group scales of the tile's columns
-        sa_pre = (tid < BM && !a.s_ag) ? a.s_a[min(m0 + tid, M - 1) / a.R] : 1.0f;
+        sa_pre = (tid < BM && !channel) ? a.s_a[min(m0 + tid, M - 1) / a.R] : 1.0f;
         {
             const unsigned short *bias_h = static_cast<const unsigned short *>(a.bias);
 #pragma unroll
@@ -282,7 +282,7 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
         } else {
             for (int n = tid % BN, g = tid / BN; g < G; g += NT / BN) sScale[n * G + g] = gsw[(size_t)min(n0 + n, N - 1) * G + g];
         }
-        if (a.s_ag && tid < G) sAlpha[tid] = a.s_ag[(size_t)(m0 / a.R) * G + tid];
+        if (channel && tid < G) sAlpha[tid] = a.s_ag[(size_t)(m0 / a.R) * G + tid];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -293,9 +293,7 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
                     fsum[i][j][r] = 0.0f;
                 }
 #pragma unroll
-        for (int j = 0; j < TN; ++j) raw[j] = 0;
-        // the first fold of a tile multiplies its empty sums by these: a scale left by the tile before, infinite or NaN, would make them NaN
-        alpha_raw = 1.0f;
+        for (int j = 0; j < TN; ++j) s16[j] = 0.0f;   // the first fold: a scale left by the tile before, infinite or NaN, would make its empty sums NaN
         grp_acc = -1;
         grp_next = 0;
         qs = 0;
@@ -345,12 +343,10 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
             auto step = [&](auto first_tag, const v4i(&afc)[TM], const bfrag_t(&bpc)[TN], auto next_read, auto hand_tag, bool on, int win,
                             int slot_a, int slot_b, int i0) {
                 if constexpr (QGF > 0) {
-                    if (decltype(first_tag)::value) close_group();
                     quarter(first_tag, afc, bpc, next_read, hand_tag, on, win, slot_a, slot_b, i0);
                     if (decltype(first_tag)::value) open_group();
                 } else {
                     const bool restart = qs == 0;
-                    if (restart) close_group();
                     quarter(restart, afc, bpc, next_read, hand_tag, on, win, slot_a, slot_b, i0);
                     if (restart) open_group();
                     qs = qs + 1 == QG ? 0 : qs + 1;
@@ -378,7 +374,6 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
             for (int kt = 0; kt < nk; ++kt) kstep(std::integral_constant<int, 0>{}, kt);
         }
         // the last group's partial sums
-        close_group();
 #pragma unroll
         for (int idx = 0; idx < T::NM; ++idx) fold_tile(idx % TM, idx / TM);
         __syncthreads();

@@ -22,16 +22,16 @@
 
 namespace ql {
 
-template <class T, int QGF, bool EXPORT, bool GLUE>
+template <class T, int QGF, bool EXPORT, bool GLUE, Channel CHANNEL>
 __global__ __launch_bounds__(T::NT, T::WPS) void qgemm_w4(GemmArgs a, int tiles_m, int tiles_n, int nblk_padded, int group_m)
 {
-    qgemm_w4_tiles<T, QGF, EXPORT, GLUE>(a, blockIdx.x, gridDim.x, tiles_m, tiles_n, nblk_padded, group_m);
+    qgemm_w4_tiles<T, QGF, EXPORT, GLUE, CHANNEL>(a, blockIdx.x, gridDim.x, tiles_m, tiles_n, nblk_padded, group_m);
 }
 
-template <class T, int QGF, bool EXPORT, bool GLUE>
+template <class T, int QGF, bool EXPORT, bool GLUE, Channel CHANNEL>
 static hipError_t run_w4(const GemmArgs &a, hipStream_t s)
 {
-    static const hipError_t lds_opt_in = hipFuncSetAttribute(reinterpret_cast<const void *>(&qgemm_w4<T, QGF, EXPORT, GLUE>),
+    static const hipError_t lds_opt_in = hipFuncSetAttribute(reinterpret_cast<const void *>(&qgemm_w4<T, QGF, EXPORT, GLUE, CHANNEL>),
                                                               hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
     if (lds_opt_in != hipSuccess) return lds_opt_in;
     const int tiles_m = (a.M + T::BM - 1) / T::BM, tiles_n = (a.N + T::BN - 1) / T::BN;
@@ -47,7 +47,7 @@ static hipError_t run_w4(const GemmArgs &a, hipStream_t s)
     }();
     if (resident <= 0) return hipErrorInvalidDevice;
     const int grid = padded < resident ? padded : resident;
-    hipLaunchKernelGGL((qgemm_w4<T, QGF, EXPORT, GLUE>), dim3(grid), dim3(T::NT), T::LDS_BYTES, s, a, tiles_m, tiles_n, padded,
+    hipLaunchKernelGGL((qgemm_w4<T, QGF, EXPORT, GLUE, CHANNEL>), dim3(grid), dim3(T::NT), T::LDS_BYTES, s, a, tiles_m, tiles_n, padded,
                        pick_group_m(T::BM));
     return hipGetLastError();
 }
@@ -62,28 +62,37 @@ bool qgemm_w4_takes(const GemmArgs &a)
     return a.w_grouped ? a.w_bits == 8 && a.K / a.group <= W4_MANY_GROUPS : a.w_bits == 4 && a.K / a.group <= W4_MANY_GROUPS;
 }
 
+// the group set of Algorithm 1 (32, 64, 128, 192, 288) with the restart pattern unrolled, when K holds whole periods of it
+template <class T, bool MANY, Channel CHANNEL>
+static hipError_t run_w4_group(const GemmArgs &a, hipStream_t stream)
+{
+    const int nk = a.K / 128;
+    if (a.group == 32) return run_w4<T, 1, false, false, CHANNEL>(a, stream);
+    if (a.group == 64) return run_w4<T, 2, false, false, CHANNEL>(a, stream);
+    if constexpr (!MANY) {                                       // larger groups number more than 40 only beyond K = 5120
+        if (a.group == 128) return run_w4<T, 4, false, false, CHANNEL>(a, stream);
+        if (a.group == 192 && nk % 3 == 0) return run_w4<T, 6, false, false, CHANNEL>(a, stream);
+        if (a.group == 288 && nk % 9 == 0) return run_w4<T, 9, false, false, CHANNEL>(a, stream);
+    }
+    return run_w4<T, 0, false, false, CHANNEL>(a, stream);
+}
+
 template <int T, bool B8, bool MANY>
 static hipError_t run_w4_tile(const GemmArgs &a, hipStream_t stream)
 {
     // int8 codes on 128x128 tiles: a third activation stage would leave one workgroup per CU
     using TT = TileW4<2, B8 && T == 2 ? 2 : 3, 2, B8, MANY ? W4_MANY_GROUPS : 40, T>;
     const bool glue = a.act != 0 || a.residual != nullptr || a.gate != nullptr || a.row_absmax != nullptr;
-    if (a.acc_out) return run_w4<TT, 0, true, !B8>(a, stream);   // verification: group partial sums exported
+    if (a.acc_out) return run_w4<TT, 0, true, !B8, Channel::ask>(a, stream);   // verification: group partial sums exported
     if constexpr (B8) {
-        if (glue) return hipErrorInvalidValue;                   // no call asks for glue on int8-held codes
+        if (glue) return hipErrorInvalidValue;                                 // no call asks for glue on int8-held codes
     } else {
-        if (glue) return a.group == 128 ? run_w4<TT, 4, false, true>(a, stream) : run_w4<TT, 0, false, true>(a, stream);
+        if (glue) return a.group == 128 ? run_w4<TT, 4, false, true, Channel::no>(a, stream) : run_w4<TT, 0, false, true, Channel::no>(a, stream);
     }
-    // the group set of Algorithm 1 (32, 64, 128, 192, 288) with the restart pattern unrolled, when K holds whole periods of it
-    const int nk = a.K / 128;
-    if (a.group == 32) return run_w4<TT, 1, false, false>(a, stream);
-    if (a.group == 64) return run_w4<TT, 2, false, false>(a, stream);
-    if constexpr (!MANY) {                                       // larger groups number more than 40 only beyond K = 5120
-        if (a.group == 128) return run_w4<TT, 4, false, false>(a, stream);
-        if (a.group == 192 && nk % 3 == 0) return run_w4<TT, 6, false, false>(a, stream);
-        if (a.group == 288 && nk % 9 == 0) return run_w4<TT, 9, false, false>(a, stream);
-    }
-    return run_w4<TT, 0, false, false>(a, stream);
+    if (a.s_ag) return run_w4_group<TT, MANY, Channel::yes>(a, stream);
+    // int8 codes without them on 128x128 tiles keep the question: where it is left out the compiler spills 18 registers instead of 8 with groups of 32
+    // (7 % slower in the mean of 18 shapes) and 8 instead of 2 with groups of 64 (1.5 %); on 64x64 tiles leaving it out gains 1 to 3 %
+    return run_w4_group<TT, MANY, B8 && T == 2 ? Channel::ask : Channel::no>(a, stream);
 }
 
 template <int T>

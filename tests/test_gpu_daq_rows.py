@@ -54,17 +54,20 @@ def test_channel_groups(ql, M, R, K, group):
     _check(v, amax, q.reshape(-1), scales.reshape(-1))
 
 
-# whole layers with channel scales on the pipelined tiles: few groups, as many as the small table holds, one more, and the most; a width at
-# which 2048 rows take the large tiles in one round
-@pytest.mark.parametrize("K,group,N", [(128, 128, 648), (1152, 288, 648), (1280, 32, 648), (1408, 32, 648), (4608, 32, 648), (768, 96, 648), (1152, 128, 3400)])
+# whole layers with channel scales on the pipelined tiles: few groups, as many as the small table holds, one more, and the most; every group whose
+# pattern is unrolled; a width at which 2048 rows take the large tiles in one round
+@pytest.mark.parametrize("K,group,N", [(128, 128, 648), (1152, 288, 648), (1152, 192, 648), (1280, 32, 648), (1408, 32, 648), (1152, 64, 648), (4608, 32, 648),
+                                       (768, 96, 648), (1152, 128, 3400)])
 @pytest.mark.parametrize("M,R", [(256, 64), (2048, 256), (4096, 2048)])
-def test_layers_with_channel_scales(ql, M, R, K, group, N):
+@pytest.mark.parametrize("storage", [8, 4])
+def test_layers_with_channel_scales(ql, storage, M, R, K, group, N):
     g = torch.Generator(device="cuda").manual_seed(K + M)
     x = torch.randn(M, K, device="cuda", generator=g).half()
-    w = torch.randint(-32, 32, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    most = 32 if storage == 8 else 8
+    w = torch.randint(-most, most, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    held = w if storage == 8 else torch.from_numpy(ql.ql_pack_w4_host(w.cpu().numpy())).cuda()
     s = (torch.rand(N, K // group, device="cuda", generator=g) * 0.02 + 0.001).half()
-    y = ql.qlinear_grouped(x, R, w, s, group, act_group=group, storage=8)
-    y = y["y"] if isinstance(y, dict) else y
+    y = ql.qlinear_grouped(x, R, held, s, group, act_group=group, storage=storage)
     q, a = ql.daq_quantize_cg(x, R, group)
     a = a.double().reshape(M // R, K // group).repeat_interleave(R, 0)
     want, scale = torch.zeros(M, N, dtype=torch.float64, device="cuda"), torch.zeros(M, N, dtype=torch.float64, device="cuda")
@@ -81,7 +84,7 @@ def test_layers_with_channel_scales(ql, M, R, K, group, N):
 # An infinite or NaN input stays inside its scale block.  More tiles than workgroups are resident, so that a workgroup walks from a tile of one
 # block to one of another: 128x128 tiles (512 resident) and 64x64 ones (768 with int8 codes, 1024 with packed ones)
 @pytest.mark.parametrize("M,K,N,R,storage", [(16384, 1152, 1152, 256, 8), (16384, 768, 2304, 1024, 4), (832, 1152, 4992, 64, 8), (3200, 768, 2560, 64, 4)])
-@pytest.mark.parametrize("group", [32, 96, 128])
+@pytest.mark.parametrize("group", [32, 64, 96, 128, 192])
 def test_channel_scales_of_one_block_reach_no_other(ql, M, K, N, R, storage, group):
     g = torch.Generator(device="cuda").manual_seed(K + group)
     x = torch.randn(M, K, device="cuda", generator=g).half()

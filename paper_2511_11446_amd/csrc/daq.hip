@@ -379,9 +379,8 @@ __global__ __launch_bounds__(256) void daq_cg_quant(DaqArgs a, int cg)
 // by cg, the scale and its reciprocal - is paid once per thread and not per piece.  Pass 1 leaves the slab's maximum per
 // group with plain stores, no clearing pass and no atomics; pass 2 takes the maximum over its block's slabs.
 // M = 4096, K = 1152, R = 256, cg = 128: 32.7 -> 13 us.
-// rows in flight per thread: all of a slab of 16 that three rows side by side leave to it (a second round of loads would wait for the first
-// one's stores)
-constexpr int DAQ_CG_ROWS = 6;
+// rows in flight per thread (six, a whole slab of 16 for three rows side by side, were not faster, and 3 % slower at K = 3072 from 64 slabs on)
+constexpr int DAQ_CG_ROWS = 4;
 // Slabs per scale block up to which every thread takes the maximum of its group over them by itself; beyond that the workgroup does it
 // together (both passes, cg = 128, M = R = 16384, 1024 slabs: K = 1152 131 -> 22 us, K = 4608 404 -> 91, where the atomic kernels take
 // 79 and 185; M = 4096, R = 1024, K = 1152: 15.5 -> 8.4)
@@ -414,8 +413,10 @@ __global__ __launch_bounds__(1024) void daq_cg_slab(DaqArgs a, int cg, int slab,
             for (int i = threadIdx.x; i < slabs * G; i += blockDim.x) atomicMax(&gmax_lds[i % G], pm[i]);
             __syncthreads();
             if (on) m = gmax_lds[g];
+        } else if (on && slabs == 1) {
+            m = pm[g];
         } else if (on) {
-            // all requested at once: in a loop each one waited for the one before (M = 1024, R = 256, K = 1152: 10.8 -> 6.8 us)
+            // all requested at once: in a loop each one waited for the one before (M = 1024, R = 256, K = 1152: 9.3 -> 6.9 us)
             unsigned o[DAQ_CG_OWN];
 #pragma unroll
             for (int s = 0; s < DAQ_CG_OWN; ++s) o[s] = pm[(s < slabs ? s : 0) * G + g];
@@ -462,10 +463,12 @@ hipError_t launch_daq_cg(const DaqArgs &a, int cg, bool slabs, hipStream_t strea
         const int rpw = P > 512 ? 1 : P > 256 ? 1024 / P : 512 / P;
         const dim3 grid(a.M / slab), block((P * rpw + 63) / 64 * 64);
         hipLaunchKernelGGL(daq_cg_slab<false>, grid, block, G * 4, stream, a, cg, slab, a.R / slab, rpw);
-        // the codes are written by workgroups of 8 rows, unless these merge many slabs or have more than 8 rows side by side (both passes, us:
-        // M = 4096, R = 256, K = 1152 11.5 -> 10.1, K = 4608 23.5 -> 20.6, M = 512, R = 64, K = 3072 10.6 -> 8.5; but M = 16384, R = 1024, K =
-        // 1152 19.5 -> 22.3)
-        const int rows = a.R / slab <= DAQ_CG_OWN && rpw <= 4 ? 8 : slab;
+        // The codes are written by workgroups of 8 rows where those of 16 make at most 8 wavefronts per CU, or walk row by row.  They merge few
+        // slabs and have at most 4 rows side by side.  Both passes, us, workgroups of 16 -> 8: M = 2048, R = 64, K = 1152 9.0 -> 7.5, K = 3072 11.6 -> 11.1,
+        // M = 4096, R = 256, K = 1152 9.3 -> 9.05, K = 4608 21.4 -> 18.9, M = 16384 72.6 -> 70.7; but M = 4096, K = 3072, R = 64 14.8 -> 15.7, M = 8192,
+        // R = 256 22.6 -> 24.3, M = 16384, K = 1152 19.1 -> 20.0
+        const bool few_waves = (int64_t)grid.x * (block.x / 64) <= 8 * 256;
+        const int rows = a.R / slab <= DAQ_CG_OWN && rpw <= 4 && (rpw == 1 || few_waves) ? 8 : slab;
         hipLaunchKernelGGL(daq_cg_slab<true>, dim3(a.M / rows), block, G * 4, stream, a, cg, rows, a.R / slab, rpw);
         return hipGetLastError();
     }

@@ -41,8 +41,9 @@ def test_rows_of_five_pieces_by_count(ql, M):
     _check(x.float(), x.abs().float().amax(dim=1, keepdim=True), q, scales)
 
 
-# blocks of one, a few and more than 16 slabs; slabs of 16 and 8 rows and none; rows side by side from one to more than four
-@pytest.mark.parametrize("M,R", [(48, 16), (96, 24), (512, 256), (544, 272), (1024, 1024), (60, 12), (96, 96)])
+# blocks of one, a few and more than 16 slabs; slabs of 16 and 8 rows and none, codes of 8 and 16 rows per workgroup; rows side by side from one to more
+# than four
+@pytest.mark.parametrize("M,R", [(48, 16), (96, 24), (512, 256), (544, 272), (1024, 1024), (60, 12), (96, 96), (6400, 256), (6400, 16)])
 @pytest.mark.parametrize("K,group", [(128, 32), (384, 64), (1152, 288), (1152, 32), (3072, 128), (4608, 128), (4608, 32)])
 def test_channel_groups(ql, M, R, K, group):
     x = torch.randn(M, K, generator=torch.Generator().manual_seed(M + K)).half()

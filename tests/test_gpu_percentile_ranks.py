@@ -45,3 +45,24 @@ def test_scale_of_every_rank(ql, R, K, kind, rank):
         t = tau[:, None]
         want = (x.float().clamp(-t, t) / alpha[:, None]).round().clamp(-31, 31)
         torch.testing.assert_close(q.cpu().reshape(blocks, n).float(), want, rtol=0, atol=0)
+
+
+# one row per scale: ranks that are walked to from the top and ranks that are searched for, in rows of every kind of kernel; rows with fewer magnitudes than the rank
+@pytest.mark.parametrize("rank", [1, 2, 3, 8, 9, 100])
+@pytest.mark.parametrize("kind", ["normal", "equal", "zeros but one", "infinite"])
+@pytest.mark.parametrize("K", [136, 512, 520, 1024, 1536, 2048, 4608, 8192])
+def test_scale_of_a_row(ql, K, kind, rank):
+    M = 70
+    x = _input(kind, M, K, torch.Generator().manual_seed(rank + K))
+    x[3] = 0
+    x[4] = torch.arange(K).remainder(3).half()        # three magnitudes
+    p_ppm = (K - rank) * 1000000 // K + 1
+    k = min(K, (K * p_ppm + 999999) // 1000000)
+    tau = x.abs().float().sort(dim=1).values[:, k - 1]
+    alpha = torch.where(tau == 0, torch.ones_like(tau), tau / 127.0)
+    q, scales = ql.daq_quantize_robust(x.cuda(), 1, p_ppm, 8)
+    torch.testing.assert_close(scales.cpu(), alpha, rtol=0, atol=0)
+    finite = tau.isfinite()
+    t = tau[:, None]
+    want = (x.float().clamp(-t, t) / alpha[:, None]).round().clamp(-127, 127)
+    torch.testing.assert_close(q.cpu().float()[finite], want[finite], rtol=0, atol=0)

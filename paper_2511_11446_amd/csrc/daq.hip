@@ -491,7 +491,10 @@ bool daq_many_takes(const DaqArgs &a, bool robust)
 {
     if (a.K % 8 != 0 || a.K > 4608 || (uintptr_t)a.x % 16 != 0 || (uintptr_t)a.q % 8 != 0) return false;
     if (a.R == 1) return true;
-    if (robust) return daq_hist_parts(a.K, a.R) <= DAQ_HIST_FEW && a.scratch_bytes >= daq_hist_bytes(a.M, a.K, a.R);
+    // Percentiles of very many blocks gain nothing: a workgroup per block, with histograms larger than its values, is what takes the time (two rows per
+    // scale, us, a launch per layer and pass -> shared: M = 4096, eight layers of K = 384 129 -> 86; but 65536 rows 1742 -> 1942, M = 16384, two of K =
+    // 1152 298 -> 311)
+    if (robust) return a.M / a.R <= 4096 && daq_hist_parts(a.K, a.R) <= DAQ_HIST_FEW && a.scratch_bytes >= daq_hist_bytes(a.M, a.K, a.R);
     // every wavefront of the quantize pass reduces the partial maxima itself
     const size_t parts = daq_parts_per_block(a.K, a.R);
     return parts > 0 && parts <= 256 && parts * (size_t)(a.M / a.R) * 4 <= a.scratch_bytes;
@@ -529,6 +532,7 @@ hipError_t launch_daq_many(DaqMany &b, hipStream_t stream)
         b.first[i] = grid;
         grid += (unsigned)b.l[i].quant_parts * (unsigned)(M / R);
     }
+    for (int i = b.count; i < PLAN_WINDOW; ++i) b.first[i] = ~0u;
     hipLaunchKernelGGL(daq_part_absmax_many, dim3(grid), dim3(256), 0, stream, b);
     hipLaunchKernelGGL(daq_rows_many<true>, rows, dim3(256), 0, stream, b);
     return hipGetLastError();

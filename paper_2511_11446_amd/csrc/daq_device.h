@@ -107,11 +107,13 @@ __device__ __forceinline__ uint2 daq_piece(const uint4 &v, float alpha, float rc
     return out;
 }
 
-// the layer of a launch over several to which a workgroup belongs
+// The layer of a launch over several to which a workgroup belongs; `first` of the layers that are not there lies behind all workgroups.  All are looked at:
+// a loop that ends where the layer is found waits for one read after the other
 __device__ __forceinline__ int many_layer(const DaqMany &b, unsigned block)
 {
     int i = 0;
-    while (i + 1 < b.count && block >= b.first[i + 1]) ++i;
+#pragma unroll
+    for (int j = 1; j < PLAN_WINDOW; ++j) i += block >= b.first[j];
     return i;
 }
 

@@ -287,17 +287,31 @@ __global__ __launch_bounds__(256) void daq_rows_robust(DaqArgs a, int mode)
     robust_rows<CH, HIST>(a, mode, mode == DAQ_QUANT ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x);
 }
 
-// the rows of several layers
-template <bool HIST>
+// The rows of several layers.  LONG: some of more than 1536 values; their registers (127 against 55) would halve the wavefronts that the shorter
+// rows' selections keep in flight (99.9th percentile of each row, M = 16384, us a plan: eight layers of K = 384 102 -> 80, four of K = 1152 172 -> 161; a
+// launch per layer 131 and 170)
+template <bool LONG, bool HIST>
 __global__ __launch_bounds__(256) void daq_rows_robust_many(DaqMany b, int mode)
 {
     const int block = mode == DAQ_QUANT ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
     const int layer = block / b.row_blocks, wg = block - layer * b.row_blocks;
     const DaqArgs &l = b.l[layer];
-    if (l.K <= 1024) robust_rows<2, HIST>(l, mode, wg);
-    else if (l.K <= 1536) robust_rows<3, HIST>(l, mode, wg);
-    else if (l.K <= 3072) robust_rows<6, HIST>(l, mode, wg);
-    else robust_rows<9, HIST>(l, mode, wg);
+    if (l.K <= 512) robust_rows<1, HIST>(l, mode, wg);
+    else if (l.K <= 1024) robust_rows<2, HIST>(l, mode, wg);
+    else if (!LONG || l.K <= 1536) robust_rows<3, HIST>(l, mode, wg);
+    else if (l.K <= 2048) robust_rows<LONG ? 4 : 3, HIST>(l, mode, wg);
+    else if (l.K <= 3072) robust_rows<LONG ? 6 : 3, HIST>(l, mode, wg);
+    else robust_rows<LONG ? 9 : 3, HIST>(l, mode, wg);
+}
+
+template <bool HIST>
+static void run_robust_rows_many(const DaqMany &b, int mode, hipStream_t s)
+{
+    bool long_rows = false;
+    for (int i = 0; i < b.count; ++i) long_rows = long_rows || b.l[i].K > 1536;
+    const dim3 grid((unsigned)b.row_blocks * (unsigned)b.count);
+    if (long_rows) hipLaunchKernelGGL((daq_rows_robust_many<true, HIST>), grid, dim3(256), 0, s, b, mode);
+    else hipLaunchKernelGGL((daq_rows_robust_many<false, HIST>), grid, dim3(256), 0, s, b, mode);
 }
 
 // any row length and alignment: the row is re-read from memory (cache) in every counting round
@@ -548,17 +562,16 @@ hipError_t launch_daq_robust(const DaqArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-// The same passes over several layers (daq_many_takes): consumers select for themselves where every layer's would
+// The same passes over several layers (daq_many_takes): a pass selects for itself where every layer's would
 hipError_t launch_daq_robust_many(DaqMany &b, hipStream_t stream)
 {
     const int M = b.l[0].M, R = b.l[0].R, nblk = M / R;
     b.row_blocks = (M + 3) / 4;
-    const dim3 rows((unsigned)b.row_blocks * (unsigned)b.count);
     if (R == 1) {
-        hipLaunchKernelGGL(daq_rows_robust_many<false>, rows, dim3(256), 0, stream, b, (int)DAQ_FUSED);
+        run_robust_rows_many<false>(b, DAQ_FUSED, stream);
         return hipGetLastError();
     }
-    bool self = R % 4 == 0;
+    bool self = true;
     unsigned grid = 0;
     for (int i = 0; i < b.count; ++i) {
         b.l[i].quant_parts = (int)daq_hist_parts(b.l[i].K, R);
@@ -566,13 +579,15 @@ hipError_t launch_daq_robust_many(DaqMany &b, hipStream_t stream)
         b.first[i] = grid;
         grid += (unsigned)b.l[i].quant_parts * (unsigned)nblk;
     }
+    for (int i = b.count; i < PLAN_WINDOW; ++i) b.first[i] = ~0u;
+    const bool self_rows = self && R % 4 == 0;
     for (int level = 0; level < 2; ++level) {
         if (self) run_hist_many<true>(b, grid, level, stream);
         else run_hist_many<false>(b, grid, level, stream);
-        if (!self) hipLaunchKernelGGL(daq_part_select_many, dim3((unsigned)(nblk * b.count)), dim3(1024), 0, stream, b, level);
+        if (level == 0 ? !self : !self_rows) hipLaunchKernelGGL(daq_part_select_many, dim3((unsigned)(nblk * b.count)), dim3(1024), 0, stream, b, level);
     }
-    if (self) hipLaunchKernelGGL(daq_rows_robust_many<true>, rows, dim3(256), 0, stream, b, (int)DAQ_QUANT);
-    else hipLaunchKernelGGL(daq_rows_robust_many<false>, rows, dim3(256), 0, stream, b, (int)DAQ_QUANT);
+    if (self_rows) run_robust_rows_many<true>(b, DAQ_QUANT, stream);
+    else run_robust_rows_many<false>(b, DAQ_QUANT, stream);
     return hipGetLastError();
 }
 

@@ -61,7 +61,7 @@ struct DaqMany {
     int count;
     // set by the launches: workgroups per layer of the row kernels, and where a layer's workgroups begin in the kernels that cut scale blocks into parts
     int row_blocks;
-    unsigned first[PLAN_WINDOW];
+    unsigned first[PLAN_WINDOW];   // (of those that are not there: behind all workgroups)
 };
 bool daq_many_takes(const DaqArgs &a, bool robust);
 // do the launches over these layers stay within the size of a launch?

@@ -40,6 +40,8 @@ PLANS = {
     "all kinds": [(1152, 1000, 4, 288, True), (1152, 264, 16, 0, True), (1152, 640, 4, 128, False), (1152, 392, 8, 0, True),
                   (1152, 130, 4, 32, True), (1152, 200, 4, 64, True), (1152, 96, 4, 192, True), (768, 96, 4, 96, True), (4608, 512, 16, 0, False)],
     "odd inner sizes": [(320, 300, 8, 0, True), (200, 256, 8, 0, True), (256, 136, 16, 0, True), (1032, 128, 8, 0, True), (1028, 64, 8, 0, True)],
+    "every row kernel": [(512, 72, 8, 0, True), (1024, 72, 8, 0, True), (1536, 72, 8, 0, True), (2048, 72, 8, 0, True), (3072, 72, 8, 0, True), (4608, 72, 8, 0, True)],
+    "short rows": [(128, 136, 8, 0, True), (512, 136, 8, 0, True), (520, 136, 8, 0, True), (1536, 136, 8, 0, True)],
     "wide and narrow": [(4608, 384, 8, 0, True), (384, 513, 8, 0, True), (384, 512, 4, 64, True), (4608, 256, 4, 32, True), (2304, 128, 4, 288, True)],
 }
 
@@ -104,11 +106,13 @@ def _alone_shared(ql, l, x, R, p_ppm, a_bits):
     return ql.qgemm_w4a8(d[0], d[1], R, l["w"], l["w_scale"], l["bias"], group=l["group"])
 
 
-# rows per scale with whole, ragged and many parts per scale block; ranks of the percentile: the maximum, few, many; R = 1 with a percentile
+# rows per scale with whole, ragged and many parts per scale block; ranks of the percentile: the maximum, few, many; R = 1 with a percentile;
+# more scale blocks than percentiles share launches for
 @pytest.mark.parametrize("M,R,p_ppm,a_bits", [(512, 64, 0, 8), (1530, 255, 0, 8), (4096, 1024, 0, 8), (2048, 2048, 0, 8), (1024, 256, 999000, 8),
                                               (518, 74, 990000, 6), (2048, 1024, 999900, 6), (770, 1, 999000, 8), (515, 1, 900000, 4),
-                                              (1024, 512, 1000000, 8), (1024, 64, 1, 8)])
-@pytest.mark.parametrize("name", ["block w8", "all kinds", "wide and narrow", "odd inner sizes"])
+                                              (1024, 512, 1000000, 8), (1024, 64, 1, 8),
+                                              (8194, 2, 750000, 8)])
+@pytest.mark.parametrize("name", ["block w8", "all kinds", "wide and narrow", "every row kernel", "short rows", "odd inner sizes"])
 @pytest.mark.parametrize("tight", [False, True])
 def test_shared_scales_and_percentiles(ql, name, M, R, p_ppm, a_bits, tight):
     g = torch.Generator(device="cuda").manual_seed(M)

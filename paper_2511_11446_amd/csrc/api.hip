@@ -813,7 +813,7 @@ static bool any_order(const ql::GemmArgs *g, size_t n)
 
 // The next layers of a plan from `first` on in one go, where their inputs are there already: their activations are quantized by
 // the launches of one layer (each layer's codes, scales and scratch in a part of its own of the workspace), then the GEMMs follow in order.  Takes
-// layers as long as no input of one is written by another one before it, they fit the workspace and the size of a launch together, and none
+// layers as long as no input of one is written by another one before it, they fit the workspace and PLAN_WINDOW_BYTES together, and none
 // is small enough to quantize its own rows inside its GEMM.  Returns how many layers it ran: 0 where that is fewer than two quantized ones.
 static size_t plan_run_window(const ql_plan *plan, size_t first, const void *const *x_in, void *const *y_out, int64_t M, int64_t R,
                               const ql_daq_params *dp, void *workspace, size_t workspace_bytes, hipStream_t stream, int &rc)
@@ -822,6 +822,7 @@ static size_t plan_run_window(const ql_plan *plan, size_t first, const void *con
     ql::GemmArgs g[ql::PLAN_WINDOW];
     ql::DaqMany daq{};
     size_t used = 0, n = 0;
+    int64_t codes = 0, outputs = 0;   // bytes; outputs: of the layers before this one
     for (; n < ql::PLAN_WINDOW && first + n < plan->layers.size(); ++n) {
         const size_t l = first + n;
         const ql_layer_desc &d = plan->layers[l];
@@ -829,6 +830,7 @@ static size_t plan_run_window(const ql_plan *plan, size_t first, const void *con
         for (size_t j = first; j < l; ++j)
             ready = ready && !overlap(x_in[l], (size_t)(M * d.K) * 2, y_out[j], (size_t)(M * plan->layers[j].N) * 2);
         if (!ready) break;
+        if (n > 0) outputs += M * plan->layers[l - 1].N * 2;
         ql::GemmArgs &a = g[n];
         a = ql::GemmArgs{};
         a.w = d.w;
@@ -847,6 +849,8 @@ static size_t plan_run_window(const ql_plan *plan, size_t first, const void *con
         }
         const LayerWs lw = layer_ws(M, d.K, R);
         if (used + lw.total > workspace_bytes) break;
+        codes += M * d.K;
+        if (codes + outputs > ql::PLAN_WINDOW_BYTES) break;
         ql::DaqArgs it = daq_args(x_in[l], M, d.K, R, base + used, lw.total);
         if ((dp && robust_args(dp, d.K, R, it) != QL_OK) || !ql::daq_many_takes(it, dp != nullptr)) break;
         a.q = it.q;
@@ -859,10 +863,6 @@ static size_t plan_run_window(const ql_plan *plan, size_t first, const void *con
             if (ql::qgemm_fuse_takes(f)) break;
         }
         daq.l[daq.count++] = it;
-        if (!ql::daq_many_fits(daq, dp != nullptr)) {
-            --daq.count;
-            break;
-        }
         used += lw.total;
     }
     if (daq.count < 2) return 0;

@@ -500,21 +500,6 @@ bool daq_many_takes(const DaqArgs &a, bool robust)
     return parts > 0 && parts <= 256 && parts * (size_t)(a.M / a.R) * 4 <= a.scratch_bytes;
 }
 
-// A launch holds fewer than 2^32 threads: do those of all passes over these layers (the row passes have 64 threads per row, the parts 256 and
-// the selections 1024 each)?  A layer alone reaches that at 2^26 rows; eight of them, or a percentile of two rows, from a few million rows on.
-bool daq_many_fits(const DaqMany &b, bool robust)
-{
-    unsigned long long parts = 0, blocks = 0, rows = 0;
-    for (int i = 0; i < b.count; ++i) {
-        const unsigned long long nblk = (unsigned long long)(b.l[i].M / b.l[i].R);
-        rows += ((unsigned long long)b.l[i].M + 3) / 4;
-        if (b.l[i].R == 1) continue;
-        blocks += nblk;
-        parts += nblk * (robust ? daq_hist_parts(b.l[i].K, b.l[i].R) : daq_parts_per_block(b.l[i].K, b.l[i].R));
-    }
-    return rows * 256 < (1ull << 32) && parts * 256 < (1ull << 32) && (!robust || blocks * 1024 < (1ull << 32));
-}
-
 // Several rows per scale: both passes take all layers, the maxima first.  us against a launch per layer and pass, whole plans with their GEMMs:
 // percentile scales, M = 8192, R = 256, width 1152 348 -> 330; other plans with shared scales up to 1.3x.
 hipError_t launch_daq_many(DaqMany &b, hipStream_t stream)

@@ -54,7 +54,7 @@ inline size_t daq_parts_per_block(int64_t K, int64_t R)
 }
 
 hipError_t launch_daq(const DaqArgs &a, hipStream_t stream);
-// DAQ of up to PLAN_WINDOW layers of the same M and R in the launches that one layer takes; every layer has to pass daq_many_takes, all together daq_many_fits
+// DAQ of up to PLAN_WINDOW layers of the same M and R in the launches that one layer takes; every layer has to pass daq_many_takes
 constexpr int PLAN_WINDOW = 8;
 struct DaqMany {
     DaqArgs l[PLAN_WINDOW];
@@ -63,9 +63,13 @@ struct DaqMany {
     int row_blocks;
     unsigned first[PLAN_WINDOW];   // (of those that are not there: behind all workgroups)
 };
+// A layer's codes are read by its GEMM after the codes of the layers with it and the outputs of those before it have been written; layers go together as far
+// as Infinity Cache (256 MB) holds these.  us a plan, a launch per layer -> as many together as there are -> within this bound: four layers of K = N = 1152,
+// M = 16384 163 -> 159 -> 160, M = 65536 520 -> 564 -> 518; eight of 384 x 384, M = 65536 316 -> 325 -> 297; four of 1160 x 1000, M = 65536 832 -> 925 -> 805.
+// It also keeps their launches below 2^32 threads: 64 threads per row of at least 8 codes.
+constexpr int64_t PLAN_WINDOW_BYTES = (int64_t)256 << 20;
+static_assert(PLAN_WINDOW_BYTES / 8 * 64 < (int64_t)1 << 32, "threads of a launch");
 bool daq_many_takes(const DaqArgs &a, bool robust);
-// do the launches over these layers stay within the size of a launch?
-bool daq_many_fits(const DaqMany &b, bool robust);
 hipError_t launch_daq_many(DaqMany &b, hipStream_t stream);
 hipError_t launch_daq_robust_many(DaqMany &b, hipStream_t stream);
 // the first pass alone: partial maxima of every scale block (daq_parts_per_block of them) into a.partmax

@@ -2,8 +2,7 @@
 // validation (always before the first HIP call), workspace carving, kernel
 // dispatch, and the plan runner (Algorithm 2, Phase B restricted to the
 // quantized linears).
-#include "../../include/diffpro_qlinear.h"
-#include "ql_internal.h"
+#include "plan_window.h"
 
 #include <algorithm>
 #include <atomic>
@@ -312,6 +311,84 @@ int qgemm_any(int w_bits, const void *q, const void *a_scales, int64_t M, int64_
 }
 
 }  // namespace
+
+namespace ql {
+
+// Do the GEMMs of these layers give the same in any order?  No output overlaps another one's, or what another layer reads (codes and
+// scales lie in the workspace).
+bool any_order(const GemmArgs *g, size_t n)
+{
+    for (size_t i = 0; i < n; ++i) {
+        const size_t y_bytes = (size_t)g[i].M * g[i].N * 2;
+        for (size_t j = 0; j < n; ++j) {
+            if (i == j) continue;
+            const GemmArgs &o = g[j];
+            const size_t w_elems = (size_t)o.N * o.K, scales = o.w_bits == 8 ? (size_t)o.N * 4 : o.w_bits == 4 ? (size_t)o.N * (o.K / o.group) * 2 : 0;
+            if (overlap(g[i].y, y_bytes, o.y, (size_t)o.M * o.N * 2) || overlap(g[i].y, y_bytes, o.w, o.w_bits == 16 ? w_elems * 2 : o.w_bits == 8 ? w_elems : w_elems / 2) ||
+                (scales && overlap(g[i].y, y_bytes, o.s_w, scales)) || (o.bias && overlap(g[i].y, y_bytes, o.bias, (size_t)o.N * 2)) ||
+                (o.w_bits == 16 && overlap(g[i].y, y_bytes, o.q, (size_t)o.M * o.K * 2)))
+                return false;
+        }
+    }
+    return true;
+}
+
+void plan_window(const ql_layer_desc *layers, size_t n_layers, size_t first, const void *const *x_in, void *const *y_out, int64_t M, int64_t R,
+                 const ql_daq_params *dp, void *workspace, size_t workspace_bytes, PlanWindow &w)
+{
+    unsigned char *base = static_cast<unsigned char *>(workspace);
+    w.n = w.count = w.daq.count = 0;
+    size_t used = 0, n = 0;
+    int64_t codes = 0, outputs = 0;   // bytes; outputs: of the layers before this one
+    for (; n < PLAN_WINDOW && first + n < n_layers; ++n) {
+        const size_t l = first + n;
+        const ql_layer_desc &d = layers[l];
+        bool ready = true;
+        for (size_t j = first; j < l; ++j)
+            ready = ready && !overlap(x_in[l], (size_t)(M * d.K) * 2, y_out[j], (size_t)(M * layers[j].N) * 2);
+        if (!ready) break;
+        if (n > 0) outputs += M * layers[l - 1].N * 2;
+        GemmArgs &a = w.g[n];
+        a = GemmArgs{};
+        a.w = d.w;
+        a.s_w = d.w_scale;
+        a.bias = d.bias;
+        a.y = y_out[l];
+        a.M = (int)M;
+        a.N = (int)d.N;
+        a.K = (int)d.K;
+        a.R = d.w_bits == 16 ? 1 : (int)R;
+        a.w_bits = d.w_bits;
+        a.group = d.w_bits == 4 ? (int)d.group : 128;
+        if (d.w_bits == 16) {
+            a.q = static_cast<const int8_t *>(x_in[l]);
+            continue;
+        }
+        const LayerWs lw = layer_ws(M, d.K, R);
+        if (used + lw.total > workspace_bytes) break;
+        codes += M * d.K;
+        if (codes + outputs > PLAN_WINDOW_BYTES) break;
+        DaqArgs it = daq_args(x_in[l], M, d.K, R, base + used, lw.total);
+        if ((dp && robust_args(dp, d.K, R, it) != QL_OK) || !daq_many_takes(it, dp != nullptr)) break;
+        a.q = it.q;
+        a.s_a = it.scales;
+        if (!dp) {
+            GemmArgs f = a;
+            f.x = x_in[l];
+            f.partmax = it.partmax;
+            f.parts = R == 1 ? 0 : (int)daq_parts_per_block(d.K, R);
+            if (qgemm_fuse_takes(f)) break;
+        }
+        w.daq.l[w.daq.count++] = it;
+        used += lw.total;
+    }
+    if (w.daq.count < 2) return;
+    w.n = (int)n;
+    // GEMMs that share a launch: none of the window's layers may read or write what another one writes
+    if (any_order(w.g, n)) w.count = qgemm_many_choice(w.g, w.n, w.together);
+}
+
+}  // namespace ql
 
 struct ql_plan {
     std::vector<ql_layer_desc> layers;
@@ -792,92 +869,17 @@ size_t ql_plan_workspace_bytes(const ql_plan *plan, int64_t M, int64_t R)
     return most;
 }
 
-// Do the GEMMs of these layers give the same in any order?  No output overlaps another one's, or what another layer reads (codes and
-// scales lie in the workspace).
-static bool any_order(const ql::GemmArgs *g, size_t n)
+// the launches of a window
+static int plan_run_window(ql::PlanWindow &w, bool robust, hipStream_t stream)
 {
-    for (size_t i = 0; i < n; ++i) {
-        const size_t y_bytes = (size_t)g[i].M * g[i].N * 2;
-        for (size_t j = 0; j < n; ++j) {
-            if (i == j) continue;
-            const ql::GemmArgs &o = g[j];
-            const size_t w_elems = (size_t)o.N * o.K, scales = o.w_bits == 8 ? (size_t)o.N * 4 : o.w_bits == 4 ? (size_t)o.N * (o.K / o.group) * 2 : 0;
-            if (overlap(g[i].y, y_bytes, o.y, (size_t)o.M * o.N * 2) || overlap(g[i].y, y_bytes, o.w, o.w_bits == 16 ? w_elems * 2 : o.w_bits == 8 ? w_elems : w_elems / 2) ||
-                (scales && overlap(g[i].y, y_bytes, o.s_w, scales)) || (o.bias && overlap(g[i].y, y_bytes, o.bias, (size_t)o.N * 2)) ||
-                (o.w_bits == 16 && overlap(g[i].y, y_bytes, o.q, (size_t)o.M * o.K * 2)))
-                return false;
-        }
-    }
-    return true;
-}
-
-// The next layers of a plan from `first` on in one go, where their inputs are there already: their activations are quantized by
-// the launches of one layer (each layer's codes, scales and scratch in a part of its own of the workspace), then the GEMMs follow in order.  Takes
-// layers as long as no input of one is written by another one before it, they fit the workspace and PLAN_WINDOW_BYTES together, and none
-// is small enough to quantize its own rows inside its GEMM.  Returns how many layers it ran: 0 where that is fewer than two quantized ones.
-static size_t plan_run_window(const ql_plan *plan, size_t first, const void *const *x_in, void *const *y_out, int64_t M, int64_t R,
-                              const ql_daq_params *dp, void *workspace, size_t workspace_bytes, hipStream_t stream, int &rc)
-{
-    unsigned char *base = static_cast<unsigned char *>(workspace);
-    ql::GemmArgs g[ql::PLAN_WINDOW];
-    ql::DaqMany daq{};
-    size_t used = 0, n = 0;
-    int64_t codes = 0, outputs = 0;   // bytes; outputs: of the layers before this one
-    for (; n < ql::PLAN_WINDOW && first + n < plan->layers.size(); ++n) {
-        const size_t l = first + n;
-        const ql_layer_desc &d = plan->layers[l];
-        bool ready = true;
-        for (size_t j = first; j < l; ++j)
-            ready = ready && !overlap(x_in[l], (size_t)(M * d.K) * 2, y_out[j], (size_t)(M * plan->layers[j].N) * 2);
-        if (!ready) break;
-        if (n > 0) outputs += M * plan->layers[l - 1].N * 2;
-        ql::GemmArgs &a = g[n];
-        a = ql::GemmArgs{};
-        a.w = d.w;
-        a.s_w = d.w_scale;
-        a.bias = d.bias;
-        a.y = y_out[l];
-        a.M = (int)M;
-        a.N = (int)d.N;
-        a.K = (int)d.K;
-        a.R = d.w_bits == 16 ? 1 : (int)R;
-        a.w_bits = d.w_bits;
-        a.group = d.w_bits == 4 ? (int)d.group : 128;
-        if (d.w_bits == 16) {
-            a.q = static_cast<const int8_t *>(x_in[l]);
-            continue;
-        }
-        const LayerWs lw = layer_ws(M, d.K, R);
-        if (used + lw.total > workspace_bytes) break;
-        codes += M * d.K;
-        if (codes + outputs > ql::PLAN_WINDOW_BYTES) break;
-        ql::DaqArgs it = daq_args(x_in[l], M, d.K, R, base + used, lw.total);
-        if ((dp && robust_args(dp, d.K, R, it) != QL_OK) || !ql::daq_many_takes(it, dp != nullptr)) break;
-        a.q = it.q;
-        a.s_a = it.scales;
-        if (!dp) {
-            ql::GemmArgs f = a;
-            f.x = x_in[l];
-            f.partmax = it.partmax;
-            f.parts = R == 1 ? 0 : (int)ql::daq_parts_per_block(d.K, R);
-            if (ql::qgemm_fuse_takes(f)) break;
-        }
-        daq.l[daq.count++] = it;
-        used += lw.total;
-    }
-    if (daq.count < 2) return 0;
-    rc = device_status(dp ? ql::launch_daq_robust_many(daq, stream) : ql::launch_daq_many(daq, stream));
-    // GEMMs that share a launch: none of the window's layers may read or write what another one writes
-    const ql::GemmArgs *together[ql::PLAN_WINDOW];
-    int count = 0;
-    if (any_order(g, n)) count = ql::qgemm_many_choice(g, (int)n, together);
-    if (count && rc == QL_OK) rc = device_status(ql::launch_qgemm_many(together, count, stream));
-    for (size_t i = 0; i < n && rc == QL_OK; ++i) {
+    int rc = device_status(robust ? ql::launch_daq_robust_many(w.daq, stream) : ql::launch_daq_many(w.daq, stream));
+    if (w.count && rc == QL_OK) rc = device_status(ql::launch_qgemm_many(w.together, w.count, stream));
+    for (int i = 0; i < w.n && rc == QL_OK; ++i) {
         bool done = false;
-        for (int j = 0; j < count; ++j) done = done || together[j] == &g[i];
-        if (!done) rc = device_status(ql::launch_qgemm(g[i], -1, stream));
+        for (int j = 0; j < w.count; ++j) done = done || w.together[j] == &w.g[i];
+        if (!done) rc = device_status(ql::launch_qgemm(w.g[i], -1, stream));
     }
-    return n;
+    return rc;
 }
 
 static int plan_run_any(const ql_plan *plan, const void *const *x_in, void *const *y_out, int64_t M, int64_t R,
@@ -902,10 +904,12 @@ static int plan_run_any(const ql_plan *plan, const void *const *x_in, void *cons
     const bool windows = !fusion && g_gemm_variant.load() < 0;
     for (size_t l = 0; l < plan->layers.size(); ++l) {
         if (windows) {
-            const size_t ran = plan_run_window(plan, l, x_in, y_out, M, R, dp, workspace, workspace_bytes, s, rc);
-            if (rc) return rc;
-            if (ran) {
-                l += ran - 1;
+            ql::PlanWindow w;
+            ql::plan_window(plan->layers.data(), plan->layers.size(), l, x_in, y_out, M, R, dp, workspace, workspace_bytes, w);
+            if (w.n) {
+                rc = plan_run_window(w, dp != nullptr, s);
+                if (rc) return rc;
+                l += (size_t)w.n - 1;
                 continue;
             }
         }

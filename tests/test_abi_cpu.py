@@ -183,6 +183,83 @@ def test_split_k_walk_stays_inside_the_row_and_the_lds(tmp_path):
     assert r.returncode == 0, r.stdout + r.stderr
 
 
+@pytest.fixture(scope="module")
+def plan_windows(tmp_path_factory):
+    """(M, R, p_ppm, a_bits, room, [(K, N, bits, group, x, y)]) -> [(first layer, layers, {those whose GEMMs share a launch})], from the library's own decision."""
+    import subprocess
+    exe = str(tmp_path_factory.mktemp("plan_window") / "check")
+    here = os.path.dirname(os.path.abspath(__file__))
+    lib = os.path.join(os.path.dirname(here), "paper_2511_11446_amd", "libdiffpro_qlinear.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-o", exe,
+                    os.path.join(here, "plan_window_check.cpp"), lib, "-Wl,-rpath," + os.path.dirname(lib)], check=True)
+
+    def ask(M, R, p_ppm, a_bits, room, layers):
+        text = "%d %d %d %d %d\n" % (M, R, p_ppm, a_bits, room) + "".join("%d %d %d %d %d %d\n" % l for l in layers)
+        r = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stderr
+        out = []
+        for line in r.stdout.splitlines():
+            head, _, together = line.partition(":")
+            first, n = map(int, head.split())
+            out.append((first, n, set(map(int, together.split()))))
+        return out
+    return ask
+
+
+def _place(buffer, element=0):
+    """A made-up address: buffers of up to 8 GiB, far apart."""
+    return (1 << 40) + (buffer << 33) + 2 * element
+
+
+def test_every_kind_of_layer_takes_part_in_a_shared_gemm_launch(plan_windows):
+    """The plans that the GPU tests run bring every kind of tile into the launch that several layers share."""
+    import test_gpu_plan_windows as pw
+    kinds = set()
+    for shapes in pw.PLANS.values():
+        for M in pw.ROWS:
+            for room in pw.ROOM:
+                layers = [(K, N, bits, group, _place(2 * i), _place(2 * i + 1)) for i, (K, N, bits, group, _) in enumerate(shapes)]
+                for _, _, together in plan_windows(M, 1, 0, 8, room, layers):
+                    kinds |= {(shapes[i][2], shapes[i][3]) for i in together}
+    assert kinds >= {(8, 0), (16, 0), (4, 32), (4, 64), (4, 128), (4, 192), (4, 288)}
+
+
+def test_layers_that_wait_for_each_other_share_no_gemm_launch(plan_windows):
+    import test_gpu_plan_windows as pw
+    want = {
+        "disjoint": [(0, 4, {0, 1, 2, 3})],
+        "one output": [(0, 4, set())],
+        "outputs five rows apart": [(0, 4, set())],
+        "outputs that meet": [(0, 4, {0, 1, 2, 3})],
+        "an output that a later layer reads": [(2, 2, {2, 3})],     # layers 0 and 1: one of them quantized
+        "an output over the input of an earlier FP16 layer": [(0, 4, set())],
+        "an output over the last rows of an FP16 input": [(0, 4, set())],
+        "an output over the input of an earlier 8-bit layer": [(0, 4, {0, 1, 2, 3})],   # which is quantized before any GEMM
+    }
+    assert set(want) == set(pw.ALIASES)
+    for name, (xs, ys) in pw.ALIASES.items():
+        layers = [(K, N, bits, group, _place(*x), _place(*y)) for (K, N, bits, group, _), x, y in zip(pw.ALIAS_LAYERS, xs, ys)]
+        assert plan_windows(pw.ALIAS_M, 1, 0, 8, 4, layers) == want[name], name
+
+
+def test_room_and_size_of_a_window(plan_windows):
+    """Layers go together as far as their codes fit the workspace, at most eight, and as far as codes and earlier outputs stay within 256 MB."""
+    def windows(M, shapes, room, R=1, p_ppm=0):
+        return plan_windows(M, R, p_ppm, 8, room, [(K, N, 8, 0, _place(2 * i), _place(2 * i + 1)) for i, (K, N) in enumerate(shapes)])
+    sizes = lambda w: [(first, n) for first, n, _ in w]
+    # the recommended workspace is the widest layer's: three layers of a quarter of its width, and none of equal width
+    assert sizes(windows(2048, [(1152, 3456), (1152, 1152), (1152, 4608), (4608, 1152)], 1)) == [(0, 3)]
+    assert sizes(windows(2048, [(1152, 1152)] * 4, 1)) == []
+    assert sizes(windows(2048, [(1152, 1152)] * 4, 2)) == [(0, 2), (2, 2)]
+    assert sizes(windows(2048, [(384, 1152)] * 10, 10)) == [(0, 8), (8, 2)]
+    # 65536 rows: 75 MB of codes and 151 MB of outputs per layer
+    assert sizes(windows(65536, [(1152, 1152)] * 4, 4)) == []
+    assert sizes(windows(16384, [(1152, 3456), (1152, 1152), (1152, 4608)], 3)) == [(0, 3)]
+    # percentiles: up to 4096 scale blocks
+    assert sizes(windows(8192, [(384, 1152)] * 2, 2, R=2, p_ppm=750000)) == [(0, 2)]
+    assert sizes(windows(8194, [(384, 1152)] * 2, 2, R=2, p_ppm=750000)) == []
+
+
 class _Prm(ctypes.Structure):
     _fields_ = [("p_ppm", ctypes.c_int32), ("a_bits", ctypes.c_int32)]
 

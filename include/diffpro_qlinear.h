@@ -354,13 +354,21 @@ int ql_plan_create(const ql_layer_desc *layers, int32_t n_layers, int64_t M_max,
 void ql_plan_destroy(ql_plan *plan);
 int32_t ql_plan_num_layers(const ql_plan *plan);
 
-/* Scratch for a run on M rows (sized for the widest layer input). */
+/* Scratch for a run on M rows (sized for the widest layer input).  Layers that
+ * share launches (below) need room for their codes, scales and scratch at the
+ * same time, qlinear_workspace_bytes(M, K_l, R) each: with more than this
+ * function asks for, more of them go together, up to eight.  Of a block with
+ * inputs of w, w, w and 4w three layers fit what it returns; of layers of one
+ * width only one does. */
 size_t ql_plan_workspace_bytes(const ql_plan *plan, int64_t M, int64_t R);
 
 /* x_in[l] (device) [M, K_l] fp16 and y_out[l] (device) [M, N_l] fp16 for every
  * layer l; the two pointer arrays themselves are host memory.  Layers run in
  * order on `stream`, so y_out[l] may alias x_in[l+1]; layers none of whose
- * buffers an earlier one of them writes may share launches. */
+ * inputs an earlier one of them writes may share launches, as far as
+ * `workspace_bytes` holds their codes together.  The outputs do not depend on
+ * that, FP16 layers' up to the order of their fp32 sums.  An FP16 layer's
+ * output must not overlap its own input. */
 int qlinear_plan_run(const ql_plan *plan, const void *const *x_in, void *const *y_out,
                      int64_t M, int64_t R,
                      void *workspace, size_t workspace_bytes, void *stream);

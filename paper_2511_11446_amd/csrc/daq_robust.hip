@@ -562,7 +562,8 @@ hipError_t launch_daq_robust(const DaqArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-// The same passes over several layers (daq_many_takes): a pass selects for itself where every layer's would
+// The same passes over several layers (daq_many_takes): a pass selects for itself where every layer's would.  us against a launch per layer and pass, block
+// of four layers of width 1152 with its GEMMs, M = 8192, R = 256: 348 -> 330.
 hipError_t launch_daq_robust_many(DaqMany &b, hipStream_t stream)
 {
     const int M = b.l[0].M, R = b.l[0].R, nblk = M / R;

@@ -7,9 +7,10 @@
 // to the accumulators in registers.  The kernel families:
 //   qgemm_big, qgemm_w4_big (qgemm_big.hip, qgemm_w4_big.hip) tiles of up to 256x288: 8-bit weights and binary16 operands,
 //               and packed 4-bit weights with groups of 128
-//   qgemm_dma   (here) tiles of 64x64 to 256x192 go global -> LDS by DMA through rings of 2-3 stages, optional
-//               persistent walk over tiles; 8-bit weights, and binary16 operands for the layers a plan leaves in FP16
-//   qgemm_w4    (qgemm_w4.hip) group scales: packed 4-bit weights and int8 codes with group scales
+//   qgemm_dma   (launched here, the tile in qgemm_dma.h) tiles of 64x64 to 256x192 go global -> LDS by DMA through rings of 2-3 stages,
+//               optional persistent walk over tiles; 8-bit weights, and binary16 operands for the layers a plan leaves in FP16
+//   qgemm_w4    (qgemm_w4.hip, the tile in qgemm_w4.h) group scales: packed 4-bit weights and int8 codes with group scales
+//   qgemm_many  (qgemm_many.hip) 128x128 tiles of these two for several layers of a plan in one launch
 //   qgemm_k64   (here) 8-bit layers of many tiles whose inner size is an odd multiple of 64
 //   qgemm_splitk, qgemm_edge (qgemm_small.hip) few rows; any inner size and alignment
 // plus a one-thread-per-element kernel: the tuning hooks' reference, and the last resort for channel-group activation

@@ -242,9 +242,10 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
         }
     };
     // Bookkeeping of a quarter that opens a group: the scales of the new group from LDS, for the next fold.  The channel groups' activation scales lie
-    // there too: read from memory here they held up every group (whole layers, us: M = 4096, K = 1152, N = 3456, groups of 128 43.1 -> 39.4, of 32 69.2 ->
-    // 58.1; M = 2048, N = 1152, groups of 32 30.6 -> 21.7).  Converted only at the fold, out of registers that keep them as they were read, they
-    // cost the 128x128 tiles 1 to 5 % (M = 8192, N = 4608, packed, groups of 32 106 -> 112): more registers are spilled.
+    // there too: with a read from memory in this place every group waits for all loads of the ring, also in layers without such scales, because the
+    // compiler waits with vmcnt(0) where the paths meet (whole layers, us: M = 4096, K = 1152, N = 3456, groups of 128 43.1 -> 39.4, of 32 69.2 -> 58.1;
+    // M = 2048, N = 1152, groups of 32 30.6 -> 21.7).  Converted only at the fold, out of registers that keep them as they were read, they cost the
+    // 128x128 tiles 1 to 5 % (M = 8192, N = 4608, packed, groups of 32 106 -> 112): more registers are spilled.
     auto open_group = [&]() {
         grp_acc = grp_next;
 #pragma unroll

@@ -116,9 +116,9 @@ hipError_t launch_qgemm_w4_128(const GemmArgs &a, hipStream_t stream)
 // than 40 groups leave the large tiles one workgroup per CU.  M = 2048, K = 4608, N = 1152, group 128: 28 against 34 us; M = 8192: 80
 // against 74; group 32: 134 against 198.
 // Int8 codes leave three small workgroups per CU instead of four: where those take more than two rounds (of 768) and the large tiles one (of
-// 512), the large ones.  K = 1152, us, 64x64 -> 128x128: M = 2048, N = 3456 29.0 -> 24.1 (groups of 32 37.4 -> 35.4), M = 1536, N = 4608 29.6
-// -> 24.6; but two rounds against one, M = 4096, N = 1152 26.6 -> 25.7 (groups of 32 33.5 -> 37.0), and three against two, M = 2048, N = 4608
-// 34.0 -> 34.5.
+// 512), the large ones.  Over the 13 such (M, N) of 1280 to 8192 rows and 640 to 4608 columns, eight K from 256 to 1536 and groups of 32 and 128, layers without
+// channel scales take 0.82 to 0.93 of their time on 64x64 tiles in the mean, at most 0.98 (K = 1152, M = 2048, N = 3456 29.0 -> 24.1 us).  Two rounds against
+// one and three against two are level: K = 1152, M = 4096, N = 1152 26.6 -> 25.7, but groups of 32 33.5 -> 37.0; M = 2048, N = 4608 34.0 -> 34.5.
 hipError_t launch_qgemm_w4(const GemmArgs &a, hipStream_t stream)
 {
     const long long tiles = (long long)((a.M + 63) / 64) * ((a.N + 63) / 64);

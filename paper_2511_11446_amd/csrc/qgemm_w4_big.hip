@@ -14,8 +14,9 @@
 //     scales by DMA and the stores straight from registers are those of qgemm_big.
 //   - Within a K step, which k an MFMA multiplies is free as long as both operands agree: lane quarter c holds k = 32 c .. 32 c + 31,
 //     so that a lane reads the packed weights of both MFMAs at once (16 bytes).
-// At M = 16384 the vector ALU is busy 69 % of the kernel, the matrix cores 34 %, and LDS bank conflicts take 15 % of the CU cycles: the group
-// scales are 2-byte reads, G values apart between neighbouring columns (profiles/qgemm_big_qgemm_w4_big_c5_stack_m16384_sq_counters.txt).
+// At M = 16384 the vector ALU is busy 69 % of the kernel, the matrix cores 34 %, and LDS bank conflicts take 15 % of the CU cycles
+// (profiles/qgemm_big_qgemm_w4_big_c5_stack_m16384_sq_counters.txt).  The 16 lanes of a group-scale read hold columns 8 apart, hence lie 16 G bytes
+// apart: on 16 different banks where G is odd (K = 1152), on 4 of the 64 where G = 36 (K = 4608).
 // Same bits as qgemm_w4.  M = 16384, random operands, us against its 128x128 tiles: K = 1152: N = 1152 36 -> 32, N = 3456 94 -> 87,
 // N = 4608 126 -> 115; K = 4608, N = 1152 111 -> 100.
 #include "qgemm_common.h"

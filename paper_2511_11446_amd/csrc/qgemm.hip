@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256) void qgemm_naive(GemmArgs a)
         float s = 0.0f;
         for (int k = 0; k < K; ++k) s = __builtin_fmaf(half_to_float_dev(xr[k]), half_to_float_dev(wr[k]), s);
         const float u16 = s + b;
-        static_cast<_Float16 *>(a.y)[(size_t)m * a.N + n] = has_glue(a) ? glue_one(a, u16, m, n, a.gate ? m / a.gate_rows : 0) : (_Float16)u16;
+        static_cast<_Float16 *>(a.y)[(size_t)m * a.N + n] = has_glue(a) ? glue_one(a, u16, m, glue_terms(a, m, n, a.gate ? m / a.gate_rows : 0)) : (_Float16)u16;
         return;
     }
     const float sa = a.s_ag ? 1.0f : a.s_a[m / a.R];
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256) void qgemm_naive(GemmArgs a)
         }
         u = bias ? __builtin_fmaf(f, sa, b) : f * sa;
     }
-    static_cast<_Float16 *>(a.y)[(size_t)m * a.N + n] = has_glue(a) ? glue_one(a, u, m, n, a.gate ? m / a.gate_rows : 0) : (_Float16)u;
+    static_cast<_Float16 *>(a.y)[(size_t)m * a.N + n] = has_glue(a) ? glue_one(a, u, m, glue_terms(a, m, n, a.gate ? m / a.gate_rows : 0)) : (_Float16)u;
 }
 
 // ---- variants -----------------------------------------------------------------
@@ -395,8 +395,8 @@ static const TileCost TILE_COSTS[] = {
 struct GlueCost {
     float act, gated, big_act, big_gated, edge, edge_act, edge_gated;
 };
-static const GlueCost GLUE_W8 = {0.537f, 0.838f, 1.316f, 2.061f, 0.069f, 0.422f, 0.630f};
-static const GlueCost GLUE_F16 = {0.671f, 1.080f, 1.425f, 3.027f, 0.007f, 0.298f, 0.800f};
+static const GlueCost GLUE_W8 = {0.537f, 0.838f, 1.316f, 2.061f, 0.069f, 0.05f, 0.5f};
+static const GlueCost GLUE_F16 = {0.671f, 1.080f, 1.425f, 3.027f, 0.007f, 0.05f, 0.63f};
 static const GlueCost GLUE_W4 = {0.834f, 1.750f, 1.002f, 3.037f, 0.045f, 0.193f, 0.835f};
 
 static int choose_tile(const GemmArgs &a, bool glue, float *us = nullptr)

@@ -358,38 +358,19 @@ __device__ __forceinline__ void qgemm_dma_tiles(const GemmArgs &a, int block, in
         if (GLUE && a.act == 1) emit_fast(std::true_type{});
         else emit_fast(std::false_type{});
     } else {
-        auto emit = [&](auto edge) {
-            constexpr bool EDGE = decltype(edge)::value;
+        const GateRows gate_rows(GLUE ? a.gate : nullptr, a.gate_rows, em0, BM);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = en0 + wn * TN * 32 + j * 32 + frag_row;
-                const bool n_ok = !EDGE || n < N;
-                const float b = bj[j];
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int row = wm * TM * 32 + i * 32 + 8 * (r / 4) + 4 * frag_half + (r % 4);
-                        const int m = em0 + row;
-                        if (!EDGE || (m < M && n_ok)) {
-                            const unsigned off = (unsigned)(m * N + n);
-                            float u;
-                            if (F16) {
-                                u = (float)acc[i][j][r] + b;
-                            } else {
-                                const float t = (float)acc[i][j][r] * sRow[row];
-                                u = bias ? __builtin_fmaf(t, swt[j], b) : t * swt[j];
-                                if (a.acc_out) a.acc_out[off] = (int)acc[i][j][r];
-                            }
-                            asm volatile("" : "+v"(u));   // keep the fp32 rounding before the fp16 one
-                            if (GLUE) y[off] = glue_one(a, u, m, n, GateRows(a.gate, a.gate_rows, em0, BM).of(row));
-                            else y[off] = (_Float16)u;
-                        }
-                    }
+            for (int i = 0; i < TM; ++i) {
+                const int row = wm * TM * 32 + i * 32 + 4 * frag_half;
+                store_column<GLUE>(a, gate_rows, em0, row, en0 + wn * TN * 32 + j * 32 + frag_row, [&](int r, unsigned off) {
+                    if (F16) return (float)acc[i][j][r] + bj[j];
+                    const float t = (float)acc[i][j][r] * sRow[row + 8 * (r / 4) + r % 4];
+                    if (a.acc_out) a.acc_out[off] = (int)acc[i][j][r];
+                    return bias ? __builtin_fmaf(t, swt[j], bj[j]) : t * swt[j];
+                });
             }
-        };
-        if (full) emit(std::false_type{});
-        else emit(std::true_type{});
     }
     QL_PHASE(4)
     if (!has_next) break;

@@ -203,6 +203,14 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
     }
     const unsigned short bias_h = a.bias ? static_cast<const unsigned short *>(a.bias)[n_in] : (unsigned short)0;
     const float sw = KIND == OP_I8 ? static_cast<const float *>(a.s_w)[n_in] : 1.0f;
+    GlueTerms terms[EPT];
+    if (GLUE) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int m = min(m0 + row_of(e), M - 1);
+            terms[e] = glue_terms(a, m, n_in, a.gate ? m / a.gate_rows : 0);
+        }
+    }
     // FUSE: the codes of the tile's rows, [K step][row][128 bytes] with the chunks of a row swizzled as in the rings, and the
     // rows' scales
     unsigned char *resident = reinterpret_cast<unsigned char *>(ctab + (GROUPED ? T * G : 0));
@@ -451,7 +459,7 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
         else u = dequant_one<KIND>(a, sum[e], 0.0f, sa[e], sw, b);
         if constexpr (KIND == OP_I8 && EXPORT) a.acc_out[(size_t)m * N + n] = sum[e];
         asm volatile("" : "+v"(u));   // keep the fp32 rounding before the fp16 one
-        static_cast<_Float16 *>(a.y)[(size_t)m * N + n] = GLUE ? glue_one(a, u, m, n, a.gate ? m / a.gate_rows : 0) : (_Float16)u;
+        static_cast<_Float16 *>(a.y)[(size_t)m * N + n] = GLUE ? glue_one(a, u, m, terms[e]) : (_Float16)u;
     }
 }
 
@@ -653,25 +661,17 @@ __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void qgemm_edge(GemmArgs
             store_tile_staged<TM, TN, true, 32>(strip, lane, y, N, m0 + wm * TM * 32, n0 + wn * TN * 32, value, gl);
         return;
     }
-    const GateRows gr(a.gate, a.gate_rows, m0, BM);
+    const GateRows gate_rows(GLUE ? a.gate : nullptr, a.gate_rows, m0, BM);
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = wm * TM * 32 + i * 32 + 8 * (r / 4) + 4 * half + (r % 4);
-                const int m = m0 + row, n = n0 + wn * TN * 32 + j * 32 + fr;
-                if (m < M && n < N) {
-                    const unsigned off = (unsigned)(m * N + n);
-                    float u = value(i, j, r);
-                    if constexpr (KIND == OP_I8) {
-                        if (a.acc_out) a.acc_out[off] = acc[i][j][r];
-                    }
-                    asm volatile("" : "+v"(u));   // keep the fp32 rounding before the fp16 one
-                    y[off] = GLUE ? glue_one(a, u, m, n, gr.of(row)) : (_Float16)u;
+            store_column<GLUE>(a, gate_rows, m0, wm * TM * 32 + i * 32 + 4 * half, n0 + wn * TN * 32 + j * 32 + fr, [&](int r, unsigned off) {
+                if constexpr (KIND == OP_I8) {
+                    if (a.acc_out) a.acc_out[off] = acc[i][j][r];
                 }
-            }
+                return value(i, j, r);
+            });
 }
 
 // ---- launches ------------------------------------------------------------------------------------------------------

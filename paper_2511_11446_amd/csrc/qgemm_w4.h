@@ -436,25 +436,17 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
             if (GLUE && a.act == 1) emit_fast(std::true_type{});
             else emit_fast(std::false_type{});
         } else {
+            const GateRows gate_rows(GLUE ? a.gate : nullptr, a.gate_rows, em0, BM);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = en0 + wn * TN * 32 + j * 32 + frag_row;
+            for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int row = wm * TM * 32 + i * 32 + 8 * (r / 4) + 4 * frag_half + (r % 4);
-                        const int m = em0 + row;
-                        if (m < M && n < N) {
-                            const float f = fsum[i][j][r];
-                            float u = a.bias ? __builtin_fmaf(f, sRow[row], bj[j]) : f * sRow[row];
-                            asm volatile("" : "+v"(u));   // keep the fp32 rounding before the fp16 one
-                            const unsigned off = (unsigned)(m * N + n);
-                            if (GLUE) y[off] = glue_one(a, u, m, n, GateRows(a.gate, a.gate_rows, em0, BM).of(row));
-                            else y[off] = (_Float16)u;
-                        }
-                    }
-            }
+                for (int i = 0; i < TM; ++i) {
+                    const int row = wm * TM * 32 + i * 32 + 4 * frag_half;
+                    store_column<GLUE, TM == 1 ? 16 : 4>(a, gate_rows, em0, row, en0 + wn * TN * 32 + j * 32 + frag_row, [&](int r, unsigned) {
+                        const float f = fsum[i][j][r], sa = sRow[row + 8 * (r / 4) + r % 4];
+                        return a.bias ? __builtin_fmaf(f, sa, bj[j]) : f * sa;
+                    });
+                }
         }
         if (!has_next) break;
         __syncthreads();   // the epilogue's scratch is free again: the rest of the next prologue may overwrite it

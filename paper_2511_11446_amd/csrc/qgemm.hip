@@ -8,7 +8,8 @@
 //   qgemm_big, qgemm_w4_big (qgemm_big.hip, qgemm_w4_big.hip) tiles of up to 256x288: 8-bit weights and binary16 operands,
 //               and packed 4-bit weights with groups of 128
 //   qgemm_dma   (launched here, the tile in qgemm_dma.h) tiles of 64x64 to 256x192 go global -> LDS by DMA through rings of 2-3 stages,
-//               optional persistent walk over tiles; 8-bit weights, and binary16 operands for the layers a plan leaves in FP16
+//               optional persistent walk over tiles; 8-bit weights, and binary16 operands for the layers a plan leaves in FP16; two of
+//               the tiles take rows of any whole number of words
 //   qgemm_w4    (qgemm_w4.hip, the tile in qgemm_w4.h) group scales: packed 4-bit weights and int8 codes with group scales
 //   qgemm_many  (qgemm_many.hip) 128x128 tiles of these two for several layers of a plan in one launch
 //   qgemm_k64   (here) 8-bit layers of many tiles whose inner size is an odd multiple of 64
@@ -163,13 +164,13 @@ static bool k64_takes(const GemmArgs &a)
     return a.w_bits == 8 && !a.w_grouped && !a.s_ag && !glue && a.K % 64 == 0 && ((uintptr_t)a.q | (uintptr_t)a.w) % 16 == 0;
 }
 
-// Where it is the faster one: more tiles than CUs (320 tiles: 10 to 25 % faster than qgemm_edge, 240: 15 to 45 % slower) and whole tile
-// columns; others are written element by element, which only a long K and more than two tiles per CU outweigh (N = 1000: M = 8192, K =
+// Where it is the faster one: more tiles than CUs (320 tiles: 10 to 25 % faster than qgemm_edge, 240: 15 to 45 % slower), not very many (640
+// tiles, K = 2240: 45 us against 47 of the DMA tile for any K, 1280: 82 against 73) and whole tile columns; others are written element by element, which only a long K and more than two tiles per CU outweigh (N = 1000: M = 8192, K =
 // 192 22.5 against 19.5 us, K = 2240 53 against 51; M = 16384, K = 2240 91 against 97).
 static bool k64_wins(const GemmArgs &a)
 {
     const long tiles = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-    return k64_takes(a) && tiles > 256 && (a.N % 128 == 0 || (a.K >= 2048 && tiles > 512));
+    return k64_takes(a) && tiles > 256 && tiles <= 1024 && (a.N % 128 == 0 || (a.K >= 2048 && tiles > 512));
 }
 
 static hipError_t run_k64(const GemmArgs &a, hipStream_t s)
@@ -287,6 +288,18 @@ using H_64x64_4w = TileD<1, 1, 2, 2, 3, 4, true, 0, 3, false, true>;
 using H_p192 = TileD<2, 3, 2, 2, 2, 2, true, 1, 2, true, true>;
 using H_p128 = TileD<2, 2, 2, 2, 3, 2, true, 1, 2, true, true>;
 
+//                                                                                            rows of any whole number of words
+using K8_64x64 = TileD<1, 1, 2, 2, 3, 4, true, 0, 3, false, false, true>;
+using K8_128x128 = TileD<2, 2, 2, 2, 3, 2, true, 1, 2, false, false, true>;
+using KH_64x64 = TileD<1, 1, 2, 2, 3, 4, true, 0, 3, false, true, true>;
+using KH_128x128 = TileD<2, 2, 2, 2, 3, 2, true, 1, 2, false, true, true>;
+
+static bool any_k_takes(const GemmArgs &a)
+{
+    const long kb = (long)a.K * (a.w_bits == 16 ? 2 : 1);
+    return (a.w_bits == 8 || a.w_bits == 16) && !a.w_grouped && !a.s_ag && kb % 4 == 0 && kb >= 16 && ((uintptr_t)a.q | (uintptr_t)a.w) % 4 == 0;
+}
+
 static const Variant VARIANTS[] = {
     {"w8 dma 64x64 s3 4w", 8, dma_takes, run_dma<D8_64x64_s3>, run_dma<D8_64x64_s3, true>},
     {"w8 dma 256x192 a3b2 8w spread1", 8, dma_takes, run_dma<D8_256x192_8w_a3b2>, run_dma<D8_256x192_8w_a3b2, true>},
@@ -318,6 +331,10 @@ static const Variant VARIANTS[] = {
     {"w4 any-group edge any-K", 4, qgemm_edge_takes, launch_qgemm_edge, launch_qgemm_edge},
     {"f16 edge any-K", 16, qgemm_edge_takes, launch_qgemm_edge, launch_qgemm_edge},
     {"w8 staged 128x128 k64", 8, k64_takes, run_k64},
+    {"w8 dma any-K 64x64 s3 4w", 8, any_k_takes, run_dma<K8_64x64>, run_dma<K8_64x64, true>},
+    {"w8 dma any-K 128x128 a3b2 4w spread1", 8, any_k_takes, run_dma<K8_128x128>, run_dma<K8_128x128, true>},
+    {"f16 dma any-K 64x64 s3 4w", 16, any_k_takes, run_dma<KH_64x64>, run_dma<KH_64x64, true>},
+    {"f16 dma any-K 128x128 a3b2 4w spread1", 16, any_k_takes, run_dma<KH_128x128>, run_dma<KH_128x128, true>},
 #ifdef QL_SWEEP_VARIANTS   // the other tile shapes of the sweeps that chose the ones above
     {"w8 dma 128x128 s3 4w", 8, dma_takes, run_dma<D8_128x128_s3>},
     {"w8 dma 128x128 s2 4w", 8, dma_takes, run_dma<D8_128x128_s2>},
@@ -364,6 +381,12 @@ static int find_variant(const char *name)
 // 43 %.  Rules that charged the large tiles per round and the others by their rate, without the glue, lost 2 % (4 bits) to 6 % (FP16) in
 // the mean of the plain layers and 5 to 17 % with gate and residual (8-bit, M = 8192, K = 256, N = 1024: 40.7 us against 14.3).
 // profiles/tile_choice_sweep.txt holds the part of the data with the common widths.
+struct GlueCost {
+    float act, gated, big_act, big_gated, edge, edge_act, edge_gated;
+};
+static const GlueCost GLUE_W8 = {0.537f, 0.838f, 1.316f, 2.061f, 0.069f, 0.05f, 0.5f};
+static const GlueCost GLUE_F16 = {0.671f, 1.080f, 1.425f, 3.027f, 0.007f, 0.05f, 0.63f};
+static const GlueCost GLUE_W4 = {0.834f, 1.750f, 1.002f, 3.037f, 0.045f, 0.193f, 0.835f};
 struct TileCost {
     const char *name;
     int bits, BM, BN, resident;
@@ -386,19 +409,21 @@ static const TileCost TILE_COSTS[] = {
     {"f16 dma 256x192 a3b2 8w spread1", 16, 256, 192, 1, 0.275f, 5.430f, 1.129f, 0, 0, 0, 4.768f},
     {"f16 big 256x256", 16, 256, 256, 1, 1.395f, 4.703f, 1.423f, 0, 0, 0, 0.007f},
     {"f16 big 256x288", 16, 256, 288, 1, 0, 6.117f, 1.753f, 0, 0, 0, 0.331f},
+    // rows that are no whole K steps: the DMA tiles as above, qgemm_edge where the rows are a few steps only (its 128x128 tiles, from 512 of them on,
+    // are never the faster ones).  us, DAQ and GEMM, qgemm_edge -> chosen, M x K x N: 8-bit 1021 x 1160 x 1000 16.5 -> 13.0, 1021 x 2244 x 1000 42 -> 32, 8192 x
+    // 1160 x 2560 59 -> 50, 64 x 1000 x 77 12.9 -> 9.5; FP16 2047 x 2244 x 1000 36 -> 25, 4096 x 1160 x 2560 55 -> 42; 8-bit 4096 x 200 x 1200 13.5 -> 13.1
+    {"w8 dma any-K 64x64 s3 4w", 8, 64, 64, 3, 4.685f, 0, 0.133f, 0, 0.154f, 0, 0.890f},
+    {"w8 dma any-K 128x128 a3b2 4w spread1", 8, 128, 128, 2, 3.178f, 1.466f, 0.183f, 0, 0.399f, 0, 1.163f},
+    {"w8 edge any-K", 8, 64, 64, 4, 3.985f, 0.173f, 0.024f, 0, 0.748f, 0, 0},
+    {"f16 dma any-K 64x64 s3 4w", 16, 64, 64, 3, 3.430f, 0.196f, 0.215f, 0, 0.120f, 0, 0.303f},
+    {"f16 dma any-K 128x128 a3b2 4w spread1", 16, 128, 128, 2, 4.531f, 0.388f, 0.458f, 0, 0.173f, 0, 2.030f},
+    {"f16 edge any-K", 16, 64, 64, 4, 1.656f, 0.341f, 0.082f, 0, 0.702f, 0, 0},
     {"w4 pipelined 64x64 a3b2 4w any-group", 4, 64, 64, 4, 4.803f, 0.011f, 0.058f, 0.043f, 0.336f, 0.013f, 0.407f},
     {"w4 pipelined 128x128 a3b2 4w any-group", 4, 128, 128, 2, 4.365f, 1.245f, 0.079f, 0.095f, 0.536f, 0.170f, 0.245f},
     {"w4 big 128x288", 4, 128, 288, 1, 5.977f, 5.191f, 1.495f, 0, 0, 0, 0.347f},
     {"w4 big 256x256", 4, 256, 256, 1, 6.465f, 3.934f, 2.029f, 0, 0, 0, 0.024f},
     {"w4 big 256x288", 4, 256, 288, 1, 12.968f, 0.069f, 2.318f, 0, 0, 0, 4.782f},
 };
-struct GlueCost {
-    float act, gated, big_act, big_gated, edge, edge_act, edge_gated;
-};
-static const GlueCost GLUE_W8 = {0.537f, 0.838f, 1.316f, 2.061f, 0.069f, 0.05f, 0.5f};
-static const GlueCost GLUE_F16 = {0.671f, 1.080f, 1.425f, 3.027f, 0.007f, 0.05f, 0.63f};
-static const GlueCost GLUE_W4 = {0.834f, 1.750f, 1.002f, 3.037f, 0.045f, 0.193f, 0.835f};
-
 static int choose_tile(const GemmArgs &a, bool glue, float *us = nullptr)
 {
     constexpr int COUNT = sizeof(TILE_COSTS) / sizeof(TILE_COSTS[0]), CUS_PER_XCD = 32;
@@ -411,7 +436,8 @@ static int choose_tile(const GemmArgs &a, bool glue, float *us = nullptr)
     const GlueCost &g = a.w_bits == 8 ? GLUE_W8 : a.w_bits == 4 ? GLUE_W4 : GLUE_F16;
     const float act = a.act != 0 || (glue && !a.gate && !a.residual) ? 1.0f : 0.0f, gated = a.gate || a.residual ? 1.0f : 0.0f;
     const int groups = a.w_bits == 4 ? a.K / a.group : 0;
-    const float steps = (float)(a.K * (a.w_bits == 16 ? 2 : 1) / 128), folds = (float)groups;
+    const float steps = (float)((a.K * (a.w_bits == 16 ? 2 : 1) + 127) / 128), folds = (float)groups;
+    const bool any_k = a.w_bits != 4 && !dma_takes(a);
     // outputs that no 16-byte piece reaches are written value by value everywhere
     const bool pieces = a.N % 8 == 0 && ((uintptr_t)a.y | (uintptr_t)a.gate | (uintptr_t)a.residual) % 16 == 0;
     int best = -1;
@@ -420,7 +446,10 @@ static int choose_tile(const GemmArgs &a, bool glue, float *us = nullptr)
         const TileCost &t = TILE_COSTS[i];
         const Variant &v = VARIANTS[variants[i]];
         if (t.bits != a.w_bits || (glue && !v.run_glue)) continue;
-        const bool big = v.takes != dma_takes && v.takes != qgemm_w4_takes;
+        const bool edge = v.takes == qgemm_edge_takes;
+        if ((edge || v.takes == any_k_takes) != any_k) continue;
+        if (edge && (long)((a.M + 127) / 128) * ((a.N + 127) / 128) >= 512) continue;
+        const bool big = !any_k && v.takes != dma_takes && v.takes != qgemm_w4_takes;
         if (big && !big_takes) continue;
         if (groups > 40 && t.BM == 128) continue;   // the large scale table leaves such a tile one workgroup per CU (134 against 198 us at 144 groups)
         const long tiles = (long)((a.M + t.BM - 1) / t.BM) * ((a.N + t.BN - 1) / t.BN);
@@ -472,7 +501,7 @@ hipError_t launch_qgemm(const GemmArgs &a, int variant, hipStream_t stream)
     auto usable = [&](const Variant &v) { return v.w_bits == a.w_bits && v.takes(a) && (!glue || v.run_glue); };
     int v = variant;
     if (v < 0 || !usable(VARIANTS[v])) {
-        if (split || !(a.w_bits == 4 ? qgemm_w4_takes(a) : dma_takes(a))) return small();
+        if (split || !(a.w_bits == 4 ? qgemm_w4_takes(a) : dma_takes(a) || (any_k_takes(a) && !k64_wins(a)))) return small();
         v = choose_tile(a, glue);
     }
     return glue ? VARIANTS[v].run_glue(a, stream) : VARIANTS[v].run(a, stream);

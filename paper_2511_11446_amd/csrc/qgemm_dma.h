@@ -16,13 +16,15 @@ namespace ql {
 // the next quarter, the hand-over barrier and the next DMA issue all sit behind an MFMA that is
 // already executing.
 // ---------------------------------------------------------------------------------------------
-template <int TM_, int TN_, int WGM_, int WGN_, int S_, int WPS_, bool STG_ = true, int EV_ = 0, int SB_ = S_, bool PERSIST_ = false, bool F16_ = false>
+template <int TM_, int TN_, int WGM_, int WGN_, int S_, int WPS_, bool STG_ = true, int EV_ = 0, int SB_ = S_, bool PERSIST_ = false, bool F16_ = false, bool ANYK_ = false>
 struct TileD {
     static constexpr int TM = TM_, TN = TN_, WGM = WGM_, WGN = WGN_, WPS = WPS_;
     // ring depth of the activation tile and of the weight tile (K steps resident or in flight); they may differ by one
     static constexpr int SA = S_, SB = SB_;
     // both operands binary16 (a layer the plan leaves unquantized): one K step is 64 values = the same 128 bytes per row
     static constexpr bool F16 = F16_;
+    // rows of any whole number of words, at least 16 bytes: their last K step may be cut short
+    static constexpr bool ANYK = ANYK_;
     static constexpr int NW = WGM * WGN, NT = NW * 64;
     static constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32, BK = 128;
     // 1024-byte DMA groups per K step: 8 rows x 128 B
@@ -88,7 +90,7 @@ __device__ __forceinline__ void qgemm_dma_tiles(const GemmArgs &a, int block, in
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keep it in a scalar register
     const int wm = wave / T::WGN, wn = wave % T::WGN;
     const int M = a.M, N = a.N, K = a.K;
-    const int nk = K * EB / 128;   // K steps (128 bytes per row)
+    const int nk = T::ANYK ? (K * EB + 127) / 128 : K * EB / 128;   // K steps (128 bytes per row)
     QL_PHASE(0)
 
     // Everything the epilogue needs from global memory is requested now, ahead of the first DMA (the oldest loads
@@ -127,12 +129,18 @@ __device__ __forceinline__ void qgemm_dma_tiles(const GemmArgs &a, int block, in
         }
     };
     set_goff();
+    // ANYK: a piece of the last K step that crosses or lies behind the end of its row reads the row's last 16 bytes instead
+    auto back = [&](int kt, int i) {
+        if (!T::ANYK || kt + 1 < nk) return 0u;
+        const int over = kt * 128 + 16 * ((lane & 7) ^ ((4 * (wave + i * NW) + (lane >> 4)) & 7)) + 16 - K * EB;
+        return (unsigned)max(over, 0);
+    };
     auto issue_a = [&](int kt, int slot, int i) {
-        __builtin_amdgcn_global_load_lds((global_void *)(a.q + (size_t)kt * 128 + goffA[i]),
+        __builtin_amdgcn_global_load_lds((global_void *)(a.q + (size_t)kt * 128 + goffA[i] - back(kt, i)),
                                          (lds_void *)(smem + slot * T::A_BYTES + (wave + i * NW) * 1024), 16, 0, 0);
     };
     auto issue_b = [&](int kt, int slot, int i) {
-        __builtin_amdgcn_global_load_lds((global_void *)(static_cast<const int8_t *>(a.w) + (size_t)kt * 128 + goffB[i]),
+        __builtin_amdgcn_global_load_lds((global_void *)(static_cast<const int8_t *>(a.w) + (size_t)kt * 128 + goffB[i] - back(kt, i)),
                                          (lds_void *)(smem + T::B_RING + slot * T::B_BYTES + (wave + i * NW) * 1024), 16, 0, 0);
     };
     // Refill window j = the loads issued after the hand-over barrier of K step j, into the slots that step used:
@@ -146,6 +154,25 @@ __device__ __forceinline__ void qgemm_dma_tiles(const GemmArgs &a, int block, in
         } else {
             if (j + SA < nk) issue_a(j + SA, slot_a, B_FIRST ? li - NB : li);
         }
+    };
+    // ANYK, once the last K step is in LDS (slots sl_a and sl_b) and before it is read: what its pieces hold twice, or from behind the end of
+    // the row, becomes zero; in one operand for integers, in both for binary16, where 0 * Inf is not 0
+    auto clear_behind = [&](int sl_a, int sl_b) {
+        const int left = K * EB - (nk - 1) * 128, first = left / 16, again = 16 - left % 16;   // again: bytes of piece `first` that are there twice
+        auto clear = [&](unsigned char *st, int rows) {
+            for (int e = tid; e < rows * 8; e += NT) {
+                const int row = e >> 3, c = e & 7;
+                if (c < first) continue;
+                int *p = reinterpret_cast<int *>(st + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    if (c > first || 4 * w < again) p[w] = 0;
+            }
+        };
+        if (left == 128) return;
+        clear(smem + sl_a * T::A_BYTES, BM);
+        if (F16) clear(smem + T::B_RING + sl_b * T::B_BYTES, BN);
+        __syncthreads();
     };
     auto wait_vm = [&](auto n_tag) {
         constexpr int n = decltype(n_tag)::value;
@@ -241,6 +268,7 @@ __device__ __forceinline__ void qgemm_dma_tiles(const GemmArgs &a, int block, in
     if (nk >= T::SMAX) wait_vm(std::integral_constant<int, T::WAIT_START>{});
     else wait_vm(std::integral_constant<int, 0>{});
     __builtin_amdgcn_s_barrier();
+    if (T::ANYK && nk == 1) clear_behind(0, 0);
     read_frags(0, 0, 0, af0, bf0);
     int sa = 0, sb = 0, pa = SA - 1, pb = SB - 1;   // ring slots of K step kt and of step kt-1
     for (int kt = 0; kt < nk; ++kt) {
@@ -275,6 +303,7 @@ __device__ __forceinline__ void qgemm_dma_tiles(const GemmArgs &a, int block, in
         if (kt + T::SMAX <= nk) wait_vm(std::integral_constant<int, T::WAIT_HAND>{});
         else wait_vm(std::integral_constant<int, 0>{});
         __builtin_amdgcn_s_barrier();
+        if (T::ANYK && kt + 2 == nk) clear_behind(na, nb);
         if (!SPREAD) {
 #pragma unroll
             for (int li = 0; li < NA + NB; ++li) issue_win(kt, sa, sb, li);

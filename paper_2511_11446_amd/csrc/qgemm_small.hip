@@ -1,8 +1,8 @@
 // GEMM + dequantization for the shapes the pipelined kernels do not serve well, for gfx950:
 //
 //   qgemm_splitk   few rows: 32x32 or 16x16 output tiles, K split over the four wavefronts of a workgroup
-//   qgemm_edge     an inner size or an alignment that the DMA kernels do not take: workgroup tiles staged through registers,
-//                the last K step padded with zeros.  Its 16-byte loads may be misaligned (the hardware splits them), and a
+//   qgemm_edge     an inner size or an alignment that the DMA kernels do not take, and rows of a few K steps that are no whole ones:
+//                workgroup tiles staged through registers, the last K step padded with zeros.  Its 16-byte loads may be misaligned (the hardware splits them), and a
 //                piece that crosses the end of a row is read byte by byte, so that no access leaves the operand.
 //
 // Both take 8-bit weights, packed 4-bit weights, int8 codes with group scales and binary16 operands.

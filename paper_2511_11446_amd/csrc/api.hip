@@ -377,7 +377,7 @@ void plan_window(const ql_layer_desc *layers, size_t n_layers, size_t first, con
             f.x = x_in[l];
             f.partmax = it.partmax;
             f.parts = R == 1 ? 0 : (int)daq_parts_per_block(d.K, R);
-            if (qgemm_fuse_takes(f)) break;
+            if (qgemm_fuse_one_tile(f)) break;
         }
         w.daq.l[w.daq.count++] = it;
         used += lw.total;

@@ -88,6 +88,22 @@ __device__ __forceinline__ GlueTerms glue_terms(const GemmArgs &a, int m, int n,
     return t;
 }
 
+// The same of C elements of column n, row m_of(e), gate row gate_row(m): whether there are any is asked once, so that all are on their way together
+template <int C, class RowFn, class GateFn>
+__device__ __forceinline__ void request_glue(const GemmArgs &a, GlueTerms (&t)[C], int n, RowFn m_of, GateFn gate_row)
+{
+#pragma unroll
+    for (int e = 0; e < C; ++e) t[e] = {0x3c00 /* 1 */, 0};
+    if (a.gate) {
+#pragma unroll
+        for (int e = 0; e < C; ++e) t[e].g = static_cast<const unsigned short *>(a.gate)[(unsigned)(gate_row(m_of(e)) * a.N + n)];
+    }
+    if (a.residual) {
+#pragma unroll
+        for (int e = 0; e < C; ++e) t[e].r = static_cast<const unsigned short *>(a.residual)[(unsigned)(m_of(e) * a.N + n)];
+    }
+}
+
 // one element of row m: u is the layer's fp32 value
 __device__ __forceinline__ _Float16 glue_one(const GemmArgs &a, float u, int m, GlueTerms t)
 {
@@ -114,13 +130,9 @@ __device__ __forceinline__ void store_column(const GemmArgs &a, const GateRows &
 #pragma unroll
     for (int first = 0; first < 16; first += AHEAD) {
         GlueTerms t[AHEAD];
-        if (GLUE && (a.gate || a.residual)) {
-#pragma unroll
-            for (int e = 0; e < AHEAD; ++e) {
-                const int m = min(m_first + row + 8 * ((first + e) / 4) + (first + e) % 4, a.M - 1);
-                t[e] = glue_terms(a, m, min(n, a.N - 1), a.gate ? gate_rows.of(max(m - m_first, 0)) : 0);
-            }
-        }
+        if (GLUE)
+            request_glue<AHEAD>(a, t, min(n, a.N - 1), [&](int e) { return min(m_first + row + 8 * ((first + e) / 4) + (first + e) % 4, a.M - 1); },
+                                [&](int m) { return gate_rows.of(max(m - m_first, 0)); });
 #pragma unroll
         for (int e = 0; e < AHEAD; ++e) {
             const int r = first + e, m = m_first + row + 8 * (r / 4) + r % 4;

@@ -1,6 +1,6 @@
 // GEMM + dequantization for the shapes the pipelined kernels do not serve well, for gfx950:
 //
-//   qgemm_splitk   few rows: 32x32 or 16x16 output tiles, K split over the four wavefronts of a workgroup
+//   qgemm_splitk   few rows: 32x32 or 16x16 output tiles, K split over the four or eight wavefronts of a workgroup
 //   qgemm_edge     an inner size or an alignment that the DMA kernels do not take, and rows of a few K steps that are no whole ones:
 //                workgroup tiles staged through registers, the last K step padded with zeros.  Its 16-byte loads may be misaligned (the hardware splits them), and a
 //                piece that crosses the end of a row is read byte by byte, so that no access leaves the operand.
@@ -78,14 +78,14 @@ __device__ __forceinline__ float dequant_one(const GemmArgs &a, int acc, float f
 }
 
 // ---- few rows ------------------------------------------------------------------------------------------------------
-// A workgroup of four wavefronts owns one T x T output tile (T = 32 or 16, one MFMA) and SPLITS K: every wavefront walks
+// A workgroup of W = 4 or 8 wavefronts owns NB neighbouring T x T output tiles (T = 32 or 16, one MFMA each) and SPLITS K: every wavefront walks
 // its own K steps, whose operand pieces go global -> LDS by DMA through a ring of its own, and waits for nobody until the
-// four partial results meet in LDS.
+// partial results meet in LDS.
 //
 // What bounds it: at these sizes neither bytes nor MFMAs but the chain launch -> first bytes -> serial walk over K ->
 // store.  The 64x64 workgroup tiles of the other kernels leave most CUs empty (M = 64, N = 1152: 18 workgroups) and pay
 // a workgroup hand-over for every K step of 128.  A wavefront's K step still costs some 400 cycles of latency (LDS
-// read, MFMA, fold), so the walk is cut into four.
+// read, MFMA, fold), so the walk is cut into four or eight.
 //
 // Group scales (4-bit weights, int8 codes with group scales): a wavefront takes whole groups and leaves every group's sum
 // in LDS; the fp32 sum over the groups, whose ascending order is part of the definition, is then taken by the thread that
@@ -93,36 +93,37 @@ __device__ __forceinline__ float dequant_one(const GemmArgs &a, int acc, float f
 //
 // FUSE: the activations arrive as fp16 and are quantized by the workgroup itself (Step 3, eq. (4) with tau = the absolute
 // maximum), its T rows of codes resident in LDS while only the weights pass through the rings.  The codes are
-// recomputed by every column tile - T * K / 256 elements per thread, about 0.8 us for 16 rows of 1152 - but a kernel launch
+// recomputed by every workgroup of the row - 36 elements per thread for 16 rows of 1152 - but a kernel launch
 // less is worth more: some 3.6 us of host time and 2.6-3.5 us of GPU time at these sizes.
-template <int KIND, int T, bool FUSE>
+// W wavefronts; NB tiles side by side; S: ring depth per wavefront
+template <int KIND, int T, bool FUSE, int W_ = 4, int NB_ = 1>
 struct SplitTile {
+    static constexpr int W = W_, NB = NB_, NTHR = 64 * W;
     static constexpr bool GROUPED = KIND == OP_W4 || KIND == OP_I8G;
-    static constexpr int A_GROUPS = FUSE ? 0 : T / 8, B_GROUPS = KIND == OP_W4 ? T / 16 : T / 8;   // 1024-byte DMA instructions per K step
+    static constexpr int A_GROUPS = FUSE ? 0 : T / 8, B_GROUPS = NB * (KIND == OP_W4 ? T / 16 : T / 8);   // 1024-byte DMA instructions per K step
     static constexpr int LOADS = A_GROUPS + B_GROUPS;
     static constexpr int STAGE = LOADS * 1024;
     // ring depth per wavefront: two workgroups' rings (and partial tiles) fit a CU
-    static constexpr int S = T == 32 ? 2 : GROUPED ? 3 : 4;
-    static constexpr int RINGS = 4 * S * STAGE;
-    static constexpr int TILE = T * T * 4;                      // one partial tile, bytes
+    static constexpr int S = T == 32 || W == 8 ? 2 : GROUPED ? 3 : 4;
+    static constexpr int TILE = NB * T * T * 4;                 // partial tiles of a wavefront or group, bytes
 };
 
 // EXPORT: the integer sums are also written to a.acc_out (verification)
-template <int KIND, int T, bool GLUE, bool EXPORT, bool FUSE>
-__global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, int tiles_n, int nblk_padded, int gpr, int rounds)
+template <int KIND, int T, bool GLUE, bool EXPORT, bool FUSE, int W, int NB>
+__global__ __launch_bounds__(64 * W, W == 8 && NB <= 2 ? 4 : 2) void qgemm_splitk(GemmArgs a, int tiles_m, int tiles_n, int nblk_padded, int gpr, int rounds, int slots)
 {
-    using W = SplitTile<KIND, T, FUSE>;
-    constexpr bool GROUPED = W::GROUPED;
+    using C = SplitTile<KIND, T, FUSE, W, NB>;
+    constexpr bool GROUPED = C::GROUPED;
     constexpr int EB = KIND == OP_F16 ? 2 : 1;
-    constexpr int S = W::S, RG = T * T / 64;        // accumulator registers per lane: 16 or 4
-    constexpr int EPT = RG / 4;                     // elements a thread finishes
+    constexpr int S = C::S, RG = T * T / 64;        // accumulator registers per lane and tile: 16 or 4
+    constexpr int EPT = (NB * RG + W - 1) / W;      // elements a thread finishes
     constexpr int BSTEP = KIND == OP_W4 ? 64 : 128; // bytes of a weight row per K step
     typedef typename std::conditional<KIND == OP_F16, float, int>::type elem_t;
     typedef elem_t acc_t __attribute__((ext_vector_type(RG)));
     extern __shared__ __align__(1024) unsigned char smem[];
     int tm, tn;
     if (!pick_tile(tiles_m, tiles_n, nblk_padded, tiles_m, tm, tn)) return;
-    const int m0 = tm * T, n0 = tn * T;
+    const int m0 = tm * T, n0 = tn * T * NB;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int fr = lane & (T - 1), kq = lane / T;   // fragment row, and the lane's part of a slice
     const int M = a.M, N = a.N, K = a.K;
@@ -130,24 +131,26 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
     const int group = GROUPED ? a.group : 128, G = GROUPED ? K / group : 0;
 
     // ---- the K steps of this wavefront; the next one to be requested, and the next one to be read
-    const SplitWalk<GROUPED> walk(wave, KB, group, G, gpr, rounds);
+    const SplitWalk<GROUPED, W> walk(wave, KB, group, G, gpr, rounds);
     const int steps = walk.steps;
-    typename SplitWalk<GROUPED>::Position ask = walk.first(wave), use = ask;
+    typename SplitWalk<GROUPED, W>::Position ask = walk.first(wave), use = ask;
 
     // ---- DMA: lane l fills bytes [16 l, 16 l + 16) of a 1024-byte group.  128-byte rows: row l/8, chunk c of row r at slot
     // c ^ ((r >> 1) & 7); packed 4-bit rows (64 bytes): row l/4, chunk c at slot c ^ ((r >> 2) & 3).
-    unsigned char *ring = smem + wave * (S * W::STAGE);
+    // slot i of a wavefront lies behind slot i of the others, so that a short row leaves nothing unused between them
+    auto slot_at = [&](int slot) { return smem + (wave + slot * W) * C::STAGE; };
+    const int rings = slots * C::STAGE;
     // The buffer form: descriptor and step offset in scalar registers, the lane's fixed offset in one vector register.
-    constexpr int NA = FUSE ? 1 : W::A_GROUPS;
-    int offA[NA], offB[W::B_GROUPS], ca[NA], cb[W::B_GROUPS];   // c*: the lane's byte inside a row's K step
+    constexpr int NA = FUSE ? 1 : C::A_GROUPS;
+    int offA[NA], offB[C::B_GROUPS], ca[NA], cb[C::B_GROUPS];   // c*: the lane's byte inside a row's K step
 #pragma unroll
-    for (int i = 0; i < W::A_GROUPS; ++i) {
+    for (int i = 0; i < C::A_GROUPS; ++i) {
         const int row = 8 * i + (lane >> 3);
         ca[i] = 16 * ((lane & 7) ^ ((row >> 1) & 7));
         offA[i] = min(m0 + row, M - 1) * KB + ca[i];
     }
 #pragma unroll
-    for (int i = 0; i < W::B_GROUPS; ++i) {
+    for (int i = 0; i < C::B_GROUPS; ++i) {
         const int row = KIND == OP_W4 ? 16 * i + (lane >> 2) : 8 * i + (lane >> 3);
         cb[i] = KIND == OP_W4 ? 16 * ((lane & 3) ^ ((row >> 2) & 3)) : 16 * ((lane & 7) ^ ((row >> 1) & 7));
         offB[i] = min(n0 + row, N - 1) * WB + cb[i];
@@ -155,76 +158,94 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
     auto issue = [&](int slot) {
         const int kb = ask.kb, wb = KIND == OP_W4 ? kb / 2 : kb;
         walk.next(ask);
-        unsigned char *dst = ring + slot * W::STAGE;
+        unsigned char *dst = slot_at(slot);
         if (kb + 128 <= KB) {
 #pragma unroll
-            for (int j = 0; j < W::A_GROUPS; ++j) dma16_buf(a.q, M * KB, dst + j * 1024, offA[j], kb);
+            for (int j = 0; j < C::A_GROUPS; ++j) dma16_buf(a.q, M * KB, dst + j * 1024, offA[j], kb);
 #pragma unroll
-            for (int j = 0; j < W::B_GROUPS; ++j)
-                dma16_buf(a.w, N * WB, dst + (W::A_GROUPS + j) * 1024, offB[j], wb);
+            for (int j = 0; j < C::B_GROUPS; ++j)
+                dma16_buf(a.w, N * WB, dst + (C::A_GROUPS + j) * 1024, offB[j], wb);
         } else {
             // a chunk past the end of its row reads the row's last one instead (such slices are skipped, or zeroed in registers)
 #pragma unroll
-            for (int j = 0; j < W::A_GROUPS; ++j)
+            for (int j = 0; j < C::A_GROUPS; ++j)
                 dma16_buf(a.q, M * KB, dst + j * 1024, offA[j] - max(kb + ca[j] - (KB - 16), 0), kb);
 #pragma unroll
-            for (int j = 0; j < W::B_GROUPS; ++j)
-                dma16_buf(a.w, N * WB, dst + (W::A_GROUPS + j) * 1024, offB[j] - max(wb + cb[j] - (WB - 16), 0), wb);
+            for (int j = 0; j < C::B_GROUPS; ++j)
+                dma16_buf(a.w, N * WB, dst + (C::A_GROUPS + j) * 1024, offB[j] - max(wb + cb[j] - (WB - 16), 0), wb);
         }
     };
-#pragma unroll
-    for (int st = 0; st < S; ++st)
-        if (st < steps) issue(st);
-    // ---- what the folds and the epilogue need: requested behind the first K steps (the waits for these, which count loads
-    // issued later, then at most wait longer than they must)
-    auto row_of = [&](int e) { return T == 32 ? 8 * wave + 4 * kq + e : 4 * kq + wave; };   // the elements a thread finishes
-    const int n = n0 + fr, n_in = min(n, N - 1);
-    // partial tiles: of every group of a round, or one per wavefront in its own ring, which by then is idle
-    unsigned char *part = smem + (GROUPED ? W::RINGS : 0);
-    constexpr int PART = GROUPED ? W::TILE : S * W::STAGE;
-    static_assert(GROUPED || S * W::STAGE >= W::TILE, "a partial tile fits its wavefront's ring");
-    float *ctab = reinterpret_cast<float *>(smem + W::RINGS + (GROUPED ? 4 * gpr * W::TILE : 0));   // [G][T] group scales of the tile's columns
-    if constexpr (GROUPED) {
-        // a thread looks after one column; nibbles enter the products as value * 16, the scale carries the 1/16 (exact)
-        const unsigned short *src = static_cast<const unsigned short *>(a.s_w) + (size_t)min(n0 + (int)threadIdx.x % T, N - 1) * G;
-        const float *sag = a.s_ag ? a.s_ag + (size_t)(min(m0, M - 1) / a.R) * G : nullptr;   // one scale block per tile
-        constexpr int P = 256 / T;
-        for (int g = threadIdx.x / T; g < G; g += 4 * P) {
-            unsigned short h[4];
-            float al[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) h[u] = src[min(g + u * P, G - 1)];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) al[u] = sag ? sag[min(g + u * P, G - 1)] : 1.0f;
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (g + u * P < G) ctab[(g + u * P) * T + threadIdx.x % T] = half_to_float_dev(h[u]) * (KIND == OP_W4 ? 0.0625f : 1.0f) * al[u];
-        }
-    }
-    const unsigned short bias_h = a.bias ? static_cast<const unsigned short *>(a.bias)[n_in] : (unsigned short)0;
-    const float sw = KIND == OP_I8 ? static_cast<const float *>(a.s_w)[n_in] : 1.0f;
-    GlueTerms terms[EPT];
-    if (GLUE) {
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            const int m = min(m0 + row_of(e), M - 1);
-            terms[e] = glue_terms(a, m, n_in, a.gate ? m / a.gate_rows : 0);
-        }
-    }
-    // FUSE: the codes of the tile's rows, [K step][row][128 bytes] with the chunks of a row swizzled as in the rings, and the
-    // rows' scales
-    unsigned char *resident = reinterpret_cast<unsigned char *>(ctab + (GROUPED ? T * G : 0));
-    float *srow = reinterpret_cast<float *>(resident + T * split_resident_steps(K, GROUPED) * 128);
+    // FUSE: the rows first, since loads return in order
+    constexpr int CH = SPLIT_FUSE_K_MAX / 512, RB = FUSE ? T / W : 1;    // 8-value pieces per lane and row; rows of this wavefront
+    uint4 v[RB][CH];
     if constexpr (FUSE) {
-        constexpr int CH = SPLIT_FUSE_K_MAX / 512, RB = T / 4;    // 8-value pieces per lane and row; rows of this wavefront
-        const int npad = (K + 127) / 128 * 16;                    // pieces of a row of codes, whole K steps
-        uint4 v[RB][CH];
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             const unsigned short *xr = static_cast<const unsigned short *>(a.x) + (size_t)min(m0 + wave * RB + r, M - 1) * K;
 #pragma unroll
             for (int i = 0; i < CH; ++i) v[r][i] = load_row_piece(xr, K * 2, lane * 16, i * 1024);
         }
+    }
+#pragma unroll
+    for (int st = 0; st < S; ++st)
+        if (st < steps) issue(st);
+    // ---- what the folds and the epilogue need: requested behind the first K steps (the waits for these, which count loads
+    // issued later, then at most wait longer than they must)
+    // the elements a thread finishes: registers EPT * wave + e, of all NB tiles one after the other
+    auto reg_of = [&](int e) { return EPT * wave + e; };
+    auto row_of = [&](int e) { return T == 32 ? 8 * (reg_of(e) % RG / 4) + 4 * kq + reg_of(e) % 4 : 4 * kq + reg_of(e) % RG; };
+    auto tile_of = [&](int e) { return NB == 1 ? 0 : reg_of(e) / RG; };
+    auto col_of = [&](int e) { return n0 + tile_of(e) * T + fr; };
+    auto owns = [&](int e) { return NB * RG % W == 0 || reg_of(e) < NB * RG; };
+    // partial tiles: of every group of a round, or one per wavefront in its own ring, which by then is idle
+    unsigned char *part = smem + (GROUPED ? rings : 0);
+    constexpr int PART = GROUPED ? C::TILE : C::STAGE;
+    static_assert(GROUPED || C::STAGE >= C::TILE, "a partial tile fits its wavefront's first slot");
+    float *ctab = reinterpret_cast<float *>(smem + rings + (GROUPED ? min(W * gpr, G) * C::TILE : 0));   // [G][T * NB] group scales of the tile's columns
+    if constexpr (GROUPED) {
+        // a thread looks after every NTHR-th entry; nibbles enter the products as value * 16, the scale carries the 1/16 (exact)
+        const unsigned short *src = static_cast<const unsigned short *>(a.s_w);
+        const float *sag = a.s_ag ? a.s_ag + (size_t)(min(m0, M - 1) / a.R) * G : nullptr;   // one scale block per tile
+        constexpr int COLS = T * NB;
+        for (int at = threadIdx.x; at < G * COLS; at += 4 * C::NTHR) {
+            unsigned short h[4];
+            float al[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int g = min((at + u * C::NTHR) / COLS, G - 1);
+                h[u] = src[(size_t)min(n0 + (at + u * C::NTHR) % COLS, N - 1) * G + g];
+                al[u] = sag ? sag[g] : 1.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (at + u * C::NTHR < G * COLS) ctab[at + u * C::NTHR] = half_to_float_dev(h[u]) * (KIND == OP_W4 ? 0.0625f : 1.0f) * al[u];
+        }
+    }
+    constexpr int COLUMNS = NB == 1 ? 1 : EPT;      // one tile: a thread's elements are of one column
+    unsigned short bias_h[COLUMNS];
+    float sw[COLUMNS];
+#pragma unroll
+    for (int e = 0; e < COLUMNS; ++e) {
+        const int n_in = min(col_of(e), N - 1);
+        bias_h[e] = a.bias ? static_cast<const unsigned short *>(a.bias)[n_in] : (unsigned short)0;
+        sw[e] = KIND == OP_I8 ? static_cast<const float *>(a.s_w)[n_in] : 1.0f;
+    }
+    GlueTerms terms[EPT];
+    if constexpr (GLUE && NB == 1) {
+        request_glue<EPT>(a, terms, min(col_of(0), N - 1), [&](int e) { return min(m0 + row_of(e), M - 1); }, [&](int m) { return m / a.gate_rows; });
+    } else if constexpr (GLUE) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int m = min(m0 + row_of(e), M - 1);
+            terms[e] = glue_terms(a, m, min(col_of(e), N - 1), a.gate ? m / a.gate_rows : 0);
+        }
+    }
+    // FUSE: the codes of the tile's rows, [K step][row][128 bytes] with the chunks of a row swizzled as in the rings, and the
+    // rows' scales
+    unsigned char *resident = reinterpret_cast<unsigned char *>(ctab + (GROUPED ? T * NB * G : 0));
+    float *srow = reinterpret_cast<float *>(resident + T * split_resident_steps(K, GROUPED) * 128);
+    if constexpr (FUSE) {
+        const int npad = (K + 127) / 128 * 16;                    // pieces of a row of codes, whole K steps
         // all rows' maxima first, then all codes: the chains of one row are short on instructions and long on latency
         unsigned mx[RB];
 #pragma unroll
@@ -279,8 +300,8 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
     typedef frag_a frag_a_alias __attribute__((may_alias));
     typedef frag_b frag_b_alias __attribute__((may_alias));
     const int keyA = (fr >> 1) & 7, key4 = (fr >> 2) & 3;
-    auto read_frags = [&](int slot, frag_a(&af)[NF], frag_b(&bf)[NF]) {
-        const unsigned char *st = ring + slot * W::STAGE, *stb = st + W::A_GROUPS * 1024;
+    auto read_frags = [&](int slot, frag_a(&af)[NF], frag_b(&bf)[NF][NB]) {
+        const unsigned char *st = slot_at(slot), *stb = st + C::A_GROUPS * 1024;
         const int c0 = use.kb >> 4;   // first chunk of the step inside its row
         walk.next(use);
 #pragma unroll
@@ -293,45 +314,53 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
             } else {
                 af[f] = *reinterpret_cast<const frag_a_alias *>(st + fr * 128 + ((chunk ^ keyA) * 16) + off);
             }
-            if constexpr (KIND == OP_W4)
-                bf[f] = *reinterpret_cast<const frag_b_alias *>(stb + fr * 64 + (((chunk >> 1) ^ key4) * 16) + (chunk & 1) * 8 + off / 2);
-            else
-                bf[f] = *reinterpret_cast<const frag_b_alias *>(stb + fr * 128 + ((chunk ^ keyA) * 16) + off);
+            // the swizzle's key repeats every 16 rows
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                if constexpr (KIND == OP_W4)
+                    bf[f][b] = *reinterpret_cast<const frag_b_alias *>(stb + (b * T + fr) * 64 + (((chunk >> 1) ^ key4) * 16) + (chunk & 1) * 8 + off / 2);
+                else
+                    bf[f][b] = *reinterpret_cast<const frag_b_alias *>(stb + (b * T + fr) * 128 + ((chunk ^ keyA) * 16) + off);
+            }
         }
     };
-    acc_t acc;
+    acc_t acc[NB];
     auto clear = [&]() {
 #pragma unroll
-        for (int r = 0; r < RG; ++r) acc[r] = 0;
+        for (int r = 0; r < NB * RG; ++r) acc[r / RG][r % RG] = 0;
     };
-    auto mma = [&](const frag_a &af, const frag_b &bf) {
+    auto mma_one = [&](const frag_a &af, const frag_b &bf, acc_t c) -> acc_t {
         if constexpr (HALF) {
             long b;
             if constexpr (KIND == OP_W4)
                 b = __builtin_bit_cast(long, v2i{(int)(((unsigned)bf << 4) & 0xf0f0f0f0u), (int)((unsigned)bf & 0xf0f0f0f0u)});
             else
                 b = __builtin_bit_cast(long, bf);
-            acc = __builtin_amdgcn_mfma_i32_16x16x32_i8(__builtin_bit_cast(long, af), b, acc, 0, 0, 0);
+            return __builtin_amdgcn_mfma_i32_16x16x32_i8(__builtin_bit_cast(long, af), b, c, 0, 0, 0);
         } else if constexpr (T == 32) {
-            if constexpr (KIND == OP_W4) acc = mfma_step<false>(af, nibbles_x16(bf[0], bf[1]), acc);
-            else acc = mfma_step<KIND == OP_F16>(af, bf, acc);
+            if constexpr (KIND == OP_W4) return mfma_step<false>(af, nibbles_x16(bf[0], bf[1]), c);
+            else return mfma_step<KIND == OP_F16>(af, bf, c);
         } else if constexpr (KIND == OP_F16) {
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, af), __builtin_bit_cast(v8h, bf), acc, 0, 0, 0);
+            return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, af), __builtin_bit_cast(v8h, bf), c, 0, 0, 0);
         } else {
-            acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(af, bf, acc, 0, 0, 0);
+            return __builtin_amdgcn_mfma_i32_16x16x64_i8(af, bf, c, 0, 0, 0);
         }
+    };
+    auto mma = [&](const frag_a &af, const frag_b(&bf)[NB]) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b] = mma_one(af, bf[b], acc[b]);
     };
     // partial tile layout: register r of a lane at [r][lane], so that thread (wavefront w, lane) finds its elements at
     // registers EPT * w + e of the same lane
     auto park = [&](int slot) {
         elem_t *p = reinterpret_cast<elem_t *>(part + slot * PART);
 #pragma unroll
-        for (int r = 0; r < RG; ++r) p[r * 64 + lane] = acc[r];
+        for (int r = 0; r < NB * RG; ++r) p[r * 64 + lane] = acc[r / RG][r % RG];
     };
     auto wait_for = [&](int later) {   // steps issued after the one that is needed
-        if (later >= S - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 1) * W::LOADS) : "memory");
-        else if (S > 3 && later == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * W::LOADS) : "memory");
-        else if (later == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(W::LOADS) : "memory");
+        if (later >= S - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 1) * C::LOADS) : "memory");
+        else if (S > 3 && later == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * C::LOADS) : "memory");
+        else if (later == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::LOADS) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
     float f[EPT];
@@ -342,11 +371,11 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
         sum[e] = 0;
     }
     frag_a af0[NF], af1[NF];
-    frag_b bf0[NF], bf1[NF];
+    frag_b bf0[NF][NB], bf1[NF][NB];
     int slot = 0;
     // Step i: its fragments are in (afc, bfc).  Their LDS slot is free once they have arrived: it is refilled with step i + S;
     // then the fragments of step i + 1 are requested, and step i is multiplied while they travel.
-    auto advance = [&](int i, frag_a(&afn)[NF], frag_b(&bfn)[NF]) {
+    auto advance = [&](int i, frag_a(&afn)[NF], frag_b(&bfn)[NF][NB]) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (i + S < steps) issue(slot);
         slot = slot + 1 == S ? 0 : slot + 1;
@@ -361,15 +390,15 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
     }
     clear();
     if constexpr (!GROUPED) {
-        auto one = [&](int i, frag_a(&afc)[NF], frag_b(&bfc)[NF], frag_a(&afn)[NF], frag_b(&bfn)[NF]) {
+        auto one = [&](int i, frag_a(&afc)[NF], frag_b(&bfc)[NF][NB], frag_a(&afn)[NF], frag_b(&bfn)[NF][NB]) {
             advance(i, afn, bfn);
-            const int kb = (wave + 4 * i) * 128;
+            const int kb = (wave + W * i) * 128;
             if (!FUSE && kb + 128 > KB) {
 #pragma unroll
                 for (int q = 0; q < NF; ++q)
                     if (kb + (q * (8 / NF) + kq) * 16 >= KB) {
                         afc[q] = frag_a{0, 0, 0, 0};
-                        if constexpr (KIND == OP_F16) bfc[q] = frag_b{0, 0, 0, 0};   // 0 * Inf is not 0
+                        if constexpr (KIND == OP_F16) bfc[q][0] = frag_b{0, 0, 0, 0};   // 0 * Inf is not 0
                     }
             }
 #pragma unroll
@@ -382,18 +411,19 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
         park(wave);
         __syncthreads();
 #pragma unroll
-        for (int w = 0; w < 4; ++w)
+        for (int w = 0; w < W; ++w)
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) sum[e] += reinterpret_cast<const elem_t *>(part + w * PART)[(EPT * wave + e) * 64 + lane];
+            for (int e = 0; e < EPT; ++e)
+                if (owns(e)) sum[e] += reinterpret_cast<const elem_t *>(part + w * PART)[reg_of(e) * 64 + lane];
     } else {
         const int QG = group / 32;
         int i = 0;
         for (int r = 0; r < rounds; ++r) {
-            const int g_first = r * 4 * gpr;                                     // of the round, over all wavefronts
+            const int g_first = r * W * gpr;                                     // of the round, over all wavefronts
             const int mine = max(0, min(gpr, G - g_first - wave * gpr));
             const int i_end = i + (mine * group + 127) / 128;
             int qs = 0, done = 0;
-            auto one = [&](frag_a(&afc)[NF], frag_b(&bfc)[NF], frag_a(&afn)[NF], frag_b(&bfn)[NF]) {
+            auto one = [&](frag_a(&afc)[NF], frag_b(&bfc)[NF][NB], frag_a(&afn)[NF], frag_b(&bfn)[NF][NB]) {
                 advance(i, afn, bfn);
 #pragma unroll
                 for (int q = 0; q < NF; ++q) {
@@ -416,28 +446,31 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
                 if (i < i_end) one(af1, bf1, af0, bf0);
             }
             __syncthreads();
-            const int have = min(4 * gpr, G - g_first);
+            const int have = min(W * gpr, G - g_first);
             // U groups at a time: their sums and scales are requested together, the fp32 sum takes them in ascending order
             constexpr int U = EPT == 4 ? 4 : 8;
             auto take = [&](int g, auto count_tag) {
-                constexpr int C = decltype(count_tag)::value;
-                int p[C][EPT];
-                float c[C];
+                constexpr int CNT = decltype(count_tag)::value;
+                int p[CNT][EPT];
+                float c[CNT][EPT];
 #pragma unroll
-                for (int u = 0; u < C; ++u) {
-                    c[u] = ctab[(g_first + g + u) * T + fr];
+                for (int u = 0; u < CNT; ++u) {
 #pragma unroll
-                    for (int e = 0; e < EPT; ++e) p[u][e] = reinterpret_cast<const int *>(part + (g + u) * PART)[(EPT * wave + e) * 64 + lane];
+                    for (int e = 0; e < EPT; ++e) {
+                        const int reg = owns(e) ? reg_of(e) : 0;
+                        c[u][e] = ctab[(g_first + g + u) * T * NB + (NB == 1 ? 0 : reg / RG * T) + fr];
+                        p[u][e] = reinterpret_cast<const int *>(part + (g + u) * PART)[reg * 64 + lane];
+                    }
                 }
 #pragma unroll
-                for (int u = 0; u < C; ++u)
+                for (int u = 0; u < CNT; ++u)
 #pragma unroll
                     for (int e = 0; e < EPT; ++e) {
                         if (EXPORT) {
-                            const int m = m0 + row_of(e);
+                            const int m = m0 + row_of(e), n = col_of(e);
                             if (m < M && n < N) a.acc_out[((size_t)m * G + g_first + g + u) * N + n] = KIND == OP_W4 ? p[u][e] >> 4 : p[u][e];
                         }
-                        f[e] = __builtin_fmaf((float)p[u][e], c[u], f[e]);
+                        f[e] = __builtin_fmaf((float)p[u][e], c[u][e], f[e]);
                     }
             };
             int g = 0;
@@ -447,16 +480,15 @@ __global__ __launch_bounds__(256, 2) void qgemm_splitk(GemmArgs a, int tiles_m, 
         }
     }
 
-    const float b = half_to_float_dev(bias_h);
-    if (n >= N) return;
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
-        const int m = m0 + row_of(e);
-        if (m >= M) continue;
+        const int m = m0 + row_of(e), n = col_of(e);
+        if (m >= M || n >= N || !owns(e)) continue;
+        const float b = half_to_float_dev(bias_h[e % COLUMNS]);
         float u;
         if constexpr (GROUPED) u = dequant_one<KIND>(a, 0, f[e], sa[e], 1.0f, b);
         else if constexpr (KIND == OP_F16) u = dequant_one<KIND>(a, 0, sum[e], 1.0f, 1.0f, b);
-        else u = dequant_one<KIND>(a, sum[e], 0.0f, sa[e], sw, b);
+        else u = dequant_one<KIND>(a, sum[e], 0.0f, sa[e], sw[e % COLUMNS], b);
         if constexpr (KIND == OP_I8 && EXPORT) a.acc_out[(size_t)m * N + n] = sum[e];
         asm volatile("" : "+v"(u));   // keep the fp32 rounding before the fp16 one
         static_cast<_Float16 *>(a.y)[(size_t)m * N + n] = GLUE ? glue_one(a, u, m, terms[e]) : (_Float16)u;
@@ -682,56 +714,90 @@ static OperandKind kind_of(const GemmArgs &a)
 
 static bool glue_of(const GemmArgs &a) { return a.act != 0 || a.residual != nullptr || a.gate != nullptr || a.row_absmax != nullptr; }
 
-template <int KIND, int T>
+template <int KIND, int T, int W>
 static int split_gpr(const GemmArgs &a)
 {
-    return SplitTile<KIND, T, false>::GROUPED ? split_groups_per_round(a.K / a.group, T) : 0;
+    return SplitTile<KIND, T, false>::GROUPED ? split_groups_per_round(a.K / a.group, T, W) : 0;
 }
 
-template <int KIND, int T, bool FUSE = false>
-static size_t split_lds(const GemmArgs &a)
+// how a layer is laid out: groups per round, rounds, LDS slots, LDS bytes
+struct SplitLayout {
+    int gpr, rounds, slots;
+    size_t lds;
+};
+template <int KIND, int T, bool FUSE, int W, int NB>
+static SplitLayout split_layout(const GemmArgs &a)
 {
-    using W = SplitTile<KIND, T, FUSE>;
-    const size_t G = W::GROUPED ? a.K / a.group : 0;
-    return W::RINGS + (size_t)(W::GROUPED ? 4 * split_gpr<KIND, T>(a) : 0) * W::TILE + T * G * 4 +
-           (FUSE ? (size_t)T * (split_resident_steps(a.K, W::GROUPED) * 128 + 4) : 0);
+    using C = SplitTile<KIND, T, FUSE, W, NB>;
+    const int G = C::GROUPED ? a.K / a.group : 0, gpr = split_gpr<KIND, T, W>(a), rounds = gpr ? (G + W * gpr - 1) / (W * gpr) : 0;
+    const int slots = split_slots<C::GROUPED, W>(C::S, a.K * (KIND == OP_F16 ? 2 : 1), C::GROUPED ? a.group : 128, G, gpr, rounds);
+    return {gpr, rounds, slots,
+            (size_t)slots * C::STAGE + (size_t)(W * gpr < G ? W * gpr : G) * C::TILE + (size_t)T * NB * G * 4 +
+                (FUSE ? (size_t)T * (split_resident_steps(a.K, C::GROUPED) * 128 + 4) : 0)};
 }
 
-template <int KIND, int T, bool GLUE, bool EXPORT, bool FUSE>
+template <int KIND, int T, bool GLUE, bool EXPORT, bool FUSE, int W, int NB>
 static hipError_t run_split_as(const GemmArgs &a, hipStream_t s)
 {
-    static const hipError_t opt_in = hipFuncSetAttribute(reinterpret_cast<const void *>(&qgemm_splitk<KIND, T, GLUE, EXPORT, FUSE>),
+    static const hipError_t opt_in = hipFuncSetAttribute(reinterpret_cast<const void *>(&qgemm_splitk<KIND, T, GLUE, EXPORT, FUSE, W, NB>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, SPLIT_LDS_MAX);
     if (opt_in != hipSuccess) return opt_in;
-    const int tiles_m = (a.M + T - 1) / T, tiles_n = (a.N + T - 1) / T;
+    const int tiles_m = (a.M + T - 1) / T, tiles_n = (a.N + T * NB - 1) / (T * NB);
     const int padded = (tiles_m * tiles_n + XCDS - 1) / XCDS * XCDS;
-    const int gpr = split_gpr<KIND, T>(a), G = SplitTile<KIND, T, FUSE>::GROUPED ? a.K / a.group : 0;
-    hipLaunchKernelGGL((qgemm_splitk<KIND, T, GLUE, EXPORT, FUSE>), dim3(padded), dim3(256), (split_lds<KIND, T, FUSE>(a)), s, a, tiles_m,
-                       tiles_n, padded, gpr, gpr ? (G + 4 * gpr - 1) / (4 * gpr) : 0);
+    const SplitLayout l = split_layout<KIND, T, FUSE, W, NB>(a);
+    if (l.lds > SPLIT_LDS_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((qgemm_splitk<KIND, T, GLUE, EXPORT, FUSE, W, NB>), dim3(padded), dim3(64 * W), l.lds, s, a, tiles_m, tiles_n, padded, l.gpr, l.rounds, l.slots);
     return hipGetLastError();
 }
 
+// rounds of workgroups that a layer takes in this form; 0: it does not fit
+template <int KIND, int T, bool FUSE, int W, int NB>
+static long long split_rounds(const GemmArgs &a)
+{
+    const size_t lds = split_layout<KIND, T, FUSE, W, NB>(a).lds;
+    if (lds > SPLIT_LDS_MAX) return 0;
+    const long long tiles = (long long)((a.M + T - 1) / T) * ((a.N + T * NB - 1) / (T * NB)), resident = 256 * (long long)min((size_t)2, SPLIT_LDS_MAX / lds);
+    return (tiles + resident - 1) / resident;
+}
+
+// Eight wavefronts share K where their workgroups, which take more LDS with group scales, are all resident at once; 16x16 tiles of integer codes come
+// two to a workgroup where there are more of them than CUs.  us, DAQ and GEMM, four wavefronts -> chosen: 8-bit, K = 4608, N = 1152: M = 16 7.5 -> 7.0,
+// 64 8.7 -> 8.2; 4-bit M = 16 9.9 -> 9.1, 64 11.2 -> 10.4, 128 14.3 -> 13.0; K = 1152, M = 256 11.3 -> 9.0.  32x32 tiles without group scales, whose steps go round
+// the wavefronts, were up to 7 % slower with eight, and binary16 ones of short rows up to 16 %.
 template <int KIND, int T>
 static hipError_t run_split(const GemmArgs &a, hipStream_t s)
 {
-    if (a.acc_out) return glue_of(a) ? hipErrorInvalidValue : run_split_as<KIND, T, false, true, false>(a, s);   // no call exports and glues
-    return glue_of(a) ? run_split_as<KIND, T, true, false, false>(a, s) : run_split_as<KIND, T, false, false, false>(a, s);
+    if (a.acc_out) return glue_of(a) ? hipErrorInvalidValue : run_split_as<KIND, T, false, true, false, 4, 1>(a, s);   // no call exports and glues
+    auto run = [&](auto w, auto nb) {
+        constexpr int W = decltype(w)::value, NB = decltype(nb)::value;
+        return glue_of(a) ? run_split_as<KIND, T, true, false, false, W, NB>(a, s) : run_split_as<KIND, T, false, false, false, W, NB>(a, s);
+    };
+    typedef std::integral_constant<int, 8> eight;
+    if constexpr (T == 16 && KIND != OP_F16) {
+        if ((long long)((a.M + 15) / 16) * ((a.N + 15) / 16) > 256 && split_rounds<KIND, T, false, 8, 2>(a) == 1) return run(eight{}, std::integral_constant<int, 2>{});
+    }
+    constexpr bool GROUPED = KIND == OP_W4 || KIND == OP_I8G;
+    if constexpr (T == 16 || GROUPED) {
+        const bool worth = KIND != OP_F16 || (a.K >= 1152 && (long long)((a.M + 15) / 16) * ((a.N + 15) / 16) <= 256);
+        if (worth && split_rounds<KIND, T, false, 8, 1>(a) == 1) return run(eight{}, std::integral_constant<int, 1>{});
+    }
+    return run(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});
 }
 
-template <int KIND>
+template <int KIND, int NB>
 static hipError_t run_split_fused(const GemmArgs &a, hipStream_t s)
 {
-    return glue_of(a) ? run_split_as<KIND, 16, true, false, true>(a, s) : run_split_as<KIND, 16, false, false, true>(a, s);
+    return glue_of(a) ? run_split_as<KIND, 16, true, false, true, 8, NB>(a, s) : run_split_as<KIND, 16, false, false, true, 8, NB>(a, s);
 }
 
 template <int T>
 static size_t split_lds_of(const GemmArgs &a)
 {
     switch (kind_of(a)) {
-    case OP_I8: return a.x ? split_lds<OP_I8, T, true>(a) : split_lds<OP_I8, T>(a);
-    case OP_W4: return a.x ? split_lds<OP_W4, T, true>(a) : split_lds<OP_W4, T>(a);
-    case OP_I8G: return split_lds<OP_I8G, T>(a);
-    default: return split_lds<OP_F16, T>(a);
+    case OP_I8: return split_layout<OP_I8, T, false, 4, 1>(a).lds;
+    case OP_W4: return split_layout<OP_W4, T, false, 4, 1>(a).lds;
+    case OP_I8G: return split_layout<OP_I8G, T, false, 4, 1>(a).lds;
+    default: return split_layout<OP_F16, T, false, 4, 1>(a).lds;
     }
 }
 
@@ -768,14 +834,36 @@ int qgemm_split_choice(const GemmArgs &a)
 // repeats the quantization of its 16 rows, which costs the GPU what the separate launch costs it (M = 16, K = 1152, N = 4608:
 // 7.5 against 6.4 us, M = 1: 4.5 against 5.6) as long as a CU has one workgroup, and twice that with two; it always saves the
 // 3.6 us that a launch costs the host, which is what bounds a sequence of such small calls.
-bool qgemm_fuse_takes(const GemmArgs &a)
+//
+// Workgroups of 16 rows and 16 NB columns, the fewest columns that leave no CU a second one: the more columns, the fewer times the codes are made.  Eight
+// wavefronts make them in half the time that four take.  us, M x K x N, two launches or four wavefronts -> now: 8-bit 16 x 384 x 384 5.0 -> 4.2, 16 x 1152 x 1152
+// 6.5 -> 5.3, 64 x 1152 x 1152 7.1 -> 5.8 (NB = 2), 128 8.4 -> 6.6 (3), 256 9.0 -> 7.9 (5); 4-bit 16 7.4 -> 5.9, 128 9.6 -> 7.4; one scale for all rows, 8-bit, 256
+// 12.2 -> 10.8.  With four wavefronts NB = 2 to 5 were no faster than the two launches, and up to 1.2 times as long.
+static int fuse_tiles(const GemmArgs &a)   // NB; 0: DAQ runs by itself
 {
-    if ((a.w_bits != 8 && a.w_bits != 4) || a.w_grouped || a.s_ag || a.acc_out || (uintptr_t)a.x % 16 != 0 || a.K > SPLIT_FUSE_K_MAX) return false;
-    return qgemm_split_takes(a, 16) && (long long)((a.M + 15) / 16) * ((a.N + 15) / 16) <= 256;
+    if ((a.w_bits != 8 && a.w_bits != 4) || a.w_grouped || a.s_ag || a.acc_out || (uintptr_t)a.x % 16 != 0 || a.K > SPLIT_FUSE_K_MAX) return 0;
+    if (!qgemm_split_takes(a, 16)) return 0;
+    auto takes = [&](auto nb) {
+        constexpr int NB = decltype(nb)::value;
+        if ((long long)((a.M + 15) / 16) * ((a.N + 16 * NB - 1) / (16 * NB)) > 256) return 0;
+        return (a.w_bits == 8 ? split_rounds<OP_I8, 16, true, 8, NB>(a) : split_rounds<OP_W4, 16, true, 8, NB>(a)) == 1 ? NB : 0;
+    };
+    int nb = takes(std::integral_constant<int, 1>{});
+    if (!nb) nb = takes(std::integral_constant<int, 2>{});
+    if (!nb) nb = takes(std::integral_constant<int, 3>{});
+    return nb ? nb : takes(std::integral_constant<int, 5>{});
 }
+bool qgemm_fuse_takes(const GemmArgs &a) { return fuse_tiles(a) != 0; }
+bool qgemm_fuse_one_tile(const GemmArgs &a) { return fuse_tiles(a) == 1; }
 hipError_t launch_qgemm_fused(const GemmArgs &a, hipStream_t stream)
 {
-    return a.w_bits == 8 ? run_split_fused<OP_I8>(a, stream) : run_split_fused<OP_W4>(a, stream);
+    switch (fuse_tiles(a)) {
+    case 1: return a.w_bits == 8 ? run_split_fused<OP_I8, 1>(a, stream) : run_split_fused<OP_W4, 1>(a, stream);
+    case 2: return a.w_bits == 8 ? run_split_fused<OP_I8, 2>(a, stream) : run_split_fused<OP_W4, 2>(a, stream);
+    case 3: return a.w_bits == 8 ? run_split_fused<OP_I8, 3>(a, stream) : run_split_fused<OP_W4, 3>(a, stream);
+    case 5: return a.w_bits == 8 ? run_split_fused<OP_I8, 5>(a, stream) : run_split_fused<OP_W4, 5>(a, stream);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 template <int T>

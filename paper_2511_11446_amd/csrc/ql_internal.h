@@ -144,6 +144,7 @@ hipError_t launch_qgemm_w4_128(const GemmArgs &a, hipStream_t stream);
 bool qgemm_split_takes(const GemmArgs &a, int tile);
 int qgemm_split_choice(const GemmArgs &a);   // tile (16 or 32) where splitting K is the fastest, else 0
 bool qgemm_fuse_takes(const GemmArgs &a);    // one launch that quantizes its own input (a.x) instead of DAQ and GEMM
+bool qgemm_fuse_one_tile(const GemmArgs &a); // ... and a CU for every 16x16 tile
 hipError_t launch_qgemm_fused(const GemmArgs &a, hipStream_t stream);
 hipError_t launch_qgemm_split32(const GemmArgs &a, hipStream_t stream);
 hipError_t launch_qgemm_split16(const GemmArgs &a, hipStream_t stream);

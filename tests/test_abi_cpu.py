@@ -183,6 +183,15 @@ def test_split_k_walk_stays_inside_the_row_and_the_lds(tmp_path):
     assert r.returncode == 0, r.stdout + r.stderr
 
 
+def test_split_k_walk_on_eight_wavefronts(tmp_path):
+    """The same on eight wavefronts, and the LDS slots of the rings."""
+    import subprocess
+    exe = str(tmp_path / "split_wide_check")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-o", exe, os.path.join(os.path.dirname(__file__), "split_wide_check.cpp")], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
 @pytest.fixture(scope="module")
 def plan_windows(tmp_path_factory):
     """(M, R, p_ppm, a_bits, room, [(K, N, bits, group, x, y)]) -> [(first layer, layers, {those whose GEMMs share a launch})], from the library's own decision."""

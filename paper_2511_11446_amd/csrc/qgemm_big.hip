@@ -55,8 +55,9 @@ struct TileBig {
     static_assert(LDS_BYTES <= 160 * 1024 && STORES < 64 && SPAN > 0, "LDS, outstanding operations");
 };
 
+// workgroup `block` of `blocks` (a multiple of XCDS) that share the layer
 template <class T, bool GLUE>
-__global__ __launch_bounds__(T::NTHR, 2) void qgemm_big(GemmArgs a, int tiles_m, int tiles_n, int nblk_padded, int group_m)
+__device__ __forceinline__ void qgemm_big_tiles(const GemmArgs &a, int block, int blocks, int tiles_m, int tiles_n, int nblk_padded, int group_m)
 {
     constexpr int MT = T::MT, NM = T::NM, TI = T::TI, NA = T::NA, NB = T::NB, FR = T::FR;
     constexpr bool F16 = T::F16;
@@ -65,9 +66,9 @@ __global__ __launch_bounds__(T::NTHR, 2) void qgemm_big(GemmArgs a, int tiles_m,
     typedef elem_t acc_t __attribute__((ext_vector_type(4)));
     extern __shared__ __align__(1024) unsigned char smem[];
 
-    const int per_xcd = nblk_padded / XCDS, slots_per_xcd = gridDim.x / XCDS;
-    const int xcd_first = (blockIdx.x % XCDS) * per_xcd;
-    int in_xcd = blockIdx.x / XCDS;
+    const int per_xcd = nblk_padded / XCDS, slots_per_xcd = blocks / XCDS;
+    const int xcd_first = (block % XCDS) * per_xcd;
+    int in_xcd = block / XCDS;
     if (in_xcd >= per_xcd || xcd_first + in_xcd >= tiles_m * tiles_n) return;
     int m0, n0;
     auto set_tile = [&](int logical) {
@@ -324,6 +325,12 @@ __global__ __launch_bounds__(T::NTHR, 2) void qgemm_big(GemmArgs a, int tiles_m,
 }
 
 template <class T, bool GLUE>
+__global__ __launch_bounds__(T::NTHR, 2) void qgemm_big(GemmArgs a, int tiles_m, int tiles_n, int nblk_padded, int group_m)
+{
+    qgemm_big_tiles<T, GLUE>(a, blockIdx.x, gridDim.x, tiles_m, tiles_n, nblk_padded, group_m);
+}
+
+template <class T, bool GLUE>
 static hipError_t run_big(const GemmArgs &a, hipStream_t s)
 {
     static const hipError_t opt_in = hipFuncSetAttribute(reinterpret_cast<const void *>(&qgemm_big<T, GLUE>),
@@ -350,6 +357,73 @@ bool qgemm_big_takes(const GemmArgs &a)
     return (a.w_bits == 8 || a.w_bits == 16) && !a.w_grouped && !a.s_ag && !a.acc_out && kb % 128 == 0 && kb >= 256 && a.N % 8 == 0 &&
            (uintptr_t)a.q % 16 == 0 && (uintptr_t)a.w % 16 == 0 && (uintptr_t)a.y % 16 == 0 && (uintptr_t)a.bias % 4 == 0 &&
            (uintptr_t)a.gate % 16 == 0 && (uintptr_t)a.residual % 16 == 0;
+}
+
+// ---- several 8-bit layers of a plan in one launch (qgemm_many.hip), where all their tiles are one round: a workgroup, a tile
+using BigMany = TileBig<4, 9, 4, 2, false>;
+struct BigManyLayer {
+    const int8_t *q, *w;
+    const float *s_a, *s_w;
+    const void *bias;
+    void *y;
+    int N, K, tiles_n, padded;
+};
+struct BigManyArgs {
+    BigManyLayer l[PLAN_WINDOW];
+    int M, R, tiles_m, group_m;
+};
+__global__ __launch_bounds__(BigMany::NTHR, 2) void qgemm_big_many(BigManyArgs b)
+{
+    int i = 0, block = blockIdx.x;
+    while (block >= b.l[i].padded) block -= b.l[i++].padded;   // the grid is the sum of all
+    const BigManyLayer &l = b.l[i];
+    GemmArgs a{};
+    a.q = l.q;
+    a.s_a = l.s_a;
+    a.w = l.w;
+    a.s_w = l.s_w;
+    a.bias = l.bias;
+    a.y = l.y;
+    a.M = b.M;
+    a.N = l.N;
+    a.K = l.K;
+    a.R = b.R;
+    qgemm_big_tiles<BigMany, false>(a, block, l.padded, b.tiles_m, l.tiles_n, l.padded, b.group_m);
+}
+
+static int big_many_padded(const GemmArgs &a)
+{
+    const int tiles = ((a.M + BigMany::BM - 1) / BigMany::BM) * ((a.N + BigMany::BN - 1) / BigMany::BN);
+    return (tiles + XCDS - 1) / XCDS * XCDS;
+}
+
+bool qgemm_big_many_takes(const GemmArgs *const *layers, int count)
+{
+    int blocks = 0;
+    for (int i = 0; i < count; ++i) {
+        if (layers[i]->w_bits != 8 || !qgemm_big_takes(*layers[i])) return false;
+        blocks += big_many_padded(*layers[i]);
+    }
+    return blocks <= 256;
+}
+
+hipError_t launch_qgemm_big_many(const GemmArgs *const *layers, int count, hipStream_t stream)
+{
+    static const hipError_t opt_in = hipFuncSetAttribute(reinterpret_cast<const void *>(&qgemm_big_many), hipFuncAttributeMaxDynamicSharedMemorySize, BigMany::LDS_BYTES);
+    if (opt_in != hipSuccess) return opt_in;
+    BigManyArgs b{};
+    b.M = layers[0]->M;
+    b.R = layers[0]->R;
+    b.tiles_m = (b.M + BigMany::BM - 1) / BigMany::BM;
+    b.group_m = pick_group_m(BigMany::BM);
+    unsigned grid = 0;
+    for (int i = 0; i < count; ++i) {
+        const GemmArgs &a = *layers[i];
+        b.l[i] = {a.q, static_cast<const int8_t *>(a.w), a.s_a, static_cast<const float *>(a.s_w), a.bias, a.y, a.N, a.K, (a.N + BigMany::BN - 1) / BigMany::BN, big_many_padded(a)};
+        grid += (unsigned)b.l[i].padded;
+    }
+    hipLaunchKernelGGL(qgemm_big_many, dim3(grid), dim3(BigMany::NTHR), BigMany::LDS_BYTES, stream, b);
+    return hipGetLastError();
 }
 
 #define BIG(name, ...)                                                                                           \

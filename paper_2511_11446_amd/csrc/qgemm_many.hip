@@ -93,6 +93,30 @@ static float tile_us(const GemmArgs &a)
     return 2.0f + 0.347f * steps + 0.18f * (float)(a.K / a.group);
 }
 
+// all tiles spread evenly over 256 CUs, and half a tile of idling at the end
+static float many_us(const GemmArgs *const *layers, int count)
+{
+    float work = 0.0f, longest = 0.0f;
+    for (int i = 0; i < count; ++i) {
+        const GemmArgs &a = *layers[i];
+        const float us = tile_us(a);
+        work += us * (float)((a.M + ManyW8::BM - 1) / ManyW8::BM) * (float)((a.N + ManyW8::BN - 1) / ManyW8::BN);
+        longest = us > longest ? us : longest;
+    }
+    return 3.2f + work / 256.0f + 0.5f * longest;
+}
+
+// The same layers on 256x288 tiles, where these are one round (one tile of qgemm_big as choose_tile prices it; the longest K decides).  Three 8-bit layers of
+// a block of width 1152 at M = 2048, 256 tiles: 28.1 us, 32.9 on the 1152 tiles of 128x128.  With DAQ and fc2, 128x128 -> here: width 768, M = 2560 48.7 ->
+// 47.0, 2816 56.4 -> 49.9; 1024, M = 1792 53.7 -> 50.4; 1152, M = 1664 58.0 -> 55.0, 2048 70.4 -> 64.5; 1536, M = 1280 70.2 -> 66.2; 2048, M = 1024 96.0 -> 88.8.
+static float big_many_us(const GemmArgs *const *layers, int count)
+{
+    if (!qgemm_big_many_takes(layers, count)) return 1e9f;
+    int longest = 0;
+    for (int i = 0; i < count; ++i) longest = layers[i]->K > longest ? layers[i]->K : longest;
+    return 11.7f + 1.773f * (float)(longest / 128);
+}
+
 // One launch for all that it takes, where that is estimated to be the faster: filling the chip once, the tiles spread evenly
 // over 256 CUs and half a tile of idling at the end, against the layers' own best tiles and 1.5 us for each launch more.  Two 8-bit blocks of width
 // 1152, us with the layers' own launches -> in one: M = 512 91 -> 72, 2048 155 -> 143, 4096 250 -> 213, 6144 317 -> 309; not taken: 8192 403 -> 421,
@@ -100,21 +124,22 @@ static float tile_us(const GemmArgs &a)
 int qgemm_many_choice(const GemmArgs *layers, int n, const GemmArgs **chosen)
 {
     int count = 0;
-    float alone = -1.5f, work = 0.0f, longest = 0.0f;
+    float alone = -1.5f;
     for (int i = 0; i < n; ++i) {
         const GemmArgs &a = layers[i];
         if (!qgemm_many_takes(a) || qgemm_split_choice(a)) continue;
         chosen[count++] = &a;
-        const float us = tile_us(a);
         alone += qgemm_alone_us(a) + 1.5f;
-        work += us * (float)((a.M + ManyW8::BM - 1) / ManyW8::BM) * (float)((a.N + ManyW8::BN - 1) / ManyW8::BN);
-        longest = us > longest ? us : longest;
     }
-    return count > 1 && 3.2f + work / 256.0f + 0.5f * longest < alone ? count : 0;
+    if (count < 2) return 0;
+    return (qgemm_many_one_round(chosen, count) ? big_many_us(chosen, count) : many_us(chosen, count)) < alone ? count : 0;
 }
+
+bool qgemm_many_one_round(const GemmArgs *const *layers, int count) { return big_many_us(layers, count) < many_us(layers, count); }
 
 hipError_t launch_qgemm_many(const GemmArgs *const *layers, int count, hipStream_t stream)
 {
+    if (qgemm_many_one_round(layers, count)) return launch_qgemm_big_many(layers, count, stream);
     static const hipError_t opt_in = hipFuncSetAttribute(reinterpret_cast<const void *>(&qgemm_many), hipFuncAttributeMaxDynamicSharedMemorySize, MANY_LDS);
     if (opt_in != hipSuccess) return opt_in;
     ManyArgs b{};

@@ -151,6 +151,9 @@ hipError_t launch_qgemm_split16(const GemmArgs &a, hipStream_t stream);
 bool qgemm_edge_takes(const GemmArgs &a);
 hipError_t launch_qgemm_edge(const GemmArgs &a, hipStream_t stream);
 bool qgemm_big_takes(const GemmArgs &a);
+// 8-bit layers of a plan whose 256x288 tiles are one round of workgroups, in one launch
+bool qgemm_big_many_takes(const GemmArgs *const *layers, int count);
+hipError_t launch_qgemm_big_many(const GemmArgs *const *layers, int count, hipStream_t stream);
 hipError_t launch_big_w8_256x288(const GemmArgs &a, hipStream_t s);
 hipError_t launch_big_w8_256x288_glue(const GemmArgs &a, hipStream_t s);
 hipError_t launch_big_w8_256x256(const GemmArgs &a, hipStream_t s);
@@ -171,6 +174,8 @@ hipError_t launch_big_w4_128x288_glue(const GemmArgs &a, hipStream_t s);
 // the GEMMs of several layers with as many rows each in one launch; every one has to pass qgemm_many_takes
 bool qgemm_many_takes(const GemmArgs &a);
 // which of them are better in one launch than one after the other (their number; fewer than two: none)
+// the launch takes 256x288 tiles (qgemm_big_many_takes) in place of 128x128
+bool qgemm_many_one_round(const GemmArgs *const *layers, int count);
 int qgemm_many_choice(const GemmArgs *layers, int n, const GemmArgs **chosen);
 hipError_t launch_qgemm_many(const GemmArgs *const *layers, int count, hipStream_t stream);
 // pair-order nibbles (device) -> the 4-bit storage order (device); blocks = N*K/8 four-byte blocks

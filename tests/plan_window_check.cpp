@@ -1,12 +1,12 @@
 // Prints which layers of a plan the library runs together: one line per window, "first n: layers whose GEMMs share a launch"; layers in no window run
-// alone.  Host arithmetic only; the addresses are never followed.  Input: "M R p_ppm a_bits room" (p_ppm 0: the maximum; room: workspace as a multiple
+// alone.  With an argument: only those layers of a window whose shared launch has one round of large tiles.  Host arithmetic only; the addresses are never followed.  Input: "M R p_ppm a_bits room" (p_ppm 0: the maximum; room: workspace as a multiple
 // of the recommended one), then "K N bits group x y" per layer.
 #include "../paper_2511_11446_amd/csrc/plan_window.h"
 
 #include <cstdio>
 #include <vector>
 
-int main()
+int main(int argc, char **)
 {
     long long M, R, p_ppm, a_bits, room, K, N, bits, group, x, y;
     if (std::scanf("%lld %lld %lld %lld %lld", &M, &R, &p_ppm, &a_bits, &room) != 5) return 1;
@@ -44,6 +44,7 @@ int main()
             continue;
         }
         std::printf("%d %d:", (int)l, w.n);
+        if (argc > 1 && !ql::qgemm_many_one_round(w.together, w.count)) w.count = 0;
         for (int i = 0; i < w.count; ++i) std::printf(" %d", (int)l + (int)(w.together[i] - w.g));
         std::printf("\n");
         l += (size_t)w.n;

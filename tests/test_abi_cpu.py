@@ -202,9 +202,9 @@ def plan_windows(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-o", exe,
                     os.path.join(here, "plan_window_check.cpp"), lib, "-Wl,-rpath," + os.path.dirname(lib)], check=True)
 
-    def ask(M, R, p_ppm, a_bits, room, layers):
+    def ask(M, R, p_ppm, a_bits, room, layers, *one_round):
         text = "%d %d %d %d %d\n" % (M, R, p_ppm, a_bits, room) + "".join("%d %d %d %d %d %d\n" % l for l in layers)
-        r = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60)
+        r = subprocess.run([exe, *one_round], input=text, capture_output=True, text=True, timeout=60)
         assert r.returncode == 0, r.stderr
         out = []
         for line in r.stdout.splitlines():
@@ -231,6 +231,24 @@ def test_every_kind_of_layer_takes_part_in_a_shared_gemm_launch(plan_windows):
                 for _, _, together in plan_windows(M, 1, 0, 8, room, layers):
                     kinds |= {(shapes[i][2], shapes[i][3]) for i in together}
     assert kinds >= {(8, 0), (16, 0), (4, 32), (4, 64), (4, 128), (4, 192), (4, 288)}
+
+
+def test_one_round_of_large_tiles(plan_windows):
+    """Rows and layers of the GPU test: 256 large tiles at most, all taken; one row tile more, short rows, a 4-bit layer, an output not in whole pieces: none."""
+    import test_gpu_plan_windows as pw
+
+    def taken(M, shapes, R=1):
+        layers = [(K, N, bits, group, _place(2 * i), _place(2 * i + 1)) for i, (K, N, bits, group, _) in enumerate(shapes)]
+        (_, _, together), = plan_windows(M, R, 0, 8, 4, layers, "one round")
+        return together
+
+    for name, M, R in pw.ROUNDS:
+        assert taken(M, pw.ROUND_LAYERS[name], R) == set(range(len(pw.ROUND_LAYERS[name]))), (name, M, R)
+    block = pw.ROUND_LAYERS["block"]
+    assert not taken(2049, block)
+    assert not taken(2048, [(256,) + l[1:] for l in block])
+    assert not taken(2048, block[:2] + [(1152, 4608, 4, 128, True)])
+    assert not taken(2048, block[:2] + [(1152, 4604, 8, 0, True)])
 
 
 def test_layers_that_wait_for_each_other_share_no_gemm_launch(plan_windows):

@@ -210,3 +210,25 @@ def test_many_rows(ql, M, R, p_ppm):
         plan.run([x] * 8, y, M, R, ws)
     for l, b in zip(layers, y):
         torch.testing.assert_close(b, _alone_shared(ql, l, x, R, p_ppm, 8), rtol=0, atol=0)
+
+
+# 8-bit layers that are one round of 256x288 tiles together: whole and partial tiles in both directions, one scale for several rows, different inner sizes
+ROUND_LAYERS = {
+    "block": [(1152, 3456, 8, 0, True), (1152, 1152, 8, 0, True), (1152, 4608, 8, 0, True)],
+    "ragged": [(1024, 3016, 8, 0, False), (1152, 4360, 8, 0, True), (640, 1032, 8, 0, True)],
+}
+ROUNDS = [("block", 2048, 1), ("block", 1793, 1), ("block", 2047, 1), ("block", 2048, 256), ("ragged", 2048, 1), ("ragged", 2001, 1), ("ragged", 1920, 64)]
+
+
+@pytest.mark.parametrize("name,M,R", ROUNDS)
+def test_one_round_of_large_tiles(ql, name, M, R):
+    g = torch.Generator(device="cuda").manual_seed(M + R)
+    layers = [_layer(g, *s) for s in ROUND_LAYERS[name]]
+    x = [torch.randn(M, l["K"], device="cuda", generator=g).half() for l in layers]
+    y = [torch.full((M, l["N"]), float("nan"), dtype=torch.float16, device="cuda") for l in layers]
+    plan = ql.Plan(layers, M_max=M)
+    ws = ql.workspace(4 * plan.workspace_bytes(M, R))
+    for _ in range(2):
+        plan.run(x, y, M, R, ws)
+    for l, a, b in zip(layers, x, y):
+        torch.testing.assert_close(b, _alone_shared(ql, l, a, R, 0, 8), rtol=0, atol=0)

@@ -119,22 +119,18 @@ __device__ __forceinline__ void qgemm_dma_tiles(const GemmArgs &a, int block, in
         for (int i = 0; i < NA; ++i) {
             const int row = 8 * (wave + i * NW) + (lane >> 3);
             const int c = (lane & 7) ^ ((row >> 1) & 7);
-            goffA[i] = row_start(min(m0 + row, M - 1), K * EB) + 16 * c;
+            goffA[i] = T::ANYK ? first_piece(min(m0 + row, M - 1), K * EB, c) : row_start(min(m0 + row, M - 1), K * EB) + 16 * c;
         }
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             const int row = 8 * (wave + i * NW) + (lane >> 3);
             const int c = (lane & 7) ^ ((row >> 1) & 7);
-            goffB[i] = row_start(min(n0 + row, N - 1), K * EB) + 16 * c;
+            goffB[i] = T::ANYK ? first_piece(min(n0 + row, N - 1), K * EB, c) : row_start(min(n0 + row, N - 1), K * EB) + 16 * c;
         }
     };
     set_goff();
     // ANYK: a piece of the last K step that crosses or lies behind the end of its row reads the row's last 16 bytes instead
-    auto back = [&](int kt, int i) {
-        if (!T::ANYK || kt + 1 < nk) return 0u;
-        const int over = kt * 128 + 16 * ((lane & 7) ^ ((4 * (wave + i * NW) + (lane >> 4)) & 7)) + 16 - K * EB;
-        return (unsigned)max(over, 0);
-    };
+    auto back = [&](int kt, int i) { return T::ANYK ? piece_back(kt, nk, K * EB, (lane & 7) ^ ((4 * (wave + i * NW) + (lane >> 4)) & 7)) : 0u; };
     auto issue_a = [&](int kt, int slot, int i) {
         __builtin_amdgcn_global_load_lds((global_void *)(a.q + (size_t)kt * 128 + goffA[i] - back(kt, i)),
                                          (lds_void *)(smem + slot * T::A_BYTES + (wave + i * NW) * 1024), 16, 0, 0);

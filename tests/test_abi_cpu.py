@@ -192,6 +192,15 @@ def test_split_k_walk_on_eight_wavefronts(tmp_path):
     assert r.returncode == 0, r.stdout + r.stderr
 
 
+def test_pieces_of_rows_that_are_no_whole_steps_stay_inside_their_row(tmp_path):
+    """Addresses of the DMA tiles for any K, from the kernel's own header, up to the largest operands that the entry points accept."""
+    import subprocess
+    exe = str(tmp_path / "dma_piece_check")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-o", exe, os.path.join(os.path.dirname(__file__), "dma_piece_check.cpp")], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
 @pytest.fixture(scope="module")
 def plan_windows(tmp_path_factory):
     """(M, R, p_ppm, a_bits, room, [(K, N, bits, group, x, y)]) -> [(first layer, layers, {those whose GEMMs share a launch})], from the library's own decision."""

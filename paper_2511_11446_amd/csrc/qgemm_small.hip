@@ -698,7 +698,7 @@ __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void qgemm_edge(GemmArgs
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
-            store_column<GLUE>(a, gate_rows, m0, wm * TM * 32 + i * 32 + 4 * half, n0 + wn * TN * 32 + j * 32 + fr, [&](int r, unsigned off) {
+            store_column<GLUE, true>(a, gate_rows, m0, wm * TM * 32 + i * 32 + 4 * half, n0 + wn * TN * 32 + j * 32 + fr, [&](int r, unsigned off) {
                 if constexpr (KIND == OP_I8) {
                     if (a.acc_out) a.acc_out[off] = acc[i][j][r];
                 }

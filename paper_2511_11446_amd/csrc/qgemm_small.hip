@@ -760,10 +760,22 @@ static long long split_rounds(const GemmArgs &a)
     return (tiles + resident - 1) / resident;
 }
 
+// What a wavefront does one after the other: its K steps, and a hand-over for every round of groups
+template <int KIND, int T, int W>
+static int split_serial(const GemmArgs &a, int rounds)
+{
+    return rounds * ((split_gpr<KIND, T, W>(a) * a.group + 127) / 128 + 1);
+}
+
 // Eight wavefronts share K where their workgroups, which take more LDS with group scales, are all resident at once; 16x16 tiles of integer codes come
 // two to a workgroup where there are more of them than CUs.  us, DAQ and GEMM, four wavefronts -> chosen: 8-bit, K = 4608, N = 1152: M = 16 7.5 -> 7.0,
 // 64 8.7 -> 8.2; 4-bit M = 16 9.9 -> 9.1, 64 11.2 -> 10.4, 128 14.3 -> 13.0; K = 1152, M = 256 11.3 -> 9.0.  32x32 tiles without group scales, whose steps go round
 // the wavefronts, were up to 7 % slower with eight, and binary16 ones of short rows up to 16 %.
+//
+// 32x32 tiles with group scales: the sums of 12 groups fit LDS at once, which are three for each of four wavefronts and only one for each of eight.  Short groups
+// then take more rounds on eight and no fewer steps (groups of 32, K = 4608, M = 133, N = 1152: 18 rounds of a step against 12, 33.0 against 27.6 us; groups of 128
+// 5 against 3 rounds of three steps, 0.90 to 0.93 of the time).  int8 codes gain on eight in a single round only (0.94 to 1.04 of the time over 17 layers, mostly 0.98;
+// in several rounds 0.99 to 1.06).
 template <int KIND, int T>
 static hipError_t run_split(const GemmArgs &a, hipStream_t s)
 {
@@ -778,7 +790,12 @@ static hipError_t run_split(const GemmArgs &a, hipStream_t s)
     }
     constexpr bool GROUPED = KIND == OP_W4 || KIND == OP_I8G;
     if constexpr (T == 16 || GROUPED) {
-        const bool worth = KIND != OP_F16 || (a.K >= 1152 && (long long)((a.M + 15) / 16) * ((a.N + 15) / 16) <= 256);
+        bool worth = KIND != OP_F16 || (a.K >= 1152 && (long long)((a.M + 15) / 16) * ((a.N + 15) / 16) <= 256);
+        if constexpr (T == 32) {
+            const int r4 = split_layout<KIND, T, false, 4, 1>(a).rounds, r8 = split_layout<KIND, T, false, 8, 1>(a).rounds;
+            const int s4 = split_serial<KIND, T, 4>(a, r4), s8 = split_serial<KIND, T, 8>(a, r8);
+            worth = KIND == OP_I8G ? r8 == 1 : s8 < s4 || (s8 == s4 && r8 == r4);
+        }
         if (worth && split_rounds<KIND, T, false, 8, 1>(a) == 1) return run(eight{}, std::integral_constant<int, 1>{});
     }
     return run(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});

@@ -103,7 +103,7 @@ struct SplitTile {
     static constexpr int A_GROUPS = FUSE ? 0 : T / 8, B_GROUPS = NB * (KIND == OP_W4 ? T / 16 : T / 8);   // 1024-byte DMA instructions per K step
     static constexpr int LOADS = A_GROUPS + B_GROUPS;
     static constexpr int STAGE = LOADS * 1024;
-    // ring depth per wavefront: two workgroups' rings (and partial tiles) fit a CU
+    // ring depth per wavefront; how many workgroups a CU holds is counted from all that they keep in LDS (split_rounds)
     static constexpr int S = T == 32 || W == 8 ? 2 : GROUPED ? 3 : 4;
     static constexpr int TILE = NB * T * T * 4;                 // partial tiles of a wavefront or group, bytes
 };
@@ -847,15 +847,15 @@ int qgemm_split_choice(const GemmArgs &a)
     return 0;
 }
 
-// Whether the layer runs in one launch, codes made by the GEMM's own workgroups (a.x is the fp16 input).  Every column tile
-// repeats the quantization of its 16 rows, which costs the GPU what the separate launch costs it (M = 16, K = 1152, N = 4608:
-// 7.5 against 6.4 us, M = 1: 4.5 against 5.6) as long as a CU has one workgroup, and twice that with two; it always saves the
-// 3.6 us that a launch costs the host, which is what bounds a sequence of such small calls.
+// Whether the layer runs in one launch, codes made by the GEMM's own workgroups (a.x is the fp16 input), and how many column tiles each of them
+// covers: the fewest that leave no CU a second workgroup, which has to fit its LDS.  Every workgroup makes the codes of its 16 rows, so that more columns are
+// fewer repetitions, but fewer CUs too.  The launch that it saves also costs the host 3.6 us, which is what bounds a sequence of such small calls.
 //
-// Workgroups of 16 rows and 16 NB columns, the fewest columns that leave no CU a second one: the more columns, the fewer times the codes are made.  Eight
-// wavefronts make them in half the time that four take.  us, M x K x N, two launches or four wavefronts -> now: 8-bit 16 x 384 x 384 5.0 -> 4.2, 16 x 1152 x 1152
-// 6.5 -> 5.3, 64 x 1152 x 1152 7.1 -> 5.8 (NB = 2), 128 8.4 -> 6.6 (3), 256 9.0 -> 7.9 (5); 4-bit 16 7.4 -> 5.9, 128 9.6 -> 7.4; one scale for all rows, 8-bit, 256
-// 12.2 -> 10.8.  With four wavefronts NB = 2 to 5 were no faster than the two launches, and up to 1.2 times as long.
+// us, M x K x N, two launches or (up to 256 tiles) four wavefronts -> now: 8-bit 16 x 384 x 384 4.9 -> 4.2, 16 x 1152 x 1152 6.4 -> 5.4, 16 x 1152 x 4608 6.9 -> 5.5 (NB
+// = 2), 64 x 1152 x 1152 7.2 -> 5.6 (2), 128 7.9 -> 6.6 (3), 256 8.6 -> 8.1 (5), 64 x 1152 x 4096 7.9 -> 6.7 (4), 64 x 1152 x 4608 8.2 -> 7.6 (5), 128 9.2 -> 9.2 (none);
+// 4-bit 16 x 1152 x 1152 7.6 -> 5.9, 128 9.5 -> 7.3; one scale for all rows, 8-bit, 256 x 1152 x 1152 11.7 -> 10.7.  Without NB = 4, rows of 1536 were slower than
+// in two launches (8-bit, 24 x 1536 x 6448: two launches 7.9, NB = 5 8.2, NB = 4 6.7; 256 x 1536 x 1024 8.3, 8.5, 7.3).  With four wavefronts NB = 2 to 5 were no
+// faster than the two launches, and up to 1.2 times as long.  Short 4-bit groups whose scales and sums do not fit beside the codes take the two launches.
 static int fuse_tiles(const GemmArgs &a)   // NB; 0: DAQ runs by itself
 {
     if ((a.w_bits != 8 && a.w_bits != 4) || a.w_grouped || a.s_ag || a.acc_out || (uintptr_t)a.x % 16 != 0 || a.K > SPLIT_FUSE_K_MAX) return 0;
@@ -868,6 +868,7 @@ static int fuse_tiles(const GemmArgs &a)   // NB; 0: DAQ runs by itself
     int nb = takes(std::integral_constant<int, 1>{});
     if (!nb) nb = takes(std::integral_constant<int, 2>{});
     if (!nb) nb = takes(std::integral_constant<int, 3>{});
+    if (!nb) nb = takes(std::integral_constant<int, 4>{});
     return nb ? nb : takes(std::integral_constant<int, 5>{});
 }
 bool qgemm_fuse_takes(const GemmArgs &a) { return fuse_tiles(a) != 0; }
@@ -878,6 +879,7 @@ hipError_t launch_qgemm_fused(const GemmArgs &a, hipStream_t stream)
     case 1: return a.w_bits == 8 ? run_split_fused<OP_I8, 1>(a, stream) : run_split_fused<OP_W4, 1>(a, stream);
     case 2: return a.w_bits == 8 ? run_split_fused<OP_I8, 2>(a, stream) : run_split_fused<OP_W4, 2>(a, stream);
     case 3: return a.w_bits == 8 ? run_split_fused<OP_I8, 3>(a, stream) : run_split_fused<OP_W4, 3>(a, stream);
+    case 4: return a.w_bits == 8 ? run_split_fused<OP_I8, 4>(a, stream) : run_split_fused<OP_W4, 4>(a, stream);
     case 5: return a.w_bits == 8 ? run_split_fused<OP_I8, 5>(a, stream) : run_split_fused<OP_W4, 5>(a, stream);
     default: return hipErrorInvalidValue;
     }

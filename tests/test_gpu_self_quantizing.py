@@ -9,8 +9,9 @@ from test_gpu_parity import assert_y_close, dev, gpu, host, say  # noqa: F401  (
 pytestmark = pytest.mark.gpu
 
 
-# M, K, N, R: 256 tiles and one row more (1 -> 2 tiles to a workgroup), 2 -> 3, 3 -> 5 with a ragged last column, 5 and beyond; all rows of one scale
+# M, K, N, R: 256 tiles and one row more (1 -> 2 tiles to a workgroup), 2 -> 3, 3 -> 4, 4 (ragged last columns) and one column more, 5 and beyond; all rows of one scale
 @pytest.mark.parametrize("M,K,N,R", [(16, 384, 4096, 1), (17, 384, 4096, 1), (250, 1152, 500, 1), (512, 272, 256, 64), (257, 1536, 640, 1), (48, 1152, 4090, 48), (64, 1520, 5113, 1),
+                                     (250, 1536, 769, 1), (64, 1520, 4090, 1), (64, 272, 4097, 64),
                                      (256, 1152, 1152, 256), (320, 1152, 1152, 1), (5, 16, 20481, 1)])
 def test_w8_tiles_of_a_workgroup(gpu, orc, M, K, N, R):
     say("self-quantizing w8", M, K, N, R)
@@ -23,7 +24,7 @@ def test_w8_tiles_of_a_workgroup(gpu, orc, M, K, N, R):
 # groups that leave wavefronts without one, several to a wavefront, several rounds; K beyond what a workgroup quantizes: eight wavefronts on 16x16, two
 # 16x16 and 32x32 tiles
 @pytest.mark.parametrize("M,K,N,group", [(16, 384, 100, 128), (40, 1152, 1152, 288), (128, 1152, 1152, 128), (64, 1536, 1530, 32), (250, 768, 768, 192), (200, 384, 1100, 32),
-                                         (16, 4608, 700, 128), (70, 4608, 1100, 288), (130, 4608, 1152, 64), (100, 2304, 500, 1152)])
+                                         (250, 1536, 1000, 128), (60, 768, 4090, 96), (16, 4608, 700, 128), (70, 4608, 1100, 288), (130, 4608, 1152, 64), (100, 2304, 500, 1152)])
 def test_w4_tiles_of_a_workgroup(gpu, orc, M, K, N, group):
     say("self-quantizing w4", M, K, N, group)
     g = workload.rng("self-q4", M, N)

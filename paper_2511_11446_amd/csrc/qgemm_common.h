@@ -88,19 +88,26 @@ __device__ __forceinline__ GlueTerms glue_terms(const GemmArgs &a, int m, int n,
     return t;
 }
 
-// The same of C elements of column n, row m_of(e), gate row gate_row(m): whether there are any is asked once, so that all are on their way together
+// The same of C elements of column n, row m_of(e), gate row gate_row(m): whether there are any is asked once, so that all are on their way together.  Of the
+// elements from `live` on, in steps of four, none is read.
 template <int C, class RowFn, class GateFn>
-__device__ __forceinline__ void request_glue(const GemmArgs &a, GlueTerms (&t)[C], int n, RowFn m_of, GateFn gate_row)
+__device__ __forceinline__ void request_glue(const GemmArgs &a, GlueTerms (&t)[C], int n, int live, RowFn m_of, GateFn gate_row)
 {
 #pragma unroll
     for (int e = 0; e < C; ++e) t[e] = {0x3c00 /* 1 */, 0};
     if (a.gate) {
 #pragma unroll
-        for (int e = 0; e < C; ++e) t[e].g = static_cast<const unsigned short *>(a.gate)[(unsigned)(gate_row(m_of(e)) * a.N + n)];
+        for (int e = 0; e < C; ++e) {
+            if (e % 4 == 0 && e >= live) break;
+            t[e].g = static_cast<const unsigned short *>(a.gate)[(unsigned)(gate_row(m_of(e)) * a.N + n)];
+        }
     }
     if (a.residual) {
 #pragma unroll
-        for (int e = 0; e < C; ++e) t[e].r = static_cast<const unsigned short *>(a.residual)[(unsigned)(m_of(e) * a.N + n)];
+        for (int e = 0; e < C; ++e) {
+            if (e % 4 == 0 && e >= live) break;
+            t[e].r = static_cast<const unsigned short *>(a.residual)[(unsigned)(m_of(e) * a.N + n)];
+        }
     }
 }
 
@@ -124,22 +131,32 @@ __device__ __forceinline__ _Float16 glue_one(const GemmArgs &a, float u, int m, 
 // row + 8 (r / 4) + r % 4 of the tile that starts at row m_first; value(r, off): fp32 value r, off its place in y.  Gate and residual of AHEAD of them
 // are requested together: between the stores each one was a trip to memory of its own.  us, gate and residual, before -> after: 8-bit, M = 2047, K =
 // 768, N = 1000 20.2 -> 17.5, M = 1021, K = 192 12.5 -> 11.2; FP16 M = 2047, K = 192 14.8 -> 11.7; 4-bit, groups of 288, M = 2047, K = 1152, N = 3456 46 -> 40
-// EDGE: the tile may cross the last row or column.  A block behind them asks for nothing (FP16, M = 6277, K = 768, N = 2304 gated, last tiles of 5 rows: 37.5 -> 34.8
-// us).  Whole tiles are not asked for every value (8-bit, M = 9530, K = 1024, N = 1295 plain: 38.4 -> 34.0; gated, M = 8192, K = 1152, N = 4601: 176 -> 161).
-template <bool GLUE, bool EDGE, int AHEAD = 16, class ValueFn>
+// EDGE: the tile may cross the last row or column.  Whole tiles are not asked for every value (8-bit, M = 9530, K = 1024, N = 1295 plain: 38.4 -> 34.0; gated, M =
+// 8192, K = 1152, N = 4601: 176 -> 161).  What lies behind the edge is then
+//   ASKED   for value by value: plain FP16 outputs and the 4-bit tiles, which go by fours (more questions cost up to 7 %: FP16, M = 8192, K = 104, N = 1000)
+//   LEFT    lane by lane at the first value: plain 8-bit outputs (M = 4195, K = 768, N = 2304 23.4 -> 22.8, FP16 2 to 3 % slower)
+//   PASSED  over in blocks and groups of 8 rows: with gate or residual a tile of a few rows otherwise runs through, and fetches, the code of all (FP16, K = 1024, N =
+//           3072, M = 200, 8 rows in the last tiles: 9.4 us value by value, 10.4 for all 16 together, 8.3 so; M = 6277, K = 768, N = 2304, 5 rows: 35.4, 37.5, 34.8)
+enum class Behind { ASKED, LEFT, PASSED };
+template <bool GLUE, bool EDGE, Behind BEHIND, int AHEAD = 16, class ValueFn>
 __device__ __forceinline__ void store_column(const GemmArgs &a, const GateRows &gate_rows, int m_first, int row, int n, ValueFn value)
 {
-    if (EDGE && (__builtin_amdgcn_readfirstlane(m_first + (row & ~31)) >= a.M || __builtin_amdgcn_readfirstlane(n & ~31) >= a.N)) return;
+    constexpr bool PASS = EDGE && BEHIND == Behind::PASSED, LEAVE = EDGE && BEHIND == Behind::LEFT;
+    const int rows = PASS ? a.M - __builtin_amdgcn_readfirstlane(m_first + (row & ~31)) : 32;   // of the block; a lane has four of each 8
+    if (PASS && (rows <= 0 || __builtin_amdgcn_readfirstlane(n & ~31) >= a.N)) return;
+    if (LEAVE && (m_first + row >= a.M || n >= a.N)) return;
 #pragma unroll
     for (int first = 0; first < 16; first += AHEAD) {
         GlueTerms t[AHEAD];
         auto row_of = [&](int e) { return m_first + row + 8 * ((first + e) / 4) + (first + e) % 4; };
         if (GLUE)
-            request_glue<AHEAD>(a, t, EDGE ? min(n, a.N - 1) : n, [&](int e) { return EDGE ? min(row_of(e), a.M - 1) : row_of(e); }, [&](int m) { return gate_rows.of(max(m - m_first, 0)); });
+            request_glue<AHEAD>(a, t, EDGE ? min(n, a.N - 1) : n, PASS ? (rows + 1) / 2 - first : AHEAD, [&](int e) { return EDGE ? min(row_of(e), a.M - 1) : row_of(e); },
+                                [&](int m) { return gate_rows.of(EDGE && !PASS ? max(m - m_first, 0) : m - m_first); });
 #pragma unroll
         for (int e = 0; e < AHEAD; ++e) {
+            if (PASS && e % 4 == 0 && 2 * (first + e) >= rows) return;
             const int m = row_of(e);
-            if (EDGE && (m >= a.M || n >= a.N)) continue;
+            if (EDGE && (m >= a.M || (!LEAVE && n >= a.N))) continue;
             const unsigned off = (unsigned)(m * a.N + n);
             float u = value(first + e, off);
             asm volatile("" : "+v"(u));   // keep the fp32 rounding before the fp16 one

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(64 * W, W == 8 && NB <= 2 ? 4 : 2) void qgemm_split
     }
     GlueTerms terms[EPT];
     if constexpr (GLUE && NB == 1) {
-        request_glue<EPT>(a, terms, min(col_of(0), N - 1), [&](int e) { return min(m0 + row_of(e), M - 1); }, [&](int m) { return m / a.gate_rows; });
+        request_glue<EPT>(a, terms, min(col_of(0), N - 1), EPT, [&](int e) { return min(m0 + row_of(e), M - 1); }, [&](int m) { return m / a.gate_rows; });
     } else if constexpr (GLUE) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
@@ -698,7 +698,7 @@ __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void qgemm_edge(GemmArgs
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
-            store_column<GLUE, true>(a, gate_rows, m0, wm * TM * 32 + i * 32 + 4 * half, n0 + wn * TN * 32 + j * 32 + fr, [&](int r, unsigned off) {
+            store_column<GLUE, true, GLUE ? Behind::PASSED : Behind::ASKED>(a, gate_rows, m0, wm * TM * 32 + i * 32 + 4 * half, n0 + wn * TN * 32 + j * 32 + fr, [&](int r, unsigned off) {
                 if constexpr (KIND == OP_I8) {
                     if (a.acc_out) a.acc_out[off] = acc[i][j][r];
                 }

@@ -442,7 +442,7 @@ __device__ __forceinline__ void qgemm_w4_tiles(const GemmArgs &a, int block, int
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
                     const int row = wm * TM * 32 + i * 32 + 4 * frag_half;
-                    store_column<GLUE, true, TM == 1 ? 16 : 4>(a, gate_rows, em0, row, en0 + wn * TN * 32 + j * 32 + frag_row, [&](int r, unsigned) {
+                    store_column<GLUE, true, Behind::ASKED, TM == 1 ? 16 : 4>(a, gate_rows, em0, row, en0 + wn * TN * 32 + j * 32 + frag_row, [&](int r, unsigned) {
                         const float f = fsum[i][j][r], sa = sRow[row + 8 * (r / 4) + r % 4];
                         return a.bias ? __builtin_fmaf(f, sa, bj[j]) : f * sa;
                     });

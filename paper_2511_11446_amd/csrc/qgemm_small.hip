@@ -699,10 +699,11 @@ __global__ __launch_bounds__(256, TM * TN == 1 ? 4 : 2) void qgemm_edge(GemmArgs
 #pragma unroll
         for (int i = 0; i < TM; ++i)
             store_column<GLUE, true, GLUE ? Behind::PASSED : Behind::ASKED>(a, gate_rows, m0, wm * TM * 32 + i * 32 + 4 * half, n0 + wn * TN * 32 + j * 32 + fr, [&](int r, unsigned off) {
+                const float u = value(i, j, r);   // ahead of the question, which the read of the row's scale would wait behind
                 if constexpr (KIND == OP_I8) {
                     if (a.acc_out) a.acc_out[off] = acc[i][j][r];
                 }
-                return value(i, j, r);
+                return u;
             });
 }
 

@@ -164,13 +164,14 @@ static bool k64_takes(const GemmArgs &a)
     return a.w_bits == 8 && !a.w_grouped && !a.s_ag && !glue && a.K % 64 == 0 && ((uintptr_t)a.q | (uintptr_t)a.w) % 16 == 0;
 }
 
-// Where it is the faster one: more tiles than CUs (320 tiles: 10 to 25 % faster than qgemm_edge, 240: 15 to 45 % slower), not very many (640
-// tiles, K = 2240: 45 us against 47 of the DMA tile for any K, 1280: 82 against 73) and whole tile columns; others are written element by element, which only a long K and more than two tiles per CU outweigh (N = 1000: M = 8192, K =
-// 192 22.5 against 19.5 us, K = 2240 53 against 51; M = 16384, K = 2240 91 against 97).
+// Where it is the faster one: more tiles than CUs (320 tiles: 10 to 25 % faster than qgemm_edge, 240: 15 to 45 % slower) and whole tile columns; others are written element by
+// element, which only a long K and more than two tiles per CU outweigh (N = 1000: M = 8192, K = 192 22.5 against 19.5 us, K = 2240 53 against 51).  Of very many tiles only with
+// rows that are mostly padding on the DMA tiles for any K, which take steps of 128 (from 1152 tiles on, DMA tiles over this kernel: K = 64 0.94 to 1.07 of the time,
+// mostly 1.04 and more; 192 0.97 to 1.06; 320 0.95 to 1.05, mostly 0.98; 576 0.95 to 1.01; 2240 0.91 to 0.94).
 static bool k64_wins(const GemmArgs &a)
 {
     const long tiles = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-    return k64_takes(a) && tiles > 256 && tiles <= 1024 && (a.N % 128 == 0 || (a.K >= 2048 && tiles > 512));
+    return k64_takes(a) && tiles > 256 && (tiles <= 1024 || a.K <= 192) && (a.N % 128 == 0 || (a.K >= 2048 && tiles > 512));
 }
 
 static hipError_t run_k64(const GemmArgs &a, hipStream_t s)

@@ -20,7 +20,7 @@ bool any_order(const GemmArgs *g, size_t n);
 // The next layers of a plan from `first` on in one go, where their inputs are there already: their activations are quantized by
 // the launches of one layer (each layer's codes, scales and scratch in a part of its own of the workspace), then the GEMMs follow in order.  Takes
 // layers as long as no input of one is written by another one before it, they fit the workspace and PLAN_WINDOW_BYTES together, and none
-// is small enough to quantize its own rows inside its GEMM.
+// quantizes its own rows inside its GEMM on one 16x16 tile per workgroup (those of two to five tiles would, on their own; here they share the DAQ launches).
 void plan_window(const ql_layer_desc *layers, size_t n_layers, size_t first, const void *const *x_in, void *const *y_out, int64_t M, int64_t R,
                  const ql_daq_params *dp, void *workspace, size_t workspace_bytes, PlanWindow &w);
 

@@ -377,11 +377,12 @@ static int find_variant(const char *name)
 //     pieces like whole ones)
 //
 // Fitted to sweeps on MI355X over M = 640..16384 and 27 (K, N) from 256 to 5120, plain, with GELU and with gate and residual; DAQ in front of
-// the layer, other weights and outputs in every call, as in a stack; 4-bit weights also with groups of 32, 64, 192 and 288.  The tile
-// chosen is in the mean 0.3 % slower than the fastest one, 2 % of 6300 cases lose more than 5 %, and the worst one (partial tiles with GELU)
-// 43 %.  Rules that charged the large tiles per round and the others by their rate, without the glue, lost 2 % (4 bits) to 6 % (FP16) in
-// the mean of the plain layers and 5 to 17 % with gate and residual (8-bit, M = 8192, K = 256, N = 1024: 40.7 us against 14.3).
-// profiles/tile_choice_sweep.txt holds the part of the data with the common widths.
+// the layer, other weights and outputs in every call, as in a stack; 4-bit weights also with groups of 32, 64, 192 and 288: 0.3 % in the mean over the fastest tile, 2 %
+// of 6300 cases more than 5 % over it.  profiles/tile_choice_sweep.txt holds the part of the data with the common widths.  Rules that charged the large tiles per round and the
+// others by their rate, without the glue, lost 2 % (4 bits) to 6 % (FP16) in the mean of the plain layers and 5 to 17 % with gate and residual (8-bit, M = 8192, K = 256, N =
+// 1024: 40.7 us against 14.3).  The edge terms of 8-bit and FP16 layers were set again when gate and residual of such values came to be requested together; since those kernels
+// changed, 1850 layers of M = 512..16384 and widths of any kind, two thirds of them with glue, stay over the fastest tile by 2.0 % (8-bit), 2.2 % (FP16) and 0.7 % (4-bit) in the mean,
+// 10, 11 and 3 % of them by more than 5 %, at worst 54 % (odd widths with gate and residual, whose every tile pays what is charged once).
 struct GlueCost {
     float act, gated, big_act, big_gated, edge, edge_act, edge_gated;
 };
@@ -410,9 +411,11 @@ static const TileCost TILE_COSTS[] = {
     {"f16 dma 256x192 a3b2 8w spread1", 16, 256, 192, 1, 0.275f, 5.430f, 1.129f, 0, 0, 0, 4.768f},
     {"f16 big 256x256", 16, 256, 256, 1, 1.395f, 4.703f, 1.423f, 0, 0, 0, 0.007f},
     {"f16 big 256x288", 16, 256, 288, 1, 0, 6.117f, 1.753f, 0, 0, 0, 0.331f},
-    // rows that are no whole K steps: the DMA tiles as above, qgemm_edge where the rows are a few steps only (its 128x128 tiles, from 512 of them on,
-    // are never the faster ones).  us, DAQ and GEMM, qgemm_edge -> chosen, M x K x N: 8-bit 1021 x 1160 x 1000 16.5 -> 13.0, 1021 x 2244 x 1000 42 -> 32, 8192 x
-    // 1160 x 2560 59 -> 50, 64 x 1000 x 77 12.9 -> 9.5; FP16 2047 x 2244 x 1000 36 -> 25, 4096 x 1160 x 2560 55 -> 42; 8-bit 4096 x 200 x 1200 13.5 -> 13.1
+    // rows that are no whole K steps: the 8-bit DMA tiles as above, those of FP16 and qgemm_edge fitted; qgemm_edge where the rows are a few steps only (its 128x128 tiles, from
+    // 512 of them on, were 1.07 to 1.9 times as slow with 8 bits, and with FP16 rows of one step 0.92 to 1.27 times).  us, DAQ and GEMM, qgemm_edge -> chosen, M x K x N: 8-bit
+    // 1021 x 1160 x 1000 16.0 -> 12.1, 1021 x 2244 x 1000 42 -> 32, 8192 x 1160 x 2560 59 -> 50, 64 x 1000 x 77 12.9 -> 9.5; FP16 2047 x 2244 x 1000 36 -> 25, 4096 x 1160 x 2560 55 ->
+    // 42; 8-bit 4096 x 200 x 1200 13.5 -> 13.1.  Over the fastest kernel 1.4 % (8-bit) and 2.9 % (FP16) in the mean of 570 layers whose rows are whole 16 bytes, 6 and 16 % of
+    // 550 others, where qgemm_edge reads the ends of rows byte by byte and is still taken for short ones.
     {"w8 dma any-K 64x64 s3 4w", 8, 64, 64, 3, 4.685f, 0, 0.133f, 0, 0.154f, 0, 0.890f},
     {"w8 dma any-K 128x128 a3b2 4w spread1", 8, 128, 128, 2, 3.178f, 1.466f, 0.183f, 0, 0.399f, 0, 1.163f},
     {"w8 edge any-K", 8, 64, 64, 4, 3.985f, 0.173f, 0.024f, 0, 0.748f, 0, 0},

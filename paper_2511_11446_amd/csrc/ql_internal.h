@@ -174,9 +174,9 @@ hipError_t launch_big_w4_128x288_glue(const GemmArgs &a, hipStream_t s);
 // the GEMMs of several layers with as many rows each in one launch; every one has to pass qgemm_many_takes
 bool qgemm_many_takes(const GemmArgs &a);
 // which of them are better in one launch than one after the other (their number; fewer than two: none)
+int qgemm_many_choice(const GemmArgs *layers, int n, const GemmArgs **chosen);
 // the launch takes 256x288 tiles (qgemm_big_many_takes) in place of 128x128
 bool qgemm_many_one_round(const GemmArgs *const *layers, int count);
-int qgemm_many_choice(const GemmArgs *layers, int n, const GemmArgs **chosen);
 hipError_t launch_qgemm_many(const GemmArgs *const *layers, int count, hipStream_t stream);
 // pair-order nibbles (device) -> the 4-bit storage order (device); blocks = N*K/8 four-byte blocks
 hipError_t launch_prepack_w4(const void *pairs, void *packed, long long blocks, hipStream_t stream);

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 # partial tiles of both edges (the last ones with blocks wholly behind the edge), whole tiles of an odd width, outputs that no 16-byte piece reaches, gate rows that end inside a tile; split-K, the register-staged kernel and the DMA tiles
 @pytest.mark.parametrize("tile,M,K,N,gate_rows", [(None, 35, 48, 33, 7), (None, 300, 136, 2050, 60), ("w8 edge any-K", 200, 136, 101, 40),
                                                   ("w8 dma 64x64 s3 4w", 300, 256, 301, 300), ("w8 dma 128x128 a3b2 4w spread1", 300, 256, 301, 50),
-                                                  ("w8 dma 256x192 a3b2 8w spread1", 259, 256, 389, 37)])
+                                                  ("w8 dma 256x192 a3b2 8w spread1", 259, 256, 389, 37), ("w8 edge any-K", 2912, 24, 2890, 56)])
 def test_w8_gate_and_residual_element_by_element(gpu, orc, tile, M, K, N, gate_rows):
     say(tile, M, K, N, gate_rows)
     g = workload.rng("elements", M, N)

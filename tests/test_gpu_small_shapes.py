@@ -1,6 +1,6 @@
 """Layers of few rows and of inner sizes that no K step divides: the split-K kernel (with and without the quantization inside
-the GEMM), the register-staged kernel and the 64x64 tiles of the pipelined 4-bit kernel, at the edges of their tiles, steps,
-rounds and alignments, against the CPU oracle."""
+the GEMM), the register-staged kernel (forced, and for odd rows and alignments, which nothing else takes) and the 64x64 tiles of the pipelined kernels, at the
+edges of their tiles, steps, rounds and alignments, against the CPU oracle."""
 import numpy as np
 import pytest
 
@@ -16,13 +16,50 @@ W8 = [(1, 16, 1, 1), (15, 48, 33, 1), (17, 144, 16, 1), (31, 1536, 31, 1), (33, 
       (100, 4608, 700, 1), (330, 2320, 1160, 1),        # 32x32 tiles, two rounds of them
       (500, 2432, 1152, 1), (3000, 256, 4090, 1),       # more 32x32 tiles than one round, 256x192 tiles just beyond one: other tiles
       (2300, 64, 2176, 1), (2177, 448, 2048, 7), (17000, 2112, 520, 17000),                      # an odd multiple of 64, more than 256 tiles
-      (130, 1160, 70, 1), (130, 1157, 70, 1), (3, 7, 5, 1), (2100, 136, 1100, 1)]   # 8-byte and byte-wise row ends, both tile sizes
+      (130, 1160, 70, 1), (130, 1157, 70, 1), (3, 7, 5, 1), (2100, 136, 1100, 1)]   # rows that end on whole words (DMA tiles) and on bytes (register-staged)
 
 
 @pytest.mark.parametrize("M,K,N,R", W8)
 def test_w8_small_and_ragged(gpu, orc, M, K, N, R):
     say("w8 small", M, K, N, R)
     run_w8(gpu, orc, M, K, N, R, ("small", M, K, N), use_bias=(M % 2 == 0), check_exact=True)
+
+
+# rows that end on 16, 8, 4 and 2 bytes and on one; 64x64 tiles and, from 512 of them on, 128x128 ones
+EDGE = [(130, 1168, 70), (130, 1160, 70), (130, 1156, 70), (130, 1154, 70), (130, 1157, 70), (2100, 136, 1100), (2900, 141, 2870)]
+
+
+@pytest.mark.parametrize("M,K,N", EDGE)
+def test_w8_register_staged(gpu, orc, M, K, N):
+    say("w8 staged", M, K, N)
+    gpu.set_gemm_variant(gpu.gemm_variants().index("w8 edge any-K"))
+    try:
+        run_w8(gpu, orc, M, K, N, 1, ("staged", M, K, N), use_bias=(M % 4 == 0), check_exact=True)
+    finally:
+        gpu.set_gemm_variant(-1)
+
+
+@pytest.mark.parametrize("M,K,N", EDGE + [(700, 136, 700), (130, 1151, 70)])
+def test_f16_register_staged(gpu, orc, M, K, N):
+    """With infinities and NaN in the last inputs of a row: what pads the last K step is not multiplied with them."""
+    say("f16 staged", M, K, N)
+    g = workload.rng("staged16", M, K, N)
+    x = workload.activations(M, K, "staged16")
+    w = (g.standard_normal((N, K), dtype=np.float32) * 0.05).astype(np.float16)
+    x[x == 0] = 1
+    w[w == 0] = 0.05
+    w[0, K - 1], w[N // 2, K - 8], w[N - 1, K - 3] = np.inf, -np.inf, np.nan
+    x[M // 2, K - 2] = np.inf
+    gpu.set_gemm_variant(gpu.gemm_variants().index("f16 edge any-K"))
+    try:
+        y = host(gpu.qlinear_f16(dev(x), dev(w), None))
+    finally:
+        gpu.set_gemm_variant(-1)
+    ref = orc.linear_f16(x, w, None, nthreads=16)
+    assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isposinf(y), np.isposinf(ref)) and np.array_equal(np.isneginf(y), np.isneginf(ref))
+    rows, cols = np.arange(M) != M // 2, ~np.isin(np.arange(N), [0, N // 2, N - 1])
+    y, ref = y[np.ix_(rows, cols)], ref[np.ix_(rows, cols)]
+    assert (np.abs(y.astype(np.float64) - ref.astype(np.float64)) <= _f16_tolerance(x[rows], w[cols], ref)).all()
 
 
 @pytest.mark.parametrize("offset", [1, 2, 8])
@@ -101,7 +138,7 @@ def test_channel_group_slabs(gpu, orc, M, K, R, cg):
     assert np.array_equal(host(a).view(np.uint32), a_ref.view(np.uint32)) and np.array_equal(host(q), q_ref)
 
 
-# 16x16 and 32x32 split-K tiles with one to seven chunks of the last K step missing, the register-staged kernel, the DMA tiles
+# 16x16 and 32x32 split-K tiles with one to seven chunks of the last K step missing, the DMA tiles
 @pytest.mark.parametrize("M,K,N", [(40, 1160, 100), (17, 24, 33), (5, 120, 16), (500, 4616, 500), (700, 136, 700), (130, 1154, 70), (96, 256, 2048)])
 def test_f16_infinite_operands(gpu, orc, M, K, N):
     """Infinities and NaN in the last inputs of a row reach the outputs that they belong to and no others: what pads a row's last K

@@ -117,6 +117,15 @@ static float big_many_us(const GemmArgs *const *layers, int count)
     return 11.7f + 1.773f * (float)(longest / 128);
 }
 
+// A layer that splits K by itself stays out, but for 4-bit ones of more 32x32 tiles than CUs whose groups are more than four wavefronts take in one go: two workgroups of them
+// fit a CU, and yet the launch costs a plan more than these tiles do (four blocks of width 768 with 4-bit projections, us, own launches -> shared: M = 325 175 -> 157, M =
+// 602 165 -> 153).
+static bool stays_out(const GemmArgs &a)
+{
+    const int split = qgemm_split_choice(a);
+    return split && !(split == 32 && a.w_bits == 4 && a.K / a.group > 4 && (long long)((a.M + 31) / 32) * ((a.N + 31) / 32) > 256);
+}
+
 // One launch for all that it takes, where that is estimated to be the faster: filling the chip once, the tiles spread evenly
 // over 256 CUs and half a tile of idling at the end, against the layers' own best tiles and 1.5 us for each launch more.  Two 8-bit blocks of width
 // 1152, us with the layers' own launches -> in one: M = 512 91 -> 72, 2048 155 -> 143, 4096 250 -> 213, 6144 317 -> 309; not taken: 8192 403 -> 421,
@@ -127,7 +136,7 @@ int qgemm_many_choice(const GemmArgs *layers, int n, const GemmArgs **chosen)
     float alone = -1.5f;
     for (int i = 0; i < n; ++i) {
         const GemmArgs &a = layers[i];
-        if (!qgemm_many_takes(a) || qgemm_split_choice(a)) continue;
+        if (!qgemm_many_takes(a) || stays_out(a)) continue;
         chosen[count++] = &a;
         alone += qgemm_alone_us(a) + 1.5f;
     }

@@ -242,6 +242,16 @@ def test_every_kind_of_layer_takes_part_in_a_shared_gemm_launch(plan_windows):
     assert kinds >= {(8, 0), (16, 0), (4, 32), (4, 64), (4, 128), (4, 192), (4, 288)}
 
 
+def test_4_bit_layers_of_more_small_tiles_than_cus_share_a_gemm_launch(plan_windows):
+    """A 4-bit projection that would split K by itself goes with its neighbours where it is more than one 32x32 tile per CU, as long as it has more groups than wavefronts."""
+    def taken(M, group):
+        shapes = [(768, 2304, 8, 0), (768, 768, 4, group), (768, 3072, 8, 0)]
+        (_, _, together), = plan_windows(M, 1, 0, 8, 4, [s + (_place(2 * i), _place(2 * i + 1)) for i, s in enumerate(shapes)])
+        return 1 in together
+    assert [taken(M, 128) for M in (320, 321, 325, 602, 682)] == [False, True, True, True, True]
+    assert not taken(325, 192)      # four groups
+
+
 def test_one_round_of_large_tiles(plan_windows):
     """Rows and layers of the GPU test: 256 large tiles at most, all taken; one row tile more, short rows, a 4-bit layer, an output not in whole pieces: none."""
     import test_gpu_plan_windows as pw

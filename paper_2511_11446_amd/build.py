@@ -18,10 +18,11 @@ FLAGS = [
     "-Wno-unused-command-line-argument",
 ]
 
-# The K loops of qgemm.hip begin at a multiple of 16 bytes.  Where they begin otherwise depends on all code in front of them, and a start 4 bytes behind a multiple of 8
-# cost FP16 layers with GELU or gate 1 % (256x192 tiles: M = 2048, K = 1152, N = 4608) to 4 % (64x64: M = 1024, K = 3072, N = 768, 16.9 -> 16.2 us).  Multiples of 64 took 1.3 %
-# from the plain 128x128 tiles, and the 8-bit kernels of few rows (qgemm_small.hip) were 0.3 % slower aligned than not.
-FILE_FLAGS = {"qgemm.hip": ["-Xarch_device", "-falign-loops=16"]}
+# The K loops of the DMA tiles and of the 4-bit ones begin at a multiple of 16 bytes.  Where they begin otherwise depends on all code in front of them, and a start 4 bytes behind
+# a multiple of 8 cost FP16 layers with GELU or gate 1 % (256x192 tiles: M = 2048, K = 1152, N = 4608) to 4 % (64x64: M = 1024, K = 3072, N = 768, 16.9 -> 16.2 us), and 64x64 tiles of
+# 4-bit weights up to 5 % (M = 384, K = 4608, N = 1152, 25.0 -> 23.9 us).  Multiples of 64 took 1.3 % from the plain FP16 tiles of 128x128, and the 8-bit kernels of few
+# rows (qgemm_small.hip) were 0.3 % slower aligned than not.
+FILE_FLAGS = {src: ["-Xarch_device", "-falign-loops=16"] for src in ("qgemm.hip", "qgemm_w4.hip")}
 
 
 def _compile(src):

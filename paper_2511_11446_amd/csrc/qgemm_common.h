@@ -131,8 +131,8 @@ __device__ __forceinline__ _Float16 glue_one(const GemmArgs &a, float u, int m, 
 // row + 8 (r / 4) + r % 4 of the tile that starts at row m_first; value(r, off): fp32 value r, off its place in y.  Gate and residual of AHEAD of them
 // are requested together: between the stores each one was a trip to memory of its own.  us, gate and residual, before -> after: 8-bit, M = 2047, K =
 // 768, N = 1000 20.2 -> 17.5, M = 1021, K = 192 12.5 -> 11.2; FP16 M = 2047, K = 192 14.8 -> 11.7; 4-bit, groups of 288, M = 2047, K = 1152, N = 3456 46 -> 40
-// EDGE: the tile may cross the last row or column.  Whole tiles are not asked for every value (8-bit, M = 9530, K = 1024, N = 1295 plain: 38.4 -> 34.0; gated, M =
-// 8192, K = 1152, N = 4601: 176 -> 161).  What lies behind the edge is then
+// EDGE: the tile may cross the last row or column.  Whole tiles of plain outputs are not asked for every value (8-bit, M = 9530, K = 1024, N = 1295: 38.4 -> 34.0).  What
+// lies behind the edge is
 //   ASKED   for value by value: plain FP16 outputs and the 4-bit tiles, which go by fours (more questions cost up to 7 %: FP16, M = 8192, K = 104, N = 1000)
 //   LEFT    lane by lane at the first value: plain 8-bit outputs (M = 4195, K = 768, N = 2304 23.4 -> 22.8, FP16 2 to 3 % slower)
 //   PASSED  over in blocks and groups of 8 rows: with gate or residual a tile of a few rows otherwise runs through, and fetches, the code of all (FP16, K = 1024, N =

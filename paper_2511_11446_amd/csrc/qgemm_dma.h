@@ -398,9 +398,9 @@ __device__ __forceinline__ void qgemm_dma_tiles(const GemmArgs &a, int block, in
                     });
                 }
         };
-        // six blocks per wavefront with glue keep one form: two of them spill, and whole tiles that never come here are 5 % slower for it (8-bit
-        // 256x192, M = 8192, K = 1152, N = 4608 gated 93.8 against 90.0 us)
-        if ((!GLUE || TM * TN <= 4) && full) emit(std::false_type{});
+        // glue keeps one form: a second one is a quarter more code in this library's largest object (with six blocks per wavefront it also spills), and a plan that
+        // uses one plain kernel of it was 1 % slower (32 images of 256 rows, percentile scales, 313 against 317 us)
+        if (!GLUE && full) emit(std::false_type{});
         else emit(std::true_type{});
     }
     QL_PHASE(4)

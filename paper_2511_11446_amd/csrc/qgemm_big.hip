@@ -3,7 +3,7 @@
 // such tiles.
 //
 // Eight wavefronts own a tile of 256 x 288, 256 x 256 or 128 x 288; a wavefront holds MT x NT blocks of 16x16 of it.
-//   - With random operands the chip is power-limited: v_mfma_i32_16x16x64_i8 from registers reaches 4.0 POPS where
+//   - With random operands (no clock or power reading is kept that would say why) v_mfma_i32_16x16x64_i8 from registers reaches 4.0 POPS where
 //     v_mfma_i32_32x32x32_i8 reaches 3.36 (4.7 and 4.8 on zeros), and a large tile moves fewer bytes through the L2 and the LDS
 //     per operation.  256 x 288: a K step of 128 bytes is 2304 MFMA clocks of a SIMD, 1660 clocks of LDS reads and 540 of
 //     LDS writes; it measured 3100.  Over a whole kernel at M = 16384 the matrix cores are busy 43

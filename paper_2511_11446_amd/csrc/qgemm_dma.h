@@ -390,7 +390,8 @@ __device__ __forceinline__ void qgemm_dma_tiles(const GemmArgs &a, int block, in
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
                     const int row = wm * TM * 32 + i * 32 + 4 * frag_half;
-                    store_column<GLUE, decltype(edge)::value, GLUE ? Behind::PASSED : F16 ? Behind::ASKED : Behind::LEFT>(a, gate_rows, em0, row, en0 + wn * TN * 32 + j * 32 + frag_row, [&](int r, unsigned off) {
+                    const int n = en0 + wn * TN * 32 + j * 32 + frag_row;
+                    store_column<GLUE, decltype(edge)::value, GLUE ? Behind::PASSED : F16 ? Behind::ASKED : Behind::LEFT>(a, gate_rows, em0, row, n, [&](int r, unsigned off) {
                         if (F16) return (float)acc[i][j][r] + bj[j];
                         const float t = (float)acc[i][j][r] * sRow[row + 8 * (r / 4) + r % 4];
                         if (a.acc_out) a.acc_out[off] = (int)acc[i][j][r];
